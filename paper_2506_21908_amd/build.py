@@ -9,7 +9,10 @@ ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libnct.so")
-SOURCES = ["nct_kernels.hip", "nct_api.cpp"]
+# (source, defines, object): the kernels are compiled once per precision, side by side
+SOURCES = [("nct_kernels.hip", ["-DNCT_FP64_TU=1"], "nct_kernels_f64.o"),
+           ("nct_kernels.hip", ["-DNCT_FP64_TU=0"], "nct_kernels_f32.o"),
+           ("nct_api.cpp", [], "nct_api.o")]
 ARCH = "gfx950"
 
 
@@ -26,20 +29,20 @@ def flags():
             "-Wno-unused-result", "-I", os.path.join(HERE, "..", "include")]
 
 
-def build(verbose: bool = False, jobs: int = 2) -> str:
+def build(verbose: bool = False) -> str:
     """Compile every source to an object (in parallel) and link libnct.so; returns its path."""
     bdir = os.path.join(HERE, "_build")
     os.makedirs(bdir, exist_ok=True)
     cc = hipcc()
     procs = []
     objs = []
-    for src in SOURCES:
-        obj = os.path.join(bdir, src + ".o")
+    for src, defines, name in SOURCES:
+        obj = os.path.join(bdir, name)
         objs.append(obj)
-        cmd = [cc] + flags() + ["-c", os.path.join(CSRC, src), "-o", obj]
+        cmd = [cc] + flags() + defines + ["-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
-        procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)))
+        procs.append((name, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)))
     failed = []
     for src, p in procs:
         out, _ = p.communicate()

@@ -64,6 +64,7 @@ struct nct_system {
   void* CB = nullptr;
   void* ECB = nullptr;
   std::string err;
+  std::vector<std::complex<double>> roots;  // of T_K (product form of the exponential)
   std::vector<DevBuf> owned;
   // the static scratch array of this system's device (allocation-free entry point), or null
   void* scr = nullptr;
@@ -90,8 +91,8 @@ struct nct_system {
   double* g2yz64 = nullptr;
   float* g2x32 = nullptr;
   float* g2yz32 = nullptr;
-  // signed G per axis (x digit-reversed, y and z per position of the transformed yz plane)
-  double *gsx64 = nullptr, *gsy64 = nullptr, *gsz64 = nullptr;
+  double* gs64[3] = {nullptr, nullptr, nullptr};  // signed G per axis (real-space form)
+  // FP32: signed G per axis (x digit-reversed, y and z per position of the transformed yz plane)
   float *gsx32 = nullptr, *gsy32 = nullptr, *gsz32 = nullptr;
   // Bloch vectors [S][3] of the states (k-point sampling); null: Gamma only
   double* kv64 = nullptr;
@@ -111,6 +112,7 @@ struct nct_system {
   double* fpart = nullptr;     // [nblk][kFieldTot]
   double* ftot = nullptr;      // [kFieldTot]
   double* epart = nullptr;     // [2S][ntiles][2]
+  double* eplane = nullptr;    // [2S][NX] (FP64)
   double* obs_dev = nullptr;   // [cap][13]
   // per-step watchdog: N_e = sum_i f_i <psi_i|psi_i> after every self-consistent step of a call
   double* ne_hist = nullptr;   // [ne_cap]: slot 0 the initial states, slot k+1 after step k
@@ -125,12 +127,13 @@ struct nct_system {
   int obs_cap = 0;
 
   // device: psi-sized work (precision of the system)
-  void* psihat = nullptr;
-  void* phi = nullptr;
+  void* psihat = nullptr;     // FP32: (y,z)-transformed psi and phi
   void* phihat = nullptr;
+  void* phi = nullptr;
   void* wbuf = nullptr;
   void* tmp = nullptr;
-  void* tmpk_phi = nullptr;   // kinetic column pass of phi (shared by the 2nd and 3rd exponentials)
+  void* tmpk_phi = nullptr;   // FP32: kinetic column pass of phi (shared by the 2nd and 3rd exponentials);
+                              // FP64: adjoint of psi~
 
   // projectors
   ProjTables pt;
@@ -336,13 +339,33 @@ nct_status build_projectors(nct_system* s) {
   pt.Jtot = ht.Jtot;
   pt.max_kchunks = ht.max_kchunks;
   pt.max_rowtiles = ht.max_rowtiles;
-  int *d_row_off, *d_pidx, *d_pr_off, *d_pr_b, *d_pr_e;
+  int *d_row_off, *d_pr_off;
   nct_status r;
   if ((r = upload(s, ht.row_off, &d_row_off)) != NCT_OK) return r;
-  if ((r = upload(s, ht.pidx, &d_pidx)) != NCT_OK) return r;
   if ((r = upload(s, ht.pr_off, &d_pr_off)) != NCT_OK) return r;
-  if ((r = upload(s, ht.pr_begin, &d_pr_b)) != NCT_OK) return r;
-  if ((r = upload(s, ht.pr_end, &d_pr_e)) != NCT_OK) return r;
+  if (s->fp64) {  // real-space form: from a grid point to its rows
+    if (ht.Jtot > kRowMask) return fail(s, NCT_ERR_UNSUPPORTED, "too many sphere rows");
+    std::vector<int> rflat(ht.pidx.size());
+    for (size_t J = 0; J < rflat.size(); ++J) rflat[J] = ht.ix_of_row[J] * s->n[1] * s->n[2] + ht.pidx[J];
+    std::vector<int> pmap = ht.pmap;
+    for (int& J : pmap)
+      if (J >= 0 && ht.rnext[J] >= 0) J |= kRowMore;
+    int *d_rflat, *d_pmap, *d_rnext;
+    if ((r = upload(s, rflat, &d_rflat)) != NCT_OK) return r;
+    if ((r = upload(s, pmap, &d_pmap)) != NCT_OK) return r;
+    if ((r = upload(s, ht.rnext, &d_rnext)) != NCT_OK) return r;
+    pt.rflat = d_rflat;
+    pt.pmap = d_pmap;
+    pt.rnext = d_rnext;
+  } else {  // transformed form: the row ranges of each plane
+    int *d_pidx, *d_pr_b, *d_pr_e;
+    if ((r = upload(s, ht.pidx, &d_pidx)) != NCT_OK) return r;
+    if ((r = upload(s, ht.pr_begin, &d_pr_b)) != NCT_OK) return r;
+    if ((r = upload(s, ht.pr_end, &d_pr_e)) != NCT_OK) return r;
+    pt.pidx = d_pidx;
+    pt.pr_begin = d_pr_b;
+    pt.pr_end = d_pr_e;
+  }
   if ((r = upload(s, ht.energy, &s->energy_dev)) != NCT_OK) return r;
   std::vector<R> braw(ht.beta.size() * 2);
   for (size_t k = 0; k < ht.beta.size(); ++k) {
@@ -356,10 +379,7 @@ nct_status build_projectors(nct_system* s) {
   if ((r = upload(s, disp, &d_disp)) != NCT_OK) return r;
   pt.disp = d_disp;
   pt.row_off = d_row_off;
-  pt.pidx = d_pidx;
   pt.pr_off = d_pr_off;
-  pt.pr_begin = d_pr_b;
-  pt.pr_end = d_pr_e;
   pt.beta = d_beta;
   pt.energy = s->energy_dev;
   const size_t rows = size_t(s->S) * 2 * pt.Jtot * s->cbytes;
@@ -487,10 +507,57 @@ bool cholesky_inverse_h(std::vector<std::complex<double>>& A, int n) {
   return true;
 }
 
+// ---------------------------------------------------------------- product form of the exponential
+// Roots r_j of T_K(z) = sum_k z^k / k!, so that T_K(z) = prod_j (1 - z / r_j): Durand-Kerner iteration in
+// long double.  Order: the upper half plane by increasing |r|, the real root, the conjugates of the
+// first in the same order.
+std::vector<std::complex<double>> taylor_roots(int K) {
+  using C = std::complex<long double>;
+  std::vector<C> r(K);
+  std::vector<long double> c(K + 1, 1.0L);  // monic: K!/k!
+  for (int k = K - 1; k >= 0; --k) c[k] = c[k + 1] * (k + 1);
+  for (int j = 0; j < K; ++j) r[j] = (0.6L * K + 0.5L) * std::polar(1.0L, 2.0L * (long double)kPi * (j + 0.3L) / K);
+  for (int it = 0; it < 200; ++it) {  // quadratic convergence; the last digits may keep moving
+    long double step = 0.0L;
+    for (int j = 0; j < K; ++j) {
+      C p = c[K], q = 1.0L;
+      for (int k = K - 1; k >= 0; --k) p = p * r[j] + c[k];
+      for (int i = 0; i < K; ++i)
+        if (i != j) q *= r[j] - r[i];
+      const C d = p / q;
+      r[j] -= d;
+      step = std::max(step, std::abs(d));
+    }
+    if (step < 1e-17L) break;
+  }
+  std::vector<C> up, re;
+  for (const C& z : r) {
+    if (z.imag() > 1e-6L) up.push_back(z);
+    else if (z.imag() > -1e-6L) re.push_back(C(z.real(), 0.0L));
+  }
+  std::sort(up.begin(), up.end(), [](const C& a, const C& b) { return std::abs(a) < std::abs(b); });
+  std::vector<std::complex<double>> out;
+  for (const C& z : up) out.push_back(std::complex<double>(z));
+  for (const C& z : re) out.push_back(std::complex<double>(z));
+  for (const C& z : up) out.push_back(std::conj(std::complex<double>(z)));
+  return out;
+}
+// The product form is used where |z| E_max (E_max: the largest kinetic energy of the grid) is at least
+// this and K is at most kProductMaxOrder.  Its rounding against long double is no larger than the
+// Horner form's there: relative errors of one exponential at K = 4, h = 0.42 bohr, |z| = 0.025 (|z|
+// E_max = 2.1) 1.0e-16 against 1.6e-16, at 1.5 0.96e-16 against 1.09e-16, at 0.95 0.93e-16 against
+// 0.78e-16 (every stage rounds w once, the Horner form adds small terms to an exact x), K = 12 1.4e-16
+// against 1.5e-16, K = 16 1.6e-16 against 1.5e-16.
+constexpr double kProductMinZE = 1.25;
+constexpr int kProductMaxOrder = 12;
+
 // ---------------------------------------------------------------- engine
 template <typename R>
 struct Engine {
   nct_system* s;
+  // FP64 applies H in real space (column pass T_x + V, plane pass T_yz and the projectors), FP32
+  // through (y,z)-transformed copies of the states
+  static constexpr bool RS = sizeof(R) == 8;
   const void* twx() const { return sizeof(R) == 8 ? s->tw64[0] : s->tw32[0]; }
   const void* twy() const { return sizeof(R) == 8 ? s->tw64[1] : s->tw32[1]; }
   const void* twz() const { return sizeof(R) == 8 ? s->tw64[2] : s->tw32[2]; }
@@ -503,12 +570,26 @@ struct Engine {
   }
   KTables<R> ktab(int state_off = 0) const {
     KTables<R> k;
-    k.gx = sizeof(R) == 8 ? (const R*)s->gsx64 : (const R*)s->gsx32;
-    k.gy = sizeof(R) == 8 ? (const R*)s->gsy64 : (const R*)s->gsy32;
-    k.gz = sizeof(R) == 8 ? (const R*)s->gsz64 : (const R*)s->gsz32;
+    if constexpr (!RS) {
+      k.gx = s->gsx32;
+      k.gy = s->gsy32;
+      k.gz = s->gsz32;
+    }
     k.kv = kvR();
     k.state_off = state_off;
     for (int d = 0; d < 3; ++d) k.ka[d] = R(ka[d]);
+    return k;
+  }
+  KinTables kint(int state_off = 0) const {
+    KinTables k;
+    if constexpr (RS) {
+      for (int d = 0; d < 3; ++d) {
+        k.g[d] = s->gs64[d];
+        k.ka[d] = ka[d];
+      }
+      k.kv = kvR();
+      k.state_off = state_off;
+    }
     return k;
   }
   const R* fieldsR() const { return sizeof(R) == 8 ? (const R*)s->fields : (const R*)s->fields32; }
@@ -579,7 +660,7 @@ struct Engine {
   nct_status contract(const void* W, hipStream_t st) {
     const double cpB = double(s->natoms) * s->pt.PP * s->S * 16.0;
     return check(timed_on(s, st, NCT_K_PROJ, rowsB() + beta_bytes() + cpB * s->pt.max_kchunks, proj_flops(), [&] {
-                   return launch_proj_contract<R>(s->pt, W, s->S, s->dV, s->Cpart, s->C, s->EC, st); }),
+                   return launch_proj_contract<R>(s->pt, W, s->S, s->dV, s->Cpart, s->C, s->EC, kint(), st); }),
                  "proj_contract");
   }
 
@@ -593,7 +674,7 @@ struct Engine {
     if ((r = contract(W, s->st2)) != NCT_OK) return r;
     const double ecB = double(s->natoms) * s->pt.PP * s->S * sizeof(R) * 2;
     if ((r = check(timed_on(s, s->st2, NCT_K_PROJ, beta_bytes() + ecB + rowsB(), proj_flops(), [&] {
-                     return launch_proj_scatter<R>(s->pt, s->EC, s->S, s->Y, s->st2); }), "proj_scatter")) != NCT_OK)
+                     return launch_proj_scatter<R>(s->pt, s->EC, s->S, s->Y, kint(), s->st2); }), "proj_scatter")) != NCT_OK)
       return r;
     HIPCHK(s, hipEventRecord(s->ev_proj, s->st2));
     return NCT_OK;
@@ -632,25 +713,34 @@ struct Engine {
     for (int k = 0; k < 3; ++k) out[k] = R(kMuB * B[k]);
   }
 
-  nct_status xpass(const void* src, void* dst) {
-    return check(timed(s, NCT_K_XPASS, 2 * psiB(), 0, [&] {
-                   return launch_xpass<R>(s->n, 2 * s->S, src, dst, g2x(), g2yz(), R(0.5 / double(s->N)),
-                                          0, twx(), s->st, s->cache_mode, ktab()); }), "xpass");
+  // column pass of S states from state i0 on stream st (pointers at that state): RS: dst = alpha x + c
+  // (T_x + V) w of the stage sa; FP32: dst = T src, both (y,z)-transformed
+  nct_status xpass(const void* src, void* dst, const StageArgs<R>& sa, int i0, int S, hipStream_t st) {
+    const double pb = psiB() * S / s->S;
+    const double b = RS ? 2 * pb + (sa.x_base && sa.x_base != sa.w_in ? pb : 0.0) + 4.0 * s->N * sizeof(R) : 2 * pb;
+    return check(timed_on(s, st, NCT_K_XPASS, b, 0, [&] {
+                   if constexpr (RS)
+                     return launch_xv(s->n, S, sa, dst, twx(), kint(i0), st);
+                   else
+                     return launch_xpass<R>(s->n, 2 * S, src, dst, g2x(), g2yz(), R(0.5 / double(s->N)), 0, twx(), st,
+                                            s->cache_mode, ktab(i0)); }), "xpass");
   }
-
-  nct_status plane_stage(const StageArgs<R>& sa) {
-    double b = psiB();                                     // tmp_in
-    if (sa.w_in) b += psiB();
-    if (sa.x_base && sa.x_base != sa.w_in) b += psiB();
-    b += 4.0 * s->N * sizeof(R);                           // fields
-    if (sa.Y) b += rowsB();
-    if (sa.w_out) b += psiB();
-    if (sa.tmp_out) b += psiB();
-    if (sa.W) b += rowsB();
-    if (sa.acc) b += 2 * psiB();
-    return check(timed(s, NCT_K_PLANE_STAGE, b, 0, [&] {
-                   return launch_plane_stage<R>(s->n, s->S, sa, s->pt, twy(), twz(), s->st); }),
-                 "plane_stage");
+  nct_status plane_pass(const StageArgs<R>& sa, int i0, int S, hipStream_t st) {
+    const double pb = psiB() * S / s->S, rb = rowsB() * S / s->S;
+    double b = pb;                                         // tmp_in
+    if (sa.w_in) b += pb;
+    if (!RS) {
+      if (sa.x_base && sa.x_base != sa.w_in) b += pb;
+      b += 4.0 * s->N * sizeof(R);                         // fields
+    }
+    if (sa.Y) b += rb;
+    if (sa.w_out) b += pb;
+    if (sa.tmp_out) b += pb;
+    if (sa.W) b += rb;
+    if (sa.acc) b += 2 * pb;
+    return check(timed_on(s, st, NCT_K_PLANE_STAGE, b, 0, [&] {
+                   if constexpr (RS) return launch_plane_yz(s->n, S, sa, kint(i0), s->pt, twy(), twz(), st);
+                   else return launch_plane_stage(s->n, S, sa, s->pt, twy(), twz(), st); }), "plane_stage");
   }
 
   // ---- state groups
@@ -692,8 +782,9 @@ struct Engine {
   }
 
   // One H application of a state group: projector chain of rows cW (second stream, joined
-  // before the plane pass), column pass of chat into tmp, fused plane pass described by sa
-  // (full-size pointers; offset here to the group).
+  // before the plane pass), column pass into tmp (FP32: of chat, the transformed copy of w), plane pass
+  // described by sa
+  // (full-size pointers; offset here to the group).  FP32 only:
   // kin_dst: column-pass output buffer (default s->tmp); chat == nullptr: skip the column pass,
   // sa_full.tmp_in already holds it.
   nct_status stage_group(const Group& g, const void* cW, const void* chat, const StageArgs<R>& sa_full,
@@ -708,23 +799,15 @@ struct Engine {
       if ((r = check(timed_on(s, g.st2, NCT_K_PROJ, frac * (rowsB() + beta_bytes()) + cpB * s->pt.max_kchunks,
                               frac * proj_flops(), [&] {
                                 return launch_proj_contract<R>(s->pt, offr(cW, g.i0), g.S, s->dV, g.Cpart, g.C,
-                                                               g.EC, g.st2); }), "proj_contract")) != NCT_OK)
+                                                               g.EC, kint(g.i0), g.st2); }), "proj_contract")) != NCT_OK)
         return r;
       const double ecB = double(s->natoms) * s->pt.PP * g.S * sizeof(R) * 2;
       if ((r = check(timed_on(s, g.st2, NCT_K_PROJ, beta_bytes() + ecB + frac * rowsB(), frac * proj_flops(), [&] {
-                       return launch_proj_scatter<R>(s->pt, g.EC, g.S, offr(ybuf, g.i0), g.st2); }),
+                       return launch_proj_scatter<R>(s->pt, g.EC, g.S, offr(ybuf, g.i0), kint(g.i0), g.st2); }),
                      "proj_scatter")) != NCT_OK)
         return r;
       HIPCHK(s, hipEventRecord(g.ev_proj, g.st2));
     }
-    if (chat) {
-      void* dst = kin_dst ? kin_dst : s->tmp;
-      if ((r = check(timed_on(s, g.st, NCT_K_XPASS, 2 * psiB() * frac, 0, [&] {
-             return launch_xpass<R>(s->n, 2 * g.S, offs(chat, g.i0), offs(dst, g.i0), g2x(), g2yz(),
-                                    R(0.5 / double(s->N)), 0, twx(), g.st, s->cache_mode, ktab(g.i0)); }), "xpass")) != NCT_OK)
-        return r;
-    }
-    if (s->natoms && !y_src) HIPCHK(s, hipStreamWaitEvent(g.st, g.ev_proj, 0));
     StageArgs<R> sa = sa_full;
     sa.tmp_in = offs(sa.tmp_in, g.i0);
     sa.tmp_out = offs(sa.tmp_out, g.i0);
@@ -735,22 +818,30 @@ struct Engine {
     sa.Y = s->natoms ? offr(y_src ? y_src : ybuf, g.i0) : nullptr;
     sa.W = offr(sa.W, g.i0);
     sa.state_off = g.i0;
-    double b = psiB();
-    if (sa.w_in) b += psiB();
-    if (sa.x_base && sa.x_base != sa.w_in) b += psiB();
-    if (sa.Y) b += rowsB();
-    if (sa.w_out) b += psiB();
-    if (sa.tmp_out) b += psiB();
-    if (sa.W) b += rowsB();
-    if (sa.acc) b += 2 * psiB();
-    b = b * frac + 4.0 * s->N * sizeof(R);
-    return check(timed_on(s, g.st, NCT_K_PLANE_STAGE, b, 0, [&] {
-                   return launch_plane_stage<R>(s->n, g.S, sa, s->pt, twy(), twz(), g.st); }),
-                 "plane_stage");
+    if (chat && (r = xpass(offs(chat, g.i0), offs(kin_dst ? kin_dst : s->tmp, g.i0), sa, g.i0, g.S, g.st)) != NCT_OK)
+      return r;
+    if (s->natoms && !y_src) HIPCHK(s, hipStreamWaitEvent(g.st, g.ev_proj, 0));
+    return plane_pass(sa, g.i0, g.S, g.st);
   }
 
   // imaginary time: when > 0, taylor() forms T_K(-imag_tau H) x (real Horner coefficients)
   double imag_tau = 0.0;
+
+  // FP64: T_K(z H) x, z = -i a or -imag_tau, as stages w_k = w_{k-1} + c_k H w_{k-1}, c_k = -z / r_k
+  // (the base of every stage is its own w: one state-sized read less than the Horner stages' x)
+  bool product_form(double z) const {
+    if (!RS || s->prm.taylor_order > kProductMaxOrder) return false;
+    double emax = 0.0;
+    for (int d = 0; d < 3; ++d) {
+      const double g = kPi * s->n[d] / s->prm.cell[d];
+      emax += 0.5 * g * g;
+    }
+    return z * emax >= kProductMinZE;
+  }
+  std::complex<double> product_coeff(int k, double a) const {
+    const std::complex<double> z = imag_tau > 0.0 ? std::complex<double>(-imag_tau, 0.0) : std::complex<double>(0.0, -a);
+    return -z / s->roots[k - 1];
+  }
 
   // Horner coefficient of stage k: -i a/(K-k+1), or -imag_tau/(K-k+1) in imaginary time
   void set_coeff(StageArgs<R>& sa, int k, int K, double a) const {
@@ -763,10 +854,11 @@ struct Engine {
     }
   }
 
-  // T_K(-i a H) x by Horner stages w_k = x + (-i a/(K-k+1)) H w_{k-1}, w_0 = x.
+  // T_K(-i a H) x by Horner stages w_k = x + (-i a/(K-k+1)) H w_{k-1}, w_0 = x, or in product form.
   // stage_out[k-1] (k = 1..K-1), if given, receives w_k (the adjoint tape); else the work buffer.
   // kin_save: keep the first stage's column pass in this buffer; kin_reuse: take the first
   // stage's column pass from this buffer instead of recomputing it (same x, fields-independent).
+  // (FP32 only: in FP64 the column pass takes the fields as well.)
   // y_save / y_reuse: the same for the first stage's projector scatter rows (they depend on x
   // and the Bloch phases only).
   nct_status taylor(const void* x, const void* xhat, const void* xW, void* out, void* outhat,
@@ -782,10 +874,12 @@ struct Engine {
     sa.kv = kvR();
     externals(t, sa);
     sa.fields = fieldsR();
+    if (RS) kin_save = nullptr, kin_reuse = nullptr;
     nct_status r;
     Group G[2];
     const int ng = groups(G);
     if ((r = fork_groups()) != NCT_OK) return r;
+    const bool product = product_form(imag_tau > 0.0 ? imag_tau : a);
     for (int k = 1; k <= K; ++k) {
       const bool last = (k == K);
       const bool first = (k == 1);
@@ -793,11 +887,17 @@ struct Engine {
       if (first && kin_reuse) sa.tmp_in = kin_reuse;
       if (first && kin_save) sa.tmp_in = kin_save;
       sa.w_in = cw;
-      sa.x_base = x;
+      sa.x_base = product ? cw : x;
       sa.alpha = R(1);
-      set_coeff(sa, k, K, a);
+      if (product) {
+        const std::complex<double> c = product_coeff(k, a);
+        sa.cre = R(c.real());
+        sa.cim = R(c.imag());
+      } else {
+        set_coeff(sa, k, K, a);
+      }
       sa.w_out = last ? out : (stage_out ? stage_out[k - 1] : s->wbuf);
-      sa.tmp_out = last ? outhat : s->tmp;
+      sa.tmp_out = RS ? nullptr : (last ? outhat : s->tmp);
       sa.W = s->natoms ? (last ? outW : s->Wwork) : nullptr;
       sa.acc = nullptr;
       for (int gi = 0; gi < ng; ++gi)
@@ -805,39 +905,49 @@ struct Engine {
                              first ? y_save : nullptr, first ? y_reuse : nullptr)) != NCT_OK)
           return r;
       cw = sa.w_out;
-      chat = sa.tmp_out;
+      chat = RS ? sa.w_out : sa.tmp_out;
       cW = sa.W;
     }
     return join_groups();
   }
 
-  // The next step's first column pass (kinetic part for psi^ at time t) into s->tmp on stK, so
+  // FP32: the next step's first column pass (kinetic part for psi^ at time t) into s->tmp on stK, so
   // that it overlaps the density and field update that follow on st; that step's first Taylor
   // stage takes it as kin_reuse after waiting for evK_out.
   nct_status early_kinetic(double t) {
+    if (RS) return NCT_OK;  // the FP64 column pass takes the new fields
     at_time(t);
     HIPCHK(s, hipEventRecord(s->evK_in, s->st));
     HIPCHK(s, hipStreamWaitEvent(s->stK, s->evK_in, 0));
-    nct_status r = check(timed_on(s, s->stK, NCT_K_XPASS, 2 * psiB(), 0, [&] {
-                           return launch_xpass<R>(s->n, 2 * s->S, s->psihat, s->tmp, g2x(), g2yz(),
-                                                  R(0.5 / double(s->N)), 0, twx(), s->stK, s->cache_mode,
-                                                  ktab()); }), "xpass");
+    nct_status r = xpass(s->psihat, s->tmp, StageArgs<R>{}, 0, s->S, s->stK);
     if (r != NCT_OK) return r;
     HIPCHK(s, hipEventRecord(s->evK_out, s->stK));
     return NCT_OK;
   }
 
-  nct_status prepare(const void* psi, void* hat, void* W) {
+  // What the first stage needs of states that no plane pass has just written: their sphere rows, and
+  // in FP32 their (y,z) transform into hat.  Returns in chat what the column pass takes.
+  nct_status prepare(const void* psi, void* hat, void* W, const void** chat = nullptr) {
+    if (chat) *chat = RS ? psi : hat;
+    if constexpr (RS) {
+      if (s->natoms == 0) return NCT_OK;
+      return check(timed(s, NCT_K_PLANE_FWD, 2 * rowsB(), 0, [&] {
+                     return launch_gather_rows(s->pt, psi, W, 2 * s->S, s->N, s->st); }), "gather");
+    } else
     return check(timed(s, NCT_K_PLANE_FWD, 2 * psiB() + (s->natoms ? rowsB() : 0.0), 0, [&] {
                    return launch_plane_fwd<R>(s->n, 2 * s->S, psi, hat, s->natoms ? W : nullptr, &s->pt,
                                               twy(), twz(), s->st, ktab()); }), "plane_fwd");
   }
 
-  nct_status obs_row(double t, double* row) {
+  nct_status obs_row(const void* psi, double t, double* row) {
     nct_status r;
     int ntiles = 0;
     at_time(t);
-    if ((r = check(timed(s, NCT_K_OBS, psiB(), 0, [&] {
+    if ((r = check(timed(s, NCT_K_OBS, (RS ? 2 : 1) * psiB(), 0, [&] {
+           if constexpr (RS)
+             return launch_energy_real(s->n, 2 * s->S, psi, twx(), twy(), twz(), kint(), s->epart, s->eplane, &ntiles,
+                                       s->st);
+           else
            return launch_xpass_energy<R>(s->n, 2 * s->S, s->psihat, g2x(), g2yz(), R(0.5 / double(s->N)),
                                          twx(), s->epart, &ntiles, s->st, ktab()); }), "energy")) != NCT_OK)
       return r;
@@ -848,6 +958,8 @@ struct Engine {
     in.field_tot = s->ftot;
     in.epart = s->epart;
     in.ntiles = ntiles;
+    in.eplane = s->eplane;
+    in.nplanes = RS ? s->n[0] : 0;
     in.C = s->natoms ? s->C : nullptr;
     in.energy = s->energy_dev;
     in.occ = s->occ;
@@ -856,7 +968,7 @@ struct Engine {
     in.PP = s->pt.PP;
     in.precision = s->prm.precision;
     in.dV = s->dV;
-    in.invN = 1.0 / double(s->N);
+    in.invN = RS ? 1.0 : 1.0 / double(s->N);
     in.t = t;
     double B[3] = {0, 0, 0}, E[3] = {0, 0, 0};
     if (!s->frozen) {
@@ -902,7 +1014,8 @@ struct Engine {
       T->t0 = t0;
     }
     at_time(t0);
-    if ((r = prepare(cur, s->psihat, s->Wpsi)) != NCT_OK) return r;
+    const void* hcur = nullptr;  // what the column pass of cur takes
+    if ((r = prepare(cur, s->psihat, s->Wpsi, &hcur)) != NCT_OK) return r;
     if (nsteps > 0 && (r = early_kinetic(t0)) != NCT_OK) return r;
     if (!s->frozen) {
       if ((r = density(cur)) != NCT_OK) return r;
@@ -944,15 +1057,16 @@ struct Engine {
         next = (k + 1 < nsteps) ? tvec(*T, k + 1, 0) : psi;
       }
       // the first column pass ran early on stK (early_kinetic)
-      HIPCHK(s, hipStreamWaitEvent(s->st, s->evK_out, 0));
-      if ((r = taylor(cur, s->psihat, s->Wpsi, phi, s->phihat, s->Wphi, t, T ? so1.data() : nullptr, nullptr,
+      if (!RS) HIPCHK(s, hipStreamWaitEvent(s->st, s->evK_out, 0));
+      if ((r = taylor(cur, hcur, s->Wpsi, phi, s->phihat, s->Wphi, t, T ? so1.data() : nullptr, nullptr,
                       s->tmp)) != NCT_OK)
         return r;
       // the second and third exponentials share phi's kinetic column pass and first scatter rows
       // unless the kinetic term and the projector phases depend on time (velocity-gauge laser)
       const bool vg = velocity_gauge(s);
       void* yphi = (vg || !s->natoms) ? nullptr : s->Yphi;
-      if ((r = taylor(phi, s->phihat, s->Wphi, ptil, nullptr, nullptr, t, T ? so2.data() : nullptr,
+      const void* hphi = RS ? phi : s->phihat;
+      if ((r = taylor(phi, hphi, s->Wphi, ptil, nullptr, nullptr, t, T ? so2.data() : nullptr,
                       vg ? nullptr : s->tmpk_phi, nullptr, yphi)) != NCT_OK)
         return r;
       if (!s->frozen) {
@@ -960,18 +1074,19 @@ struct Engine {
         if ((r = fields_from_rho(true)) != NCT_OK) return r;
       }
       if (T && (r = save_fields(*T, k, 1)) != NCT_OK) return r;
-      if (vg && s->natoms) {  // phi's rows were gathered under A(t): carry them to A(t + dt)
+      if (!RS && vg && s->natoms) {  // phi's rows were gathered under A(t): carry them to A(t + dt)
         double a0[3], a1[3], dA[3];
         vector_potential_at(s, t, a0);
         vector_potential_at(s, t + dt, a1);
         for (int d = 0; d < 3; ++d) dA[d] = a1[d] - a0[d];
-        if ((r = check(launch_rephase_rows<R>(s->pt, s->Wphi, s->S, dA, s->st), "rephase")) != NCT_OK)
-          return r;
+        if constexpr (!RS)
+          if ((r = check(launch_rephase_rows<R>(s->pt, s->Wphi, s->S, dA, s->st), "rephase")) != NCT_OK) return r;
       }
-      if ((r = taylor(phi, s->phihat, s->Wphi, next, s->psihat, s->Wpsi, t + dt, T ? so3.data() : nullptr,
+      if ((r = taylor(phi, hphi, s->Wphi, next, s->psihat, s->Wpsi, t + dt, T ? so3.data() : nullptr,
                       nullptr, vg ? nullptr : s->tmpk_phi, nullptr, yphi)) != NCT_OK)
         return r;
       cur = next;
+      hcur = RS ? cur : s->psihat;
       if (k + 1 < nsteps && (r = early_kinetic(t + dt)) != NCT_OK) return r;
       if (!s->frozen || obs_host) {
         if ((r = density(cur)) != NCT_OK) return r;
@@ -981,7 +1096,7 @@ struct Engine {
         if (r != NCT_OK) return r;
       }
       if (obs_host) {
-        if ((r = obs_row(t + dt, s->obs_dev + size_t(k) * kObsWidth)) != NCT_OK) return r;
+        if ((r = obs_row(cur, t + dt, s->obs_dev + size_t(k) * kObsWidth)) != NCT_OK) return r;
       }
     }
     if (s->frozen && !obs_host) {  // frozen fields: one density at the end for the finiteness check
@@ -1019,17 +1134,21 @@ struct Engine {
     return NCT_OK;
   }
 
-  // Adjoint of one Taylor exponential w_K = T(-i a H) x (Horner stages, fields frozen):
-  // given mu_K = lam_out, mu_{k-1} = conj(c_k) H mu_k, lam_x = sum_{k=0}^{K} mu_k (into acc,
-  // which is set to mu_K first when acc_init, else mu_K is added), and for each stage the pair
-  // term of dL/d(v, b) into g.  xs[k] = w_k (k = 0..K-1) from the forward tape.
+  // Adjoint of one Taylor exponential w_K = T(-i a H) x (fields frozen), given mu_K = lam_out:
+  //   Horner stages:  mu_{k-1} = conj(c_k) H mu_k, lam_x = sum_{k=0}^{K} mu_k;
+  //   product stages: mu_{k-1} = mu_k + conj(c_k) H mu_k, lam_x = mu_0.
+  // lam_x goes into acc (set when acc_init, else added), the pair term of dL/d(v, b) of each stage
+  // into g.  xs[k] = w_k (k = 0..K-1) from the forward tape.
   nct_status adjoint_taylor(const void* lam_out, void* const* xs, void* acc, bool acc_init, double* g,
                             double t) {
     nct_status r;
     const int K = s->prm.taylor_order;
     const double a = 0.5 * s->prm.dt;
     const size_t cnt = size_t(s->S) * 2 * s->N;
-    if (acc_init) {
+    const bool product = product_form(a);
+    if (product) {
+      // nothing to accumulate but mu_0
+    } else if (acc_init) {
       HIPCHK(s, hipMemcpyAsync(acc, lam_out, size_t(psiB()), hipMemcpyDeviceToDevice, s->st));
     } else {
       if ((r = check(timed(s, NCT_K_ADJOINT, 3 * psiB(), 0, [&] {
@@ -1041,29 +1160,32 @@ struct Engine {
     sa.kv = kvR();
     externals(t, sa);  // first: the rows gathered below carry the Bloch phases at time t
     sa.fields = fieldsR();
-    if ((r = prepare(lam_out, s->tmp, s->Wwork)) != NCT_OK) return r;
+    const void* chat = nullptr;
+    if ((r = prepare(lam_out, s->tmp, s->Wwork, &chat)) != NCT_OK) return r;
     const void* cur = lam_out;
     for (int k = K; k >= 1; --k) {
-      const double gamma = a / double(K - k + 1);
+      const std::complex<double> c =
+          product ? product_coeff(k, a) : std::complex<double>(0.0, -a / double(K - k + 1));
       if ((r = check(timed(s, NCT_K_ADJOINT, 2 * psiB() + 64.0 * s->N, 0, [&] {
-             return launch_pair<R>(cur, xs[k - 1], s->S, s->N, gamma, g, s->st); }), "pair")) != NCT_OK)
+             return launch_pair<R>(cur, xs[k - 1], s->S, s->N, c.real(), c.imag(), g, s->st); }), "pair")) != NCT_OK)
         return r;
       if ((r = projections(s->Wwork)) != NCT_OK) return r;
-      if ((r = xpass(s->tmp, s->tmp)) != NCT_OK) return r;
-      if ((r = join_projections()) != NCT_OK) return r;
       sa.tmp_in = s->tmp;
       sa.w_in = cur;
-      sa.x_base = nullptr;
-      sa.alpha = R(0);
-      sa.cre = R(0);
-      sa.cim = R(gamma);
+      sa.x_base = product ? cur : nullptr;
+      sa.alpha = product ? R(1) : R(0);
+      sa.cre = R(c.real());
+      sa.cim = R(-c.imag());
+      if ((r = xpass(chat, s->tmp, sa, 0, s->S, s->st)) != NCT_OK) return r;
+      if ((r = join_projections()) != NCT_OK) return r;
       sa.Y = s->natoms ? s->Y : nullptr;
-      sa.w_out = s->wbuf;
-      sa.tmp_out = k > 1 ? s->tmp : nullptr;
+      sa.w_out = product && k == 1 && acc_init ? acc : s->wbuf;
+      sa.tmp_out = (!RS && k > 1) ? s->tmp : nullptr;
       sa.W = (s->natoms && k > 1) ? s->Wwork : nullptr;
-      sa.acc = acc;
-      if ((r = plane_stage(sa)) != NCT_OK) return r;
-      cur = s->wbuf;
+      sa.acc = !product || (k == 1 && !acc_init) ? acc : nullptr;
+      if ((r = plane_pass(sa, 0, s->S, s->st)) != NCT_OK) return r;
+      cur = sa.w_out;
+      chat = RS ? cur : s->tmp;
     }
     return NCT_OK;
   }
@@ -1117,7 +1239,7 @@ struct Engine {
       xs3[j] = tvec(T, idx, 2 * K + j - 1);
     }
     void* lamphi = s->phi;
-    void* lamtil = s->phihat;
+    void* lamtil = RS ? s->tmpk_phi : s->phihat;
     // third exponential, fields of H~ at t_{n+1}
     if ((r = load_fields(tfld(T, idx, 1))) != NCT_OK) return r;
     HIPCHK(s, hipMemsetAsync(s->gA, 0, gb, s->st));
@@ -1241,13 +1363,14 @@ struct Engine {
     imag_tau = tau;
     for (int it = 0; it < niter; ++it) {
       at_time(0.0);
-      if ((r = prepare(psi, s->psihat, s->Wpsi)) != NCT_OK) break;
-      if ((r = taylor(psi, s->psihat, s->Wpsi, s->phi, nullptr, nullptr, 0.0)) != NCT_OK) break;
+      const void* hpsi = nullptr;
+      if ((r = prepare(psi, s->psihat, s->Wpsi, &hpsi)) != NCT_OK) break;
+      if ((r = taylor(psi, hpsi, s->Wpsi, s->phi, nullptr, nullptr, 0.0)) != NCT_OK) break;
       if ((r = orthonormalize(s->phi, psi)) != NCT_OK) break;
       if ((r = density(psi)) != NCT_OK) break;
       if ((r = fields_from_rho(!s->frozen)) != NCT_OK) break;
       if ((r = prepare(psi, s->psihat, s->Wpsi)) != NCT_OK) break;
-      if ((r = obs_row(0.0, s->obs_dev + size_t(it) * kObsWidth)) != NCT_OK) break;
+      if ((r = obs_row(psi, 0.0, s->obs_dev + size_t(it) * kObsWidth)) != NCT_OK) break;
     }
     imag_tau = 0.0;
     if (r != NCT_OK) return r;
@@ -1267,10 +1390,9 @@ struct Engine {
   nct_status apply(const void* psi, void* hpsi, double t) {
     nct_status r;
     at_time(t);
-    if ((r = prepare(psi, s->tmp, s->Wwork)) != NCT_OK) return r;
+    const void* chat = nullptr;
+    if ((r = prepare(psi, s->tmp, s->Wwork, &chat)) != NCT_OK) return r;
     if ((r = projections(s->Wwork)) != NCT_OK) return r;
-    if ((r = xpass(s->tmp, s->tmp)) != NCT_OK) return r;
-    if ((r = join_projections()) != NCT_OK) return r;
     StageArgs<R> sa;
     sa.cache_mode = s->cache_mode;
     sa.kv = kvR();
@@ -1282,9 +1404,11 @@ struct Engine {
     sa.alpha = R(0);
     sa.cre = R(1);
     sa.cim = R(0);
+    if ((r = xpass(chat, s->tmp, sa, 0, s->S, s->st)) != NCT_OK) return r;
+    if ((r = join_projections()) != NCT_OK) return r;
     sa.Y = s->natoms ? s->Y : nullptr;
     sa.w_out = hpsi;
-    return plane_stage(sa);
+    return plane_pass(sa, 0, s->S, s->st);
   }
 };
 
@@ -1303,11 +1427,13 @@ nct_status build_fft_tables(nct_system* s) {
       t32[2 * e + 1] = float(t64[2 * e + 1]);
     }
     double* p64;
-    float* p32;
     if ((r = upload(s, t64, &p64)) != NCT_OK) return r;
-    if ((r = upload(s, t32, &p32)) != NCT_OK) return r;
     s->tw64[d] = p64;
-    s->tw32[d] = p32;
+    if (!s->fp64) {
+      float* p32;
+      if ((r = upload(s, t32, &p32)) != NCT_OK) return r;
+      s->tw32[d] = p32;
+    }
   }
   std::vector<int> kx = dif_position_to_freq(s->n[0]);
   std::vector<int> ky = dif_position_to_freq(s->n[1]);
@@ -1323,6 +1449,17 @@ nct_status build_fft_tables(nct_system* s) {
       const double g2 = gval(kz[j], s->n[2], s->prm.cell[2]);
       gyz[size_t(i) * s->n[2] + j] = g1 * g1 + g2 * g2;
     }
+  if ((r = upload(s, gx, &s->g2x64)) != NCT_OK) return r;
+  if ((r = upload(s, gyz, &s->g2yz64)) != NCT_OK) return r;
+  if (s->fp64) {  // real-space form: one line of G per axis
+    const std::vector<int>* kk[3] = {&kx, &ky, &kz};
+    for (int d = 0; d < 3; ++d) {
+      std::vector<double> g(s->n[d]);
+      for (int i = 0; i < s->n[d]; ++i) g[i] = gval((*kk[d])[i], s->n[d], s->prm.cell[d]);
+      if ((r = upload(s, g, &s->gs64[d])) != NCT_OK) return r;
+    }
+    return NCT_OK;
+  }
   std::vector<double> sx(s->n[0]), sy(size_t(s->n[1]) * s->n[2]), sz(size_t(s->n[1]) * s->n[2]);
   for (int i = 0; i < s->n[0]; ++i) sx[i] = gval(kx[i], s->n[0], s->prm.cell[0]);
   for (int i = 0; i < s->n[1]; ++i)
@@ -1331,15 +1468,10 @@ nct_status build_fft_tables(nct_system* s) {
       sz[size_t(i) * s->n[2] + j] = gval(kz[j], s->n[2], s->prm.cell[2]);
     }
   std::vector<float> sx32(sx.begin(), sx.end()), sy32(sy.begin(), sy.end()), sz32(sz.begin(), sz.end());
-  if ((r = upload(s, sx, &s->gsx64)) != NCT_OK) return r;
-  if ((r = upload(s, sy, &s->gsy64)) != NCT_OK) return r;
-  if ((r = upload(s, sz, &s->gsz64)) != NCT_OK) return r;
   if ((r = upload(s, sx32, &s->gsx32)) != NCT_OK) return r;
   if ((r = upload(s, sy32, &s->gsy32)) != NCT_OK) return r;
   if ((r = upload(s, sz32, &s->gsz32)) != NCT_OK) return r;
   std::vector<float> gx32(gx.begin(), gx.end()), gyz32(gyz.begin(), gyz.end());
-  if ((r = upload(s, gx, &s->g2x64)) != NCT_OK) return r;
-  if ((r = upload(s, gyz, &s->g2yz64)) != NCT_OK) return r;
   if ((r = upload(s, gx32, &s->g2x32)) != NCT_OK) return r;
   if ((r = upload(s, gyz32, &s->g2yz32)) != NCT_OK) return r;
   return NCT_OK;
@@ -1439,6 +1571,7 @@ nct_status create_impl(const nct_params* p, nct_system** out) {
   s->S = p->nstates;
   s->dV = p->cell[0] * p->cell[1] * p->cell[2] / double(s->N);
   s->fp64 = p->precision == NCT_FP64;
+  s->roots = taylor_roots(p->taylor_order);
   s->cbytes = s->fp64 ? 16 : 8;
   s->cache_mode = stream_cache_mode(size_t(2) * s->S * s->N * s->cbytes);
   s->st = static_cast<hipStream_t>(p->stream);
@@ -1465,8 +1598,10 @@ nct_status create_impl(const nct_params* p, nct_system** out) {
   s->fields = (double*)p0;
   if ((r = dalloc(s, 4 * N * 8, &p0)) != NCT_OK) return bail(r);
   s->fields_scr = (double*)p0;
-  if ((r = dalloc(s, 4 * N * 4, &p0)) != NCT_OK) return bail(r);
-  s->fields32 = (float*)p0;
+  if (!s->fp64) {
+    if ((r = dalloc(s, 4 * N * 4, &p0)) != NCT_OK) return bail(r);
+    s->fields32 = (float*)p0;
+  }
   if ((r = dalloc(s, N * 16, &s->ncpx)) != NCT_OK) return bail(r);
   if ((r = dalloc(s, ((N + 255) / 256) * kFieldTot * 8, &p0)) != NCT_OK) return bail(r);
   s->fpart = (double*)p0;
@@ -1475,10 +1610,16 @@ nct_status create_impl(const nct_params* p, nct_system** out) {
   const size_t nyz = size_t(p->n[1]) * p->n[2];
   if ((r = dalloc(s, size_t(2 * s->S) * (nyz / 16) * 2 * 8, &p0)) != NCT_OK) return bail(r);
   s->epart = (double*)p0;
+  if (s->fp64) {
+    if ((r = dalloc(s, size_t(2 * s->S) * p->n[0] * 8, &p0)) != NCT_OK) return bail(r);
+    s->eplane = (double*)p0;
+  }
   const size_t psib = size_t(s->S) * 2 * N * s->cbytes;
-  if ((r = dalloc(s, psib, &s->psihat)) != NCT_OK) return bail(r);
+  if (!s->fp64) {
+    if ((r = dalloc(s, psib, &s->psihat)) != NCT_OK) return bail(r);
+    if ((r = dalloc(s, psib, &s->phihat)) != NCT_OK) return bail(r);
+  }
   if ((r = dalloc(s, psib, &s->phi)) != NCT_OK) return bail(r);
-  if ((r = dalloc(s, psib, &s->phihat)) != NCT_OK) return bail(r);
   if ((r = dalloc(s, psib, &s->wbuf)) != NCT_OK) return bail(r);
   if ((r = dalloc(s, psib, &s->tmp)) != NCT_OK) return bail(r);
   if ((r = dalloc(s, psib, &s->tmpk_phi)) != NCT_OK) return bail(r);

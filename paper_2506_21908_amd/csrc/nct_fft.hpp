@@ -198,6 +198,10 @@ __host__ __device__ constexpr int plan_span(int N, int s) {
   return L;
 }
 
+// Nothing is scheduled across this point: it keeps the loads of a later batch from being hoisted,
+// whose registers would spill.
+__device__ __forceinline__ void sched_fence() { __builtin_amdgcn_sched_barrier(0); }
+
 // ---------------------------------------------------------------- one LDS stage
 // NCT_TW_PRODUCTS (tuning macro): FP64 radix-8 butterflies read w1, w2 and w4 (1), w1 and w2 (2)
 // or w1 (3) from the table and form the other twiddles as products (at most three roundings).
@@ -362,6 +366,77 @@ __device__ __forceinline__ void stage_to(const cpx<R>* lds, const cpx<R>* tw, in
         st(line * GLS + (k0 + q * M) * GES, line * LS + (k0 + q * M) * ES, x[q], u[k][q]);
     }
   }
+}
+
+// The same stage by one wave on lines of its own (lane: 0..63), unrolled.  Surplus lanes of a partial
+// round repeat the last item: all lanes read before any writes, so they write the same values.
+template <typename R, int N, int STAGE, int NLINES, int LS, int ES, bool FWD>
+__device__ __forceinline__ void wave_stage(cpx<R>* lds, const cpx<R>* tw, int lane) {
+  constexpr int RAD = plan_radix(N, STAGE);
+  constexpr int SPAN = plan_span(N, STAGE);
+  constexpr int M = SPAN / RAD;
+  constexpr int TOTAL = NLINES * (N / RAD);
+  constexpr int IT = (TOTAL + 63) / 64;
+#pragma unroll
+  for (int u = 0; u < IT; ++u) {
+    const int it = min(lane + 64 * u, TOTAL - 1);
+    {
+      const int bfi = it / NLINES;
+      const int blk = bfi / M;
+      const int b = bfi - blk * M;
+      cpx<R>* base = lds + (it % NLINES) * LS + (blk * SPAN + b) * ES;
+      cpx<R> x[RAD];
+#pragma unroll
+      for (int q = 0; q < RAD; ++q) x[q] = base[q * M * ES];
+      stage_butterfly<R, N, STAGE, FWD>(x, tw, b);
+#pragma unroll
+      for (int q = 0; q < RAD; ++q) base[q * M * ES] = x[q];
+    }
+    if (u + 1 < IT) sched_fence();
+  }
+}
+
+// Middle of a forward-multiply-inverse transform by one wave: the last forward stage, the factor
+// mult(line, k) of every position k, and the first inverse stage.  Both stages work on the same RAD
+// consecutive positions without twiddles, so the values stay in registers in between.
+template <typename R, int N, int NLINES, int LS, int ES, typename MULT>
+__device__ __forceinline__ void wave_middle(cpx<R>* lds, int lane, MULT mult) {
+  constexpr int RAD = plan_radix(N, plan_nstages(N) - 1);
+  constexpr int TOTAL = NLINES * (N / RAD);
+  constexpr int IT = (TOTAL + 63) / 64;
+#pragma unroll
+  for (int u = 0; u < IT; ++u) {
+    const int it = min(lane + 64 * u, TOTAL - 1);
+    {
+      const int line = it % NLINES;
+      const int k0 = (it / NLINES) * RAD;
+      cpx<R>* base = lds + line * LS + k0 * ES;
+      cpx<R> x[RAD];
+#pragma unroll
+      for (int q = 0; q < RAD; ++q) x[q] = base[q * ES];
+      dft<R, -1, RAD>(x);
+#pragma unroll
+      for (int q = 0; q < RAD; ++q) x[q] = cscale(x[q], mult(line, k0 + q));
+      dft<R, +1, RAD>(x);
+#pragma unroll
+      for (int q = 0; q < RAD; ++q) base[q * ES] = x[q];
+    }
+    if (u + 1 < IT) sched_fence();
+  }
+}
+
+// Order the LDS operations of one wave: what a lane wrote before is read by any lane after.  The
+// hardware keeps a wave's LDS operations in order, so this only holds the compiler to it.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+// The same over a workgroup of NW waves.
+template <int NW>
+__device__ __forceinline__ void group_sync() {
+  if constexpr (NW == 1) wave_sync();
+  else __syncthreads();
 }
 
 // All stages of a line transform, a barrier after each stage.

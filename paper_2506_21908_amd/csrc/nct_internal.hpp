@@ -13,6 +13,7 @@ struct cpx;
 // Projector tables on the device.  Sphere rows of all atoms are numbered
 // J = 0..Jtot-1; atom a owns rows [row_off[a], row_off[a] + ns[a]), sorted by
 // flat grid index, so the rows of one x-plane form a contiguous range.
+constexpr int kRowMask = (1 << 30) - 1, kRowMore = 1 << 30;
 struct ProjTables {
   int natoms = 0;
   int P = 0;            // projectors per atom
@@ -25,6 +26,9 @@ struct ProjTables {
   const int* pr_off = nullptr;    // [NX+1] plane -> range list
   const int* pr_begin = nullptr;  // [nranges]
   const int* pr_end = nullptr;    // [nranges]
+  const int* rflat = nullptr;     // [Jtot] flat grid index of each row
+  const int* pmap = nullptr;      // [N] first row at a grid point, + kRowMore if there are further ones; -1: none
+  const int* rnext = nullptr;     // [Jtot] next row at the same grid point (spheres overlap), -1: none
   const void* beta = nullptr;     // complex R [Jtot][2][PP]
   const void* disp = nullptr;     // R [Jtot][3]: displacement of each sphere row from its atom
   const double* energy = nullptr; // [natoms][PP] (0 beyond P)
@@ -32,8 +36,8 @@ struct ProjTables {
 
 template <typename R>
 struct StageArgs {
-  const void* tmp_in = nullptr;   // kinetic-applied mixed representation of w_in
-  void* tmp_out = nullptr;        // 2D (y,z) transform of w_out, or null
+  const void* tmp_in = nullptr;   // column-pass output: FP64 alpha x + c (T_x + V) w_in; FP32 T w_in, (y,z)-transformed
+  void* tmp_out = nullptr;        // FP32: 2D (y,z) transform of w_out, or null
   const void* w_in = nullptr;     // real-space input of this H application
   const void* x_base = nullptr;   // Taylor base x (null: alpha ignored)
   void* w_out = nullptr;          // alpha x + c H w_in
@@ -68,9 +72,34 @@ struct KTables {
   R ka[3] = {0, 0, 0};     // velocity-gauge vector potential added to every Bloch vector
 };
 
+// Kinetic factors of the real-space (FP64) form: signed G per axis (digit-reversed order of the line
+// transforms) and, with Bloch vectors (k-points, or the velocity gauge), the shift G + k of each state.
+struct KinTables {
+  const double* g[3] = {nullptr, nullptr, nullptr};
+  const double* kv = nullptr;        // [S][3], null: Gamma only
+  int state_off = 0;                 // this launch's state 0 is state state_off of kv
+  double ka[3] = {0, 0, 0};          // velocity-gauge vector potential added to every Bloch vector
+  __host__ __device__ double shift(int i, int d) const {
+    return kv ? kv[3 * size_t(state_off + i) + d] + ka[d] : 0.0;
+  }
+};
+
 // Launchers (return hipError_t of the launch).  n = {NX, NY, NZ}.
-template <typename R>
-hipError_t launch_plane_stage(const int n[3], int S, const StageArgs<R>& a, const ProjTables& pt,
+// FP64, real-space form (kv, state_off and ka of the stage arguments are unused: they are in kt):
+// column pass dst = alpha x_base + c (T_x + V) w_in, plane pass w_out = tmp_in + c (T_yz w_in + Y rows)
+// (w_out may be w_in), sphere rows of states, and kinetic energy partials: part [B][ntiles][2] (x part
+// of sum 1/2 |G + k|^2 |X|^2 / N and the norm sum |psi|^2 per column tile), eplane [B][NX] (y,z part
+// per plane).
+hipError_t launch_xv(const int n[3], int S, const StageArgs<double>& a, void* dst, const void* twx,
+                     const KinTables& kt, hipStream_t st);
+hipError_t launch_plane_yz(const int n[3], int S, const StageArgs<double>& a, const KinTables& kt,
+                           const ProjTables& pt, const void* twy, const void* twz, hipStream_t st);
+hipError_t launch_gather_rows(const ProjTables& pt, const void* psi, void* W, int B, size_t N, hipStream_t st);
+hipError_t launch_energy_real(const int n[3], int B, const void* src, const void* twx, const void* twy,
+                              const void* twz, const KinTables& kt, double* part, double* eplane, int* ntiles_out,
+                              hipStream_t st);
+// FP32, transformed form (launch_xpass below also serves the FP64 Poisson solve)
+hipError_t launch_plane_stage(const int n[3], int S, const StageArgs<float>& a, const ProjTables& pt,
                               const void* twy, const void* twz, hipStream_t st);
 // Forward 2D transform of B planes-sets (batch entries, each [NX][NY][NZ]); optionally gathers
 // sphere rows of the input into W (batch must then be 2S in state/spinor order).
@@ -129,12 +158,13 @@ hipError_t launch_add_bext(const double* fields, const int n[3], const double b[
                            const double lg[4], double* out, hipStream_t st);
 hipError_t launch_to_float(const double* in, size_t n, float* out, hipStream_t st);
 
-// Projectors: C = dV beta^H W (per atom), EC = E * C; Y = beta EC.
+// Projectors: C = dV beta^H W (per atom), EC = E * C; Y = beta EC.  FP64 with Bloch vectors (kt.kv): the
+// rows of W are taken times exp(i k.d), those of Y times exp(-i k.d); in FP32 the plane pass does that.
 template <typename R>
 hipError_t launch_proj_contract(const ProjTables& pt, const void* W, int S, double dV,
-                                void* Cpart, void* C, void* EC, hipStream_t st);
+                                void* Cpart, void* C, void* EC, const KinTables& kt, hipStream_t st);
 template <typename R>
-hipError_t launch_proj_scatter(const ProjTables& pt, const void* EC, int S, void* Y,
+hipError_t launch_proj_scatter(const ProjTables& pt, const void* EC, int S, void* Y, const KinTables& kt,
                                hipStream_t st);
 
 // Observables of the current state: assembles one 13-double row.
@@ -142,6 +172,8 @@ struct ObsInputs {
   const double* field_tot;  // [8] reduced field partials
   const double* epart;      // [2S][ntiles][2] energy-pass partials
   int ntiles;
+  const double* eplane;     // [2S][nplanes] further energy partials (real-space form)
+  int nplanes;
   const void* C;            // [natoms][PP][S] complex R (already times dV)
   const double* energy;     // [natoms][PP]
   const double* occ;        // [S]
@@ -160,8 +192,9 @@ hipError_t launch_axpby(void* y, const void* x, size_t count, R a_re, R a_im, R 
                         hipStream_t st);
 
 // Adjoint kernels
+// g += Re c mu^dagger (1, sigma) w, c = cre + i cim (FP32: cre is 0)
 template <typename R>
-hipError_t launch_pair(const void* mu, const void* w, int S, size_t N, double gamma, double* g,
+hipError_t launch_pair(const void* mu, const void* w, int S, size_t N, double cre, double cim, double* g,
                        hipStream_t st);
 // pg: the complex adjoint Poisson output (its real parts, stride 2 doubles, are used), or null
 hipError_t launch_field_adjoint(const double* rho, const double* g, const double* pg, int xc,

@@ -1,14 +1,13 @@
 // HIP kernels of the non-collinear TDDFT step for gfx950 (MI355X), wave64.
 //
-// H application (Eq. HNC-SDFT / TDSDFT) as two passes over HBM:
-//   column pass  (k_xpass):  DFT_x -> multiply 1/2|G|^2/N -> IDFT_x on the
-//                            (y,z)-transformed states, tiles of TC columns in LDS;
-//   plane pass   (k_plane_stage): per (state, x-plane), both spinor components:
-//                            IDFT_yz -> T w; V w with the 2x2 local potential
-//                            [v + b.sigma]; + projector scatter rows; Taylor
-//                            (Horner) update out = alpha x + c H w; sphere rows of
-//                            out for the next projection; DFT_yz of out for the
-//                            next column pass.
+// H application (Eq. HNC-SDFT / TDSDFT) as two passes over HBM, in one of two forms:
+//   FP64, real space (the kinetic operator is a sum T_x + T_yz): k_xv, per column block and both
+//     spinor components, forms T_x w and the 2x2 local potential V w = [v + b.sigma] w on the Taylor
+//     base; k_plane_yz, per (spinor component, x-plane), adds T_yz w and the projector scatter rows, and
+//     gathers the sphere rows of the result for the next projection;
+//   FP32-mixed, with (y,z)-transformed copies: k_xpass (DFT_x -> multiply 1/2|G|^2/N -> IDFT_x on the
+//     transformed states) and k_plane_stage2 / k_plane_stage_r (IDFT_yz -> T w; V w; + scatter rows;
+//     Taylor update; sphere rows; DFT_yz of the result for the next column pass).
 // Densities, exchange, Hartree and reductions are FP64.  The projector
 // contraction <beta|psi> and its scatter-back run on the matrix cores
 // (v_mfma_f64_16x16x4f64 / v_mfma_f32_16x16x4f32).
@@ -19,9 +18,16 @@
 #include <cmath>
 #include <cstdint>
 #include <mutex>
+#include <type_traits>
 
 #include "nct_fft.hpp"
 #include "nct_internal.hpp"
+
+// This file is compiled once per precision (in parallel): NCT_FP64_TU 1 holds the FP64 instantiations
+// and everything that has no precision of its own, 0 the FP32 ones.
+#ifndef NCT_FP64_TU
+#error "compile with -DNCT_FP64_TU=1 and -DNCT_FP64_TU=0"
+#endif
 
 namespace nct {
 
@@ -96,208 +102,30 @@ __device__ __forceinline__ cpx<float> bloch_phase(float q0, float q1, float q2, 
   return {cs, sn};
 }
 
-// ---------------------------------------------------------------- plane pass: fused H stage
-template <typename R, int NY, int NZ, int M>
-__global__ __launch_bounds__(plane_nt(NY* NZ)) void k_plane_stage(StageArgs<R> a, ProjTables pt,
-                                                                   const cpx<R>* __restrict__ twy_g,
-                                                                   const cpx<R>* __restrict__ twz_g,
-                                                                   int S, int NX) {
-  constexpr int NP = NY * NZ;
-  constexpr int NT = plane_nt(NP);
-  constexpr int PZ = NZ + 1;
-  constexpr int PPT = (NP + NT - 1) / NT;
-  extern __shared__ double4 smem_d4[];
-  cpx<R>* plane = reinterpret_cast<cpx<R>*>(smem_d4);
-  cpx<R>* twy = plane + NY * PZ;
-  cpx<R>* twz = twy + NY;
-  const int tid = threadIdx.x;
-  const int L = xcd_logical(blockIdx.x, gridDim.x);
-  const int x = L / S;
-  const int i = L - x * S;
-  for (int k = tid; k < NY; k += NT) twy[k] = twy_g[k];
-  for (int k = tid; k < NZ; k += NT) twz[k] = twz_g[k];
-  const size_t N = size_t(NX) * NP;
-  size_t off[2];
-  off[0] = (size_t(2 * i) * NX + x) * NP;
-  off[1] = (size_t(2 * i + 1) * NX + x) * NP;
-  const cpx<R>* __restrict__ tin = reinterpret_cast<const cpx<R>*>(a.tmp_in);
-  cpx<R> hv[2][PPT];
-
-  // 1) kinetic part: inverse 2D transform of the column-pass output, both spinors
-#pragma unroll
-  for (int s = 0; s < 2; ++s) {
-#pragma unroll
-    for (int j = 0; j < PPT; ++j) {
-      const int e = tid + j * NT;
-      if (e < NP) plane[(e / NZ) * PZ + (e % NZ)] = ld_stream<M>(&tin[off[s] + e]);
-    }
-    __syncthreads();
-    plane_fft_inv<R, NY, NZ, PZ>(plane, twy, twz, tid, NT);
-#pragma unroll
-    for (int j = 0; j < PPT; ++j) {
-      const int e = tid + j * NT;
-      if (e < NP) hv[s][j] = plane[(e / NZ) * PZ + (e % NZ)];
-    }
-    __syncthreads();
-  }
-
-  // 2) local 2x2 potential and Taylor update, pointwise
-  const cpx<R>* __restrict__ win = reinterpret_cast<const cpx<R>*>(a.w_in);
-  const cpx<R>* __restrict__ xb = reinterpret_cast<const cpx<R>*>(a.x_base);
-  const R* __restrict__ F = a.fields;
-  const R lx = a.lg[0] * R(x) + a.lg[3];  // laser potential of this plane, less its y, z terms
-#pragma unroll
-  for (int j = 0; j < PPT; ++j) {
-    const int e = tid + j * NT;
-    if (e < NP) {
-      const size_t p = size_t(x) * NP + e;
-      const R v = F[p] + (lx + a.lg[1] * R(e / NZ) + a.lg[2] * R(e % NZ));
-      const R bx = F[N + p] + a.bext[0];
-      const R by = F[2 * N + p] + a.bext[1];
-      const R bz = F[3 * N + p] + a.bext[2];
-      const cpx<R> wu = ld_stream<M>(&win[off[0] + e]);
-      const cpx<R> wd = ld_stream<M>(&win[off[1] + e]);
-      // up' = (v+bz) up + (bx - i by) dn ; dn' = (bx + i by) up + (v - bz) dn
-      cpx<R> hu, hd;
-      hu.x = hv[0][j].x + (v + bz) * wu.x + bx * wd.x + by * wd.y;
-      hu.y = hv[0][j].y + (v + bz) * wu.y + bx * wd.y - by * wd.x;
-      hd.x = hv[1][j].x + bx * wu.x - by * wu.y + (v - bz) * wd.x;
-      hd.y = hv[1][j].y + bx * wu.y + by * wu.x + (v - bz) * wd.y;
-      cpx<R> ou = {a.cre * hu.x - a.cim * hu.y, a.cre * hu.y + a.cim * hu.x};
-      cpx<R> od = {a.cre * hd.x - a.cim * hd.y, a.cre * hd.y + a.cim * hd.x};
-      if (xb) {
-        const cpx<R> xu = ld_stream<M>(&xb[off[0] + e]);
-        const cpx<R> xd = ld_stream<M>(&xb[off[1] + e]);
-        ou.x += a.alpha * xu.x;
-        ou.y += a.alpha * xu.y;
-        od.x += a.alpha * xd.x;
-        od.y += a.alpha * xd.y;
-      }
-      hv[0][j] = ou;
-      hv[1][j] = od;
-    }
-  }
-
-  // 3) per spinor: projector rows, outputs, forward 2D transform
-  const cpx<R>* __restrict__ Y = reinterpret_cast<const cpx<R>*>(a.Y);
-  cpx<R>* __restrict__ Wr = reinterpret_cast<cpx<R>*>(a.W);
-  cpx<R>* __restrict__ wout = reinterpret_cast<cpx<R>*>(a.w_out);
-  cpx<R>* __restrict__ acc = reinterpret_cast<cpx<R>*>(a.acc);
-  cpx<R>* __restrict__ tout = reinterpret_cast<cpx<R>*>(a.tmp_out);
-  const int r0 = pt.pr_off ? pt.pr_off[x] : 0;
-  const int r1 = pt.pr_off ? pt.pr_off[x + 1] : 0;
-#pragma unroll
-  for (int s = 0; s < 2; ++s) {
-#pragma unroll
-    for (int j = 0; j < PPT; ++j) {
-      const int e = tid + j * NT;
-      if (e < NP) plane[(e / NZ) * PZ + (e % NZ)] = hv[s][j];
-    }
-    __syncthreads();
-    const size_t rowbase = size_t(2 * i + s) * pt.Jtot;
-    const bool kq = a.kv != nullptr;
-    R q0 = 0, q1 = 0, q2 = 0;
-    if (kq) {
-      const R* k0 = a.kv + 3 * (a.state_off + i);
-      q0 = k0[0] + a.ka[0];
-      q1 = k0[1] + a.ka[1];
-      q2 = k0[2] + a.ka[2];
-    }
-    const R* disp = reinterpret_cast<const R*>(pt.disp);
-    if (Y) {
-      for (int r = r0; r < r1; ++r) {
-        const int jb = pt.pr_begin[r], je = pt.pr_end[r];
-        for (int J = jb + tid; J < je; J += NT) {
-          const int e = pt.pidx[J];
-          cpx<R> y = Y[rowbase + J];
-          if (kq) y = cmulc(y, bloch_phase(q0, q1, q2, disp + 3 * J));
-          cpx<R>& d = plane[(e / NZ) * PZ + (e % NZ)];
-          d.x += a.cre * y.x - a.cim * y.y;
-          d.y += a.cre * y.y + a.cim * y.x;
-        }
-        __syncthreads();
-      }
-    }
-    if (Wr) {
-      for (int r = r0; r < r1; ++r) {
-        const int jb = pt.pr_begin[r], je = pt.pr_end[r];
-        for (int J = jb + tid; J < je; J += NT) {
-          const int e = pt.pidx[J];
-          cpx<R> o = plane[(e / NZ) * PZ + (e % NZ)];
-          if (kq) o = cmul(o, bloch_phase(q0, q1, q2, disp + 3 * J));
-          Wr[rowbase + J] = o;
-        }
-      }
-    }
-    if (wout || acc) {
-#pragma unroll
-      for (int j = 0; j < PPT; ++j) {
-        const int e = tid + j * NT;
-        if (e < NP) {
-          const cpx<R> o = plane[(e / NZ) * PZ + (e % NZ)];
-          if (wout) st_stream<M>(&wout[off[s] + e], o);
-          if (acc) {
-            cpx<R> q = acc[off[s] + e];
-            acc[off[s] + e] = q + o;
-          }
-        }
-      }
-    }
-    if (tout) {
-      __syncthreads();
-      plane_fft_fwd<R, NY, NZ, PZ>(plane, twy, twz, tid, NT);
-#pragma unroll
-      for (int j = 0; j < PPT; ++j) {
-        const int e = tid + j * NT;
-        if (e < NP) st_stream<M>(&tout[off[s] + e], plane[(e / NZ) * PZ + (e % NZ)]);
-      }
-    }
-    __syncthreads();
-  }
-}
-
 // ---------------------------------------------------------------- plane pass, two halves
-// Same stage as k_plane_stage, with the two spinor components of the (state, x-plane) held as
-// two LDS planes and transformed concurrently by the two halves of the workgroup; the pointwise
-// 2x2 update then reads both planes.  Used when two planes fit in LDS.
-// Threads per spinor half: plane_nt's choice capped at NCT_PLANE2_NTH_MAX (tuning macro), except
-// FP64 48^2 planes.  There LDS admits two workgroups per CU, and 256 threads per half at 98 VGPRs
-// keep only 16 waves per CU; 384 threads (6 points each, 2304 = 6 x 384) with a register target
-// of 6 waves per SIMD (80 VGPRs) keep 24 and measured 3 % faster on MI355X.  320 and 448 threads
-// (a partial last round) and 512 (spills at 64 VGPRs) measured slower.
-#ifndef NCT_PLANE2_NTH_MAX_F64
-#define NCT_PLANE2_NTH_MAX_F64 512
-#endif
+// FP32 stage in transformed form: inverse (y,z) transform of the column-pass output, 2x2 local
+// potential on w, projector rows, Horner update out = alpha x + c H w, sphere rows of out, forward
+// (y,z) transform of out.  The two spinor components of the (state, x-plane) are held as two LDS planes
+// and transformed concurrently by the two halves of the workgroup; the pointwise 2x2 update then reads
+// both planes.  Threads per spinor half: plane_nt's choice capped at NCT_PLANE2_NTH_MAX (tuning macro).
 #ifndef NCT_PLANE2_NTH_MAX_F32
 #define NCT_PLANE2_NTH_MAX_F32 512
 #endif
 template <typename R>
 __host__ __device__ constexpr int plane2_nth(int np) {
-  if (sizeof(R) == 8 && np == 48 * 48) return 384;
-  const int cap = sizeof(R) == 8 ? NCT_PLANE2_NTH_MAX_F64 : NCT_PLANE2_NTH_MAX_F32;
-  return plane_nt(np) > cap ? cap : plane_nt(np);
+  return plane_nt(np) > NCT_PLANE2_NTH_MAX_F32 ? NCT_PLANE2_NTH_MAX_F32 : plane_nt(np);
 }
 // Minimum waves per SIMD the register allocation of the two-half kernel must allow, where LDS
-// admits more workgroups per CU than the registers would: FP64 48^2 (above), and FP32 64^2,
-// whose two 66 KB workgroups of 16 waves need 8 waves per SIMD: at 68 VGPRs only one fitted, at
-// 63 both do (measured 1159 -> 949 us per launch at 64^3 x 256).
+// admits more workgroups per CU than the registers would: 64^2, whose two 66 KB workgroups of 16
+// waves need 8 waves per SIMD: at 68 VGPRs only one fitted, at 63 both do (measured 1159 -> 949 us
+// per launch at 64^3 x 256).
 template <typename R>
 __host__ __device__ constexpr int plane2_min_waves(int np) {
-  if (sizeof(R) == 8 && np == 48 * 48) return 6;
-  if (sizeof(R) == 4 && np == 64 * 64) return 8;
-  return 1;
+  return np == 64 * 64 ? 8 : 1;
 }
 template <int NY, int NZ>
 constexpr size_t plane2_lds_bytes(size_t elem) {
   return (size_t(2) * NY * (NZ + 1) + NY + NZ) * elem;
-}
-// LDS budget of the two-plane kernel (tuning macro; 160 KiB per CU less a margin)
-#ifndef NCT_PLANE2_MAX_LDS
-#define NCT_PLANE2_MAX_LDS (160 * 1024 - 1024)
-#endif
-template <typename R, int NY, int NZ>
-constexpr bool plane2_fits() {
-  return plane2_lds_bytes<NY, NZ>(sizeof(cpx<R>)) <= NCT_PLANE2_MAX_LDS;
 }
 
 template <typename R, int NY, int NZ, int M>
@@ -312,14 +140,10 @@ __global__ __launch_bounds__(2 * plane2_nth<R>(NY* NZ), plane2_min_waves<R>(NY* 
   constexpr int PL = NY * PZ;
   constexpr int PPH = (NP + NTH - 1) / NTH;
   constexpr int PPT = (NP + NT - 1) / NT;
-#ifndef NCT_PLANE2_G_F64
-#define NCT_PLANE2_G_F64 3
-#endif
 #ifndef NCT_PLANE2_G_F32
 #define NCT_PLANE2_G_F32 3
 #endif
-  // pointwise points per load batch (2 for FP64 48^2, where 3 spills at that case's register target)
-  constexpr int G = (sizeof(R) == 8 && NP == 48 * 48) ? 2 : (sizeof(R) == 8 ? NCT_PLANE2_G_F64 : NCT_PLANE2_G_F32);
+  constexpr int G = NCT_PLANE2_G_F32;  // pointwise points per load batch
   extern __shared__ double4 smem_d4[];
   cpx<R>* planes = reinterpret_cast<cpx<R>*>(smem_d4);
   cpx<R>* twy = planes + 2 * PL;
@@ -475,7 +299,7 @@ __global__ __launch_bounds__(2 * plane2_nth<R>(NY* NZ), plane2_min_waves<R>(NY* 
 
 // ---------------------------------------------------------------- plane pass, one plane in LDS
 // Same stage as k_plane_stage2 for planes where two LDS planes would admit only one workgroup per
-// CU but one plane admits two (FP64 64^2: 67 KB; FP32 96^2: 76 KB).  The spinor components go
+// CU but one plane admits two (96^2: 76 KB).  The spinor components go
 // through the single LDS plane one after the other: the up component's kinetic part waits in
 // registers (PPT values per thread, the last of them in a private LDS slot per thread) while the
 // down component is transformed; after the 2x2 update the up result waits there again while the
@@ -498,8 +322,6 @@ constexpr bool planer_use() {
 
 // Values per thread of the held spinor component that live in LDS left over by the plane
 // (tuning macro NCT_PLANER_KL: at most that many, within the 80 KB of two workgroups per CU).
-// One slot takes four of the 128 VGPRs off the held values: FP64 64^2 spills 36 instead of 56 B
-// per lane and its plane pass runs 5707 instead of 5575 GB/s (64^3 x 256).
 #ifndef NCT_PLANER_KL
 #define NCT_PLANER_KL 1
 #endif
@@ -516,8 +338,7 @@ constexpr size_t planer_lds_bytes() {
   return plane_lds_bytes<NY, NZ>(sizeof(cpx<R>)) + size_t(planer_kl<R, NY, NZ>()) * NCT_PLANER_NT * sizeof(cpx<R>);
 }
 
-// ACC: the kernel carries the adjoint's accumulation acc += w_out (only the adjoint passes acc).
-template <typename R, int NY, int NZ, int M, bool ACC>
+template <typename R, int NY, int NZ, int M>
 __global__ __launch_bounds__(NCT_PLANER_NT, 4) void k_plane_stage_r(StageArgs<R> a, ProjTables pt,
                                                                      const cpx<R>* __restrict__ twy_g,
                                                                      const cpx<R>* __restrict__ twz_g,
@@ -527,10 +348,7 @@ __global__ __launch_bounds__(NCT_PLANER_NT, 4) void k_plane_stage_r(StageArgs<R>
   constexpr int PZ = NZ + 1;
   constexpr int PPT = (NP + NT - 1) / NT;
   constexpr int KR = PPT - planer_kl<R, NY, NZ>();  // held values in registers, the rest in LDS
-#ifndef NCT_PLANER_G_F64  // points per load batch of the FP64 2x2 update (tuning macro)
-#define NCT_PLANER_G_F64 2
-#endif
-  constexpr int G = sizeof(R) == 8 ? NCT_PLANER_G_F64 : 3;  // points per load batch of the 2x2 update
+  constexpr int G = 3;  // points per load batch of the 2x2 update
   extern __shared__ double4 smem_d4[];
   cpx<R>* pl = reinterpret_cast<cpx<R>*>(smem_d4);
   cpx<R>* twy = pl + NY * PZ;
@@ -681,7 +499,7 @@ __global__ __launch_bounds__(NCT_PLANER_NT, 4) void k_plane_stage_r(StageArgs<R>
         }
       }
     }
-    if (ACC && acc) {
+    if (acc) {
       cpx<R> v[PPT];
 #pragma unroll
       for (int j = 0; j < PPT; ++j) v[j] = acc[offh + min(tid + j * NT, NP - 1)];
@@ -704,6 +522,483 @@ __global__ __launch_bounds__(NCT_PLANER_NT, 4) void k_plane_stage_r(StageArgs<R>
       plane_fft_fwd_to<R, NY, NZ, PZ, NT>(pl, twy, twz, tid, [](int) { return 0; },
                                           [&](int g, int, cpx<R> v, int) { st_stream<M>(&to[g], v); });
     }
+  }
+}
+
+// ---------------------------------------------------------------- FP64: real-space H stage
+// The kinetic operator is a sum of one operator per axis, T = T_x + T_yz, so FP64 applies H in real
+// space on both sides, nothing kept in transformed form: the column pass (k_xv) writes
+// r = alpha x + c (T_x + V) w, with V the 2x2 local potential, and the plane pass (k_plane_yz) adds
+// c (T_yz w + projector rows) to it.  The two passes of a stage read w twice and r once and write r and
+// out: 5 |psi| (6 where the Taylor base x is not w), against 7 |psi| with (y,z)-transformed copies of
+// w.  V sits in the column pass because that pass holds both spinor components of a point at once in
+// little LDS; in the plane pass it cost a second read of w (a plane of either component and the
+// transforms leave no room to keep w), which misses L2 and counts on the fabric like HBM: 6.2 instead
+// of 4.3 GB fetched per launch at 64^3 x 256, 1478 us.
+//
+// Element at a byte offset from a wave-uniform base: the base stays in scalar registers (the empty
+// asm keeps the compiler from folding the offset into a 64-bit vector address per operand) and one
+// 32-bit vector register addresses every operand of the same shape.
+template <typename T>
+__device__ __forceinline__ T* at_bytes(T* base, uint32_t bytes) {
+  asm volatile("" : "+s"(base));
+  return reinterpret_cast<T*>(reinterpret_cast<char*>(const_cast<std::remove_const_t<T>*>(base)) + bytes);
+}
+
+// Waves per workgroup of the plane pass and the waves per SIMD its registers must allow.
+#ifndef NCT_REAL_NW64
+#define NCT_REAL_NW64 8
+#endif
+#ifndef NCT_REAL_NW48
+#define NCT_REAL_NW48 6
+#endif
+#ifndef NCT_REAL_NW32
+#define NCT_REAL_NW32 2
+#endif
+__host__ __device__ constexpr int real_nw(int ny, int nz) {
+  if (ny == 64 && nz == 64) return NCT_REAL_NW64;
+  if (ny == 48 && nz == 48) return NCT_REAL_NW48;
+  if (ny == 96 && nz == 96) return 12;
+  if (ny == 32 && nz == 32) return NCT_REAL_NW32;
+  if (ny == 24 && nz == 24) return 3;
+  if (ny * nz == 384) return 2;  // 16 x 24, 24 x 16
+  return 1;
+}
+#ifndef NCT_REAL_MW64
+#define NCT_REAL_MW64 4
+#endif
+#ifndef NCT_REAL_MW48
+#define NCT_REAL_MW48 4
+#endif
+#ifndef NCT_REAL_MW
+#define NCT_REAL_MW 4
+#endif
+__host__ __device__ constexpr int real_mw(int ny, int nz) {
+  if (ny == 64 && nz == 64) return NCT_REAL_MW64;
+  if (ny == 48 && nz == 48) return NCT_REAL_MW48;
+  if (ny == 96 && nz == 96) return 3;
+  return NCT_REAL_MW;
+}
+template <int NY, int NZ>
+constexpr size_t real_lds_bytes() {
+  return (size_t(NY) * (NZ + 1) + NY + NZ) * sizeof(cpx<double>) + (NY + NZ) * sizeof(double);
+}
+
+// Plane pass: out = r + c (T_yz w + projector rows), one workgroup per (spinor component, x-plane), one
+// LDS plane.  All loads (the thread's points of w and of r) are issued up front; r waits in registers
+// while w goes through the plane.  out may be w.
+//
+// Each wave owns NZ / NW columns of the y transforms and NY / NW rows of the z transforms, so the
+// stages of one axis run without a workgroup barrier (LDS operations of a wave stay in order); only
+// the two changes of axis take one.  The last forward z stage, the kinetic factor and the first inverse
+// z stage work on the same values and stay in registers.  Where the work items of a wave are no
+// multiple of 64, the surplus lanes repeat the last item: they write the same values to the same places.
+//
+// ACC: acc += out (the adjoint).
+template <int NY, int NZ, int M, bool ACC>
+__global__ __launch_bounds__(64 * real_nw(NY, NZ), real_mw(NY, NZ)) void k_plane_yz(
+    StageArgs<double> a, KinTables kt, ProjTables pt, const cpx<double>* __restrict__ twy_g,
+    const cpx<double>* __restrict__ twz_g, int B, int NX) {
+  using C = cpx<double>;
+  constexpr int NP = NY * NZ, PZ = NZ + 1;
+  constexpr int NW = real_nw(NY, NZ), NT = 64 * NW;
+  constexpr int CW = NZ / NW, RW = NY / NW;
+  constexpr int RY = plan_radix(NY, 0), MY = NY / RY;
+  constexpr int ITEMS = CW * MY, IT = (ITEMS + 63) / 64;
+  static_assert(NZ % NW == 0 && NY % NW == 0 && plan_nstages(NY) <= 2 && plan_nstages(NZ) <= 2, "plane split");
+  extern __shared__ double4 smem_d4[];
+  C* pl = reinterpret_cast<C*>(smem_d4);
+  C* twy = pl + NY * PZ;
+  C* twz = twy + NY;
+  double* ty = reinterpret_cast<double*>(twz + NZ);
+  double* tz = ty + NY;
+  const int tid = threadIdx.x;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int L = xcd_logical(blockIdx.x, gridDim.x);
+  const int x = L / B;
+  const int b = L - x * B;  // 2 state + component
+  const size_t off = (size_t(b) * NX + x) * NP;
+  const C* win = reinterpret_cast<const C*>(a.w_in);
+  const C* __restrict__ rin = reinterpret_cast<const C*>(a.tmp_in);
+
+  // sphere rows on this plane (RowMap): their scatter values go into r with the other operands
+  const C* __restrict__ Y = reinterpret_cast<const C*>(a.Y);
+  C* __restrict__ Wr = reinterpret_cast<C*>(a.W);
+  const bool on_plane = (Y || Wr) && pt.pr_off[x + 1] > pt.pr_off[x];
+  const int* __restrict__ pm = pt.pmap + size_t(x) * NP;
+  const size_t rb = size_t(b) * pt.Jtot;
+
+  // thread (column z, butterfly c) of the y transform holds the points y = c + q MY
+  C v[IT][RY], r[IT][RY];
+#pragma unroll
+  for (int u = 0; u < IT; ++u) {
+    const int it = min(lane + 64 * u, ITEMS - 1);
+    const uint32_t l0 = uint32_t((it / CW) * NZ + it % CW), o = l0 * 16u;
+    int J[RY];
+    if (on_plane && Y) {
+#pragma unroll
+      for (int q = 0; q < RY; ++q) J[q] = *at_bytes(pm + (w * CW + q * MY * NZ), l0 * 4u);
+    }
+#pragma unroll
+    for (int q = 0; q < RY; ++q) v[u][q] = ld_stream<M>(at_bytes(win + off + (w * CW + q * MY * NZ), o));
+#pragma unroll
+    for (int q = 0; q < RY; ++q) r[u][q] = ld_stream<M>(at_bytes(rin + off + (w * CW + q * MY * NZ), o));
+    if (on_plane && Y) {
+      int any = J[0], more = J[0];
+#pragma unroll
+      for (int q = 1; q < RY; ++q) {
+        any &= J[q];   // all negative (no row) only if every J is
+        more = max(more, J[q]);
+      }
+      if (__any(any >= 0)) {
+        // every load at once: points without a row read row 0 and drop it
+        C y[RY];
+#pragma unroll
+        for (int q = 0; q < RY; ++q) y[q] = Y[rb + (J[q] >= 0 ? (J[q] & kRowMask) : 0)];
+#pragma unroll
+        for (int q = 0; q < RY; ++q) {
+          const C z = J[q] >= 0 ? y[q] : C{0.0, 0.0};
+          r[u][q].x += a.cre * z.x - a.cim * z.y;
+          r[u][q].y += a.cre * z.y + a.cim * z.x;
+        }
+        if (__any(more > kRowMask)) {  // further rows at a point: overlapping spheres
+#pragma unroll
+          for (int q = 0; q < RY; ++q)
+            if (J[q] > kRowMask)
+              for (int k = pt.rnext[J[q] & kRowMask]; k >= 0; k = pt.rnext[k]) {
+                const C z = Y[rb + k];
+                r[u][q].x += a.cre * z.x - a.cim * z.y;
+                r[u][q].y += a.cre * z.y + a.cim * z.x;
+              }
+        }
+      }
+    }
+  }
+  {
+    const double ky = kt.shift(b >> 1, 1), kz = kt.shift(b >> 1, 2);
+    for (int k = tid; k < NY; k += NT) {
+      twy[k] = twy_g[k];
+      const double g = kt.g[1][k] + ky;
+      ty[k] = 0.5 / NP * (g * g);
+    }
+    for (int k = tid; k < NZ; k += NT) {
+      twz[k] = twz_g[k];
+      const double g = kt.g[2][k] + kz;
+      tz[k] = 0.5 / NP * (g * g);
+    }
+  }
+  group_sync<NW>();  // tables
+  C* cols = pl + w * CW;       // this wave's columns
+  C* rows = pl + w * RW * PZ;  // this wave's rows
+#pragma unroll
+  for (int u = 0; u < IT; ++u) {
+    const int it = min(lane + 64 * u, ITEMS - 1);
+    {
+      stage_butterfly<double, NY, 0, true>(v[u], twy, it / CW);
+      C* p = cols + (it / CW) * PZ + it % CW;
+#pragma unroll
+      for (int q = 0; q < RY; ++q) p[q * MY * PZ] = v[u][q];
+    }
+  }
+  if constexpr (plan_nstages(NY) > 1) {
+    wave_sync();
+    wave_stage<double, NY, 1, CW, 1, PZ, true>(cols, twy, lane);
+  }
+  group_sync<NW>();
+  if constexpr (plan_nstages(NZ) > 1) {
+    wave_stage<double, NZ, 0, RW, PZ, 1, true>(rows, twz, lane);
+    wave_sync();
+  }
+  wave_middle<double, NZ, RW, PZ, 1>(rows, lane, [&](int line, int k) { return ty[w * RW + line] + tz[k]; });
+  if constexpr (plan_nstages(NZ) > 1) {
+    wave_sync();
+    wave_stage<double, NZ, 0, RW, PZ, 1, false>(rows, twz, lane);
+  }
+  group_sync<NW>();
+  if constexpr (plan_nstages(NY) > 1) {
+    wave_stage<double, NY, 1, CW, 1, PZ, false>(cols, twy, lane);
+    wave_sync();
+  }
+
+  // out = r + c T_yz w, and its sphere rows
+  C* wout = reinterpret_cast<C*>(a.w_out);
+  C* acc = reinterpret_cast<C*>(a.acc);
+#pragma unroll
+  for (int u = 0; u < IT; ++u) {
+    const int it = min(lane + 64 * u, ITEMS - 1);
+    const uint32_t l0 = uint32_t((it / CW) * NZ + it % CW), oc = l0 * 16u;
+    const C* p = cols + (it / CW) * PZ + it % CW;
+    int J[RY];
+    if (on_plane && Wr) {
+#pragma unroll
+      for (int q = 0; q < RY; ++q) J[q] = *at_bytes(pm + (w * CW + q * MY * NZ), l0 * 4u);
+    }
+#pragma unroll
+    for (int q = 0; q < RY; ++q) v[u][q] = p[q * MY * PZ];
+    stage_butterfly<double, NY, 0, false>(v[u], twy, it / CW);
+#pragma unroll
+    for (int q = 0; q < RY; ++q) {
+      const C h = v[u][q];
+      r[u][q].x += a.cre * h.x - a.cim * h.y;
+      r[u][q].y += a.cre * h.y + a.cim * h.x;
+      const int eu = w * CW + q * MY * NZ;
+      st_stream<M>(at_bytes(wout + off + eu, oc), r[u][q]);
+      if constexpr (ACC) {
+        C* ap = at_bytes(acc + off + eu, oc);
+        *ap = *ap + r[u][q];
+      }
+    }
+    if (on_plane && Wr) {
+#pragma unroll
+      for (int q = 0; q < RY; ++q)
+        if (J[q] >= 0) {
+          Wr[rb + (J[q] & kRowMask)] = r[u][q];
+          if (J[q] > kRowMask)
+            for (int k = pt.rnext[J[q] & kRowMask]; k >= 0; k = pt.rnext[k]) Wr[rb + k] = r[u][q];
+        }
+    }
+  }
+}
+
+// Sphere rows W[b][J] of B batch entries (state b / 2, spinor component b % 2): the rows the plane
+// pass gathers from its own output, for states that no plane pass has just written.
+static __global__ __launch_bounds__(256) void k_gather_rows(const cpx<double>* __restrict__ psi,
+                                                            cpx<double>* __restrict__ W, ProjTables pt, size_t N) {
+  const int J = blockIdx.y * 256 + threadIdx.x;
+  const int b = blockIdx.x;
+  if (J < pt.Jtot) W[size_t(b) * pt.Jtot + J] = psi[size_t(b) * N + pt.rflat[J]];
+}
+
+// Column pass: r = alpha x + c (T_x + V) w, T_x = IDFT_x 1/2 (G_x + k_x)^2 / NX DFT_x, in real space along
+// y and z.  Each wave takes XK_COLS consecutive yz columns of one spinor component (one 128-byte line
+// per x-plane); the neighbouring wave takes the other component of the same columns, and the two swap
+// their values of w through their LDS tiles for the 2x2 potential.  r waits in registers while w goes
+// through the tile: the first forward stage works on the values as they are loaded, the last forward
+// stage, the factor and the first inverse stage stay in registers.  No workgroup barrier is needed
+// after the swap, so the waves' phases interleave freely.  Each XCD takes one eighth of the columns for
+// every state (where the column blocks divide by eight): its eighth of the fields stays in its L2, and
+// consecutive workgroups still read consecutive columns of one state.
+// XS: the Taylor base x is another array than w (else alpha w is used).
+constexpr int XK_COLS = 8;    // columns per wave
+// Column blocks per workgroup (two waves each): four blocks of lines from 48 points on (512 bytes of a row
+// per workgroup: 824 against 862 us per pass at 64^3 x 256 with two, 1021 with one), two below, where the
+// grids are small and need the workgroups (21 against 26 us at 32^3 x 32) and at 96 points (LDS).
+constexpr int xv_pairs(int nx) { return nx == 48 || nx == 64 ? 4 : 2; }
+// waves per SIMD that the registers must allow
+constexpr int xv_mw(int nx) { return nx == 96 ? 3 : 4; }
+template <int NX, int PAIRS, int M, bool XS>
+__global__ __launch_bounds__(128 * PAIRS, xv_mw(NX)) void k_xv(StageArgs<double> a, cpx<double>* __restrict__ dst, int NY, int NZ,
+                                                       int S, const cpx<double>* __restrict__ twx_g, KinTables kt) {
+  using C = cpx<double>;
+  constexpr int CW = XK_COLS;
+  constexpr int RX = plan_radix(NX, 0), MX = NX / RX;
+  constexpr int ITEMS = CW * MX, IT = (ITEMS + 63) / 64;
+  static_assert(plan_nstages(NX) <= 2, "column split");
+  __shared__ C tiles[2 * PAIRS][NX * CW];
+  __shared__ C tw[NX];
+  __shared__ double tx[NX];
+  const int tid = threadIdx.x;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int s = w & 1;
+  const int NYZ = NY * NZ;
+  const size_t N = size_t(NX) * NYZ;
+  const int nblk = NYZ / (CW * PAIRS);
+  int blk, i;
+  if (nblk % 8 == 0) {
+    const int per = nblk >> 3, j = blockIdx.x >> 3;
+    i = j / per;
+    blk = (blockIdx.x & 7) * per + (j - i * per);
+  } else {
+    i = blockIdx.x / nblk;
+    blk = blockIdx.x - i * nblk;
+  }
+  const int q0 = (blk * PAIRS + (w >> 1)) * CW;
+  const size_t off = size_t(2 * i + s) * N + q0;
+  const C* __restrict__ win = reinterpret_cast<const C*>(a.w_in);
+  const C* __restrict__ xb = reinterpret_cast<const C*>(a.x_base);
+  const double* __restrict__ F = a.fields + q0;
+  C* tile = tiles[w];
+  const C* other = tiles[w ^ 1];
+  C v[IT][RX], r[IT][RX];
+#pragma unroll
+  for (int u = 0; u < IT; ++u) {
+    const int it = min(lane + 64 * u, ITEMS - 1);
+    const uint32_t o = uint32_t(it / CW * NYZ + it % CW) * 16u;
+#pragma unroll
+    for (int q = 0; q < RX; ++q) v[u][q] = ld_stream<M>(at_bytes(win + (off + size_t(q * MX) * NYZ), o));
+  }
+  // the fields are loaded along with w where their registers allow
+  constexpr bool PRE = IT * RX <= 8;
+  double f[PRE ? RX : 1][4];
+  if constexpr (PRE) {
+    const int it = min(lane, ITEMS - 1);
+    const uint32_t of = uint32_t(it / CW * NYZ + it % CW) * 8u;
+#pragma unroll
+    for (int q = 0; q < RX; ++q)
+#pragma unroll
+      for (int d = 0; d < 4; ++d) f[q][d] = *at_bytes(F + d * N + size_t(q * MX) * NYZ, of);
+  }
+  const double kx = kt.shift(i, 0);
+  for (int k = tid; k < NX; k += 128 * PAIRS) {
+    tw[k] = twx_g[k];
+    const double g = kt.g[0][k] + kx;
+    tx[k] = 0.5 / NX * (g * g);
+  }
+#pragma unroll
+  for (int u = 0; u < IT; ++u) {
+    const int it = min(lane + 64 * u, ITEMS - 1);
+    {
+#pragma unroll
+      for (int q = 0; q < RX; ++q) tile[it + q * MX * CW] = v[u][q];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < IT; ++u) {
+    const int it = min(lane + 64 * u, ITEMS - 1);
+    const int x0 = it / CW, col = q0 + it % CW;
+    const uint32_t l0 = uint32_t(x0 * NYZ + it % CW), oc = l0 * 16u, of = l0 * 8u;
+    // laser potential, less its x term
+    const double lyz = a.lg[3] + a.lg[1] * double(col / NZ) + a.lg[2] * double(col % NZ);
+#pragma unroll
+    for (int q = 0; q < RX; ++q) {
+      const size_t eu = size_t(q * MX) * NYZ;
+      double fq[4];
+#pragma unroll
+      for (int d = 0; d < 4; ++d) fq[d] = PRE ? f[PRE ? q : 0][d] : *at_bytes(F + d * N + eu, of);
+      const double vl = fq[0] + (lyz + a.lg[0] * double(x0 + q * MX));
+      const double bx = fq[1] + a.bext[0], by = fq[2] + a.bext[1], bz = fq[3] + a.bext[2];
+      const C ws = v[u][q], wo = other[it + q * MX * CW];
+      // up: (v+bz) up + (bx - i by) dn ; dn: (v-bz) dn + (bx + i by) up
+      const double d = s ? vl - bz : vl + bz, e = s ? -by : by;
+      const C h = {d * ws.x + bx * wo.x + e * wo.y, d * ws.y + bx * wo.y - e * wo.x};
+      C xv = ws;
+      if constexpr (XS) xv = ld_stream<M>(at_bytes(xb + (off + eu), oc));
+      r[u][q].x = a.alpha * xv.x + (a.cre * h.x - a.cim * h.y);
+      r[u][q].y = a.alpha * xv.y + (a.cre * h.y + a.cim * h.x);
+      if constexpr (!PRE) sched_fence();
+    }
+  }
+  __syncthreads();  // the other wave has read this tile
+#pragma unroll
+  for (int u = 0; u < IT; ++u) {
+    const int it = min(lane + 64 * u, ITEMS - 1);
+    {
+      stage_butterfly<double, NX, 0, true>(v[u], tw, it / CW);
+      if constexpr (plan_nstages(NX) > 1) {
+#pragma unroll
+        for (int q = 0; q < RX; ++q) tile[it + q * MX * CW] = v[u][q];
+      } else {  // one stage: all of a column's values are in this lane
+#pragma unroll
+        for (int q = 0; q < RX; ++q) v[u][q] = cscale(v[u][q], tx[q]);
+      }
+    }
+  }
+  if constexpr (plan_nstages(NX) > 1) {
+    wave_sync();
+    wave_middle<double, NX, CW, 1, CW>(tile, lane, [&](int, int k) { return tx[k]; });
+    wave_sync();
+  }
+  C* out = dst + off;
+#pragma unroll
+  for (int u = 0; u < IT; ++u) {
+    const int it = min(lane + 64 * u, ITEMS - 1);
+    {
+      const uint32_t o = uint32_t(it / CW * NYZ + it % CW) * 16u;
+      if constexpr (plan_nstages(NX) > 1) {
+#pragma unroll
+        for (int q = 0; q < RX; ++q) v[u][q] = tile[it + q * MX * CW];
+      }
+      stage_butterfly<double, NX, 0, false>(v[u], tw, it / CW);
+#pragma unroll
+      for (int q = 0; q < RX; ++q) {
+        const C h = v[u][q];
+        const C t = {r[u][q].x + (a.cre * h.x - a.cim * h.y), r[u][q].y + (a.cre * h.y + a.cim * h.x)};
+        st_stream<M>(at_bytes(out + size_t(q * MX) * NYZ, o), t);
+      }
+    }
+  }
+}
+
+// (y,z) part of the kinetic energy: part[b][x] = sum over the plane of 1/2 |G_yz + k|^2 |X|^2 /
+// (NY NZ), X the (y,z) transform of batch entry b (state b / 2) on plane x.
+template <int NY, int NZ>
+__global__ __launch_bounds__(plane_nt(NY* NZ)) void k_plane_energy(const cpx<double>* __restrict__ in,
+                                                                    const cpx<double>* __restrict__ twy_g,
+                                                                    const cpx<double>* __restrict__ twz_g, int B,
+                                                                    int NX, double* __restrict__ part, KinTables kt) {
+  constexpr int NP = NY * NZ;
+  constexpr int NT = plane_nt(NP);
+  constexpr int PZ = NZ + 1;
+  extern __shared__ double4 smem_d4[];
+  cpx<double>* plane = reinterpret_cast<cpx<double>*>(smem_d4);
+  cpx<double>* twy = plane + NY * PZ;
+  cpx<double>* twz = twy + NY;
+  __shared__ double red[NT / 64];
+  const int tid = threadIdx.x;
+  const int L = xcd_logical(blockIdx.x, gridDim.x);
+  const int x = L / B;
+  const int b = L - x * B;
+  for (int k = tid; k < NY; k += NT) twy[k] = twy_g[k];
+  for (int k = tid; k < NZ; k += NT) twz[k] = twz_g[k];
+  const size_t off = (size_t(b) * NX + x) * NP;
+  for (int e = tid; e < NP; e += NT) plane[(e / NZ) * PZ + (e % NZ)] = in[off + e];
+  __syncthreads();
+  plane_fft_fwd<double, NY, NZ, PZ>(plane, twy, twz, tid, NT);
+  const double ky = kt.shift(b / 2, 1), kz = kt.shift(b / 2, 2);
+  double s = 0.0;
+  for (int e = tid; e < NP; e += NT) {
+    const double gy = kt.g[1][e / NZ] + ky, gz = kt.g[2][e % NZ] + kz;
+    const cpx<double> v = plane[(e / NZ) * PZ + (e % NZ)];
+    s += (gy * gy + gz * gz) * (v.x * v.x + v.y * v.y);
+  }
+  const double t = block_sum<NT>(s, red);
+  if (tid == 0) part[size_t(b) * NX + x] = t * (0.5 / NP);
+}
+
+// x part of the kinetic energy and the norm: per (batch entry, tile of TC columns) sums of
+// 1/2 (G_x + k_x)^2 |X|^2 / NX and |X|^2 / NX, X the x transform of the states.
+template <int NX, int TC>
+__global__ __launch_bounds__(256) void k_xkin_energy(const cpx<double>* __restrict__ src, int NYZ,
+                                                     const cpx<double>* __restrict__ twx_g,
+                                                     double* __restrict__ part, KinTables kt) {
+  __shared__ cpx<double> tile[NX * TC];
+  __shared__ cpx<double> tw[NX];
+  __shared__ double red[4];
+  const int tid = threadIdx.x;
+  const int tiles = NYZ / TC;
+  const int b = blockIdx.x / tiles;
+  for (int k = tid; k < NX; k += 256) tw[k] = twx_g[k];
+  const size_t base = size_t(b) * NX * NYZ + (blockIdx.x - b * tiles) * TC;
+  constexpr int PER = (NX * TC + 255) / 256;
+  {
+    cpx<double> v[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int e = min(tid + j * 256, NX * TC - 1);  // clamped: every load unconditional
+      v[j] = src[base + size_t(e / TC) * NYZ + (e % TC)];
+    }
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int e = tid + j * 256;
+      if (e < NX * TC) tile[e] = v[j];
+    }
+  }
+  __syncthreads();
+  lds_fft<double, NX, TC, 1, TC, true>(tile, tw, tid, 256);
+  const double kx = kt.shift(b / 2, 0);
+  double s1 = 0.0, s2 = 0.0;
+  for (int e = tid; e < NX * TC; e += 256) {
+    const double gx = kt.g[0][e / TC] + kx;
+    const double a2 = tile[e].x * tile[e].x + tile[e].y * tile[e].y;
+    s1 += gx * gx * a2;
+    s2 += a2;
+  }
+  const double t1 = block_sum<256>(s1, red);
+  const double t2 = block_sum<256>(s2, red);
+  if (tid == 0) {
+    part[size_t(blockIdx.x) * 2 + 0] = t1 * (0.5 / NX);
+    part[size_t(blockIdx.x) * 2 + 1] = t2 * (1.0 / NX);
   }
 }
 
@@ -1063,7 +1358,7 @@ __device__ void pw92_lc(T n, T mu, T& vbar, T& bmag, T& ec) {
   bmag = dz;
   ec = n * eps;
 }
-__global__ __launch_bounds__(256) void k_fields(const double* __restrict__ rho,
+static __global__ __launch_bounds__(256) void k_fields(const double* __restrict__ rho,
                                                 const double* __restrict__ vext,
                                                 const double* __restrict__ vH, int xc, double thr,
                                                 int ny, int nz, double hx, double hy, double hz,
@@ -1140,7 +1435,7 @@ __global__ __launch_bounds__(256) void k_fields(const double* __restrict__ rho,
 }
 
 // out[w] = sum_r part[r*width + w], fixed order; copy0, if given, receives out[0] as well
-__global__ __launch_bounds__(256) void k_reduce_rows(const double* __restrict__ part, int nrows,
+static __global__ __launch_bounds__(256) void k_reduce_rows(const double* __restrict__ part, int nrows,
                                                      int width, double* __restrict__ out,
                                                      double* __restrict__ copy0) {
   __shared__ double red[4];
@@ -1155,7 +1450,7 @@ __global__ __launch_bounds__(256) void k_reduce_rows(const double* __restrict__ 
   }
 }
 
-__global__ void k_add_bext(const double* __restrict__ f, int ny, int nz, size_t N, double b0,
+static __global__ void k_add_bext(const double* __restrict__ f, int ny, int nz, size_t N, double b0,
                            double b1, double b2, double l0, double l1, double l2, double l3,
                            double* __restrict__ out) {
   const size_t p = size_t(blockIdx.x) * 256 + threadIdx.x;
@@ -1171,7 +1466,7 @@ __global__ void k_add_bext(const double* __restrict__ f, int ny, int nz, size_t 
     out[3 * N + p] = f[3 * N + p] + b2;
   }
 }
-__global__ void k_to_float(const double* __restrict__ in, size_t n, float* __restrict__ out) {
+static __global__ void k_to_float(const double* __restrict__ in, size_t n, float* __restrict__ out) {
   const size_t p = size_t(blockIdx.x) * 256 + threadIdx.x;
   if (p < n) out[p] = float(in[p]);
 }
@@ -1209,9 +1504,11 @@ constexpr int KU = 4;   // k-steps whose operands are loaded together
 // Cpart[a][kc][p][i] = sum_{k in chunk} conj(beta[a][k][p]) W[i][k], k = 2 (J - off_a) + s.
 // One wave: PP/16 output tiles of 16 projectors x 16 states; A/B operands as
 // A[row = lane%16][k = lane/16], B[k = lane/16][col = lane%16]; D rows from mfma16::row.
-template <typename R, int PP>
+// KQ: the rows of W are taken times exp(i k.d) (FP64 with Bloch vectors; in FP32 the plane pass has
+// put the phase on them).
+template <typename R, int PP, bool KQ>
 __global__ __launch_bounds__(64) void k_proj_contract(ProjTables pt, const cpx<R>* __restrict__ W,
-                                                      int S, cpx<double>* __restrict__ Cpart) {
+                                                      int S, cpx<double>* __restrict__ Cpart, KinTables kt) {
   using M = mfma16<R>;
   constexpr int NMT = PP / 16;
   const int a = blockIdx.x, nt = blockIdx.y, kc = blockIdx.z;
@@ -1238,7 +1535,12 @@ __global__ __launch_bounds__(64) void k_proj_contract(ProjTables pt, const cpx<R
       const bool ok = k < kend;
       const int kk = ok ? k : kc * KC;  // clamped index, value zeroed below
       const int J = off + (kk >> 1), s = kk & 1;
-      const cpx<R> w = W[size_t(2 * min(i, S - 1) + s) * pt.Jtot + J];
+      cpx<R> w = W[size_t(2 * min(i, S - 1) + s) * pt.Jtot + J];
+      if constexpr (KQ) {
+        const int ii = min(i, S - 1);
+        w = cmul(w, bloch_phase(R(kt.shift(ii, 0)), R(kt.shift(ii, 1)), R(kt.shift(ii, 2)),
+                                reinterpret_cast<const R*>(pt.disp) + 3 * J));
+      }
       bw[u] = (ok && i < S) ? w : cpx<R>{R(0), R(0)};
 #pragma unroll
       for (int mt = 0; mt < NMT; ++mt) {
@@ -1309,9 +1611,10 @@ __global__ __launch_bounds__(256) void k_proj_reduce(ProjTables pt, const cpx<do
 }
 
 // Y[i][s][J] = sum_p beta[J][s][p] EC[a][p][i]; rows k = 2 (J - off_a) + s
-template <typename R, int PP>
+// (KQ: times exp(-i k.d))
+template <typename R, int PP, bool KQ>
 __global__ __launch_bounds__(64) void k_proj_scatter(ProjTables pt, const cpx<R>* __restrict__ EC,
-                                                     int S, cpx<R>* __restrict__ Y) {
+                                                     int S, cpx<R>* __restrict__ Y, KinTables kt) {
   using M = mfma16<R>;
   constexpr int KS = PP / 4;
   const int a = blockIdx.x, rt = blockIdx.y, nt = blockIdx.z;
@@ -1345,29 +1648,35 @@ __global__ __launch_bounds__(64) void k_proj_scatter(ProjTables pt, const cpx<R>
     const int rr = rt * 16 + M::row(r, kl);
     if (rr < K2 && i < S) {
       const int J = off + (rr >> 1), s = rr & 1;
-      Y[size_t(2 * i + s) * pt.Jtot + J] = {yr[r], yi[r]};
+      cpx<R> y = {yr[r], yi[r]};
+      if constexpr (KQ)
+        y = cmulc(y, bloch_phase(R(kt.shift(i, 0)), R(kt.shift(i, 1)), R(kt.shift(i, 2)),
+                                 reinterpret_cast<const R*>(pt.disp) + 3 * J));
+      Y[size_t(2 * i + s) * pt.Jtot + J] = y;
     }
   }
 }
 
 // ---------------------------------------------------------------- adjoint kernels
-// Pair reduction of one adjoint Taylor stage:
-//   g[0][p] += gamma sum_i Im(mu_i^dagger w_i),  g[1+q][p] += gamma sum_i Im(mu_i^dagger sigma_q w_i)
-// i.e. dL = sum_r (g_v dv + g_b . db) for a perturbation dH = dv + db.sigma of the stage
-// w_k = x + (-i gamma) H w_{k-1} with adjoint mu_k.
+// Pair reduction of one adjoint Taylor stage w_k = x + c H w_{k-1} with adjoint mu_k:
+//   g[0][p] += Re c sum_i mu_i^dagger w_i,  g[1+q][p] += Re c sum_i mu_i^dagger sigma_q w_i
+// i.e. dL = sum_r (g_v dv + g_b . db) for a perturbation dH = dv + db.sigma of the stage.  FP64 takes any
+// c = cre + i cim; the FP32 stages have c = -i gamma (cim = -gamma) and reduce the imaginary parts alone.
 template <typename R>
 __global__ __launch_bounds__(256) void k_pair(const cpx<R>* __restrict__ mu, const cpx<R>* __restrict__ w,
-                                              int S, size_t N, double gamma, double* __restrict__ g) {
+                                              int S, size_t N, double cre, double cim, double* __restrict__ g) {
   const size_t p = size_t(blockIdx.x) * 256 + threadIdx.x;
   if (p >= N) return;
+  const double gamma = -cim;
   double s0 = 0, s1 = 0, s2 = 0, s3 = 0;
+  double t0 = 0, t1 = 0, t2 = 0, t3 = 0;  // real parts (FP64)
 #pragma unroll 2
   for (int i = 0; i < S; ++i) {
     const cpx<R> mu_u = mu[size_t(2 * i) * N + p], mu_d = mu[size_t(2 * i + 1) * N + p];
     const cpx<R> w_u = w[size_t(2 * i) * N + p], w_d = w[size_t(2 * i + 1) * N + p];
     const double ar = mu_u.x, ai = mu_u.y, br = mu_d.x, bi = mu_d.y;
     const double ur = w_u.x, ui = w_u.y, dr = w_d.x, di = w_d.y;
-    // Im(conj(a) u) = ar ui - ai ur
+    // Im(conj(a) u) = ar ui - ai ur, Re(conj(a) u) = ar ur + ai ui
     const double im_au = ar * ui - ai * ur, im_bd = br * di - bi * dr;
     const double im_ad = ar * di - ai * dr, im_bu = br * ui - bi * ur;
     const double re_ad = ar * dr + ai * di, re_bu = br * ur + bi * ui;
@@ -1375,11 +1684,25 @@ __global__ __launch_bounds__(256) void k_pair(const cpx<R>* __restrict__ mu, con
     s1 += im_ad + im_bu;                 // sigma_x: conj(a) d + conj(b) u
     s2 += -re_ad + re_bu;                // sigma_y: -i conj(a) d + i conj(b) u  -> Im = -Re(a*d) + Re(b*u)
     s3 += im_au - im_bd;                 // sigma_z
+    if constexpr (sizeof(R) == 8) {
+      const double re_au = ar * ur + ai * ui, re_bd = br * dr + bi * di;
+      t0 += re_au + re_bd;
+      t1 += re_ad + re_bu;
+      t2 += im_ad - im_bu;               // Re(-i a*d + i b*u) = Im(a*d) - Im(b*u)
+      t3 += re_au - re_bd;
+    }
   }
-  g[p] += gamma * s0;
-  g[N + p] += gamma * s1;
-  g[2 * N + p] += gamma * s2;
-  g[3 * N + p] += gamma * s3;
+  if constexpr (sizeof(R) == 8) {
+    g[p] += gamma * s0 + cre * t0;
+    g[N + p] += gamma * s1 + cre * t1;
+    g[2 * N + p] += gamma * s2 + cre * t2;
+    g[3 * N + p] += gamma * s3 + cre * t3;
+  } else {
+    g[p] += gamma * s0;
+    g[N + p] += gamma * s1;
+    g[2 * N + p] += gamma * s2;
+    g[3 * N + p] += gamma * s3;
+  }
 }
 
 // Transpose of the field map (v, b) <- (n, m) at the density rho, for gradients g = (g_v, g_b):
@@ -1388,7 +1711,7 @@ __global__ __launch_bounds__(256) void k_pair(const cpx<R>* __restrict__ mu, con
 // with beta = (v_up - v_dn)/2, v_s' = -(1/3)(6/pi)^(1/3) n_s^(-2/3) (0 on a clamped channel),
 // b_xc = 0 (and its derivatives) below the |m| threshold.  pg = P g_v (Poisson) or null.
 // part[blk][0..2] = block sums of g_b (for dL/dB_ext).
-__global__ __launch_bounds__(256) void k_field_adjoint(const double* __restrict__ rho,
+static __global__ __launch_bounds__(256) void k_field_adjoint(const double* __restrict__ rho,
                                                        const double* __restrict__ g,
                                                        const double* __restrict__ pg, int xc,
                                                        double thr, size_t N, double* __restrict__ gnm,
@@ -1497,7 +1820,7 @@ __global__ __launch_bounds__(256) void k_density_backprop(const cpx<R>* __restri
 
 
 // ---------------------------------------------------------------- observables row
-__global__ __launch_bounds__(256) void k_obs_row(ObsInputs in, double* __restrict__ row) {
+static __global__ __launch_bounds__(256) void k_obs_row(ObsInputs in, double* __restrict__ row) {
   __shared__ double red[4];
   __shared__ double maxerr[256];
   const int tid = threadIdx.x;
@@ -1510,6 +1833,7 @@ __global__ __launch_bounds__(256) void k_obs_row(ObsInputs in, double* __restric
         e += q[0];
         nn += q[1];
       }
+      for (int t = 0; t < in.nplanes; ++t) e += in.eplane[size_t(2 * i + s) * in.nplanes + t];
     }
     ekin += in.occ[i] * e * in.dV;
     mx = fmax(mx, fabs(nn * in.invN * in.dV - 1.0));
@@ -1599,7 +1923,7 @@ __global__ __launch_bounds__(256) void k_rephase_rows(cpx<R>* __restrict__ rows,
 }
 
 // ---------------------------------------------------------------- initial spin-density matrix
-__global__ __launch_bounds__(256) void k_dm_init(int nx, int ny, int nz, double hx, double hy,
+static __global__ __launch_bounds__(256) void k_dm_init(int nx, int ny, int nz, double hx, double hy,
                                                  double hz, double Lx, double Ly, double Lz, int natoms,
                                                  const double* __restrict__ atoms,
                                                  const double* __restrict__ moments,
@@ -1705,7 +2029,7 @@ __global__ __launch_bounds__(256) void k_gram_partial(const cpx<R>* __restrict__
 }
 
 // out[i][j] = scale sum_c part[c][i][j] (chunk order) for j >= i, and its conjugate at [j][i].
-__global__ __launch_bounds__(256) void k_gram_reduce(const cpx<double>* __restrict__ part, int S, int nchunks,
+static __global__ __launch_bounds__(256) void k_gram_reduce(const cpx<double>* __restrict__ part, int S, int nchunks,
                                                      double scale, cpx<double>* __restrict__ out) {
   const size_t idx = size_t(blockIdx.x) * 256 + threadIdx.x;
   if (idx >= size_t(S) * S) return;
@@ -1793,6 +2117,7 @@ __global__ __launch_bounds__(256) void k_basis_transform(const cpx<R>* __restric
 // ---------------------------------------------------------------- static scratch
 // Temporaries of the allocation-free entry point.  Host code never passes this name to a kernel:
 // it takes the per-device address from static_scratch().
+#if NCT_FP64_TU
 static __device__ __align__(256) unsigned char scratch[NCT_STATIC_SCRATCH_BYTES];
 
 hipError_t static_scratch(void** ptr, size_t* bytes) {
@@ -1814,14 +2139,17 @@ hipError_t static_scratch(void** ptr, size_t* bytes) {
   *bytes = NCT_STATIC_SCRATCH_BYTES;
   return hipSuccess;
 }
+#endif
 
 // ================================================================ launchers
 static inline unsigned nblocks(size_t n, unsigned bs) { return unsigned((n + bs - 1) / bs); }
 
+#if NCT_FP64_TU
 LaunchEvents& launch_events() {
   static thread_local LaunchEvents ev;
   return ev;
 }
+#endif
 
 // Every dispatch goes through here: with timing events pending they ride on the dispatch itself.
 template <typename F, typename... Args>
@@ -1836,11 +2164,14 @@ static void nct_launch(F kern, dim3 grid, dim3 block, size_t lds, hipStream_t st
   }
 }
 
+#ifndef NCT_PLANE_PAIRS
 #define NCT_PLANE_PAIRS(X) \
   X(8, 8) X(12, 12) X(16, 16) X(24, 24) X(32, 32) X(48, 48) X(64, 64) X(96, 96) \
   X(8, 16) X(16, 8) X(12, 16) X(16, 12) X(16, 24) X(24, 16)
 #define NCT_LINES(X) X(8) X(12) X(16) X(24) X(32) X(48) X(64) X(96)
+#endif
 
+#if NCT_FP64_TU
 bool plane_pair_supported(int ny, int nz) {
 #define X(a, b) if (ny == a && nz == b) return true;
   NCT_PLANE_PAIRS(X)
@@ -1853,6 +2184,7 @@ bool line_supported(int n) {
 #undef X
   return false;
 }
+#endif
 
 template <typename K>
 static hipError_t set_lds(K kern, size_t bytes) {
@@ -1861,6 +2193,112 @@ static hipError_t set_lds(K kern, size_t bytes) {
                              hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
 }
 
+#if NCT_FP64_TU
+// ---- FP64, real-space form
+template <int A, int B, int M, bool ACC>
+static hipError_t launch_plane_yz_m(int S, int NX, const StageArgs<double>& a, const KinTables& kt,
+                                    const ProjTables& pt, const void* twy, const void* twz, hipStream_t st) {
+  constexpr size_t lds = real_lds_bytes<A, B>();
+  auto kern = k_plane_yz<A, B, M, ACC>;
+  hipError_t e = set_lds(kern, lds);
+  if (e != hipSuccess) return e;
+  nct_launch(kern, dim3(2u * unsigned(S) * unsigned(NX)), dim3(64 * real_nw(A, B)), lds, st, a, kt, pt,
+             reinterpret_cast<const cpx<double>*>(twy), reinterpret_cast<const cpx<double>*>(twz), 2 * S, NX);
+  return hipGetLastError();
+}
+
+hipError_t launch_plane_yz(const int n[3], int S, const StageArgs<double>& a, const KinTables& kt,
+                           const ProjTables& pt, const void* twy, const void* twz, hipStream_t st) {
+#define Y(A, B, M)                                                                             \
+  return a.acc ? launch_plane_yz_m<A, B, M, true>(S, n[0], a, kt, pt, twy, twz, st)            \
+               : launch_plane_yz_m<A, B, M, false>(S, n[0], a, kt, pt, twy, twz, st)
+#define X(A, B)                          \
+  if (n[1] == A && n[2] == B) {          \
+    if (a.cache_mode >= 2) Y(A, B, 2);   \
+    if (a.cache_mode == 1) Y(A, B, 1);   \
+    Y(A, B, 0);                          \
+  }
+  NCT_PLANE_PAIRS(X)
+#undef X
+#undef Y
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_gather_rows(const ProjTables& pt, const void* psi, void* W, int B, size_t N, hipStream_t st) {
+  if (pt.natoms == 0 || pt.Jtot == 0) return hipSuccess;
+  nct_launch(k_gather_rows, dim3(unsigned(B), nblocks(size_t(pt.Jtot), 256)), dim3(256), 0, st,
+             reinterpret_cast<const cpx<double>*>(psi), reinterpret_cast<cpx<double>*>(W), pt, N);
+  return hipGetLastError();
+}
+
+template <int NX, int PAIRS, int M>
+static hipError_t launch_xv_m(const int n[3], int S, const StageArgs<double>& a, void* dst, const void* twx,
+                              const KinTables& kt, hipStream_t st) {
+  const dim3 grid(unsigned(n[1] * n[2] / (XK_COLS * PAIRS)) * unsigned(S)), block(128 * PAIRS);
+  const auto d_ = reinterpret_cast<cpx<double>*>(dst);
+  const auto t_ = reinterpret_cast<const cpx<double>*>(twx);
+  if (a.x_base && a.x_base != a.w_in) nct_launch((k_xv<NX, PAIRS, M, true>), grid, block, 0, st, a, d_, n[1], n[2], S, t_, kt);
+  else nct_launch((k_xv<NX, PAIRS, M, false>), grid, block, 0, st, a, d_, n[1], n[2], S, t_, kt);
+  return hipGetLastError();
+}
+hipError_t launch_xv(const int n[3], int S, const StageArgs<double>& a, void* dst, const void* twx,
+                     const KinTables& kt, hipStream_t st) {
+  // every built plane holds a multiple of 16 columns, the larger ones of 32
+  const bool wide = (n[1] * n[2]) % (XK_COLS * 4) == 0;
+#define Y(A, P)                                                                    \
+  {                                                                                \
+    if (a.cache_mode >= 2) return launch_xv_m<A, P, 2>(n, S, a, dst, twx, kt, st); \
+    if (a.cache_mode == 1) return launch_xv_m<A, P, 1>(n, S, a, dst, twx, kt, st); \
+    return launch_xv_m<A, P, 0>(n, S, a, dst, twx, kt, st);                        \
+  }
+#define X(A)                                                     \
+  if (n[0] == A) {                                               \
+    if constexpr (xv_pairs(A) == 4) { if (wide) Y(A, 4) }        \
+    Y(A, 2)                                                      \
+  }
+  NCT_LINES(X)
+#undef X
+#undef Y
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_energy_real(const int n[3], int B, const void* src, const void* twx, const void* twy,
+                              const void* twz, const KinTables& kt, double* part, double* eplane, int* ntiles_out,
+                              hipStream_t st) {
+  const int NYZ = n[1] * n[2];
+  const auto s_ = reinterpret_cast<const cpx<double>*>(src);
+  const auto t_ = reinterpret_cast<const cpx<double>*>(twx);
+  hipError_t e = hipErrorInvalidValue;
+#define X(A)                                                                                       \
+  if (n[0] == A) {                                                                                 \
+    constexpr int TC = xpass_tc<double>(A);                                                        \
+    const int tc = NYZ % TC == 0 ? TC : 16;                                                        \
+    *ntiles_out = NYZ / tc;                                                                        \
+    const dim3 grid(unsigned(B) * unsigned(NYZ / tc));                                             \
+    if (tc == TC) nct_launch((k_xkin_energy<A, TC>), grid, dim3(256), 0, st, s_, NYZ, t_, part, kt); \
+    else nct_launch((k_xkin_energy<A, 16>), grid, dim3(256), 0, st, s_, NYZ, t_, part, kt);        \
+    e = hipGetLastError();                                                                         \
+  }
+  NCT_LINES(X)
+#undef X
+  if (e != hipSuccess) return e;
+#define X(A, BB)                                                                                   \
+  if (n[1] == A && n[2] == BB) {                                                                   \
+    constexpr size_t lds = plane_lds_bytes<A, BB>(sizeof(cpx<double>));                            \
+    auto kern = k_plane_energy<A, BB>;                                                             \
+    e = set_lds(kern, lds);                                                                        \
+    if (e != hipSuccess) return e;                                                                 \
+    nct_launch(kern, dim3(unsigned(B) * unsigned(n[0])), dim3(plane_nt(A * BB)), lds, st, s_,      \
+               reinterpret_cast<const cpx<double>*>(twy), reinterpret_cast<const cpx<double>*>(twz), B, n[0], \
+               eplane, kt);                                                                        \
+    return hipGetLastError();                                                                      \
+  }
+  NCT_PLANE_PAIRS(X)
+#undef X
+  return hipErrorInvalidValue;
+}
+#else
+// ---- FP32, transformed form
 template <typename R, int A, int B, int M>
 static hipError_t launch_plane_stage_m(int S, int NX, const StageArgs<R>& a, const ProjTables& pt,
                                        const void* twy, const void* twz, hipStream_t st) {
@@ -1869,47 +2307,35 @@ static hipError_t launch_plane_stage_m(int S, int NX, const StageArgs<R>& a, con
   const auto tz = reinterpret_cast<const cpx<R>*>(twz);
   if constexpr (planer_use<R, A, B>()) {
     constexpr size_t ldsr = planer_lds_bytes<R, A, B>();
-    // FP64 stages without accumulation take an instantiation without that path: four fewer
-    // live values leave the FP64 64^2 kernel without register spill.  FP32 keeps one
-    // instantiation: without the path the compiler allocates the FP32 96^2 kernel worse (36 B of
-    // spill per lane instead of 28).
-    auto kernr = k_plane_stage_r<R, A, B, M, true>;
-    if constexpr (sizeof(R) == 8) {
-      if (!a.acc) kernr = k_plane_stage_r<R, A, B, M, false>;
-    }
+    auto kernr = k_plane_stage_r<R, A, B, M>;
     hipError_t er = set_lds(kernr, ldsr);
     if (er != hipSuccess) return er;
     nct_launch(kernr, dim3(grid), dim3(NCT_PLANER_NT), ldsr, st, a, pt, ty, tz, S, NX);
-  } else if constexpr (plane2_fits<R, A, B>()) {
+  } else {
     constexpr size_t lds2 = plane2_lds_bytes<A, B>(sizeof(cpx<R>));
     auto kern2 = k_plane_stage2<R, A, B, M>;
     hipError_t e2 = set_lds(kern2, lds2);
     if (e2 != hipSuccess) return e2;
     nct_launch(kern2, dim3(grid), dim3(2 * plane2_nth<R>(A * B)), lds2, st, a, pt, ty, tz, S, NX);
-  } else {
-    constexpr size_t lds = plane_lds_bytes<A, B>(sizeof(cpx<R>));
-    auto kern = k_plane_stage<R, A, B, M>;
-    hipError_t e = set_lds(kern, lds);
-    if (e != hipSuccess) return e;
-    nct_launch(kern, dim3(grid), dim3(plane_nt(A * B)), lds, st, a, pt, ty, tz, S, NX);
   }
   return hipGetLastError();
 }
 
-template <typename R>
-hipError_t launch_plane_stage(const int n[3], int S, const StageArgs<R>& a, const ProjTables& pt,
+hipError_t launch_plane_stage(const int n[3], int S, const StageArgs<float>& a, const ProjTables& pt,
                               const void* twy, const void* twz, hipStream_t st) {
 #define X(A, B)                                                                              \
   if (n[1] == A && n[2] == B) {                                                              \
-    if (a.cache_mode >= 2) return launch_plane_stage_m<R, A, B, 2>(S, n[0], a, pt, twy, twz, st); \
-    if (a.cache_mode == 1) return launch_plane_stage_m<R, A, B, 1>(S, n[0], a, pt, twy, twz, st); \
-    return launch_plane_stage_m<R, A, B, 0>(S, n[0], a, pt, twy, twz, st);                  \
+    if (a.cache_mode >= 2) return launch_plane_stage_m<float, A, B, 2>(S, n[0], a, pt, twy, twz, st); \
+    if (a.cache_mode == 1) return launch_plane_stage_m<float, A, B, 1>(S, n[0], a, pt, twy, twz, st); \
+    return launch_plane_stage_m<float, A, B, 0>(S, n[0], a, pt, twy, twz, st);              \
   }
   NCT_PLANE_PAIRS(X)
 #undef X
   return hipErrorInvalidValue;
 }
+#endif
 
+#if !NCT_FP64_TU
 template <typename R>
 hipError_t launch_plane_fwd(const int n[3], int B, const void* in, void* out, void* W,
                             const ProjTables* pt, const void* twy, const void* twz, hipStream_t st,
@@ -1963,7 +2389,9 @@ hipError_t launch_dm_init(const int n[3], const double cell[3], int natoms, cons
              cell[1] / n[1], cell[2] / n[2], cell[0], cell[1], cell[2], natoms, atoms, moments, rho);
   return hipGetLastError();
 }
+#endif
 
+#if !NCT_FP64_TU
 template <typename R>
 hipError_t launch_rephase_rows(const ProjTables& pt, void* rows, int S, const double dA[3],
                                hipStream_t st) {
@@ -1974,6 +2402,7 @@ hipError_t launch_rephase_rows(const ProjTables& pt, void* rows, int S, const do
              R(dA[0]), R(dA[1]), R(dA[2]));
   return hipGetLastError();
 }
+#endif
 
 template <typename R>
 hipError_t launch_plane_inv(const int n[3], int B, const void* in, void* out, R scale,
@@ -2007,12 +2436,17 @@ static hipError_t launch_xpass_tc(int B, int NYZ, const void* src, void* dst, co
   // one tile per workgroup (a second, prefetched tile per workgroup measured no faster on
   // MI355X and costs occupancy)
   const dim3 grid(unsigned(B) * unsigned(tiles));
-  if (cache_mode >= 2)
-    nct_launch((k_xpass<R, NX, TC, 2>), grid, dim3(xp_nt<R, NX, TC>()), 0, st, s_, d_, NYZ, g2x, g2yz, kscale, mode, t_, kt);
-  else if (cache_mode == 1)
-    nct_launch((k_xpass<R, NX, TC, 1>), grid, dim3(xp_nt<R, NX, TC>()), 0, st, s_, d_, NYZ, g2x, g2yz, kscale, mode, t_, kt);
-  else
-    nct_launch((k_xpass<R, NX, TC, 0>), grid, dim3(xp_nt<R, NX, TC>()), 0, st, s_, d_, NYZ, g2x, g2yz, kscale, mode, t_, kt);
+  if constexpr (sizeof(R) == 4) {  // FP64 only runs the Poisson solve here: plain accesses
+    if (cache_mode >= 2) {
+      nct_launch((k_xpass<R, NX, TC, 2>), grid, dim3(xp_nt<R, NX, TC>()), 0, st, s_, d_, NYZ, g2x, g2yz, kscale, mode, t_, kt);
+      return hipGetLastError();
+    }
+    if (cache_mode == 1) {
+      nct_launch((k_xpass<R, NX, TC, 1>), grid, dim3(xp_nt<R, NX, TC>()), 0, st, s_, d_, NYZ, g2x, g2yz, kscale, mode, t_, kt);
+      return hipGetLastError();
+    }
+  }
+  nct_launch((k_xpass<R, NX, TC, 0>), grid, dim3(xp_nt<R, NX, TC>()), 0, st, s_, d_, NYZ, g2x, g2yz, kscale, mode, t_, kt);
   return hipGetLastError();
 }
 
@@ -2033,6 +2467,7 @@ hipError_t launch_xpass(const int n[3], int B, const void* src, void* dst, const
   return hipErrorInvalidValue;
 }
 
+#if !NCT_FP64_TU
 template <typename R>
 hipError_t launch_xpass_energy(const int n[3], int B, const void* src, const R* g2x,
                                const R* g2yz, R kscale, const void* twx, double* part,
@@ -2058,6 +2493,7 @@ hipError_t launch_xpass_energy(const int n[3], int B, const void* src, const R* 
 #undef X
   return hipErrorInvalidValue;
 }
+#endif
 
 template <typename R>
 hipError_t launch_density(const void* psi, const double* occ, int S, size_t N, double* rho,
@@ -2067,6 +2503,7 @@ hipError_t launch_density(const void* psi, const double* occ, int S, size_t N, d
   return hipGetLastError();
 }
 
+#if NCT_FP64_TU
 hipError_t launch_fields(const double* rho, const double* vext, const double* vH, int xc,
                          double thr, const int n[3], const double cell[3], double* fields,
                          float* fields32, double* part, int* nblk_out, hipStream_t st) {
@@ -2095,20 +2532,25 @@ hipError_t launch_to_float(const double* in, size_t n, float* out, hipStream_t s
   nct_launch(k_to_float, dim3(nblocks(n, 256)), dim3(256), 0, st, in, n, out);
   return hipGetLastError();
 }
+#endif
 
+template <typename R, int PP, bool KQ>
+static hipError_t launch_contract_pp(const ProjTables& pt, const void* W, int S, void* Cpart, const KinTables& kt,
+                                     hipStream_t st) {
+  const dim3 grid(pt.natoms, unsigned((S + 15) / 16), pt.max_kchunks);
+  nct_launch((k_proj_contract<R, PP, KQ>), grid, dim3(64), 0, st, pt, reinterpret_cast<const cpx<R>*>(W), S,
+             reinterpret_cast<cpx<double>*>(Cpart), kt);
+  return hipGetLastError();
+}
 template <typename R>
 hipError_t launch_proj_contract(const ProjTables& pt, const void* W, int S, double dV,
-                                void* Cpart, void* C, void* EC, hipStream_t st) {
+                                void* Cpart, void* C, void* EC, const KinTables& kt, hipStream_t st) {
   if (pt.natoms == 0) return hipSuccess;
-  const unsigned ntile = unsigned((S + 15) / 16);
-  const dim3 grid(pt.natoms, ntile, pt.max_kchunks);
-  if (pt.PP == 16)
-    nct_launch((k_proj_contract<R, 16>), grid, dim3(64), 0, st, pt,
-                       reinterpret_cast<const cpx<R>*>(W), S, reinterpret_cast<cpx<double>*>(Cpart));
-  else
-    nct_launch((k_proj_contract<R, 32>), grid, dim3(64), 0, st, pt,
-                       reinterpret_cast<const cpx<R>*>(W), S, reinterpret_cast<cpx<double>*>(Cpart));
-  hipError_t e = hipGetLastError();
+  const bool kq = sizeof(R) == 8 && kt.kv;
+  hipError_t e = pt.PP == 16 ? (kq ? launch_contract_pp<R, 16, sizeof(R) == 8>(pt, W, S, Cpart, kt, st)
+                                   : launch_contract_pp<R, 16, false>(pt, W, S, Cpart, kt, st))
+                             : (kq ? launch_contract_pp<R, 32, sizeof(R) == 8>(pt, W, S, Cpart, kt, st)
+                                   : launch_contract_pp<R, 32, false>(pt, W, S, Cpart, kt, st));
   if (e != hipSuccess) return e;
   const size_t total = size_t(pt.natoms) * pt.PP * S;
   nct_launch((k_proj_reduce<R>), dim3(nblocks(total, 256)), dim3(256), 0, st, pt,
@@ -2117,21 +2559,27 @@ hipError_t launch_proj_contract(const ProjTables& pt, const void* W, int S, doub
   return hipGetLastError();
 }
 
-template <typename R>
-hipError_t launch_proj_scatter(const ProjTables& pt, const void* EC, int S, void* Y,
-                               hipStream_t st) {
-  if (pt.natoms == 0) return hipSuccess;
-  const unsigned ntile = unsigned((S + 15) / 16);
-  const dim3 grid(pt.natoms, pt.max_rowtiles, ntile);
-  if (pt.PP == 16)
-    nct_launch((k_proj_scatter<R, 16>), grid, dim3(64), 0, st, pt,
-                       reinterpret_cast<const cpx<R>*>(EC), S, reinterpret_cast<cpx<R>*>(Y));
-  else
-    nct_launch((k_proj_scatter<R, 32>), grid, dim3(64), 0, st, pt,
-                       reinterpret_cast<const cpx<R>*>(EC), S, reinterpret_cast<cpx<R>*>(Y));
+template <typename R, int PP, bool KQ>
+static hipError_t launch_scatter_pp(const ProjTables& pt, const void* EC, int S, void* Y, const KinTables& kt,
+                                    hipStream_t st) {
+  const dim3 grid(pt.natoms, pt.max_rowtiles, unsigned((S + 15) / 16));
+  nct_launch((k_proj_scatter<R, PP, KQ>), grid, dim3(64), 0, st, pt, reinterpret_cast<const cpx<R>*>(EC), S,
+             reinterpret_cast<cpx<R>*>(Y), kt);
   return hipGetLastError();
 }
+template <typename R>
+hipError_t launch_proj_scatter(const ProjTables& pt, const void* EC, int S, void* Y, const KinTables& kt,
+                               hipStream_t st) {
+  if (pt.natoms == 0) return hipSuccess;
+  const bool kq = sizeof(R) == 8 && kt.kv;
+  if (pt.PP == 16)
+    return kq ? launch_scatter_pp<R, 16, sizeof(R) == 8>(pt, EC, S, Y, kt, st)
+              : launch_scatter_pp<R, 16, false>(pt, EC, S, Y, kt, st);
+  return kq ? launch_scatter_pp<R, 32, sizeof(R) == 8>(pt, EC, S, Y, kt, st)
+            : launch_scatter_pp<R, 32, false>(pt, EC, S, Y, kt, st);
+}
 
+#if NCT_FP64_TU
 int gram_chunks(int S, size_t K) {
   const int T = (S + GRAM_T - 1) / GRAM_T;
   const size_t pairs = size_t(T) * (T + 1) / 2;
@@ -2141,6 +2589,7 @@ int gram_chunks(int S, size_t K) {
   nc = std::min<size_t>(nc, std::max<size_t>(1, K / (4 * GRAM_KB)));   // chunks of >= 64 values
   return int(std::max<size_t>(nc, 1));
 }
+#endif
 
 template <typename R>
 hipError_t launch_gram(const void* A, int S, size_t K, double scale, void* part, int nchunks, void* out,
@@ -2169,10 +2618,12 @@ hipError_t launch_basis_transform(const void* A, const void* Mt, int S, size_t K
   return hipGetLastError();
 }
 
+#if NCT_FP64_TU
 hipError_t launch_obs_row(const ObsInputs& in, double* row, hipStream_t st) {
   nct_launch(k_obs_row, dim3(1), dim3(256), 0, st, in, row);
   return hipGetLastError();
 }
+#endif
 
 template <typename R>
 hipError_t launch_seed(const void* psi, const double* occ, int S, size_t N, double w0, double w1,
@@ -2192,13 +2643,14 @@ hipError_t launch_axpby(void* y, const void* x, size_t count, R a_re, R a_im, R 
 }
 
 template <typename R>
-hipError_t launch_pair(const void* mu, const void* w, int S, size_t N, double gamma, double* g,
+hipError_t launch_pair(const void* mu, const void* w, int S, size_t N, double cre, double cim, double* g,
                        hipStream_t st) {
   nct_launch((k_pair<R>), dim3(nblocks(N, 256)), dim3(256), 0, st,
                      reinterpret_cast<const cpx<R>*>(mu), reinterpret_cast<const cpx<R>*>(w), S, N,
-                     gamma, g);
+                     cre, cim, g);
   return hipGetLastError();
 }
+#if NCT_FP64_TU
 hipError_t launch_field_adjoint(const double* rho, const double* g, const double* pg, int xc,
                                 double thr, size_t N, double* gnm, double* part, int* nblk_out,
                                 hipStream_t st) {
@@ -2207,6 +2659,7 @@ hipError_t launch_field_adjoint(const double* rho, const double* g, const double
   nct_launch(k_field_adjoint, dim3(nb), dim3(256), 0, st, rho, g, pg, xc, thr, N, gnm, part);
   return hipGetLastError();
 }
+#endif
 template <typename R>
 hipError_t launch_density_backprop(const void* psi, const double* occ, const double* gnm, int S,
                                    size_t N, int add, void* lam, hipStream_t st) {
@@ -2218,35 +2671,34 @@ hipError_t launch_density_backprop(const void* psi, const double* occ, const dou
 
 // explicit instantiations
 #define NCT_INST(R)                                                                                \
-  template hipError_t launch_plane_stage<R>(const int*, int, const StageArgs<R>&, const ProjTables&, \
-                                            const void*, const void*, hipStream_t);                \
-  template hipError_t launch_plane_fwd<R>(const int*, int, const void*, void*, void*,              \
-                                          const ProjTables*, const void*, const void*, hipStream_t, \
-                                          KTables<R>);                                             \
-  template hipError_t launch_rephase_rows<R>(const ProjTables&, void*, int, const double*,       \
-                                             hipStream_t);                                         \
-  template hipError_t launch_plane_inv<R>(const int*, int, const void*, void*, R, const void*,     \
-                                          const void*, hipStream_t);                               \
   template hipError_t launch_xpass<R>(const int*, int, const void*, void*, const R*, const R*, R,  \
                                       int, const void*, hipStream_t, int, KTables<R>);             \
-  template hipError_t launch_xpass_energy<R>(const int*, int, const void*, const R*, const R*, R,  \
-                                             const void*, double*, int*, hipStream_t, KTables<R>); \
   template hipError_t launch_density<R>(const void*, const double*, int, size_t, double*,          \
                                         hipStream_t);                                              \
   template hipError_t launch_proj_contract<R>(const ProjTables&, const void*, int, double, void*,  \
-                                              void*, void*, hipStream_t);                          \
+                                              void*, void*, const KinTables&, hipStream_t);        \
   template hipError_t launch_proj_scatter<R>(const ProjTables&, const void*, int, void*,           \
-                                             hipStream_t);                                         \
+                                             const KinTables&, hipStream_t);                       \
   template hipError_t launch_seed<R>(const void*, const double*, int, size_t, double, double,      \
                                      double, double, void*, hipStream_t);                          \
   template hipError_t launch_axpby<R>(void*, const void*, size_t, R, R, R, hipStream_t);          \
-  template hipError_t launch_pair<R>(const void*, const void*, int, size_t, double, double*,      \
+  template hipError_t launch_pair<R>(const void*, const void*, int, size_t, double, double, double*, \
                                      hipStream_t);                                               \
   template hipError_t launch_density_backprop<R>(const void*, const double*, const double*, int,  \
                                                  size_t, int, void*, hipStream_t);               \
   template hipError_t launch_gram<R>(const void*, int, size_t, double, void*, int, void*, hipStream_t); \
   template hipError_t launch_basis_transform<R>(const void*, const void*, int, size_t, void*, hipStream_t);
+#if NCT_FP64_TU
 NCT_INST(double)
+template hipError_t launch_plane_inv<double>(const int*, int, const void*, void*, double, const void*, const void*,
+                                             hipStream_t);
+#else
 NCT_INST(float)
+template hipError_t launch_plane_fwd<float>(const int*, int, const void*, void*, void*, const ProjTables*,
+                                            const void*, const void*, hipStream_t, KTables<float>);
+template hipError_t launch_rephase_rows<float>(const ProjTables&, void*, int, const double*, hipStream_t);
+template hipError_t launch_xpass_energy<float>(const int*, int, const void*, const float*, const float*, float,
+                                               const void*, double*, int*, hipStream_t, KTables<float>);
+#endif
 
 }  // namespace nct

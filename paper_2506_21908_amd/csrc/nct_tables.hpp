@@ -127,6 +127,8 @@ struct ProjectorTables {
   std::vector<int> ix_of_row;                 // [Jtot] plane of each row
   std::vector<int> pr_off;                    // [NX + 1]
   std::vector<int> pr_begin, pr_end;          // [nranges]
+  std::vector<int> pmap;                      // [N] first row at a grid point, -1: none
+  std::vector<int> rnext;                     // [Jtot] next row at the same grid point, -1: none
   std::vector<std::complex<double>> beta;     // [Jtot][2][PP]: beta_p(r, s), zero beyond P
   std::vector<double> disp;                   // [Jtot][3] minimum-image displacement r - R_a
   std::vector<double> energy;                 // [natoms][PP] KB energy E_p, zero beyond P
@@ -229,6 +231,14 @@ inline std::string build_projector_tables(const int n[3], const double cell[3], 
       }
     }
     out.pr_off[x + 1] = int(out.pr_begin.size());
+  }
+  // point -> its rows: filled from the last row to the first, so each chain runs in atom order
+  out.pmap.assign(size_t(NX) * NY * NZ, -1);
+  out.rnext.assign(size_t(out.Jtot), -1);
+  for (int J = out.Jtot - 1; J >= 0; --J) {
+    int& head = out.pmap[size_t(out.ix_of_row[J]) * NY * NZ + out.pidx[J]];
+    out.rnext[J] = head;
+    head = J;
   }
   return "";
 }

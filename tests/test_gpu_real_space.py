@@ -1,0 +1,65 @@
+"""FP64 real-space form of the H application and product form of the exponential against the oracle.
+
+Bars: 1e-12 of the largest entry for one H application (the bar of the other single applications: a few
+roundings per transform stage, times the spread of the kinetic factors), 1e-12 for one step.
+"""
+import numpy as np
+import pytest
+
+from oracle import nct_oracle as O
+from paper_2506_21908_amd import inputs as I
+from parity_metrics import max_rel
+
+pytestmark = pytest.mark.gpu
+
+PLANES = [(8, 8), (12, 12), (16, 16), (24, 24), (32, 32), (48, 48), (64, 64), (96, 96),
+          (8, 16), (16, 8), (12, 16), (16, 12), (16, 24), (24, 16)]
+LINES = [8, 12, 16, 24, 32, 48, 64, 96]
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2506_21908_amd import nct
+    return torch, nct
+
+
+@pytest.mark.parametrize("k", range(len(PLANES)))
+def test_apply_every_plane_with_overlapping_spheres(gpu, k):
+    """Every built plane pair (partial waves, partial work items) with another column length, an odd
+    number of states and projector spheres that overlap (several rows at one grid point)."""
+    torch, nct = gpu
+    ny, nz = PLANES[k]
+    n = (LINES[(3 * k + 1) % len(LINES)] if ny * nz < 2000 else 8, ny, nz)
+    L = tuple(0.5 * v for v in n)
+    print(f"[case] apply n={n}", flush=True)
+    w = I.make_system(n=n, L=L, nstates=3, case=70 + k, natoms=3, min_sep=0.2 * min(L), r_sphere=0.45 * min(L))
+    F = np.random.default_rng(k).uniform(-0.5, 0.5, (4,) + n)
+    sysd = O.system_from_workload(w)
+    ref = (O.kinetic(w.psi0, sysd.grid) + O.apply_local(w.psi0, F[0], F[1:])
+           + O.apply_nonlocal(w.psi0, sysd.projs, sysd.grid))
+    s = nct.system_from_workload(w)
+    s.set_potentials(fields=torch.from_numpy(F).cuda())
+    psi = nct.states_to_device(w.psi0)
+    hpsi = torch.empty_like(psi)
+    s.apply_hamiltonian(psi, hpsi, 0.0)
+    assert max_rel(hpsi.cpu().numpy(), ref) < 1e-12
+
+
+# the product form starts where |z| E_max = 1.25, z = dt / 2: at h = 0.42 (E_max = 83.9) dt = 0.0298
+@pytest.mark.parametrize("K,dt", [(4, 0.029), (4, 0.031), (1, 0.031), (2, 0.031), (3, 0.031), (5, 0.04),
+                                  (8, 0.05), (12, 0.05), (13, 0.05)])
+def test_step_both_forms(gpu, K, dt):
+    """One step on either side of the rule that chooses Horner or product stages, odd and even orders."""
+    torch, nct = gpu
+    print(f"[case] step K={K} dt={dt}", flush=True)
+    w = I.make_system(n=(12, 12, 12), L=(5.04,) * 3, nstates=6, natoms=1, case=90, dt=dt, taylor_order=K,
+                      full_spinors=False, bfield=I.BField(B0=(0.01, -0.02, 0.03)), r_sphere=2.0)
+    psi_ref, _ = O.run(O.system_from_workload(w), w.psi0, 1)
+    s = nct.system_from_workload(w)
+    s.set_watchdog(0.0)  # low orders do not conserve the norm
+    psi = nct.states_to_device(w.psi0)
+    s.step(psi, 0.0, 1)
+    assert max_rel(psi.cpu().numpy(), psi_ref) < 1e-12

@@ -61,8 +61,6 @@ struct nct_system {
   hipStream_t stB = nullptr, stB2 = nullptr;
   hipEvent_t evB_rows = nullptr, evB_proj = nullptr, ev_fork = nullptr, ev_join = nullptr;
   void* CpartB = nullptr;
-  void* CB = nullptr;
-  void* ECB = nullptr;
   std::string err;
   std::vector<std::complex<double>> roots;  // of T_K (product form of the exponential)
   std::vector<DevBuf> owned;
@@ -145,8 +143,15 @@ struct nct_system {
   void* Yphi = nullptr;       // scatter rows of phi's first stage, shared by the 2nd and 3rd exponentials
   void* Cpart = nullptr;
   void* C = nullptr;
-  void* EC = nullptr;
   double* energy_dev = nullptr;
+  // FP64 Bloch phases of the sphere rows: distinct vectors, run of each state, table for the vector
+  // potential phase_ka (valid if phase_ok)
+  double* kruns = nullptr;    // [runs][3]
+  int* run_of = nullptr;      // [S]
+  void* phases = nullptr;     // complex double [runs][Jtot]
+  int phase_runs = 0, phase_cap = 0;
+  bool phase_ok = false;
+  double phase_ka[3] = {0, 0, 0};
 
   // adjoint tape: per step 3K state vectors (Taylor iterates of the three exponentials,
   // psi_n, phi, psi~) and the densities / fields of H_n and H~
@@ -339,6 +344,14 @@ nct_status build_projectors(nct_system* s) {
   pt.Jtot = ht.Jtot;
   pt.max_kchunks = ht.max_kchunks;
   pt.max_rowtiles = ht.max_rowtiles;
+  if (s->fp64) {
+    // longer chunks (fewer partials to write and sum) while a thousand waves remain; in FP32 the chunk
+    // is also the length of the FP32 sums, which stays 64
+    const int maxk = 8 * 2 * ht.max_rowtiles;  // rows of the largest atom, rounded up to a tile
+    const long pairs = long(s->natoms) * ((s->S + 15) / 16);
+    while (pt.kc < 256 && pairs * ((maxk + 2 * pt.kc - 1) / (2 * pt.kc)) >= 1024) pt.kc *= 2;
+    pt.max_kchunks = std::max(1, (maxk + pt.kc - 1) / pt.kc);
+  }
   int *d_row_off, *d_pr_off;
   nct_status r;
   if ((r = upload(s, ht.row_off, &d_row_off)) != NCT_OK) return r;
@@ -391,7 +404,6 @@ nct_status build_projectors(nct_system* s) {
   const size_t cp = size_t(s->natoms) * pt.PP * s->S;
   if ((r = dalloc(s, cp * pt.max_kchunks * 16, &s->Cpart)) != NCT_OK) return r;
   if ((r = dalloc(s, cp * 16, &s->C)) != NCT_OK) return r;
-  if ((r = dalloc(s, cp * s->cbytes, &s->EC)) != NCT_OK) return r;
   return NCT_OK;
 }
 
@@ -657,25 +669,58 @@ struct Engine {
   double proj_flops() const { return 8.0 * s->pt.P * 2.0 * s->pt.Jtot * s->S; }
   double beta_bytes() const { return 2.0 * s->pt.Jtot * s->pt.PP * sizeof(R) * 2; }
 
-  nct_status contract(const void* W, hipStream_t st) {
-    const double cpB = double(s->natoms) * s->pt.PP * s->S * 16.0;
-    return check(timed_on(s, st, NCT_K_PROJ, rowsB() + beta_bytes() + cpB * s->pt.max_kchunks, proj_flops(), [&] {
-                   return launch_proj_contract<R>(s->pt, W, s->S, s->dV, s->Cpart, s->C, s->EC, kint(), st); }),
+  // useful bytes: rows and projector values once, one partial per coefficient
+  double coeff_bytes(double frac = 1.0) const { return frac * double(s->natoms) * s->pt.PP * s->S * 16.0; }
+  // contraction of g's rows, and scatter rows from its partials, on stream st
+  nct_status contract(const void* W, int S, void* Cpart, const PhaseTab& ph, hipStream_t st) {
+    const double frac = double(S) / s->S;
+    return check(timed_on(s, st, NCT_K_PROJ, frac * rowsB() + beta_bytes() + coeff_bytes(frac) * s->pt.max_kchunks,
+                          frac * proj_flops(), [&] { return launch_proj_contract<R>(s->pt, W, S, Cpart, ph, st); }),
                  "proj_contract");
   }
+  nct_status scatter(const void* Cpart, int S, void* Y, const PhaseTab& ph, hipStream_t st) {
+    const double frac = double(S) / s->S;
+    return check(timed_on(s, st, NCT_K_PROJ, frac * rowsB() + beta_bytes() + coeff_bytes(frac) * s->pt.max_kchunks,
+                          frac * proj_flops(),
+                          [&] { return launch_proj_scatter<R>(s->pt, Cpart, S, s->dV, Y, ph, st); }), "proj_scatter");
+  }
 
-  // NL projections of the sphere rows W -> Y (scatter rows) and C.  Enqueued on the second
+  // The FP64 phase table of the current Bloch vectors and vector potential (null without either).
+  // Called with ka set, on the main stream, after every earlier use of the table has joined it.
+  nct_status phase_table(PhaseTab& ph) {
+    ph = PhaseTab{};
+    if (!RS || s->natoms == 0 || !kvR()) return NCT_OK;
+    nct_status r;
+    const int runs = s->has_k ? s->phase_runs : 1;
+    if (s->phase_cap < runs) {
+      s->phase_cap = 0;
+      if ((r = dalloc(s, size_t(runs) * s->pt.Jtot * 16, &s->phases)) != NCT_OK) return r;
+      s->phase_cap = runs;
+      s->phase_ok = false;
+    }
+    if (!s->phase_ok || ka[0] != s->phase_ka[0] || ka[1] != s->phase_ka[1] || ka[2] != s->phase_ka[2]) {
+      if ((r = check(launch_phases(s->has_k ? s->kruns : s->kv_zero64, runs, ka, s->pt, s->phases, s->st), "phases")) !=
+          NCT_OK)
+        return r;
+      for (int d = 0; d < 3; ++d) s->phase_ka[d] = ka[d];
+      s->phase_ok = true;
+    }
+    ph.tab = static_cast<const cpx<double>*>(s->phases);
+    ph.run = s->has_k ? s->run_of : nullptr;
+    return NCT_OK;
+  }
+
+  // NL projections of the sphere rows W -> Y (scatter rows).  Enqueued on the second
   // stream after the rows are ready; join_projections() makes the main stream wait for Y.
   nct_status projections(const void* W) {
     if (s->natoms == 0) return NCT_OK;
     nct_status r;
+    PhaseTab ph;
+    if ((r = phase_table(ph)) != NCT_OK) return r;
     HIPCHK(s, hipEventRecord(s->ev_rows, s->st));
     HIPCHK(s, hipStreamWaitEvent(s->st2, s->ev_rows, 0));
-    if ((r = contract(W, s->st2)) != NCT_OK) return r;
-    const double ecB = double(s->natoms) * s->pt.PP * s->S * sizeof(R) * 2;
-    if ((r = check(timed_on(s, s->st2, NCT_K_PROJ, beta_bytes() + ecB + rowsB(), proj_flops(), [&] {
-                     return launch_proj_scatter<R>(s->pt, s->EC, s->S, s->Y, kint(), s->st2); }), "proj_scatter")) != NCT_OK)
-      return r;
+    if ((r = contract(W, s->S, s->Cpart, ph, s->st2)) != NCT_OK) return r;
+    if ((r = scatter(s->Cpart, s->S, s->Y, ph, s->st2)) != NCT_OK) return r;
     HIPCHK(s, hipEventRecord(s->ev_proj, s->st2));
     return NCT_OK;
   }
@@ -748,12 +793,12 @@ struct Engine {
     int i0, S;
     hipStream_t st, st2;
     hipEvent_t ev_rows, ev_proj;
-    void *Cpart, *C, *EC;
+    void* Cpart;
   };
   int groups(Group* g) const {
-    g[0] = {0, s->ngroups > 1 ? s->S0 : s->S, s->st, s->st2, s->ev_rows, s->ev_proj, s->Cpart, s->C, s->EC};
+    g[0] = {0, s->ngroups > 1 ? s->S0 : s->S, s->st, s->st2, s->ev_rows, s->ev_proj, s->Cpart};
     if (s->ngroups == 1) return 1;
-    g[1] = {s->S0, s->S - s->S0, s->stB, s->stB2, s->evB_rows, s->evB_proj, s->CpartB, s->CB, s->ECB};
+    g[1] = {s->S0, s->S - s->S0, s->stB, s->stB2, s->evB_rows, s->evB_proj, s->CpartB};
     return 2;
   }
   template <typename P>
@@ -787,25 +832,16 @@ struct Engine {
   // (full-size pointers; offset here to the group).  FP32 only:
   // kin_dst: column-pass output buffer (default s->tmp); chat == nullptr: skip the column pass,
   // sa_full.tmp_in already holds it.
-  nct_status stage_group(const Group& g, const void* cW, const void* chat, const StageArgs<R>& sa_full,
+  nct_status stage_group(const Group& g, const void* cW, const void* chat, const StageArgs<R>& sa_full, PhaseTab ph,
                          void* kin_dst = nullptr, void* y_dst = nullptr, const void* y_src = nullptr) {
     nct_status r;
-    const double frac = double(g.S) / double(s->S);
     void* ybuf = y_dst ? y_dst : s->Y;
     if (s->natoms && !y_src) {
       HIPCHK(s, hipEventRecord(g.ev_rows, g.st));
       HIPCHK(s, hipStreamWaitEvent(g.st2, g.ev_rows, 0));
-      const double cpB = double(s->natoms) * s->pt.PP * g.S * 16.0;
-      if ((r = check(timed_on(s, g.st2, NCT_K_PROJ, frac * (rowsB() + beta_bytes()) + cpB * s->pt.max_kchunks,
-                              frac * proj_flops(), [&] {
-                                return launch_proj_contract<R>(s->pt, offr(cW, g.i0), g.S, s->dV, g.Cpart, g.C,
-                                                               g.EC, kint(g.i0), g.st2); }), "proj_contract")) != NCT_OK)
-        return r;
-      const double ecB = double(s->natoms) * s->pt.PP * g.S * sizeof(R) * 2;
-      if ((r = check(timed_on(s, g.st2, NCT_K_PROJ, beta_bytes() + ecB + frac * rowsB(), frac * proj_flops(), [&] {
-                       return launch_proj_scatter<R>(s->pt, g.EC, g.S, offr(ybuf, g.i0), kint(g.i0), g.st2); }),
-                     "proj_scatter")) != NCT_OK)
-        return r;
+      ph.state_off = g.i0;
+      if ((r = contract(offr(cW, g.i0), g.S, g.Cpart, ph, g.st2)) != NCT_OK) return r;
+      if ((r = scatter(g.Cpart, g.S, offr(ybuf, g.i0), ph, g.st2)) != NCT_OK) return r;
       HIPCHK(s, hipEventRecord(g.ev_proj, g.st2));
     }
     StageArgs<R> sa = sa_full;
@@ -876,6 +912,8 @@ struct Engine {
     sa.fields = fieldsR();
     if (RS) kin_save = nullptr, kin_reuse = nullptr;
     nct_status r;
+    PhaseTab ph;
+    if ((r = phase_table(ph)) != NCT_OK) return r;
     Group G[2];
     const int ng = groups(G);
     if ((r = fork_groups()) != NCT_OK) return r;
@@ -901,7 +939,7 @@ struct Engine {
       sa.W = s->natoms ? (last ? outW : s->Wwork) : nullptr;
       sa.acc = nullptr;
       for (int gi = 0; gi < ng; ++gi)
-        if ((r = stage_group(G[gi], cW, (first && kin_reuse) ? nullptr : chat, sa, first ? kin_save : nullptr,
+        if ((r = stage_group(G[gi], cW, (first && kin_reuse) ? nullptr : chat, sa, ph, first ? kin_save : nullptr,
                              first ? y_save : nullptr, first ? y_reuse : nullptr)) != NCT_OK)
           return r;
       cw = sa.w_out;
@@ -952,7 +990,10 @@ struct Engine {
                                          twx(), s->epart, &ntiles, s->st, ktab()); }), "energy")) != NCT_OK)
       return r;
     if (s->natoms) {
-      if ((r = contract(s->Wpsi, s->st)) != NCT_OK) return r;
+      PhaseTab ph;
+      if ((r = phase_table(ph)) != NCT_OK) return r;
+      if ((r = contract(s->Wpsi, s->S, s->Cpart, ph, s->st)) != NCT_OK) return r;
+      if ((r = check(launch_proj_reduce(s->pt, s->Cpart, s->S, s->dV, s->C, s->st), "proj_reduce")) != NCT_OK) return r;
     }
     ObsInputs in;
     in.field_tot = s->ftot;
@@ -1661,8 +1702,6 @@ nct_status create_impl(const nct_params* p, nct_system** out) {
     if (s->natoms) {
       const size_t cp = size_t(s->natoms) * s->pt.PP * s->S;
       if ((r = dalloc(s, cp * s->pt.max_kchunks * 16, &s->CpartB)) != NCT_OK) return bail(r);
-      if ((r = dalloc(s, cp * 16, &s->CB)) != NCT_OK) return bail(r);
-      if ((r = dalloc(s, cp * s->cbytes, &s->ECB)) != NCT_OK) return bail(r);
     }
   }
   {  // this device's static scratch (allocation-free entry point): looked up once per device
@@ -1839,6 +1878,7 @@ nct_status nct_set_kpoints(nct_system* s, const double* kvec) {
   if (!s) return NCT_ERR_ARG;
   if (!kvec) {
     s->has_k = false;
+    s->phase_ok = false;  // a velocity gauge now takes the zero vectors
     return NCT_OK;
   }
   const size_t n = size_t(s->S) * 3;
@@ -1867,8 +1907,30 @@ nct_status nct_set_kpoints(nct_system* s, const double* kvec) {
   std::vector<float> k32(kvec, kvec + n);
   HIPCHK(s, hipMemcpyAsync(s->kv64, kvec, n * sizeof(double), hipMemcpyHostToDevice, s->st));
   HIPCHK(s, hipMemcpyAsync(s->kv32, k32.data(), n * sizeof(float), hipMemcpyHostToDevice, s->st));
+  if (s->fp64 && s->natoms) {  // distinct vectors of the phase table
+    const int runs = int(s->krun.size()) - 1;
+    std::vector<double> kr(size_t(runs) * 3);
+    std::vector<int> ro(s->S);
+    for (int b = 0; b < runs; ++b) {
+      for (int d = 0; d < 3; ++d) kr[3 * b + d] = kvec[3 * size_t(s->krun[b]) + d];
+      for (int i = s->krun[b]; i < s->krun[b + 1]; ++i) ro[i] = b;
+    }
+    if (!s->run_of) {
+      void* p;
+      if ((r = dalloc(s, size_t(s->S) * 3 * sizeof(double), &p)) != NCT_OK) return r;
+      s->kruns = static_cast<double*>(p);
+      if ((r = dalloc(s, size_t(s->S) * sizeof(int), &p)) != NCT_OK) return r;
+      s->run_of = static_cast<int*>(p);
+    }
+    HIPCHK(s, hipMemcpyAsync(s->kruns, kr.data(), kr.size() * sizeof(double), hipMemcpyHostToDevice, s->st));
+    HIPCHK(s, hipMemcpyAsync(s->run_of, ro.data(), ro.size() * sizeof(int), hipMemcpyHostToDevice, s->st));
+    s->phase_runs = runs;
+    s->phase_ok = false;
+    HIPCHK(s, hipStreamSynchronize(s->st));
+  }
   HIPCHK(s, hipStreamSynchronize(s->st));
   s->has_k = true;
+  s->phase_ok = false;
   return NCT_OK;
 }
 

@@ -19,7 +19,8 @@ struct ProjTables {
   int P = 0;            // projectors per atom
   int PP = 0;           // P padded to a multiple of 16
   int Jtot = 0;         // total sphere rows
-  int max_kchunks = 0;  // max over atoms of ceil(2 ns / KC)
+  int kc = 64;          // rows of one contraction chunk
+  int max_kchunks = 0;  // max over atoms of ceil(2 ns / kc)
   int max_rowtiles = 0; // max over atoms of ceil(2 ns / 16)
   const int* row_off = nullptr;   // [natoms+1]
   const int* pidx = nullptr;      // [Jtot] in-plane index y*NZ + z
@@ -158,13 +159,28 @@ hipError_t launch_add_bext(const double* fields, const int n[3], const double b[
                            const double lg[4], double* out, hipStream_t st);
 hipError_t launch_to_float(const double* in, size_t n, float* out, hipStream_t st);
 
-// Projectors: C = dV beta^H W (per atom), EC = E * C; Y = beta EC.  FP64 with Bloch vectors (kt.kv): the
-// rows of W are taken times exp(i k.d), those of Y times exp(-i k.d); in FP32 the plane pass does that.
+// Phases exp(i (k + A).d) of the sphere rows per distinct Bloch vector (FP64; in FP32 the plane pass
+// computes them).
+struct PhaseTab {
+  const cpx<double>* tab = nullptr;  // [runs][Jtot], null: no Bloch vectors
+  const int* run = nullptr;          // [S] run of each state, null: run 0
+  int state_off = 0;                 // this launch's state 0
+  __host__ __device__ const cpx<double>* row(int i, int Jtot) const {
+    return tab + size_t(run ? run[state_off + i] : 0) * Jtot;
+  }
+};
+hipError_t launch_phases(const double* kruns, int nruns, const double ka[3], const ProjTables& pt, void* tab,
+                         hipStream_t st);
+
+// Projectors: chunk partials of beta^H W (per atom); C = dV times their sum (observables);
+// Y = beta E C from the partials.  With phases (ph.tab) the rows of W are taken times them, those of Y
+// times their conjugates.
 template <typename R>
-hipError_t launch_proj_contract(const ProjTables& pt, const void* W, int S, double dV,
-                                void* Cpart, void* C, void* EC, const KinTables& kt, hipStream_t st);
+hipError_t launch_proj_contract(const ProjTables& pt, const void* W, int S, void* Cpart, const PhaseTab& ph,
+                                hipStream_t st);
+hipError_t launch_proj_reduce(const ProjTables& pt, const void* Cpart, int S, double dV, void* C, hipStream_t st);
 template <typename R>
-hipError_t launch_proj_scatter(const ProjTables& pt, const void* EC, int S, void* Y, const KinTables& kt,
+hipError_t launch_proj_scatter(const ProjTables& pt, const void* Cpart, int S, double dV, void* Y, const PhaseTab& ph,
                                hipStream_t st);
 
 // Observables of the current state: assembles one 13-double row.

@@ -89,7 +89,7 @@ __device__ __forceinline__ void st_stream(cpx<R>* p, cpx<R> v) {
 }
 
 // Bloch phase exp(i q.d) of one sphere row (q: Bloch vector, d: the row's displacement from its
-// atom).  Rows gathered for the projections carry it, scattered rows its conjugate.
+// atom).  Rows taken into the projections carry it, scattered rows its conjugate.
 // (q passed as scalars: an addressable local array would live in scratch memory)
 __device__ __forceinline__ cpx<double> bloch_phase(double q0, double q1, double q2, const double* d) {
   double sn, cs;
@@ -1498,28 +1498,29 @@ struct mfma16<float> {
   }
 };
 
-constexpr int KC = 64;  // contraction K chunk per wave
 constexpr int KU = 4;   // k-steps whose operands are loaded together
 
 // Cpart[a][kc][p][i] = sum_{k in chunk} conj(beta[a][k][p]) W[i][k], k = 2 (J - off_a) + s.
 // One wave: PP/16 output tiles of 16 projectors x 16 states; A/B operands as
 // A[row = lane%16][k = lane/16], B[k = lane/16][col = lane%16]; D rows from mfma16::row.
-// KQ: the rows of W are taken times exp(i k.d) (FP64 with Bloch vectors; in FP32 the plane pass has
-// put the phase on them).
+// KQ: the rows of W are taken times the phases exp(i k.d) of PhaseTab (FP64 with Bloch vectors; in FP32
+// the plane pass has put the phase on them).
 template <typename R, int PP, bool KQ>
 __global__ __launch_bounds__(64) void k_proj_contract(ProjTables pt, const cpx<R>* __restrict__ W,
-                                                      int S, cpx<double>* __restrict__ Cpart, KinTables kt) {
+                                                      int S, cpx<double>* __restrict__ Cpart, PhaseTab ph) {
   using M = mfma16<R>;
   constexpr int NMT = PP / 16;
   const int a = blockIdx.x, nt = blockIdx.y, kc = blockIdx.z;
   const int off = pt.row_off[a];
   const int K = 2 * (pt.row_off[a + 1] - off);
-  const int nch_a = (K + KC - 1) / KC;
-  if (kc >= nch_a) return;
+  const int KC = pt.kc;
+  if (kc * KC >= K) return;
   const int lane = threadIdx.x;
   const int col = lane & 15, kl = lane >> 4;
   const int i = nt * 16 + col;
   const cpx<R>* __restrict__ beta = reinterpret_cast<const cpx<R>*>(pt.beta);
+  const cpx<double>* __restrict__ phase = nullptr;
+  if constexpr (KQ) phase = ph.row(min(i, S - 1), pt.Jtot);
   typename M::acc ar[NMT], ai[NMT];
 #pragma unroll
   for (int mt = 0; mt < NMT; ++mt) {
@@ -1536,11 +1537,7 @@ __global__ __launch_bounds__(64) void k_proj_contract(ProjTables pt, const cpx<R
       const int kk = ok ? k : kc * KC;  // clamped index, value zeroed below
       const int J = off + (kk >> 1), s = kk & 1;
       cpx<R> w = W[size_t(2 * min(i, S - 1) + s) * pt.Jtot + J];
-      if constexpr (KQ) {
-        const int ii = min(i, S - 1);
-        w = cmul(w, bloch_phase(R(kt.shift(ii, 0)), R(kt.shift(ii, 1)), R(kt.shift(ii, 2)),
-                                reinterpret_cast<const R*>(pt.disp) + 3 * J));
-      }
+      if constexpr (KQ) w = cmul(w, phase[J]);
       bw[u] = (ok && i < S) ? w : cpx<R>{R(0), R(0)};
 #pragma unroll
       for (int mt = 0; mt < NMT; ++mt) {
@@ -1571,19 +1568,11 @@ __global__ __launch_bounds__(64) void k_proj_contract(ProjTables pt, const cpx<R
   }
 }
 
-// C[a][p][i] = dV sum_kc Cpart (chunk order); EC = E[a][p] C (R precision)
-template <typename R>
-__global__ __launch_bounds__(256) void k_proj_reduce(ProjTables pt, const cpx<double>* __restrict__ Cpart,
-                                                     int S, double dV, cpx<double>* __restrict__ C,
-                                                     cpx<R>* __restrict__ EC) {
-  const size_t idx = size_t(blockIdx.x) * 256 + threadIdx.x;
-  const size_t total = size_t(pt.natoms) * pt.PP * S;
-  if (idx >= total) return;
-  const int i = int(idx % S);
-  const int p = int((idx / S) % pt.PP);
-  const int a = int(idx / (size_t(S) * pt.PP));
+// dV sum_kc Cpart[a][kc][p][i] in chunk order
+__device__ __forceinline__ cpx<double> proj_sum(const ProjTables& pt, const cpx<double>* __restrict__ Cpart, int S,
+                                                double dV, int a, int p, int i) {
   const int K = 2 * (pt.row_off[a + 1] - pt.row_off[a]);
-  const int nch_a = (K + KC - 1) / KC;
+  const int nch_a = (K + pt.kc - 1) / pt.kc;
   const size_t stride = size_t(pt.PP) * S;
   const cpx<double>* src = Cpart + (size_t(a) * pt.max_kchunks * pt.PP + p) * S + i;
   double sr = 0, si = 0;
@@ -1603,58 +1592,88 @@ __global__ __launch_bounds__(256) void k_proj_reduce(ProjTables pt, const cpx<do
     sr += v.x;
     si += v.y;
   }
-  sr *= dV;
-  si *= dV;
-  C[idx] = {sr, si};
-  const double e = pt.energy[size_t(a) * pt.PP + p];
-  EC[idx] = {R(e * sr), R(e * si)};
+  return {sr * dV, si * dV};
+}
+// C[a][p][i] of the observables
+static __global__ __launch_bounds__(256) void k_proj_reduce(ProjTables pt, const cpx<double>* __restrict__ Cpart,
+                                                            int S, double dV, cpx<double>* __restrict__ C) {
+  const size_t idx = size_t(blockIdx.x) * 256 + threadIdx.x;
+  if (idx >= size_t(pt.natoms) * pt.PP * S) return;
+  C[idx] = proj_sum(pt, Cpart, S, dV, int(idx / (size_t(S) * pt.PP)), int((idx / S) % pt.PP), int(idx % S));
 }
 
-// Y[i][s][J] = sum_p beta[J][s][p] EC[a][p][i]; rows k = 2 (J - off_a) + s
-// (KQ: times exp(-i k.d))
+// Y[i][s][J] = sum_p beta[J][s][p] E[a][p] C[a][p][i]; rows k = 2 (J - off_a) + s (KQ: times exp(-i k.d)).
+// One workgroup per (atom, 16 states, share of the atom's row tiles).  It first sums the chunk partials
+// of its own 16 x PP coefficients, which all shares of an atom repeat: they are few and in L2, and a
+// launch of their own stood between the contraction and this one (5-39 us each time, on the path that
+// the plane pass waits for where the column pass is short).
+constexpr int PS_NT = 256;
 template <typename R, int PP, bool KQ>
-__global__ __launch_bounds__(64) void k_proj_scatter(ProjTables pt, const cpx<R>* __restrict__ EC,
-                                                     int S, cpx<R>* __restrict__ Y, KinTables kt) {
+__global__ __launch_bounds__(PS_NT) void k_proj_scatter(ProjTables pt, const cpx<double>* __restrict__ Cpart,
+                                                        int S, double dV, cpx<R>* __restrict__ Y, PhaseTab ph) {
   using M = mfma16<R>;
   constexpr int KS = PP / 4;
-  const int a = blockIdx.x, rt = blockIdx.y, nt = blockIdx.z;
+  __shared__ cpx<R> ecs[PP][16];
+  const int a = blockIdx.x, nt = blockIdx.y;
   const int off = pt.row_off[a];
   const int K2 = 2 * (pt.row_off[a + 1] - off);
-  if (rt * 16 >= K2) return;
-  const int lane = threadIdx.x;
+#pragma unroll
+  for (int e = threadIdx.x; e < PP * 16; e += PS_NT) {
+    const int p = e >> 4, i = nt * 16 + (e & 15);
+    cpx<R> v = {R(0), R(0)};
+    if (i < S) {
+      const cpx<double> c = proj_sum(pt, Cpart, S, dV, a, p, i);
+      const double en = pt.energy[size_t(a) * PP + p];
+      v = {R(en * c.x), R(en * c.y)};
+    }
+    ecs[p][e & 15] = v;
+  }
+  __syncthreads();
+  const int lane = threadIdx.x & 63;
   const int col = lane & 15, kl = lane >> 4;
-  const int row = rt * 16 + col;
   const int i = nt * 16 + col;
   const cpx<R>* __restrict__ beta = reinterpret_cast<const cpx<R>*>(pt.beta);
-  cpx<R> xb[KS], ec[KS];
+  const cpx<double>* __restrict__ phase = nullptr;
+  if constexpr (KQ) phase = ph.row(min(i, S - 1), pt.Jtot);
+  cpx<R> ec[KS];
 #pragma unroll
-  for (int u = 0; u < KS; ++u) {
-    const int p = 4 * u + kl;
-    const cpx<R> bv = beta[(size_t(2 * off) + min(row, K2 - 1)) * PP + p];
-    xb[u] = row < K2 ? bv : cpx<R>{R(0), R(0)};
-    const cpx<R> ev = EC[(size_t(a) * PP + p) * S + min(i, S - 1)];
-    ec[u] = i < S ? ev : cpx<R>{R(0), R(0)};
-  }
-  typename M::acc yr = M::zero(), yi = M::zero();
+  for (int u = 0; u < KS; ++u) ec[u] = ecs[4 * u + kl][col];
+  for (int rt = blockIdx.z * (PS_NT / 64) + (threadIdx.x >> 6); rt * 16 < K2; rt += gridDim.z * (PS_NT / 64)) {
+    const int row = rt * 16 + col;
+    cpx<R> xb[KS];
 #pragma unroll
-  for (int u = 0; u < KS; ++u) {
-    yr = M::op(xb[u].x, ec[u].x, yr);
-    yr = M::op(-xb[u].y, ec[u].y, yr);
-    yi = M::op(xb[u].x, ec[u].y, yi);
-    yi = M::op(xb[u].y, ec[u].x, yi);
-  }
+    for (int u = 0; u < KS; ++u) {
+      const cpx<R> bv = beta[(size_t(2 * off) + min(row, K2 - 1)) * PP + 4 * u + kl];
+      xb[u] = row < K2 ? bv : cpx<R>{R(0), R(0)};
+    }
+    typename M::acc yr = M::zero(), yi = M::zero();
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int rr = rt * 16 + M::row(r, kl);
-    if (rr < K2 && i < S) {
-      const int J = off + (rr >> 1), s = rr & 1;
-      cpx<R> y = {yr[r], yi[r]};
-      if constexpr (KQ)
-        y = cmulc(y, bloch_phase(R(kt.shift(i, 0)), R(kt.shift(i, 1)), R(kt.shift(i, 2)),
-                                 reinterpret_cast<const R*>(pt.disp) + 3 * J));
-      Y[size_t(2 * i + s) * pt.Jtot + J] = y;
+    for (int u = 0; u < KS; ++u) {
+      yr = M::op(xb[u].x, ec[u].x, yr);
+      yr = M::op(-xb[u].y, ec[u].y, yr);
+      yi = M::op(xb[u].x, ec[u].y, yi);
+      yi = M::op(xb[u].y, ec[u].x, yi);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int rr = rt * 16 + M::row(r, kl);
+      if (rr < K2 && i < S) {
+        const int J = off + (rr >> 1), sp = rr & 1;
+        cpx<R> y = {yr[r], yi[r]};
+        if constexpr (KQ) y = cmulc(y, phase[J]);
+        Y[size_t(2 * i + sp) * pt.Jtot + J] = y;
+      }
     }
   }
+}
+
+// Phases exp(i (k + A).d) of every sphere row for each distinct Bloch vector.
+static __global__ __launch_bounds__(256) void k_phases(const double* __restrict__ kruns, double a0, double a1, double a2,
+                                                       const double* __restrict__ disp, int Jtot,
+                                                       cpx<double>* __restrict__ out) {
+  const int J = blockIdx.y * 256 + threadIdx.x;
+  const double* k = kruns + 3 * size_t(blockIdx.x);
+  if (J < Jtot) out[size_t(blockIdx.x) * Jtot + J] = bloch_phase(k[0] + a0, k[1] + a1, k[2] + a2, disp + 3 * J);
 }
 
 // ---------------------------------------------------------------- adjoint kernels
@@ -2535,48 +2554,64 @@ hipError_t launch_to_float(const double* in, size_t n, float* out, hipStream_t s
 #endif
 
 template <typename R, int PP, bool KQ>
-static hipError_t launch_contract_pp(const ProjTables& pt, const void* W, int S, void* Cpart, const KinTables& kt,
+static hipError_t launch_contract_pp(const ProjTables& pt, const void* W, int S, void* Cpart, const PhaseTab& ph,
                                      hipStream_t st) {
   const dim3 grid(pt.natoms, unsigned((S + 15) / 16), pt.max_kchunks);
   nct_launch((k_proj_contract<R, PP, KQ>), grid, dim3(64), 0, st, pt, reinterpret_cast<const cpx<R>*>(W), S,
-             reinterpret_cast<cpx<double>*>(Cpart), kt);
+             reinterpret_cast<cpx<double>*>(Cpart), ph);
   return hipGetLastError();
 }
 template <typename R>
-hipError_t launch_proj_contract(const ProjTables& pt, const void* W, int S, double dV,
-                                void* Cpart, void* C, void* EC, const KinTables& kt, hipStream_t st) {
+hipError_t launch_proj_contract(const ProjTables& pt, const void* W, int S, void* Cpart, const PhaseTab& ph,
+                                hipStream_t st) {
   if (pt.natoms == 0) return hipSuccess;
-  const bool kq = sizeof(R) == 8 && kt.kv;
-  hipError_t e = pt.PP == 16 ? (kq ? launch_contract_pp<R, 16, sizeof(R) == 8>(pt, W, S, Cpart, kt, st)
-                                   : launch_contract_pp<R, 16, false>(pt, W, S, Cpart, kt, st))
-                             : (kq ? launch_contract_pp<R, 32, sizeof(R) == 8>(pt, W, S, Cpart, kt, st)
-                                   : launch_contract_pp<R, 32, false>(pt, W, S, Cpart, kt, st));
-  if (e != hipSuccess) return e;
-  const size_t total = size_t(pt.natoms) * pt.PP * S;
-  nct_launch((k_proj_reduce<R>), dim3(nblocks(total, 256)), dim3(256), 0, st, pt,
-                     reinterpret_cast<const cpx<double>*>(Cpart), S, dV,
-                     reinterpret_cast<cpx<double>*>(C), reinterpret_cast<cpx<R>*>(EC));
+  if constexpr (sizeof(R) == 8) {
+    if (ph.tab)
+      return pt.PP == 16 ? launch_contract_pp<R, 16, true>(pt, W, S, Cpart, ph, st)
+                         : launch_contract_pp<R, 32, true>(pt, W, S, Cpart, ph, st);
+  }
+  return pt.PP == 16 ? launch_contract_pp<R, 16, false>(pt, W, S, Cpart, ph, st)
+                     : launch_contract_pp<R, 32, false>(pt, W, S, Cpart, ph, st);
+}
+#if NCT_FP64_TU
+hipError_t launch_proj_reduce(const ProjTables& pt, const void* Cpart, int S, double dV, void* C, hipStream_t st) {
+  if (pt.natoms == 0) return hipSuccess;
+  nct_launch(k_proj_reduce, dim3(nblocks(size_t(pt.natoms) * pt.PP * S, 256)), dim3(256), 0, st, pt,
+             reinterpret_cast<const cpx<double>*>(Cpart), S, dV, reinterpret_cast<cpx<double>*>(C));
   return hipGetLastError();
 }
+hipError_t launch_phases(const double* kruns, int nruns, const double ka[3], const ProjTables& pt, void* tab,
+                         hipStream_t st) {
+  if (pt.natoms == 0 || pt.Jtot == 0) return hipSuccess;
+  nct_launch(k_phases, dim3(unsigned(nruns), nblocks(size_t(pt.Jtot), 256)), dim3(256), 0, st, kruns, ka[0], ka[1],
+             ka[2], reinterpret_cast<const double*>(pt.disp), pt.Jtot, reinterpret_cast<cpx<double>*>(tab));
+  return hipGetLastError();
+}
+#endif
 
 template <typename R, int PP, bool KQ>
-static hipError_t launch_scatter_pp(const ProjTables& pt, const void* EC, int S, void* Y, const KinTables& kt,
-                                    hipStream_t st) {
-  const dim3 grid(pt.natoms, pt.max_rowtiles, unsigned((S + 15) / 16));
-  nct_launch((k_proj_scatter<R, PP, KQ>), grid, dim3(64), 0, st, pt, reinterpret_cast<const cpx<R>*>(EC), S,
-             reinterpret_cast<cpx<R>*>(Y), kt);
+static hipError_t launch_scatter_pp(const ProjTables& pt, const void* Cpart, int S, double dV, void* Y,
+                                    const PhaseTab& ph, hipStream_t st) {
+  // shares of an atom's row tiles: one tile per wave where there are few (atom, states) pairs, down to
+  // all tiles in one workgroup from 512 pairs on, where the repeated sums would cost more than they win
+  const int waves = PS_NT / 64, ntile = (S + 15) / 16;
+  const int shares = std::max(1, std::min((pt.max_rowtiles + waves - 1) / waves, 512 / (pt.natoms * ntile)));
+  const dim3 grid(pt.natoms, unsigned(ntile), unsigned(shares));
+  nct_launch((k_proj_scatter<R, PP, KQ>), grid, dim3(PS_NT), 0, st, pt, reinterpret_cast<const cpx<double>*>(Cpart), S,
+             dV, reinterpret_cast<cpx<R>*>(Y), ph);
   return hipGetLastError();
 }
 template <typename R>
-hipError_t launch_proj_scatter(const ProjTables& pt, const void* EC, int S, void* Y, const KinTables& kt,
+hipError_t launch_proj_scatter(const ProjTables& pt, const void* Cpart, int S, double dV, void* Y, const PhaseTab& ph,
                                hipStream_t st) {
   if (pt.natoms == 0) return hipSuccess;
-  const bool kq = sizeof(R) == 8 && kt.kv;
-  if (pt.PP == 16)
-    return kq ? launch_scatter_pp<R, 16, sizeof(R) == 8>(pt, EC, S, Y, kt, st)
-              : launch_scatter_pp<R, 16, false>(pt, EC, S, Y, kt, st);
-  return kq ? launch_scatter_pp<R, 32, sizeof(R) == 8>(pt, EC, S, Y, kt, st)
-            : launch_scatter_pp<R, 32, false>(pt, EC, S, Y, kt, st);
+  if constexpr (sizeof(R) == 8) {
+    if (ph.tab)
+      return pt.PP == 16 ? launch_scatter_pp<R, 16, true>(pt, Cpart, S, dV, Y, ph, st)
+                         : launch_scatter_pp<R, 32, true>(pt, Cpart, S, dV, Y, ph, st);
+  }
+  return pt.PP == 16 ? launch_scatter_pp<R, 16, false>(pt, Cpart, S, dV, Y, ph, st)
+                     : launch_scatter_pp<R, 32, false>(pt, Cpart, S, dV, Y, ph, st);
 }
 
 #if NCT_FP64_TU
@@ -2675,10 +2710,10 @@ hipError_t launch_density_backprop(const void* psi, const double* occ, const dou
                                       int, const void*, hipStream_t, int, KTables<R>);             \
   template hipError_t launch_density<R>(const void*, const double*, int, size_t, double*,          \
                                         hipStream_t);                                              \
-  template hipError_t launch_proj_contract<R>(const ProjTables&, const void*, int, double, void*,  \
-                                              void*, void*, const KinTables&, hipStream_t);        \
-  template hipError_t launch_proj_scatter<R>(const ProjTables&, const void*, int, void*,           \
-                                             const KinTables&, hipStream_t);                       \
+  template hipError_t launch_proj_contract<R>(const ProjTables&, const void*, int, void*, const PhaseTab&, \
+                                              hipStream_t);                                        \
+  template hipError_t launch_proj_scatter<R>(const ProjTables&, const void*, int, double, void*,   \
+                                             const PhaseTab&, hipStream_t);                        \
   template hipError_t launch_seed<R>(const void*, const double*, int, size_t, double, double,      \
                                      double, double, void*, hipStream_t);                          \
   template hipError_t launch_axpby<R>(void*, const void*, size_t, R, R, R, hipStream_t);          \

@@ -63,3 +63,32 @@ def test_step_both_forms(gpu, K, dt):
     psi = nct.states_to_device(w.psi0)
     s.step(psi, 0.0, 1)
     assert max_rel(psi.cpu().numpy(), psi_ref) < 1e-12
+
+
+@pytest.mark.parametrize("S,natoms,nch,prec", [(1, 1, 1, 0), (17, 2, 2, 0), (33, 3, 5, 0), (1025, 8, 5, 0),
+                                               (17, 2, 2, 1), (1025, 8, 3, 1)])
+def test_projector_chain_splits(gpu, S, natoms, nch, prec):
+    """Contraction and scatter over few and many (atom, states) pairs (shares of the row tiles, chunk
+    lengths), 16 and 32 padded projectors, ragged states: the nonlocal term alone, with the kinetic part
+    taken off by a second application at zero projector energy.  Mixed: FP32 sums of 64 products."""
+    torch, nct = gpu
+    print(f"[case] chain S={S} natoms={natoms} channels={nch} prec={prec}", flush=True)
+    n, L = (8, 8, 8), (6.0,) * 3
+    w = I.make_system(n=n, L=L, nstates=min(S, 40), case=110, natoms=natoms, min_sep=1.0)
+    w.channels = w.channels[:nch]
+    w.nstates, w.occ = S, np.ones(S)
+    w.psi0 = np.resize(w.psi0, (S,) + w.psi0.shape[1:]) * np.linspace(0.5, 1.5, S)[:, None, None, None, None]
+    sysd = O.system_from_workload(w)
+    ref = O.apply_nonlocal(w.psi0, sysd.projs, sysd.grid)
+    psi = nct.states_to_device(w.psi0, prec)
+    out = []
+    for scale in (1.0, 0.0):
+        for c in w.channels:
+            c.energy = c.energy if scale else 0.0
+        s = nct.system_from_workload(w, precision=prec)
+        s.set_potentials(fields=torch.zeros((4,) + n, dtype=torch.float64, device="cuda"))
+        hpsi = torch.empty_like(psi)
+        s.apply_hamiltonian(psi, hpsi, 0.0)
+        out.append(hpsi.cpu().numpy().astype(np.complex128))
+        s.close()
+    assert max_rel(out[0] - out[1], ref) < (2e-5 if prec else 1e-11)

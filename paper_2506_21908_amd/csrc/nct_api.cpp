@@ -50,6 +50,7 @@ struct nct_system {
   hipStream_t st2 = nullptr;       // projector chain, overlapped with the column pass
   hipEvent_t ev_rows = nullptr;    // sphere rows ready (recorded on st)
   hipEvent_t ev_proj = nullptr;    // scatter rows ready (recorded on st2)
+  bool one_stream = false;         // small systems: everything on st (see one_stream_max_bytes)
   // stream of the early kinetic pass: the next step's first column pass runs there while the
   // density and fields of the new states are formed on st
   hipStream_t stK = nullptr;
@@ -717,15 +718,25 @@ struct Engine {
     nct_status r;
     PhaseTab ph;
     if ((r = phase_table(ph)) != NCT_OK) return r;
-    HIPCHK(s, hipEventRecord(s->ev_rows, s->st));
-    HIPCHK(s, hipStreamWaitEvent(s->st2, s->ev_rows, 0));
-    if ((r = contract(W, s->S, s->Cpart, ph, s->st2)) != NCT_OK) return r;
-    if ((r = scatter(s->Cpart, s->S, s->Y, ph, s->st2)) != NCT_OK) return r;
-    HIPCHK(s, hipEventRecord(s->ev_proj, s->st2));
+    return projections_on(W, s->S, s->Cpart, s->Y, ph, s->st, s->st2, s->ev_rows, s->ev_proj);
+  }
+  // contraction and scatter of S states: on st2 once st has written the rows (the plane pass waits
+  // for ev_proj), or on st itself
+  nct_status projections_on(const void* W, int S, void* Cpart, void* Y, const PhaseTab& ph, hipStream_t st,
+                            hipStream_t st2, hipEvent_t ev_rows, hipEvent_t ev_proj) {
+    nct_status r;
+    if (!s->one_stream) {
+      HIPCHK(s, hipEventRecord(ev_rows, st));
+      HIPCHK(s, hipStreamWaitEvent(st2, ev_rows, 0));
+    }
+    hipStream_t q = s->one_stream ? st : st2;
+    if ((r = contract(W, S, Cpart, ph, q)) != NCT_OK) return r;
+    if ((r = scatter(Cpart, S, Y, ph, q)) != NCT_OK) return r;
+    if (!s->one_stream) HIPCHK(s, hipEventRecord(ev_proj, st2));
     return NCT_OK;
   }
   nct_status join_projections() {
-    if (s->natoms == 0) return NCT_OK;
+    if (s->natoms == 0 || s->one_stream) return NCT_OK;
     HIPCHK(s, hipStreamWaitEvent(s->st, s->ev_proj, 0));
     return NCT_OK;
   }
@@ -837,12 +848,10 @@ struct Engine {
     nct_status r;
     void* ybuf = y_dst ? y_dst : s->Y;
     if (s->natoms && !y_src) {
-      HIPCHK(s, hipEventRecord(g.ev_rows, g.st));
-      HIPCHK(s, hipStreamWaitEvent(g.st2, g.ev_rows, 0));
       ph.state_off = g.i0;
-      if ((r = contract(offr(cW, g.i0), g.S, g.Cpart, ph, g.st2)) != NCT_OK) return r;
-      if ((r = scatter(g.Cpart, g.S, offr(ybuf, g.i0), ph, g.st2)) != NCT_OK) return r;
-      HIPCHK(s, hipEventRecord(g.ev_proj, g.st2));
+      if ((r = projections_on(offr(cW, g.i0), g.S, g.Cpart, offr(ybuf, g.i0), ph, g.st, g.st2, g.ev_rows,
+                              g.ev_proj)) != NCT_OK)
+        return r;
     }
     StageArgs<R> sa = sa_full;
     sa.tmp_in = offs(sa.tmp_in, g.i0);
@@ -856,7 +865,7 @@ struct Engine {
     sa.state_off = g.i0;
     if (chat && (r = xpass(offs(chat, g.i0), offs(kin_dst ? kin_dst : s->tmp, g.i0), sa, g.i0, g.S, g.st)) != NCT_OK)
       return r;
-    if (s->natoms && !y_src) HIPCHK(s, hipStreamWaitEvent(g.st, g.ev_proj, 0));
+    if (s->natoms && !y_src && !s->one_stream) HIPCHK(s, hipStreamWaitEvent(g.st, g.ev_proj, 0));
     return plane_pass(sa, g.i0, g.S, g.st);
   }
 
@@ -955,6 +964,7 @@ struct Engine {
   nct_status early_kinetic(double t) {
     if (RS) return NCT_OK;  // the FP64 column pass takes the new fields
     at_time(t);
+    if (s->one_stream) return xpass(s->psihat, s->tmp, StageArgs<R>{}, 0, s->S, s->st);
     HIPCHK(s, hipEventRecord(s->evK_in, s->st));
     HIPCHK(s, hipStreamWaitEvent(s->stK, s->evK_in, 0));
     nct_status r = xpass(s->psihat, s->tmp, StageArgs<R>{}, 0, s->S, s->stK);
@@ -1098,7 +1108,7 @@ struct Engine {
         next = (k + 1 < nsteps) ? tvec(*T, k + 1, 0) : psi;
       }
       // the first column pass ran early on stK (early_kinetic)
-      if (!RS) HIPCHK(s, hipStreamWaitEvent(s->st, s->evK_out, 0));
+      if (!RS && !s->one_stream) HIPCHK(s, hipStreamWaitEvent(s->st, s->evK_out, 0));
       if ((r = taylor(cur, hcur, s->Wpsi, phi, s->phihat, s->Wphi, t, T ? so1.data() : nullptr, nullptr,
                       s->tmp)) != NCT_OK)
         return r;
@@ -1569,6 +1579,14 @@ static int stream_cache_mode(size_t psi_bytes) {
   return 0;
 }
 
+// Up to this size of one state set the projector chain and the early kinetic pass run on the main
+// stream: waiting for another stream costs about 10 us each time, more than the overlap wins on
+// kernels of a few us.  Measured per step, second stream against main stream: FP64 16^3 x 8 (1 MB) 527
+// against 375 us, 32^3 x 16 (17 MB) 675 / 608, 32^3 x 32 (34 MB) 796 / 783, 48^3 x 16 (57 MB) 1157 /
+// 1200; FP32 16^3 x 8 500 / 333, 32^3 x 32 (17 MB) 657 / 537, 48^3 x 32 (57 MB) 1181 / 1155, 48^3 x 64
+// (113 MB) 2034 / 2047.
+static size_t one_stream_max_bytes(bool fp64) { return size_t(fp64 ? 32 : 64) << 20; }
+
 nct_status create_impl(const nct_params* p, nct_system** out) {
   if (!p || !out) return fail(nullptr, NCT_ERR_ARG, "null params or out");
   *out = nullptr;
@@ -1616,6 +1634,7 @@ nct_status create_impl(const nct_params* p, nct_system** out) {
   s->cbytes = s->fp64 ? 16 : 8;
   s->cache_mode = stream_cache_mode(size_t(2) * s->S * s->N * s->cbytes);
   s->st = static_cast<hipStream_t>(p->stream);
+  s->one_stream = size_t(2) * s->S * s->N * s->cbytes <= one_stream_max_bytes(s->fp64);
   s->occ_h.assign(p->nstates, 1.0);
   if (p->occ)
     for (int i = 0; i < p->nstates; ++i) s->occ_h[i] = p->occ[i];

@@ -126,7 +126,7 @@ struct nct_system {
   int obs_cap = 0;
 
   // device: psi-sized work (precision of the system)
-  void* psihat = nullptr;     // FP32: (y,z)-transformed psi and phi
+  void* psihat = nullptr;     // FP32, transformed form: (y,z)-transformed psi and phi
   void* phihat = nullptr;
   void* phi = nullptr;
   void* wbuf = nullptr;
@@ -145,11 +145,11 @@ struct nct_system {
   void* Cpart = nullptr;
   void* C = nullptr;
   double* energy_dev = nullptr;
-  // FP64 Bloch phases of the sphere rows: distinct vectors, run of each state, table for the vector
+  // Bloch phases of the sphere rows (real-space form): distinct vectors, run of each state, table for the vector
   // potential phase_ka (valid if phase_ok)
   double* kruns = nullptr;    // [runs][3]
   int* run_of = nullptr;      // [S]
-  void* phases = nullptr;     // complex double [runs][Jtot]
+  void* phases = nullptr;     // complex [runs][Jtot]
   int phase_runs = 0, phase_cap = 0;
   bool phase_ok = false;
   double phase_ka[3] = {0, 0, 0};
@@ -357,7 +357,7 @@ nct_status build_projectors(nct_system* s) {
   nct_status r;
   if ((r = upload(s, ht.row_off, &d_row_off)) != NCT_OK) return r;
   if ((r = upload(s, ht.pr_off, &d_pr_off)) != NCT_OK) return r;
-  if (s->fp64) {  // real-space form: from a grid point to its rows
+  {  // real-space form: from a grid point to its rows
     if (ht.Jtot > kRowMask) return fail(s, NCT_ERR_UNSUPPORTED, "too many sphere rows");
     std::vector<int> rflat(ht.pidx.size());
     for (size_t J = 0; J < rflat.size(); ++J) rflat[J] = ht.ix_of_row[J] * s->n[1] * s->n[2] + ht.pidx[J];
@@ -371,7 +371,8 @@ nct_status build_projectors(nct_system* s) {
     pt.rflat = d_rflat;
     pt.pmap = d_pmap;
     pt.rnext = d_rnext;
-  } else {  // transformed form: the row ranges of each plane
+  }
+  if (!s->fp64) {  // transformed form: the row ranges of each plane
     int *d_pidx, *d_pr_b, *d_pr_e;
     if ((r = upload(s, ht.pidx, &d_pidx)) != NCT_OK) return r;
     if ((r = upload(s, ht.pr_begin, &d_pr_b)) != NCT_OK) return r;
@@ -568,9 +569,20 @@ constexpr int kProductMaxOrder = 12;
 template <typename R>
 struct Engine {
   nct_system* s;
-  // FP64 applies H in real space (column pass T_x + V, plane pass T_yz and the projectors), FP32
-  // through (y,z)-transformed copies of the states
-  static constexpr bool RS = sizeof(R) == 8;
+  static constexpr bool D = sizeof(R) == 8;
+  // Real-space form of H (column pass T_x + V, plane pass T_yz and the projectors), else through
+  // (y,z)-transformed copies of the states.  FP64 always takes it; FP32 takes it for H applications
+  // (48^3 x 64 with its density and fields: 205 against 249 us) and for large steps that return the
+  // states alone (real_step).  Steps with observables or a tape, adjoint steps and ground states keep the
+  // transformed form in FP32: they return FP64 observables, energies and field gradients, into which
+  // the rounding of the FP32 states enters at 1e-8, and these stay reproducible digit for digit with
+  // earlier versions.
+  bool RS = D;
+  // FP32 steps: from two last-level caches (256 MiB each) of states on, where each pass over them counts
+  // in full.  64^3 x 256 with 16 atoms 13.1 against 17.9 ms, 96^3 x 128 26.7 against 29.7; below, where
+  // steps whose states go on into an adjoint are usual and the digits above matter, 48^3 x 64 1.70
+  // against 1.96 ms and 96 x 24 x 24 x 40 about even, it is not taken.
+  bool real_step() const { return size_t(2) * s->S * s->N * sizeof(cpx<R>) > (size_t(512) << 20); }
   const void* twx() const { return sizeof(R) == 8 ? s->tw64[0] : s->tw32[0]; }
   const void* twy() const { return sizeof(R) == 8 ? s->tw64[1] : s->tw32[1]; }
   const void* twz() const { return sizeof(R) == 8 ? s->tw64[2] : s->tw32[2]; }
@@ -583,7 +595,7 @@ struct Engine {
   }
   KTables<R> ktab(int state_off = 0) const {
     KTables<R> k;
-    if constexpr (!RS) {
+    if constexpr (!D) {
       k.gx = s->gsx32;
       k.gy = s->gsy32;
       k.gz = s->gsz32;
@@ -595,14 +607,12 @@ struct Engine {
   }
   KinTables kint(int state_off = 0) const {
     KinTables k;
-    if constexpr (RS) {
-      for (int d = 0; d < 3; ++d) {
-        k.g[d] = s->gs64[d];
-        k.ka[d] = ka[d];
-      }
-      k.kv = kvR();
-      k.state_off = state_off;
+    for (int d = 0; d < 3; ++d) {
+      k.g[d] = s->gs64[d];
+      k.ka[d] = ka[d];
     }
+    k.kv = s->has_k ? s->kv64 : (velocity_gauge(s) ? s->kv_zero64 : nullptr);
+    k.state_off = state_off;
     return k;
   }
   const R* fieldsR() const { return sizeof(R) == 8 ? (const R*)s->fields : (const R*)s->fields32; }
@@ -686,7 +696,7 @@ struct Engine {
                           [&] { return launch_proj_scatter<R>(s->pt, Cpart, S, s->dV, Y, ph, st); }), "proj_scatter");
   }
 
-  // The FP64 phase table of the current Bloch vectors and vector potential (null without either).
+  // The phase table (real-space form) of the current Bloch vectors and vector potential (null without either).
   // Called with ka set, on the main stream, after every earlier use of the table has joined it.
   nct_status phase_table(PhaseTab& ph) {
     ph = PhaseTab{};
@@ -695,18 +705,18 @@ struct Engine {
     const int runs = s->has_k ? s->phase_runs : 1;
     if (s->phase_cap < runs) {
       s->phase_cap = 0;
-      if ((r = dalloc(s, size_t(runs) * s->pt.Jtot * 16, &s->phases)) != NCT_OK) return r;
+      if ((r = dalloc(s, size_t(runs) * s->pt.Jtot * s->cbytes, &s->phases)) != NCT_OK) return r;
       s->phase_cap = runs;
       s->phase_ok = false;
     }
     if (!s->phase_ok || ka[0] != s->phase_ka[0] || ka[1] != s->phase_ka[1] || ka[2] != s->phase_ka[2]) {
-      if ((r = check(launch_phases(s->has_k ? s->kruns : s->kv_zero64, runs, ka, s->pt, s->phases, s->st), "phases")) !=
+      if ((r = check(launch_phases<R>(s->has_k ? s->kruns : s->kv_zero64, runs, ka, s->pt, s->phases, s->st), "phases")) !=
           NCT_OK)
         return r;
       for (int d = 0; d < 3; ++d) s->phase_ka[d] = ka[d];
       s->phase_ok = true;
     }
-    ph.tab = static_cast<const cpx<double>*>(s->phases);
+    ph.tab = s->phases;
     ph.run = s->has_k ? s->run_of : nullptr;
     return NCT_OK;
   }
@@ -775,11 +785,13 @@ struct Engine {
     const double pb = psiB() * S / s->S;
     const double b = RS ? 2 * pb + (sa.x_base && sa.x_base != sa.w_in ? pb : 0.0) + 4.0 * s->N * sizeof(R) : 2 * pb;
     return check(timed_on(s, st, NCT_K_XPASS, b, 0, [&] {
-                   if constexpr (RS)
-                     return launch_xv(s->n, S, sa, dst, twx(), kint(i0), st);
-                   else
-                     return launch_xpass<R>(s->n, 2 * S, src, dst, g2x(), g2yz(), R(0.5 / double(s->N)), 0, twx(), st,
+                   if (RS) return launch_xv<R>(s->n, S, sa, dst, twx(), kint(i0), st);
+                   return launch_xpass<R>(s->n, 2 * S, src, dst, g2x(), g2yz(), R(0.5 / double(s->N)), 0, twx(), st,
                                             s->cache_mode, ktab(i0)); }), "xpass");
+  }
+  hipError_t transformed_stage(const StageArgs<R>& sa, int S, hipStream_t st) {
+    if constexpr (D) return hipErrorInvalidValue;
+    else return launch_plane_stage(s->n, S, sa, s->pt, twy(), twz(), st);
   }
   nct_status plane_pass(const StageArgs<R>& sa, int i0, int S, hipStream_t st) {
     const double pb = psiB() * S / s->S, rb = rowsB() * S / s->S;
@@ -795,8 +807,8 @@ struct Engine {
     if (sa.W) b += rb;
     if (sa.acc) b += 2 * pb;
     return check(timed_on(s, st, NCT_K_PLANE_STAGE, b, 0, [&] {
-                   if constexpr (RS) return launch_plane_yz(s->n, S, sa, kint(i0), s->pt, twy(), twz(), st);
-                   else return launch_plane_stage(s->n, S, sa, s->pt, twy(), twz(), st); }), "plane_stage");
+                   if (RS) return launch_plane_yz<R>(s->n, S, sa, kint(i0), s->pt, twy(), twz(), st);
+                   return transformed_stage(sa, S, st); }), "plane_stage");
   }
 
   // ---- state groups
@@ -872,7 +884,7 @@ struct Engine {
   // imaginary time: when > 0, taylor() forms T_K(-imag_tau H) x (real Horner coefficients)
   double imag_tau = 0.0;
 
-  // FP64: T_K(z H) x, z = -i a or -imag_tau, as stages w_k = w_{k-1} + c_k H w_{k-1}, c_k = -z / r_k
+  // Real-space form: T_K(z H) x, z = -i a or -imag_tau, as stages w_k = w_{k-1} + c_k H w_{k-1}, c_k = -z / r_k
   // (the base of every stage is its own w: one state-sized read less than the Horner stages' x)
   bool product_form(double z) const {
     if (!RS || s->prm.taylor_order > kProductMaxOrder) return false;
@@ -962,7 +974,7 @@ struct Engine {
   // that it overlaps the density and field update that follow on st; that step's first Taylor
   // stage takes it as kin_reuse after waiting for evK_out.
   nct_status early_kinetic(double t) {
-    if (RS) return NCT_OK;  // the FP64 column pass takes the new fields
+    if (RS) return NCT_OK;  // this form's column pass takes the new fields
     at_time(t);
     if (s->one_stream) return xpass(s->psihat, s->tmp, StageArgs<R>{}, 0, s->S, s->st);
     HIPCHK(s, hipEventRecord(s->evK_in, s->st));
@@ -977,12 +989,13 @@ struct Engine {
   // in FP32 their (y,z) transform into hat.  Returns in chat what the column pass takes.
   nct_status prepare(const void* psi, void* hat, void* W, const void** chat = nullptr) {
     if (chat) *chat = RS ? psi : hat;
-    if constexpr (RS) {
+    if (RS) {
       if (s->natoms == 0) return NCT_OK;
       return check(timed(s, NCT_K_PLANE_FWD, 2 * rowsB(), 0, [&] {
-                     return launch_gather_rows(s->pt, psi, W, 2 * s->S, s->N, s->st); }), "gather");
-    } else
-    return check(timed(s, NCT_K_PLANE_FWD, 2 * psiB() + (s->natoms ? rowsB() : 0.0), 0, [&] {
+                     return launch_gather_rows<R>(s->pt, psi, W, 2 * s->S, s->N, s->st); }), "gather");
+    }
+    if constexpr (D) return NCT_ERR_UNSUPPORTED;
+    else return check(timed(s, NCT_K_PLANE_FWD, 2 * psiB() + (s->natoms ? rowsB() : 0.0), 0, [&] {
                    return launch_plane_fwd<R>(s->n, 2 * s->S, psi, hat, s->natoms ? W : nullptr, &s->pt,
                                               twy(), twz(), s->st, ktab()); }), "plane_fwd");
   }
@@ -991,12 +1004,11 @@ struct Engine {
     nct_status r;
     int ntiles = 0;
     at_time(t);
-    if ((r = check(timed(s, NCT_K_OBS, (RS ? 2 : 1) * psiB(), 0, [&] {
-           if constexpr (RS)
+    if ((r = check(timed(s, NCT_K_OBS, (D ? 2 : 1) * psiB(), 0, [&] {
+           if constexpr (D)
              return launch_energy_real(s->n, 2 * s->S, psi, twx(), twy(), twz(), kint(), s->epart, s->eplane, &ntiles,
                                        s->st);
-           else
-           return launch_xpass_energy<R>(s->n, 2 * s->S, s->psihat, g2x(), g2yz(), R(0.5 / double(s->N)),
+           else return launch_xpass_energy<R>(s->n, 2 * s->S, s->psihat, g2x(), g2yz(), R(0.5 / double(s->N)),
                                          twx(), s->epart, &ntiles, s->st, ktab()); }), "energy")) != NCT_OK)
       return r;
     if (s->natoms) {
@@ -1010,7 +1022,7 @@ struct Engine {
     in.epart = s->epart;
     in.ntiles = ntiles;
     in.eplane = s->eplane;
-    in.nplanes = RS ? s->n[0] : 0;
+    in.nplanes = D ? s->n[0] : 0;
     in.C = s->natoms ? s->C : nullptr;
     in.energy = s->energy_dev;
     in.occ = s->occ;
@@ -1019,7 +1031,7 @@ struct Engine {
     in.PP = s->pt.PP;
     in.precision = s->prm.precision;
     in.dV = s->dV;
-    in.invN = RS ? 1.0 : 1.0 / double(s->N);
+    in.invN = D ? 1.0 : 1.0 / double(s->N);
     in.t = t;
     double B[3] = {0, 0, 0}, E[3] = {0, 0, 0};
     if (!s->frozen) {
@@ -1058,6 +1070,7 @@ struct Engine {
     const double dt = s->prm.dt;
     const int K = s->prm.taylor_order;
     void* cur = psi;
+    RS = D || (!obs_host && !T && real_step());
     if (T) {
       HIPCHK(s, hipMemcpyAsync(tvec(*T, 0, 0), psi, size_t(psiB()), hipMemcpyDeviceToDevice, s->st));
       cur = tvec(*T, 0, 0);
@@ -1130,7 +1143,7 @@ struct Engine {
         vector_potential_at(s, t, a0);
         vector_potential_at(s, t + dt, a1);
         for (int d = 0; d < 3; ++d) dA[d] = a1[d] - a0[d];
-        if constexpr (!RS)
+        if constexpr (!D)
           if ((r = check(launch_rephase_rows<R>(s->pt, s->Wphi, s->S, dA, s->st), "rephase")) != NCT_OK) return r;
       }
       if ((r = taylor(phi, hphi, s->Wphi, next, s->psihat, s->Wpsi, t + dt, T ? so3.data() : nullptr,
@@ -1440,6 +1453,7 @@ struct Engine {
 
   nct_status apply(const void* psi, void* hpsi, double t) {
     nct_status r;
+    RS = true;
     at_time(t);
     const void* chat = nullptr;
     if ((r = prepare(psi, s->tmp, s->Wwork, &chat)) != NCT_OK) return r;
@@ -1502,15 +1516,15 @@ nct_status build_fft_tables(nct_system* s) {
     }
   if ((r = upload(s, gx, &s->g2x64)) != NCT_OK) return r;
   if ((r = upload(s, gyz, &s->g2yz64)) != NCT_OK) return r;
-  if (s->fp64) {  // real-space form: one line of G per axis
+  {  // real-space form: one line of G per axis
     const std::vector<int>* kk[3] = {&kx, &ky, &kz};
     for (int d = 0; d < 3; ++d) {
       std::vector<double> g(s->n[d]);
       for (int i = 0; i < s->n[d]; ++i) g[i] = gval((*kk[d])[i], s->n[d], s->prm.cell[d]);
       if ((r = upload(s, g, &s->gs64[d])) != NCT_OK) return r;
     }
-    return NCT_OK;
   }
+  if (s->fp64) return NCT_OK;
   std::vector<double> sx(s->n[0]), sy(size_t(s->n[1]) * s->n[2]), sz(size_t(s->n[1]) * s->n[2]);
   for (int i = 0; i < s->n[0]; ++i) sx[i] = gval(kx[i], s->n[0], s->prm.cell[0]);
   for (int i = 0; i < s->n[1]; ++i)
@@ -1926,7 +1940,7 @@ nct_status nct_set_kpoints(nct_system* s, const double* kvec) {
   std::vector<float> k32(kvec, kvec + n);
   HIPCHK(s, hipMemcpyAsync(s->kv64, kvec, n * sizeof(double), hipMemcpyHostToDevice, s->st));
   HIPCHK(s, hipMemcpyAsync(s->kv32, k32.data(), n * sizeof(float), hipMemcpyHostToDevice, s->st));
-  if (s->fp64 && s->natoms) {  // distinct vectors of the phase table
+  if (s->natoms) {  // distinct vectors of the phase table
     const int runs = int(s->krun.size()) - 1;
     std::vector<double> kr(size_t(runs) * 3);
     std::vector<int> ro(s->S);

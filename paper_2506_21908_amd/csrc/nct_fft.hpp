@@ -169,6 +169,10 @@ __device__ __forceinline__ void dft(cpx<R>* x) {
 // ---------------------------------------------------------------- radix plans
 // Radix of DIF stage s for a line of length N (0 = no such stage).  Radices stay <= 8 where a
 // two-stage plan allows it, so a butterfly's data and twiddles fit in registers together.
+//
+// N | kSwap names a second plan of the same line with its two stages in the other order, for kernels
+// whose waves take whole rounds of 64 first-stage butterflies that way (real_plan).
+constexpr int kSwap = 1024;
 __host__ __device__ constexpr int plan_radix(int N, int s) {
   switch (N) {
     case 4: return s == 0 ? 4 : 0;
@@ -183,6 +187,7 @@ __host__ __device__ constexpr int plan_radix(int N, int s) {
     case 64: return s == 0 ? 8 : (s == 1 ? 8 : 0);
     case 72: return s == 0 ? 8 : (s == 1 ? 3 : (s == 2 ? 3 : 0));
     case 96: return s == 0 ? 8 : (s == 1 ? 12 : 0);
+    case 96 | kSwap: return s == 0 ? 12 : (s == 1 ? 8 : 0);
     case 128: return s == 0 ? 8 : (s == 1 ? 4 : (s == 2 ? 4 : 0));
     default: return 0;
   }
@@ -192,16 +197,36 @@ __host__ __device__ constexpr int plan_nstages(int N) {
   while (k < 4 && plan_radix(N, k) != 0) ++k;
   return k;
 }
+__host__ __device__ constexpr int plan_len(int N) { return N & (kSwap - 1); }
 __host__ __device__ constexpr int plan_span(int N, int s) {
-  int L = N;
+  int L = plan_len(N);
   for (int i = 0; i < s; ++i) L /= plan_radix(N, i);
   return L;
 }
+// Position k of plan N | kSwap as the position of the same frequency in plan N (two stages r0, r1:
+// frequency f stands at (f % r0) r1 + f / r0).
+template <int N>
+__device__ __forceinline__ int plan_position(int k) {
+  if constexpr (N == plan_len(N)) {
+    return k;
+  } else {
+    constexpr int S0 = plan_radix(N, 0), S1 = plan_radix(N, 1);
+    constexpr int R0 = plan_radix(plan_len(N), 0), R1 = plan_radix(plan_len(N), 1);
+    const int f = k / S1 + S0 * (k % S1);
+    return (f % R0) * R1 + f / R0;
+  }
+}
+// The plan of the real-space kernels: 96 = 12 x 8, eight butterflies to a line in the first and the
+// last stage (8 x 12 makes twelve: a wave's eight lines are one and a half rounds of its lanes).
+__host__ __device__ constexpr int real_plan(int N) { return N == 96 ? N | kSwap : N; }
 
 // Nothing is scheduled across this point: it keeps the loads of a later batch from being hoisted,
 // whose registers would spill.
 __device__ __forceinline__ void sched_fence() { __builtin_amdgcn_sched_barrier(0); }
 
+// Rounds of a wave's stage are fenced from this many bytes of operand reals on (48: FP32 radix 12, FP64
+// radix 6); below, the next round's LDS reads may start early.
+constexpr int kFenceBytes = 48;
 // ---------------------------------------------------------------- one LDS stage
 // NCT_TW_PRODUCTS (tuning macro): FP64 radix-8 butterflies read w1, w2 and w4 (1), w1 and w2 (2)
 // or w1 (3) from the table and form the other twiddles as products (at most three roundings).
@@ -219,7 +244,7 @@ __device__ __forceinline__ void stage_butterfly(cpx<R>* x, const cpx<R>* tw, int
   constexpr int RAD = plan_radix(N, STAGE);
   constexpr int SPAN = plan_span(N, STAGE);
   constexpr int M = SPAN / RAD;
-  constexpr int TWS = N / SPAN;
+  constexpr int TWS = plan_len(N) / SPAN;
   if constexpr (M > 1) {
     cpx<R> w[RAD - 1];
     if constexpr (NCT_TW_PRODUCTS && sizeof(R) == 8 && RAD == 8) {
@@ -235,6 +260,16 @@ __device__ __forceinline__ void stage_butterfly(cpx<R>* x, const cpx<R>* tw, int
       w[4] = cmul(w1, w4);
       w[5] = cmul(w2, w4);
       w[6] = cmul(w[2], w4);
+    } else if constexpr (NCT_TW_PRODUCTS && sizeof(R) == 8 && RAD == 12) {
+      w[0] = tw[b * TWS];
+      w[1] = tw[b * 2 * TWS];
+      w[3] = tw[b * 4 * TWS];
+      w[2] = cmul(w[0], w[1]);
+      w[7] = cmul(w[3], w[3]);
+#pragma unroll
+      for (int p = 4; p < 7; ++p) w[p] = cmul(w[p - 4], w[3]);
+#pragma unroll
+      for (int p = 8; p < 11; ++p) w[p] = cmul(w[p - 8], w[7]);
     } else {
 #pragma unroll
       for (int p = 1; p < RAD; ++p) w[p - 1] = tw[b * p * TWS];
@@ -375,7 +410,7 @@ __device__ __forceinline__ void wave_stage(cpx<R>* lds, const cpx<R>* tw, int la
   constexpr int RAD = plan_radix(N, STAGE);
   constexpr int SPAN = plan_span(N, STAGE);
   constexpr int M = SPAN / RAD;
-  constexpr int TOTAL = NLINES * (N / RAD);
+  constexpr int TOTAL = NLINES * (plan_len(N) / RAD);
   constexpr int IT = (TOTAL + 63) / 64;
 #pragma unroll
   for (int u = 0; u < IT; ++u) {
@@ -392,7 +427,7 @@ __device__ __forceinline__ void wave_stage(cpx<R>* lds, const cpx<R>* tw, int la
 #pragma unroll
       for (int q = 0; q < RAD; ++q) base[q * M * ES] = x[q];
     }
-    if (u + 1 < IT) sched_fence();
+    if (u + 1 < IT && sizeof(R) * RAD >= kFenceBytes) sched_fence();
   }
 }
 
@@ -402,7 +437,7 @@ __device__ __forceinline__ void wave_stage(cpx<R>* lds, const cpx<R>* tw, int la
 template <typename R, int N, int NLINES, int LS, int ES, typename MULT>
 __device__ __forceinline__ void wave_middle(cpx<R>* lds, int lane, MULT mult) {
   constexpr int RAD = plan_radix(N, plan_nstages(N) - 1);
-  constexpr int TOTAL = NLINES * (N / RAD);
+  constexpr int TOTAL = NLINES * (plan_len(N) / RAD);
   constexpr int IT = (TOTAL + 63) / 64;
 #pragma unroll
   for (int u = 0; u < IT; ++u) {
@@ -421,7 +456,7 @@ __device__ __forceinline__ void wave_middle(cpx<R>* lds, int lane, MULT mult) {
 #pragma unroll
       for (int q = 0; q < RAD; ++q) base[q * ES] = x[q];
     }
-    if (u + 1 < IT) sched_fence();
+    if (u + 1 < IT && sizeof(R) * RAD >= kFenceBytes) sched_fence();
   }
 }
 

@@ -73,7 +73,7 @@ struct KTables {
   R ka[3] = {0, 0, 0};     // velocity-gauge vector potential added to every Bloch vector
 };
 
-// Kinetic factors of the real-space (FP64) form: signed G per axis (digit-reversed order of the line
+// Kinetic factors of the real-space form: signed G per axis (digit-reversed order of the line
 // transforms) and, with Bloch vectors (k-points, or the velocity gauge), the shift G + k of each state.
 struct KinTables {
   const double* g[3] = {nullptr, nullptr, nullptr};
@@ -86,15 +86,18 @@ struct KinTables {
 };
 
 // Launchers (return hipError_t of the launch).  n = {NX, NY, NZ}.
-// FP64, real-space form (kv, state_off and ka of the stage arguments are unused: they are in kt):
+// Real-space form (kv, state_off and ka of the stage arguments are unused: they are in kt):
 // column pass dst = alpha x_base + c (T_x + V) w_in, plane pass w_out = tmp_in + c (T_yz w_in + Y rows)
 // (w_out may be w_in), sphere rows of states, and kinetic energy partials: part [B][ntiles][2] (x part
 // of sum 1/2 |G + k|^2 |X|^2 / N and the norm sum |psi|^2 per column tile), eplane [B][NX] (y,z part
 // per plane).
-hipError_t launch_xv(const int n[3], int S, const StageArgs<double>& a, void* dst, const void* twx,
+template <typename R>
+hipError_t launch_xv(const int n[3], int S, const StageArgs<R>& a, void* dst, const void* twx,
                      const KinTables& kt, hipStream_t st);
-hipError_t launch_plane_yz(const int n[3], int S, const StageArgs<double>& a, const KinTables& kt,
+template <typename R>
+hipError_t launch_plane_yz(const int n[3], int S, const StageArgs<R>& a, const KinTables& kt,
                            const ProjTables& pt, const void* twy, const void* twz, hipStream_t st);
+template <typename R>
 hipError_t launch_gather_rows(const ProjTables& pt, const void* psi, void* W, int B, size_t N, hipStream_t st);
 hipError_t launch_energy_real(const int n[3], int B, const void* src, const void* twx, const void* twy,
                               const void* twz, const KinTables& kt, double* part, double* eplane, int* ntiles_out,
@@ -159,16 +162,18 @@ hipError_t launch_add_bext(const double* fields, const int n[3], const double b[
                            const double lg[4], double* out, hipStream_t st);
 hipError_t launch_to_float(const double* in, size_t n, float* out, hipStream_t st);
 
-// Phases exp(i (k + A).d) of the sphere rows per distinct Bloch vector (FP64; in FP32 the plane pass
-// computes them).
+// Phases exp(i (k + A).d) of the sphere rows per distinct Bloch vector (real-space form; in the transformed
+// form the plane pass computes them).
 struct PhaseTab {
-  const cpx<double>* tab = nullptr;  // [runs][Jtot], null: no Bloch vectors
-  const int* run = nullptr;          // [S] run of each state, null: run 0
-  int state_off = 0;                 // this launch's state 0
-  __host__ __device__ const cpx<double>* row(int i, int Jtot) const {
-    return tab + size_t(run ? run[state_off + i] : 0) * Jtot;
+  const void* tab = nullptr;  // complex R [runs][Jtot], null: no Bloch vectors
+  const int* run = nullptr;   // [S] run of each state, null: run 0
+  int state_off = 0;          // this launch's state 0
+  template <typename R>
+  __host__ __device__ const cpx<R>* row(int i, int Jtot) const {
+    return static_cast<const cpx<R>*>(tab) + size_t(run ? run[state_off + i] : 0) * Jtot;
   }
 };
+template <typename R>
 hipError_t launch_phases(const double* kruns, int nruns, const double ka[3], const ProjTables& pt, void* tab,
                          hipStream_t st);
 

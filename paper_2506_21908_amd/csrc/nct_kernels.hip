@@ -525,8 +525,8 @@ __global__ __launch_bounds__(NCT_PLANER_NT, 4) void k_plane_stage_r(StageArgs<R>
   }
 }
 
-// ---------------------------------------------------------------- FP64: real-space H stage
-// The kinetic operator is a sum of one operator per axis, T = T_x + T_yz, so FP64 applies H in real
+// ---------------------------------------------------------------- real-space H stage
+// The kinetic operator is a sum of one operator per axis, T = T_x + T_yz, so H is applied in real
 // space on both sides, nothing kept in transformed form: the column pass (k_xv) writes
 // r = alpha x + c (T_x + V) w, with V the 2x2 local potential, and the plane pass (k_plane_yz) adds
 // c (T_yz w + projector rows) to it.  The two passes of a stage read w twice and r once and write r and
@@ -538,55 +538,53 @@ __global__ __launch_bounds__(NCT_PLANER_NT, 4) void k_plane_stage_r(StageArgs<R>
 //
 // Element at a byte offset from a wave-uniform base: the base stays in scalar registers (the empty
 // asm keeps the compiler from folding the offset into a 64-bit vector address per operand) and one
-// 32-bit vector register addresses every operand of the same shape.
+// 32-bit vector register addresses every operand of the same shape.  The pointer is named as global
+// memory: an asm that hides where it points leaves flat loads with 64-bit address sums, which also
+// count as LDS operations in every wait (64^3 x 128: column pass 377 against 414 us; 48^3 x 64: 92
+// against 106).
 template <typename T>
 __device__ __forceinline__ T* at_bytes(T* base, uint32_t bytes) {
-  asm volatile("" : "+s"(base));
-  return reinterpret_cast<T*>(reinterpret_cast<char*>(const_cast<std::remove_const_t<T>*>(base)) + bytes);
+  typedef __attribute__((address_space(1))) char* gptr;  // in global memory, which the asm would hide
+  gptr p = (gptr)base;
+  asm volatile("" : "+s"(p));
+  return (T*)(p + bytes);
 }
 
+// Value that is computed here, not where it is used next: the fences order memory operations only, and
+// the operands of sums put off to their use spilled (96 points: 35 registers FP64, 39 FP32).
+template <typename R>
+__device__ __forceinline__ void pin(cpx<R>& v) { asm volatile("" : "+v"(v.x), "+v"(v.y)); }
+
 // Waves per workgroup of the plane pass and the waves per SIMD its registers must allow.
-#ifndef NCT_REAL_NW64
-#define NCT_REAL_NW64 8
-#endif
-#ifndef NCT_REAL_NW48
-#define NCT_REAL_NW48 6
-#endif
-#ifndef NCT_REAL_NW32
-#define NCT_REAL_NW32 2
-#endif
+// FP64 64^2: eight waves in each of the two workgroups that the LDS holds (1055 us per pass at 64^3 x
+// 256, 6.1 TB/s); more waves per SIMD than the four of 128 registers spill (48^2 with five 172 against
+// 143 us at 48^3 x 64 with 4 atoms).  FP32 has half the registers per point: each wave takes twice the
+// lines (64^2 four waves 553 us at 64^3 x 256, eight 650 to 746).  96^2: 74 KB (FP32) or 147 KB (FP64) of
+// LDS allow 12 waves per CU, three per SIMD (FP32 with 24 waves of 80 registers 1413 to 1650 against
+// 1282 us at 96^3 x 128).
+template <typename R>
 __host__ __device__ constexpr int real_nw(int ny, int nz) {
-  if (ny == 64 && nz == 64) return NCT_REAL_NW64;
-  if (ny == 48 && nz == 48) return NCT_REAL_NW48;
-  if (ny == 96 && nz == 96) return 12;
-  if (ny == 32 && nz == 32) return NCT_REAL_NW32;
+  if (ny == 64 && nz == 64) return sizeof(R) == 8 ? 8 : 4;
+  if (ny == 48 && nz == 48) return sizeof(R) == 8 ? 6 : 3;
+  if (ny == 96 && nz == 96) return sizeof(R) == 8 ? 12 : 6;
+  if (ny == 32 && nz == 32) return 2;
   if (ny == 24 && nz == 24) return 3;
   if (ny * nz == 384) return 2;  // 16 x 24, 24 x 16
   return 1;
 }
-#ifndef NCT_REAL_MW64
-#define NCT_REAL_MW64 4
-#endif
-#ifndef NCT_REAL_MW48
-#define NCT_REAL_MW48 4
-#endif
-#ifndef NCT_REAL_MW
-#define NCT_REAL_MW 4
-#endif
-__host__ __device__ constexpr int real_mw(int ny, int nz) {
-  if (ny == 64 && nz == 64) return NCT_REAL_MW64;
-  if (ny == 48 && nz == 48) return NCT_REAL_MW48;
-  if (ny == 96 && nz == 96) return 3;
-  return NCT_REAL_MW;
-}
-template <int NY, int NZ>
+__host__ __device__ constexpr int real_mw(int ny, int nz) { return ny == 96 && nz == 96 ? 3 : 4; }
+// r is loaded before the last stages, not along with w: at 96^2, whose twelve values per thread and
+// operand leave few registers for the radix-12 stages (609 -> 566 us FP64 96^3 x 32, 1356 -> 1282 us FP32
+// 96^3 x 128; no gain where the registers are there: 48^2 143 against 146 us, 64^2 583 against 588).
+__host__ __device__ constexpr bool real_late(int ny, int nz) { return ny == 96 && nz == 96; }
+template <typename R, int NY, int NZ>
 constexpr size_t real_lds_bytes() {
-  return (size_t(NY) * (NZ + 1) + NY + NZ) * sizeof(cpx<double>) + (NY + NZ) * sizeof(double);
+  return (size_t(NY) * (NZ + 1) + NY + NZ) * sizeof(cpx<R>) + (NY + NZ) * sizeof(R);
 }
 
 // Plane pass: out = r + c (T_yz w + projector rows), one workgroup per (spinor component, x-plane), one
-// LDS plane.  All loads (the thread's points of w and of r) are issued up front; r waits in registers
-// while w goes through the plane.  out may be w.
+// LDS plane.  All loads (the thread's points of w and of r) are issued up front (but see real_late); r
+// waits in registers while w goes through the plane.  out may be w.
 //
 // Each wave owns NZ / NW columns of the y transforms and NY / NW rows of the z transforms, so the
 // stages of one axis run without a workgroup barrier (LDS operations of a wave stay in order); only
@@ -594,24 +592,30 @@ constexpr size_t real_lds_bytes() {
 // z stage work on the same values and stay in registers.  Where the work items of a wave are no
 // multiple of 64, the surplus lanes repeat the last item: they write the same values to the same places.
 //
+// The projector rows of a plane come in at the end: the map of its points is read before the last change
+// of axis and the rows before the last stages, so neither wait stands before the transforms (64^3 x 128
+// with 16 atoms 583 against 600 us per pass, without atoms 530; 48^3 x 64 with 4 atoms 143 against 162,
+// without 131), and one read of the map serves the rows taken from out too.
+//
 // ACC: acc += out (the adjoint).
-template <int NY, int NZ, int M, bool ACC>
-__global__ __launch_bounds__(64 * real_nw(NY, NZ), real_mw(NY, NZ)) void k_plane_yz(
-    StageArgs<double> a, KinTables kt, ProjTables pt, const cpx<double>* __restrict__ twy_g,
-    const cpx<double>* __restrict__ twz_g, int B, int NX) {
-  using C = cpx<double>;
+template <typename R, int NY, int NZ, int M, bool ACC>
+__global__ __launch_bounds__(64 * real_nw<R>(NY, NZ), real_mw(NY, NZ)) void k_plane_yz(
+    StageArgs<R> a, KinTables kt, ProjTables pt, const cpx<R>* __restrict__ twy_g,
+    const cpx<R>* __restrict__ twz_g, int B, int NX) {
+  using C = cpx<R>;
   constexpr int NP = NY * NZ, PZ = NZ + 1;
-  constexpr int NW = real_nw(NY, NZ), NT = 64 * NW;
+  constexpr int NW = real_nw<R>(NY, NZ), NT = 64 * NW;
   constexpr int CW = NZ / NW, RW = NY / NW;
-  constexpr int RY = plan_radix(NY, 0), MY = NY / RY;
+  constexpr int FY = real_plan(NY), FZ = real_plan(NZ);
+  constexpr int RY = plan_radix(FY, 0), MY = NY / RY;
   constexpr int ITEMS = CW * MY, IT = (ITEMS + 63) / 64;
   static_assert(NZ % NW == 0 && NY % NW == 0 && plan_nstages(NY) <= 2 && plan_nstages(NZ) <= 2, "plane split");
   extern __shared__ double4 smem_d4[];
   C* pl = reinterpret_cast<C*>(smem_d4);
   C* twy = pl + NY * PZ;
   C* twz = twy + NY;
-  double* ty = reinterpret_cast<double*>(twz + NZ);
-  double* tz = ty + NY;
+  R* ty = reinterpret_cast<R*>(twz + NZ);
+  R* tz = ty + NY;
   const int tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int L = xcd_logical(blockIdx.x, gridDim.x);
@@ -630,61 +634,34 @@ __global__ __launch_bounds__(64 * real_nw(NY, NZ), real_mw(NY, NZ)) void k_plane
 
   // thread (column z, butterfly c) of the y transform holds the points y = c + q MY
   C v[IT][RY], r[IT][RY];
+  const auto load_r = [&]() {
+#pragma unroll
+    for (int u = 0; u < IT; ++u) {
+      const int it = min(lane + 64 * u, ITEMS - 1);
+      const uint32_t o = uint32_t((it / CW) * NZ + it % CW) * uint32_t(sizeof(C));
+#pragma unroll
+      for (int q = 0; q < RY; ++q) r[u][q] = ld_stream<M>(at_bytes(rin + off + (w * CW + q * MY * NZ), o));
+    }
+  };
 #pragma unroll
   for (int u = 0; u < IT; ++u) {
     const int it = min(lane + 64 * u, ITEMS - 1);
-    const uint32_t l0 = uint32_t((it / CW) * NZ + it % CW), o = l0 * 16u;
-    int J[RY];
-    if (on_plane && Y) {
-#pragma unroll
-      for (int q = 0; q < RY; ++q) J[q] = *at_bytes(pm + (w * CW + q * MY * NZ), l0 * 4u);
-    }
+    const uint32_t o = uint32_t((it / CW) * NZ + it % CW) * uint32_t(sizeof(C));
 #pragma unroll
     for (int q = 0; q < RY; ++q) v[u][q] = ld_stream<M>(at_bytes(win + off + (w * CW + q * MY * NZ), o));
-#pragma unroll
-    for (int q = 0; q < RY; ++q) r[u][q] = ld_stream<M>(at_bytes(rin + off + (w * CW + q * MY * NZ), o));
-    if (on_plane && Y) {
-      int any = J[0], more = J[0];
-#pragma unroll
-      for (int q = 1; q < RY; ++q) {
-        any &= J[q];   // all negative (no row) only if every J is
-        more = max(more, J[q]);
-      }
-      if (__any(any >= 0)) {
-        // every load at once: points without a row read row 0 and drop it
-        C y[RY];
-#pragma unroll
-        for (int q = 0; q < RY; ++q) y[q] = Y[rb + (J[q] >= 0 ? (J[q] & kRowMask) : 0)];
-#pragma unroll
-        for (int q = 0; q < RY; ++q) {
-          const C z = J[q] >= 0 ? y[q] : C{0.0, 0.0};
-          r[u][q].x += a.cre * z.x - a.cim * z.y;
-          r[u][q].y += a.cre * z.y + a.cim * z.x;
-        }
-        if (__any(more > kRowMask)) {  // further rows at a point: overlapping spheres
-#pragma unroll
-          for (int q = 0; q < RY; ++q)
-            if (J[q] > kRowMask)
-              for (int k = pt.rnext[J[q] & kRowMask]; k >= 0; k = pt.rnext[k]) {
-                const C z = Y[rb + k];
-                r[u][q].x += a.cre * z.x - a.cim * z.y;
-                r[u][q].y += a.cre * z.y + a.cim * z.x;
-              }
-        }
-      }
-    }
   }
+  if constexpr (!real_late(NY, NZ)) load_r();
   {
     const double ky = kt.shift(b >> 1, 1), kz = kt.shift(b >> 1, 2);
     for (int k = tid; k < NY; k += NT) {
       twy[k] = twy_g[k];
-      const double g = kt.g[1][k] + ky;
-      ty[k] = 0.5 / NP * (g * g);
+      const double g = kt.g[1][plan_position<FY>(k)] + ky;
+      ty[k] = R(0.5 / NP * (g * g));
     }
     for (int k = tid; k < NZ; k += NT) {
       twz[k] = twz_g[k];
-      const double g = kt.g[2][k] + kz;
-      tz[k] = 0.5 / NP * (g * g);
+      const double g = kt.g[2][plan_position<FZ>(k)] + kz;
+      tz[k] = R(0.5 / NP * (g * g));
     }
   }
   group_sync<NW>();  // tables
@@ -694,7 +671,7 @@ __global__ __launch_bounds__(64 * real_nw(NY, NZ), real_mw(NY, NZ)) void k_plane
   for (int u = 0; u < IT; ++u) {
     const int it = min(lane + 64 * u, ITEMS - 1);
     {
-      stage_butterfly<double, NY, 0, true>(v[u], twy, it / CW);
+      stage_butterfly<R, FY, 0, true>(v[u], twy, it / CW);
       C* p = cols + (it / CW) * PZ + it % CW;
 #pragma unroll
       for (int q = 0; q < RY; ++q) p[q * MY * PZ] = v[u][q];
@@ -702,22 +679,75 @@ __global__ __launch_bounds__(64 * real_nw(NY, NZ), real_mw(NY, NZ)) void k_plane
   }
   if constexpr (plan_nstages(NY) > 1) {
     wave_sync();
-    wave_stage<double, NY, 1, CW, 1, PZ, true>(cols, twy, lane);
+    wave_stage<R, FY, 1, CW, 1, PZ, true>(cols, twy, lane);
   }
   group_sync<NW>();
   if constexpr (plan_nstages(NZ) > 1) {
-    wave_stage<double, NZ, 0, RW, PZ, 1, true>(rows, twz, lane);
+    wave_stage<R, FZ, 0, RW, PZ, 1, true>(rows, twz, lane);
     wave_sync();
   }
-  wave_middle<double, NZ, RW, PZ, 1>(rows, lane, [&](int line, int k) { return ty[w * RW + line] + tz[k]; });
+  wave_middle<R, FZ, RW, PZ, 1>(rows, lane, [&](int line, int k) { return ty[w * RW + line] + tz[k]; });
   if constexpr (plan_nstages(NZ) > 1) {
     wave_sync();
-    wave_stage<double, NZ, 0, RW, PZ, 1, false>(rows, twz, lane);
+    wave_stage<R, FZ, 0, RW, PZ, 1, false>(rows, twz, lane);
+  }
+  if constexpr (real_late(NY, NZ)) load_r();
+  // the map of the plane's sphere rows, then the rows themselves, are under way during the last stages
+  int J[IT][RY];
+  if (on_plane) {
+#pragma unroll
+    for (int u = 0; u < IT; ++u) {
+      const int it = min(lane + 64 * u, ITEMS - 1);
+      const uint32_t o = uint32_t((it / CW) * NZ + it % CW) * 4u;
+#pragma unroll
+      for (int q = 0; q < RY; ++q) J[u][q] = *at_bytes(pm + (w * CW + q * MY * NZ), o);
+    }
   }
   group_sync<NW>();
+  bool rows_here = false;  // (wave-uniform)
+  C y[IT][RY];
+  if (on_plane) {
+    int any = J[0][0];
+#pragma unroll
+    for (int u = 0; u < IT; ++u)
+#pragma unroll
+      for (int q = 0; q < RY; ++q) any &= J[u][q];  // all negative (no row) only if every J is
+    rows_here = __any(any >= 0);
+    if (Y && rows_here) {
+      // every load at once: points without a row read row 0 and drop it
+#pragma unroll
+      for (int u = 0; u < IT; ++u)
+#pragma unroll
+        for (int q = 0; q < RY; ++q) y[u][q] = Y[rb + (J[u][q] >= 0 ? (J[u][q] & kRowMask) : 0)];
+    }
+  }
   if constexpr (plan_nstages(NY) > 1) {
-    wave_stage<double, NY, 1, CW, 1, PZ, false>(cols, twy, lane);
+    wave_stage<R, FY, 1, CW, 1, PZ, false>(cols, twy, lane);
     wave_sync();
+  }
+  if (Y && rows_here) {
+    int more = -1;
+#pragma unroll
+    for (int u = 0; u < IT; ++u)
+#pragma unroll
+      for (int q = 0; q < RY; ++q) {
+        const C z = J[u][q] >= 0 ? y[u][q] : C{R(0), R(0)};
+        r[u][q].x += a.cre * z.x - a.cim * z.y;
+        r[u][q].y += a.cre * z.y + a.cim * z.x;
+        more = max(more, J[u][q]);
+      }
+    if (__any(more > kRowMask)) {  // further rows at a point: overlapping spheres
+#pragma unroll
+      for (int u = 0; u < IT; ++u)
+#pragma unroll
+        for (int q = 0; q < RY; ++q)
+          if (J[u][q] > kRowMask)
+            for (int k = pt.rnext[J[u][q] & kRowMask]; k >= 0; k = pt.rnext[k]) {
+              const C z = Y[rb + k];
+              r[u][q].x += a.cre * z.x - a.cim * z.y;
+              r[u][q].y += a.cre * z.y + a.cim * z.x;
+            }
+    }
   }
 
   // out = r + c T_yz w, and its sphere rows
@@ -726,16 +756,11 @@ __global__ __launch_bounds__(64 * real_nw(NY, NZ), real_mw(NY, NZ)) void k_plane
 #pragma unroll
   for (int u = 0; u < IT; ++u) {
     const int it = min(lane + 64 * u, ITEMS - 1);
-    const uint32_t l0 = uint32_t((it / CW) * NZ + it % CW), oc = l0 * 16u;
+    const uint32_t oc = uint32_t((it / CW) * NZ + it % CW) * uint32_t(sizeof(C));
     const C* p = cols + (it / CW) * PZ + it % CW;
-    int J[RY];
-    if (on_plane && Wr) {
-#pragma unroll
-      for (int q = 0; q < RY; ++q) J[q] = *at_bytes(pm + (w * CW + q * MY * NZ), l0 * 4u);
-    }
 #pragma unroll
     for (int q = 0; q < RY; ++q) v[u][q] = p[q * MY * PZ];
-    stage_butterfly<double, NY, 0, false>(v[u], twy, it / CW);
+    stage_butterfly<R, FY, 0, false>(v[u], twy, it / CW);
 #pragma unroll
     for (int q = 0; q < RY; ++q) {
       const C h = v[u][q];
@@ -748,13 +773,13 @@ __global__ __launch_bounds__(64 * real_nw(NY, NZ), real_mw(NY, NZ)) void k_plane
         *ap = *ap + r[u][q];
       }
     }
-    if (on_plane && Wr) {
+    if (Wr && rows_here) {
 #pragma unroll
       for (int q = 0; q < RY; ++q)
-        if (J[q] >= 0) {
-          Wr[rb + (J[q] & kRowMask)] = r[u][q];
-          if (J[q] > kRowMask)
-            for (int k = pt.rnext[J[q] & kRowMask]; k >= 0; k = pt.rnext[k]) Wr[rb + k] = r[u][q];
+        if (J[u][q] >= 0) {
+          Wr[rb + (J[u][q] & kRowMask)] = r[u][q];
+          if (J[u][q] > kRowMask)
+            for (int k = pt.rnext[J[u][q] & kRowMask]; k >= 0; k = pt.rnext[k]) Wr[rb + k] = r[u][q];
         }
     }
   }
@@ -762,15 +787,16 @@ __global__ __launch_bounds__(64 * real_nw(NY, NZ), real_mw(NY, NZ)) void k_plane
 
 // Sphere rows W[b][J] of B batch entries (state b / 2, spinor component b % 2): the rows the plane
 // pass gathers from its own output, for states that no plane pass has just written.
-static __global__ __launch_bounds__(256) void k_gather_rows(const cpx<double>* __restrict__ psi,
-                                                            cpx<double>* __restrict__ W, ProjTables pt, size_t N) {
+template <typename R>
+__global__ __launch_bounds__(256) void k_gather_rows(const cpx<R>* __restrict__ psi, cpx<R>* __restrict__ W,
+                                                     ProjTables pt, size_t N) {
   const int J = blockIdx.y * 256 + threadIdx.x;
   const int b = blockIdx.x;
   if (J < pt.Jtot) W[size_t(b) * pt.Jtot + J] = psi[size_t(b) * N + pt.rflat[J]];
 }
 
 // Column pass: r = alpha x + c (T_x + V) w, T_x = IDFT_x 1/2 (G_x + k_x)^2 / NX DFT_x, in real space along
-// y and z.  Each wave takes XK_COLS consecutive yz columns of one spinor component (one 128-byte line
+// y and z.  Each wave takes xk_cols consecutive yz columns of one spinor component (one 128-byte line
 // per x-plane); the neighbouring wave takes the other component of the same columns, and the two swap
 // their values of w through their LDS tiles for the 2x2 potential.  r waits in registers while w goes
 // through the tile: the first forward stage works on the values as they are loaded, the last forward
@@ -779,24 +805,29 @@ static __global__ __launch_bounds__(256) void k_gather_rows(const cpx<double>* _
 // every state (where the column blocks divide by eight): its eighth of the fields stays in its L2, and
 // consecutive workgroups still read consecutive columns of one state.
 // XS: the Taylor base x is another array than w (else alpha w is used).
-constexpr int XK_COLS = 8;    // columns per wave
-// Column blocks per workgroup (two waves each): four blocks of lines from 48 points on (512 bytes of a row
-// per workgroup: 824 against 862 us per pass at 64^3 x 256 with two, 1021 with one), two below, where the
+// A wave's columns: one 128-byte line per x-plane (FP32 with 64-byte halves 667 against 425 us per pass
+// at 64^3 x 256)
+template <typename R>
+constexpr int xk_cols() { return 128 / int(sizeof(cpx<R>)); }
+// Column blocks per workgroup (two waves each): four blocks of lines of 48 and 64 points (FP64 64^3 x 256:
+// 512 bytes of a row per workgroup, 824 against 862 us per pass with two, 1021 with one, all with the
+// slower addressing above; 752 us = 5.7 TB/s now; FP32 373 us against 432 with two), two below, where the
 // grids are small and need the workgroups (21 against 26 us at 32^3 x 32) and at 96 points (LDS).
 constexpr int xv_pairs(int nx) { return nx == 48 || nx == 64 ? 4 : 2; }
 // waves per SIMD that the registers must allow
 constexpr int xv_mw(int nx) { return nx == 96 ? 3 : 4; }
-template <int NX, int PAIRS, int M, bool XS>
-__global__ __launch_bounds__(128 * PAIRS, xv_mw(NX)) void k_xv(StageArgs<double> a, cpx<double>* __restrict__ dst, int NY, int NZ,
-                                                       int S, const cpx<double>* __restrict__ twx_g, KinTables kt) {
-  using C = cpx<double>;
-  constexpr int CW = XK_COLS;
-  constexpr int RX = plan_radix(NX, 0), MX = NX / RX;
+template <typename R, int NX, int PAIRS, int M, bool XS>
+__global__ __launch_bounds__(128 * PAIRS, xv_mw(NX)) void k_xv(StageArgs<R> a, cpx<R>* __restrict__ dst, int NY, int NZ,
+                                                       int S, const cpx<R>* __restrict__ twx_g, KinTables kt) {
+  using C = cpx<R>;
+  constexpr int CW = xk_cols<R>();
+  constexpr int FX = real_plan(NX);
+  constexpr int RX = plan_radix(FX, 0), MX = NX / RX;
   constexpr int ITEMS = CW * MX, IT = (ITEMS + 63) / 64;
   static_assert(plan_nstages(NX) <= 2, "column split");
   __shared__ C tiles[2 * PAIRS][NX * CW];
   __shared__ C tw[NX];
-  __shared__ double tx[NX];
+  __shared__ R tx[NX];
   const int tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int s = w & 1;
@@ -816,33 +847,36 @@ __global__ __launch_bounds__(128 * PAIRS, xv_mw(NX)) void k_xv(StageArgs<double>
   const size_t off = size_t(2 * i + s) * N + q0;
   const C* __restrict__ win = reinterpret_cast<const C*>(a.w_in);
   const C* __restrict__ xb = reinterpret_cast<const C*>(a.x_base);
-  const double* __restrict__ F = a.fields + q0;
+  const R* __restrict__ F = a.fields + q0;
   C* tile = tiles[w];
   const C* other = tiles[w ^ 1];
   C v[IT][RX], r[IT][RX];
 #pragma unroll
   for (int u = 0; u < IT; ++u) {
     const int it = min(lane + 64 * u, ITEMS - 1);
-    const uint32_t o = uint32_t(it / CW * NYZ + it % CW) * 16u;
+    const uint32_t o = uint32_t(it / CW * NYZ + it % CW) * uint32_t(sizeof(C));
 #pragma unroll
     for (int q = 0; q < RX; ++q) v[u][q] = ld_stream<M>(at_bytes(win + (off + size_t(q * MX) * NYZ), o));
   }
-  // the fields are loaded along with w where their registers allow
-  constexpr bool PRE = IT * RX <= 8;
-  double f[PRE ? RX : 1][4];
-  if constexpr (PRE) {
-    const int it = min(lane, ITEMS - 1);
-    const uint32_t of = uint32_t(it / CW * NYZ + it % CW) * 8u;
+  // the fields are loaded along with w where their registers allow, else FD points ahead of their use
+  // (96: 350 us FP64 96^3 x 32, 452 with one point at a time)
+  constexpr int NPT = IT * RX;
+  constexpr int FD = NPT * int(sizeof(R)) <= 64 ? NPT : 32 / int(sizeof(R));
+  constexpr bool PRE = FD == NPT;
+  R f[FD][4];
+  const auto load_f = [&](int p) {
+    const int it = min(lane + 64 * (p / RX), ITEMS - 1);
+    const uint32_t of = uint32_t(it / CW * NYZ + it % CW) * uint32_t(sizeof(R));
 #pragma unroll
-    for (int q = 0; q < RX; ++q)
+    for (int d = 0; d < 4; ++d) f[p % FD][d] = *at_bytes(F + d * N + size_t(p % RX * MX) * NYZ, of);
+  };
 #pragma unroll
-      for (int d = 0; d < 4; ++d) f[q][d] = *at_bytes(F + d * N + size_t(q * MX) * NYZ, of);
-  }
+  for (int p = 0; p < FD; ++p) load_f(p);
   const double kx = kt.shift(i, 0);
   for (int k = tid; k < NX; k += 128 * PAIRS) {
     tw[k] = twx_g[k];
-    const double g = kt.g[0][k] + kx;
-    tx[k] = 0.5 / NX * (g * g);
+    const double g = kt.g[0][plan_position<FX>(k)] + kx;
+    tx[k] = R(0.5 / NX * (g * g));
   }
 #pragma unroll
   for (int u = 0; u < IT; ++u) {
@@ -857,26 +891,31 @@ __global__ __launch_bounds__(128 * PAIRS, xv_mw(NX)) void k_xv(StageArgs<double>
   for (int u = 0; u < IT; ++u) {
     const int it = min(lane + 64 * u, ITEMS - 1);
     const int x0 = it / CW, col = q0 + it % CW;
-    const uint32_t l0 = uint32_t(x0 * NYZ + it % CW), oc = l0 * 16u, of = l0 * 8u;
+    const uint32_t l0 = uint32_t(x0 * NYZ + it % CW), oc = l0 * uint32_t(sizeof(C)), of = l0 * uint32_t(sizeof(R));
     // laser potential, less its x term
-    const double lyz = a.lg[3] + a.lg[1] * double(col / NZ) + a.lg[2] * double(col % NZ);
+    const R lyz = a.lg[3] + a.lg[1] * R(col / NZ) + a.lg[2] * R(col % NZ);
 #pragma unroll
     for (int q = 0; q < RX; ++q) {
       const size_t eu = size_t(q * MX) * NYZ;
-      double fq[4];
+      const int p = u * RX + q;
+      R fq[4];
 #pragma unroll
-      for (int d = 0; d < 4; ++d) fq[d] = PRE ? f[PRE ? q : 0][d] : *at_bytes(F + d * N + eu, of);
-      const double vl = fq[0] + (lyz + a.lg[0] * double(x0 + q * MX));
-      const double bx = fq[1] + a.bext[0], by = fq[2] + a.bext[1], bz = fq[3] + a.bext[2];
+      for (int d = 0; d < 4; ++d) fq[d] = f[p % FD][d];
+      if (p + FD < NPT) load_f(p + FD);
+      const R vl = fq[0] + (lyz + a.lg[0] * R(x0 + q * MX));
+      const R bx = fq[1] + a.bext[0], by = fq[2] + a.bext[1], bz = fq[3] + a.bext[2];
       const C ws = v[u][q], wo = other[it + q * MX * CW];
       // up: (v+bz) up + (bx - i by) dn ; dn: (v-bz) dn + (bx + i by) up
-      const double d = s ? vl - bz : vl + bz, e = s ? -by : by;
+      const R d = s ? vl - bz : vl + bz, e = s ? -by : by;
       const C h = {d * ws.x + bx * wo.x + e * wo.y, d * ws.y + bx * wo.y - e * wo.x};
       C xv = ws;
       if constexpr (XS) xv = ld_stream<M>(at_bytes(xb + (off + eu), oc));
       r[u][q].x = a.alpha * xv.x + (a.cre * h.x - a.cim * h.y);
       r[u][q].y = a.alpha * xv.y + (a.cre * h.y + a.cim * h.x);
-      if constexpr (!PRE) sched_fence();
+      if (!PRE) {
+        pin(r[u][q]);
+        sched_fence();
+      }
     }
   }
   __syncthreads();  // the other wave has read this tile
@@ -884,7 +923,7 @@ __global__ __launch_bounds__(128 * PAIRS, xv_mw(NX)) void k_xv(StageArgs<double>
   for (int u = 0; u < IT; ++u) {
     const int it = min(lane + 64 * u, ITEMS - 1);
     {
-      stage_butterfly<double, NX, 0, true>(v[u], tw, it / CW);
+      stage_butterfly<R, FX, 0, true>(v[u], tw, it / CW);
       if constexpr (plan_nstages(NX) > 1) {
 #pragma unroll
         for (int q = 0; q < RX; ++q) tile[it + q * MX * CW] = v[u][q];
@@ -893,10 +932,11 @@ __global__ __launch_bounds__(128 * PAIRS, xv_mw(NX)) void k_xv(StageArgs<double>
         for (int q = 0; q < RX; ++q) v[u][q] = cscale(v[u][q], tx[q]);
       }
     }
+    if (!PRE) sched_fence();
   }
   if constexpr (plan_nstages(NX) > 1) {
     wave_sync();
-    wave_middle<double, NX, CW, 1, CW>(tile, lane, [&](int, int k) { return tx[k]; });
+    wave_middle<R, FX, CW, 1, CW>(tile, lane, [&](int, int k) { return tx[k]; });
     wave_sync();
   }
   C* out = dst + off;
@@ -904,12 +944,12 @@ __global__ __launch_bounds__(128 * PAIRS, xv_mw(NX)) void k_xv(StageArgs<double>
   for (int u = 0; u < IT; ++u) {
     const int it = min(lane + 64 * u, ITEMS - 1);
     {
-      const uint32_t o = uint32_t(it / CW * NYZ + it % CW) * 16u;
+      const uint32_t o = uint32_t(it / CW * NYZ + it % CW) * uint32_t(sizeof(C));
       if constexpr (plan_nstages(NX) > 1) {
 #pragma unroll
         for (int q = 0; q < RX; ++q) v[u][q] = tile[it + q * MX * CW];
       }
-      stage_butterfly<double, NX, 0, false>(v[u], tw, it / CW);
+      stage_butterfly<R, FX, 0, false>(v[u], tw, it / CW);
 #pragma unroll
       for (int q = 0; q < RX; ++q) {
         const C h = v[u][q];
@@ -917,6 +957,7 @@ __global__ __launch_bounds__(128 * PAIRS, xv_mw(NX)) void k_xv(StageArgs<double>
         st_stream<M>(at_bytes(out + size_t(q * MX) * NYZ, o), t);
       }
     }
+    if (!PRE) sched_fence();
   }
 }
 
@@ -1503,8 +1544,8 @@ constexpr int KU = 4;   // k-steps whose operands are loaded together
 // Cpart[a][kc][p][i] = sum_{k in chunk} conj(beta[a][k][p]) W[i][k], k = 2 (J - off_a) + s.
 // One wave: PP/16 output tiles of 16 projectors x 16 states; A/B operands as
 // A[row = lane%16][k = lane/16], B[k = lane/16][col = lane%16]; D rows from mfma16::row.
-// KQ: the rows of W are taken times the phases exp(i k.d) of PhaseTab (FP64 with Bloch vectors; in FP32
-// the plane pass has put the phase on them).
+// KQ: the rows of W are taken times the phases exp(i k.d) of PhaseTab (real-space form with Bloch vectors;
+// in the transformed form the plane pass has put the phase on them).
 template <typename R, int PP, bool KQ>
 __global__ __launch_bounds__(64) void k_proj_contract(ProjTables pt, const cpx<R>* __restrict__ W,
                                                       int S, cpx<double>* __restrict__ Cpart, PhaseTab ph) {
@@ -1519,8 +1560,8 @@ __global__ __launch_bounds__(64) void k_proj_contract(ProjTables pt, const cpx<R
   const int col = lane & 15, kl = lane >> 4;
   const int i = nt * 16 + col;
   const cpx<R>* __restrict__ beta = reinterpret_cast<const cpx<R>*>(pt.beta);
-  const cpx<double>* __restrict__ phase = nullptr;
-  if constexpr (KQ) phase = ph.row(min(i, S - 1), pt.Jtot);
+  const cpx<R>* __restrict__ phase = nullptr;
+  if constexpr (KQ) phase = ph.row<R>(min(i, S - 1), pt.Jtot);
   typename M::acc ar[NMT], ai[NMT];
 #pragma unroll
   for (int mt = 0; mt < NMT; ++mt) {
@@ -1633,8 +1674,8 @@ __global__ __launch_bounds__(PS_NT) void k_proj_scatter(ProjTables pt, const cpx
   const int col = lane & 15, kl = lane >> 4;
   const int i = nt * 16 + col;
   const cpx<R>* __restrict__ beta = reinterpret_cast<const cpx<R>*>(pt.beta);
-  const cpx<double>* __restrict__ phase = nullptr;
-  if constexpr (KQ) phase = ph.row(min(i, S - 1), pt.Jtot);
+  const cpx<R>* __restrict__ phase = nullptr;
+  if constexpr (KQ) phase = ph.row<R>(min(i, S - 1), pt.Jtot);
   cpx<R> ec[KS];
 #pragma unroll
   for (int u = 0; u < KS; ++u) ec[u] = ecs[4 * u + kl][col];
@@ -1668,12 +1709,13 @@ __global__ __launch_bounds__(PS_NT) void k_proj_scatter(ProjTables pt, const cpx
 }
 
 // Phases exp(i (k + A).d) of every sphere row for each distinct Bloch vector.
-static __global__ __launch_bounds__(256) void k_phases(const double* __restrict__ kruns, double a0, double a1, double a2,
-                                                       const double* __restrict__ disp, int Jtot,
-                                                       cpx<double>* __restrict__ out) {
+template <typename R>
+__global__ __launch_bounds__(256) void k_phases(const double* __restrict__ kruns, double a0, double a1, double a2,
+                                                const R* __restrict__ disp, int Jtot, cpx<R>* __restrict__ out) {
   const int J = blockIdx.y * 256 + threadIdx.x;
   const double* k = kruns + 3 * size_t(blockIdx.x);
-  if (J < Jtot) out[size_t(blockIdx.x) * Jtot + J] = bloch_phase(k[0] + a0, k[1] + a1, k[2] + a2, disp + 3 * J);
+  if (J < Jtot)
+    out[size_t(blockIdx.x) * Jtot + J] = bloch_phase(R(k[0] + a0), R(k[1] + a1), R(k[2] + a2), disp + 3 * J);
 }
 
 // ---------------------------------------------------------------- adjoint kernels
@@ -2212,25 +2254,27 @@ static hipError_t set_lds(K kern, size_t bytes) {
                              hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
 }
 
-#if NCT_FP64_TU
-// ---- FP64, real-space form
-template <int A, int B, int M, bool ACC>
-static hipError_t launch_plane_yz_m(int S, int NX, const StageArgs<double>& a, const KinTables& kt,
+// ---- real-space form
+template <typename R, int A, int B, int M, bool ACC>
+static hipError_t launch_plane_yz_m(int S, int NX, const StageArgs<R>& a, const KinTables& kt,
                                     const ProjTables& pt, const void* twy, const void* twz, hipStream_t st) {
-  constexpr size_t lds = real_lds_bytes<A, B>();
-  auto kern = k_plane_yz<A, B, M, ACC>;
+  constexpr size_t lds = real_lds_bytes<R, A, B>();
+  auto kern = k_plane_yz<R, A, B, M, ACC>;
   hipError_t e = set_lds(kern, lds);
   if (e != hipSuccess) return e;
-  nct_launch(kern, dim3(2u * unsigned(S) * unsigned(NX)), dim3(64 * real_nw(A, B)), lds, st, a, kt, pt,
-             reinterpret_cast<const cpx<double>*>(twy), reinterpret_cast<const cpx<double>*>(twz), 2 * S, NX);
+  nct_launch(kern, dim3(2u * unsigned(S) * unsigned(NX)), dim3(64 * real_nw<R>(A, B)), lds, st, a, kt, pt,
+             reinterpret_cast<const cpx<R>*>(twy), reinterpret_cast<const cpx<R>*>(twz), 2 * S, NX);
   return hipGetLastError();
 }
 
-hipError_t launch_plane_yz(const int n[3], int S, const StageArgs<double>& a, const KinTables& kt,
+template <typename R>
+hipError_t launch_plane_yz(const int n[3], int S, const StageArgs<R>& a, const KinTables& kt,
                            const ProjTables& pt, const void* twy, const void* twz, hipStream_t st) {
+  constexpr bool D = sizeof(R) == 8;  // only the FP64 adjoint accumulates
+  if (a.acc && !D) return hipErrorInvalidValue;
 #define Y(A, B, M)                                                                             \
-  return a.acc ? launch_plane_yz_m<A, B, M, true>(S, n[0], a, kt, pt, twy, twz, st)            \
-               : launch_plane_yz_m<A, B, M, false>(S, n[0], a, kt, pt, twy, twz, st)
+  return a.acc ? launch_plane_yz_m<R, A, B, M, D>(S, n[0], a, kt, pt, twy, twz, st)            \
+               : launch_plane_yz_m<R, A, B, M, false>(S, n[0], a, kt, pt, twy, twz, st)
 #define X(A, B)                          \
   if (n[1] == A && n[2] == B) {          \
     if (a.cache_mode >= 2) Y(A, B, 2);   \
@@ -2243,44 +2287,50 @@ hipError_t launch_plane_yz(const int n[3], int S, const StageArgs<double>& a, co
   return hipErrorInvalidValue;
 }
 
+template <typename R>
 hipError_t launch_gather_rows(const ProjTables& pt, const void* psi, void* W, int B, size_t N, hipStream_t st) {
   if (pt.natoms == 0 || pt.Jtot == 0) return hipSuccess;
-  nct_launch(k_gather_rows, dim3(unsigned(B), nblocks(size_t(pt.Jtot), 256)), dim3(256), 0, st,
-             reinterpret_cast<const cpx<double>*>(psi), reinterpret_cast<cpx<double>*>(W), pt, N);
+  nct_launch(k_gather_rows<R>, dim3(unsigned(B), nblocks(size_t(pt.Jtot), 256)), dim3(256), 0, st,
+             reinterpret_cast<const cpx<R>*>(psi), reinterpret_cast<cpx<R>*>(W), pt, N);
   return hipGetLastError();
 }
 
-template <int NX, int PAIRS, int M>
-static hipError_t launch_xv_m(const int n[3], int S, const StageArgs<double>& a, void* dst, const void* twx,
+template <typename R, int NX, int PAIRS, int M>
+static hipError_t launch_xv_m(const int n[3], int S, const StageArgs<R>& a, void* dst, const void* twx,
                               const KinTables& kt, hipStream_t st) {
-  const dim3 grid(unsigned(n[1] * n[2] / (XK_COLS * PAIRS)) * unsigned(S)), block(128 * PAIRS);
-  const auto d_ = reinterpret_cast<cpx<double>*>(dst);
-  const auto t_ = reinterpret_cast<const cpx<double>*>(twx);
-  if (a.x_base && a.x_base != a.w_in) nct_launch((k_xv<NX, PAIRS, M, true>), grid, block, 0, st, a, d_, n[1], n[2], S, t_, kt);
-  else nct_launch((k_xv<NX, PAIRS, M, false>), grid, block, 0, st, a, d_, n[1], n[2], S, t_, kt);
+  const dim3 grid(unsigned(n[1] * n[2] / (xk_cols<R>() * PAIRS)) * unsigned(S)), block(128 * PAIRS);
+  const auto d_ = reinterpret_cast<cpx<R>*>(dst);
+  const auto t_ = reinterpret_cast<const cpx<R>*>(twx);
+  if (a.x_base && a.x_base != a.w_in) nct_launch((k_xv<R, NX, PAIRS, M, true>), grid, block, 0, st, a, d_, n[1], n[2], S, t_, kt);
+  else nct_launch((k_xv<R, NX, PAIRS, M, false>), grid, block, 0, st, a, d_, n[1], n[2], S, t_, kt);
   return hipGetLastError();
 }
-hipError_t launch_xv(const int n[3], int S, const StageArgs<double>& a, void* dst, const void* twx,
+template <typename R, int NX, int PAIRS>
+static hipError_t launch_xv_p(const int n[3], int S, const StageArgs<R>& a, void* dst, const void* twx,
+                              const KinTables& kt, hipStream_t st) {
+  if (a.cache_mode >= 2) return launch_xv_m<R, NX, PAIRS, 2>(n, S, a, dst, twx, kt, st);
+  if (a.cache_mode == 1) return launch_xv_m<R, NX, PAIRS, 1>(n, S, a, dst, twx, kt, st);
+  return launch_xv_m<R, NX, PAIRS, 0>(n, S, a, dst, twx, kt, st);
+}
+template <typename R>
+hipError_t launch_xv(const int n[3], int S, const StageArgs<R>& a, void* dst, const void* twx,
                      const KinTables& kt, hipStream_t st) {
-  // every built plane holds a multiple of 16 columns, the larger ones of 32
-  const bool wide = (n[1] * n[2]) % (XK_COLS * 4) == 0;
-#define Y(A, P)                                                                    \
-  {                                                                                \
-    if (a.cache_mode >= 2) return launch_xv_m<A, P, 2>(n, S, a, dst, twx, kt, st); \
-    if (a.cache_mode == 1) return launch_xv_m<A, P, 1>(n, S, a, dst, twx, kt, st); \
-    return launch_xv_m<A, P, 0>(n, S, a, dst, twx, kt, st);                        \
-  }
-#define X(A)                                                     \
-  if (n[0] == A) {                                               \
-    if constexpr (xv_pairs(A) == 4) { if (wide) Y(A, 4) }        \
-    Y(A, 2)                                                      \
+  // every built plane holds a multiple of 16 columns, all but 12 x 12 a multiple of 32
+#define X(A)                                                                        \
+  if (n[0] == A) {                                                                  \
+    const int blocks = n[1] * n[2] / xk_cols<R>();                                  \
+    if constexpr (xv_pairs(A) == 4) {                                            \
+      if (blocks % 4 == 0) return launch_xv_p<R, A, 4>(n, S, a, dst, twx, kt, st);  \
+    }                                                                               \
+    if (blocks % 2 == 0) return launch_xv_p<R, A, 2>(n, S, a, dst, twx, kt, st);    \
+    return launch_xv_p<R, A, 1>(n, S, a, dst, twx, kt, st);                         \
   }
   NCT_LINES(X)
 #undef X
-#undef Y
   return hipErrorInvalidValue;
 }
 
+#if NCT_FP64_TU
 hipError_t launch_energy_real(const int n[3], int B, const void* src, const void* twx, const void* twy,
                               const void* twz, const KinTables& kt, double* part, double* eplane, int* ntiles_out,
                               hipStream_t st) {
@@ -2317,7 +2367,7 @@ hipError_t launch_energy_real(const int n[3], int B, const void* src, const void
   return hipErrorInvalidValue;
 }
 #else
-// ---- FP32, transformed form
+// ---- transformed form (FP32)
 template <typename R, int A, int B, int M>
 static hipError_t launch_plane_stage_m(int S, int NX, const StageArgs<R>& a, const ProjTables& pt,
                                        const void* twy, const void* twz, hipStream_t st) {
@@ -2565,11 +2615,9 @@ template <typename R>
 hipError_t launch_proj_contract(const ProjTables& pt, const void* W, int S, void* Cpart, const PhaseTab& ph,
                                 hipStream_t st) {
   if (pt.natoms == 0) return hipSuccess;
-  if constexpr (sizeof(R) == 8) {
-    if (ph.tab)
-      return pt.PP == 16 ? launch_contract_pp<R, 16, true>(pt, W, S, Cpart, ph, st)
-                         : launch_contract_pp<R, 32, true>(pt, W, S, Cpart, ph, st);
-  }
+  if (ph.tab)
+    return pt.PP == 16 ? launch_contract_pp<R, 16, true>(pt, W, S, Cpart, ph, st)
+                       : launch_contract_pp<R, 32, true>(pt, W, S, Cpart, ph, st);
   return pt.PP == 16 ? launch_contract_pp<R, 16, false>(pt, W, S, Cpart, ph, st)
                      : launch_contract_pp<R, 32, false>(pt, W, S, Cpart, ph, st);
 }
@@ -2580,14 +2628,15 @@ hipError_t launch_proj_reduce(const ProjTables& pt, const void* Cpart, int S, do
              reinterpret_cast<const cpx<double>*>(Cpart), S, dV, reinterpret_cast<cpx<double>*>(C));
   return hipGetLastError();
 }
+#endif
+template <typename R>
 hipError_t launch_phases(const double* kruns, int nruns, const double ka[3], const ProjTables& pt, void* tab,
                          hipStream_t st) {
   if (pt.natoms == 0 || pt.Jtot == 0) return hipSuccess;
-  nct_launch(k_phases, dim3(unsigned(nruns), nblocks(size_t(pt.Jtot), 256)), dim3(256), 0, st, kruns, ka[0], ka[1],
-             ka[2], reinterpret_cast<const double*>(pt.disp), pt.Jtot, reinterpret_cast<cpx<double>*>(tab));
+  nct_launch(k_phases<R>, dim3(unsigned(nruns), nblocks(size_t(pt.Jtot), 256)), dim3(256), 0, st, kruns, ka[0], ka[1],
+             ka[2], reinterpret_cast<const R*>(pt.disp), pt.Jtot, reinterpret_cast<cpx<R>*>(tab));
   return hipGetLastError();
 }
-#endif
 
 template <typename R, int PP, bool KQ>
 static hipError_t launch_scatter_pp(const ProjTables& pt, const void* Cpart, int S, double dV, void* Y,
@@ -2605,11 +2654,9 @@ template <typename R>
 hipError_t launch_proj_scatter(const ProjTables& pt, const void* Cpart, int S, double dV, void* Y, const PhaseTab& ph,
                                hipStream_t st) {
   if (pt.natoms == 0) return hipSuccess;
-  if constexpr (sizeof(R) == 8) {
-    if (ph.tab)
-      return pt.PP == 16 ? launch_scatter_pp<R, 16, true>(pt, Cpart, S, dV, Y, ph, st)
-                         : launch_scatter_pp<R, 32, true>(pt, Cpart, S, dV, Y, ph, st);
-  }
+  if (ph.tab)
+    return pt.PP == 16 ? launch_scatter_pp<R, 16, true>(pt, Cpart, S, dV, Y, ph, st)
+                       : launch_scatter_pp<R, 32, true>(pt, Cpart, S, dV, Y, ph, st);
   return pt.PP == 16 ? launch_scatter_pp<R, 16, false>(pt, Cpart, S, dV, Y, ph, st)
                      : launch_scatter_pp<R, 32, false>(pt, Cpart, S, dV, Y, ph, st);
 }
@@ -2706,6 +2753,12 @@ hipError_t launch_density_backprop(const void* psi, const double* occ, const dou
 
 // explicit instantiations
 #define NCT_INST(R)                                                                                \
+  template hipError_t launch_plane_yz<R>(const int*, int, const StageArgs<R>&, const KinTables&,   \
+                                         const ProjTables&, const void*, const void*, hipStream_t); \
+  template hipError_t launch_xv<R>(const int*, int, const StageArgs<R>&, void*, const void*,       \
+                                   const KinTables&, hipStream_t);                                 \
+  template hipError_t launch_gather_rows<R>(const ProjTables&, const void*, void*, int, size_t, hipStream_t); \
+  template hipError_t launch_phases<R>(const double*, int, const double*, const ProjTables&, void*, hipStream_t); \
   template hipError_t launch_xpass<R>(const int*, int, const void*, void*, const R*, const R*, R,  \
                                       int, const void*, hipStream_t, int, KTables<R>);             \
   template hipError_t launch_density<R>(const void*, const double*, int, size_t, double*,          \

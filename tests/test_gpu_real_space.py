@@ -92,3 +92,53 @@ def test_projector_chain_splits(gpu, S, natoms, nch, prec):
         out.append(hpsi.cpu().numpy().astype(np.complex128))
         s.close()
     assert max_rel(out[0] - out[1], ref) < (2e-5 if prec else 1e-11)
+
+
+# Mixed precision: FP32 unit roundoff 6e-8, some 16 roundings on a point's way through the transforms and
+# the sum of the terms, times a spread of kinetic factors of up to 4 against their mean: 4e-6, bar 1e-5.
+@pytest.mark.parametrize("k", range(len(PLANES)))
+def test_mixed_apply_every_plane_with_overlapping_spheres(gpu, k):
+    """The same in mixed precision, every plane with another column length than above."""
+    torch, nct = gpu
+    ny, nz = PLANES[k]
+    n = (LINES[(5 * k + 2) % len(LINES)] if ny * nz < 2000 else 12, ny, nz)
+    L = tuple(0.5 * v for v in n)
+    print(f"[case] mixed apply n={n}", flush=True)
+    w = I.make_system(n=n, L=L, nstates=3, case=130 + k, natoms=3, min_sep=0.2 * min(L), r_sphere=0.45 * min(L))
+    F = np.random.default_rng(k).uniform(-0.5, 0.5, (4,) + n)
+    sysd = O.system_from_workload(w)
+    ref = (O.kinetic(w.psi0, sysd.grid) + O.apply_local(w.psi0, F[0], F[1:])
+           + O.apply_nonlocal(w.psi0, sysd.projs, sysd.grid))
+    s = nct.system_from_workload(w, precision=nct.NCT_FP32_MIXED)
+    s.set_potentials(fields=torch.from_numpy(F).cuda())
+    psi = nct.states_to_device(w.psi0, nct.NCT_FP32_MIXED)
+    hpsi = torch.empty_like(psi)
+    s.apply_hamiltonian(psi, hpsi, 0.0)
+    assert max_rel(hpsi.cpu().numpy(), ref) < 1e-5
+
+
+@pytest.mark.parametrize("n,S,K,dt,laser", [((12, 12, 12), 19440, 4, 0.029, ""), ((96, 8, 8), 5470, 4, 0.05, "velocity"),
+                                            ((12, 24, 24), 4870, 13, 0.05, "length"), ((8, 96, 96), 456, 5, 0.04, "")])
+def test_mixed_step_of_large_states(gpu, n, S, K, dt, laser):
+    """One mixed-precision step just above 512 MiB of states, where FP32 takes the real-space form, against
+    the FP64 step: both exponential forms, shifted kinetic factors, ragged groups of states."""
+    torch, nct = gpu
+    print(f"[case] mixed step n={n} S={S} K={K} dt={dt} laser={laser!r}", flush=True)
+    assert 2 * S * np.prod(n) * 8 > 512 * 2 ** 20
+    w = I.make_system(n=n, L=tuple(0.42 * v for v in n), nstates=2, natoms=1, case=95, dt=dt, taylor_order=K,
+                      bfield=I.BField(B0=(0.01, -0.02, 0.03)), r_sphere=1.6,
+                      laser=[I.LaserPulse(A=0.02, omega=0.3, t0=0.0, tau=5.0)] if laser else None)
+    if laser:
+        w.laser_gauge = laser
+    w.nstates, w.occ = S, np.full(S, 2.0 / S)
+    psi = torch.randn((S, 2) + n, dtype=torch.complex64, generator=torch.Generator("cuda").manual_seed(5), device="cuda")
+    psi /= float(torch.linalg.vector_norm(psi[0]) * np.sqrt(0.42 ** 3))
+    out = []
+    for p in (nct.NCT_FP64, nct.NCT_FP32_MIXED):
+        x = psi.to(torch.complex128) if p == nct.NCT_FP64 else psi.clone()
+        s = nct.system_from_workload(w, precision=p)
+        s.set_watchdog(0.0)
+        s.step(x, 0.0, 1)
+        s.close()
+        out.append(x)
+    assert float((out[1] - out[0]).abs().max() / out[0].abs().max()) < 1e-5

@@ -2074,100 +2074,136 @@ static __global__ __launch_bounds__(256) void k_dm_init(int nx, int ny, int nz, 
 
 // Partial Gram matrices over K-chunks: part[c][i][j] = sum_{k in chunk c} conj(A[i][k]) A[j][k]
 // for the tile pairs (ti <= tj) of 32 x 32 state tiles; A is [S][K] (states are rows of K = 2N
-// complex values).  Four waves per workgroup, one 16 x 16 output tile each.
+// complex values).  Four waves per workgroup, one 16 x 16 output tile each (the one below the diagonal
+// is left out).  Bound by the matrix cores, so the next KB values are loaded while this iteration's
+// products run, into the other of two LDS tiles, with one barrier per iteration; the pairs of a chunk run on
+// one XCD and find each other's rows in its L2.  At least four waves per SIMD are asked for: with more
+// registers allowed, the compiler keeps the sums in accumulation registers and copies them back and forth
+// every iteration.  96 states of 48^3 FP64: 223 against 239 us (9.5 GFLOP of products, 43 TFLOP/s).
 constexpr int GRAM_T = 32;   // output tile (states)
 constexpr int GRAM_KB = 16;  // k values staged per iteration
 template <typename R>
-__global__ __launch_bounds__(256) void k_gram_partial(const cpx<R>* __restrict__ A, int S, size_t K,
+__global__ __launch_bounds__(256, 4) void k_gram_partial(const cpx<R>* __restrict__ A, int S, size_t K,
                                                       size_t kchunk, cpx<double>* __restrict__ part) {
   using M = mfma16<double>;
-  __shared__ cpx<double> sa[GRAM_T][GRAM_KB + 1];
-  __shared__ cpx<double> sb[GRAM_T][GRAM_KB + 1];
+  constexpr int E = GRAM_T * GRAM_KB / 256;
+  __shared__ cpx<double> sa[2][GRAM_T][GRAM_KB + 1];
+  __shared__ cpx<double> sb[2][GRAM_T][GRAM_KB + 1];
   const int T = (S + GRAM_T - 1) / GRAM_T;
-  int pidx = blockIdx.x, ti = 0;
+  const int L = xcd_logical(blockIdx.x, gridDim.x);
+  const int chunk = L / (T * (T + 1) / 2);
+  int pidx = L - chunk * (T * (T + 1) / 2), ti = 0;
   while (pidx >= T - ti) {
     pidx -= T - ti;
     ++ti;
   }
   const int tj = ti + pidx;
-  const size_t k0 = size_t(blockIdx.y) * kchunk;
+  const size_t k0 = size_t(chunk) * kchunk;
   const size_t k1 = min(K, k0 + kchunk);
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int wi = w >> 1, wj = w & 1;
   const int c = lane & 15, kl = lane >> 4;
+  const bool below = ti == tj && wi > wj;
   M::acc cr = M::zero(), ci = M::zero();
-  for (size_t kb = k0; kb < k1; kb += GRAM_KB) {
+  cpx<R> va[E], vb[E];
+  const auto load = [&](size_t kb) {
 #pragma unroll
-    for (int e = tid; e < GRAM_T * GRAM_KB; e += 256) {
-      const int r = e / GRAM_KB, kk = e % GRAM_KB;
-      const size_t k = kb + kk;
-      const int ri = ti * GRAM_T + r, rj = tj * GRAM_T + r;
-      cpx<double> va = {0.0, 0.0}, vb = {0.0, 0.0};
-      if (k < k1 && ri < S) {
-        const cpx<R> v = A[size_t(ri) * K + k];
-        va = {double(v.x), double(v.y)};
-      }
-      if (k < k1 && rj < S) {
-        const cpx<R> v = A[size_t(rj) * K + k];
-        vb = {double(v.x), double(v.y)};
-      }
-      sa[r][kk] = va;
-      sb[r][kk] = vb;
+    for (int e = 0; e < E; ++e) {
+      const int r = (tid + 256 * e) / GRAM_KB;
+      const size_t k = kb + (tid + 256 * e) % GRAM_KB, kc = min(k, k1 - 1);
+      // rows past the last state repeat it: their products are not stored
+      va[e] = A[size_t(min(ti * GRAM_T + r, S - 1)) * K + kc];
+      vb[e] = A[size_t(min(tj * GRAM_T + r, S - 1)) * K + kc];
+      if (k >= k1) va[e] = vb[e] = {R(0), R(0)};
     }
-    __syncthreads();
+  };
+  load(k0);
+  int buf = 0;
+  for (size_t kb = k0; kb < k1; kb += GRAM_KB, buf ^= 1) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int r = (tid + 256 * e) / GRAM_KB, kk = (tid + 256 * e) % GRAM_KB;
+      sa[buf][r][kk] = {double(va[e].x), double(va[e].y)};
+      sb[buf][r][kk] = {double(vb[e].x), double(vb[e].y)};
+    }
+    __syncthreads();  // also: every wave is past the products of the other buffer, written next
+    load(kb + GRAM_KB);  // (past the end: the last values again, dropped)
+    if (!below) {
 #pragma unroll
     for (int ks = 0; ks < GRAM_KB; ks += 4) {
-      const cpx<double> a = sa[wi * 16 + c][ks + kl];  // A operand: row i, column k
-      const cpx<double> b = sb[wj * 16 + c][ks + kl];  // B operand: row k, column j
+      const cpx<double> a = sa[buf][wi * 16 + c][ks + kl];  // A operand: row i, column k
+      const cpx<double> b = sb[buf][wj * 16 + c][ks + kl];  // B operand: row k, column j
       cr = M::op(a.x, b.x, cr);
-      cr = M::op(a.y, b.y, cr);
       ci = M::op(a.x, b.y, ci);
+      cr = M::op(a.y, b.y, cr);
       ci = M::op(-a.y, b.x, ci);
     }
-    __syncthreads();
+    }
   }
+  if (below) return;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int i = ti * GRAM_T + wi * 16 + M::row(r, kl);
     const int j = tj * GRAM_T + wj * 16 + c;
-    if (i < S && j < S) part[(size_t(blockIdx.y) * S + i) * S + j] = {cr[r], ci[r]};
+    if (i < S && j < S) part[(size_t(chunk) * S + i) * S + j] = {cr[r], ci[r]};
   }
 }
 
-// out[i][j] = scale sum_c part[c][i][j] (chunk order) for j >= i, and its conjugate at [j][i].
+// out[i][j] = scale sum_c part[c][i][j] for j >= i, and its conjugate at [j][i].  Sixteen entries per
+// workgroup, sixteen threads each: thread q adds the chunks c = q mod 16 in order, then the sixteen
+// sums are added in order (one thread per entry was a chain of up to 256 reads on few CUs: 79 against 6.4 us for
+// 96 states).
+constexpr int GRAM_RED = 16;
 static __global__ __launch_bounds__(256) void k_gram_reduce(const cpx<double>* __restrict__ part, int S, int nchunks,
                                                      double scale, cpx<double>* __restrict__ out) {
-  const size_t idx = size_t(blockIdx.x) * 256 + threadIdx.x;
-  if (idx >= size_t(S) * S) return;
+  __shared__ cpx<double> sums[GRAM_RED][GRAM_RED];
+  const int e = threadIdx.x % GRAM_RED, q = threadIdx.x / GRAM_RED;
+  const size_t idx = size_t(blockIdx.x) * GRAM_RED + e;
   const int i = int(idx / S), j = int(idx - size_t(i) * S);
-  if (j < i) return;
+  const bool mine = idx < size_t(S) * S && j >= i;
   double sr = 0.0, si = 0.0;
-  for (int cch = 0; cch < nchunks; ++cch) {
-    const cpx<double> v = part[(size_t(cch) * S + i) * S + j];
-    sr += v.x;
-    si += v.y;
+  if (mine)
+    for (int cch = q; cch < nchunks; cch += GRAM_RED) {
+      const cpx<double> v = part[(size_t(cch) * S + i) * S + j];
+      sr += v.x;
+      si += v.y;
+    }
+  sums[q][e] = {sr, si};
+  __syncthreads();
+  if (q != 0 || !mine) return;
+  for (int k = 1; k < GRAM_RED; ++k) {
+    sr += sums[k][e].x;
+    si += sums[k][e].y;
   }
   out[size_t(i) * S + j] = {scale * sr, scale * si};
   if (j != i) out[size_t(j) * S + i] = {scale * sr, -scale * si};
 }
 
 // D[j][p] = sum_{i <= j} Mt[i][j] A[i][p] (Mt upper triangular, FP64): the states D_j = sum_i
-// A_i M_ij.  One workgroup: 64 states j x 64 columns p; wave w owns states w*16 .. w*16+15 and
-// four 16-column MFMA tiles.  Only i below the tile's last j contribute.
+// A_i M_ij.  One workgroup: 64 states j x 64 columns p; wave w owns 16 columns and four 16-state MFMA
+// tiles.  Bound by the matrix cores: a tile of states takes only the i up to its own last j, which costs
+// every wave the same, since each holds all four tiles; the waves read A's columns straight
+// into the operand layout (four rows of 256 bytes per load) and share Mt through LDS, and both are loaded
+// one block of i ahead (96 states of 48^3 FP64: 226 against
+// 426 us with 16 states per wave and every i of the workgroup's block; three waves per SIMD for the reason
+// given at the overlap).
 constexpr int BT_J = 64;
 constexpr int BT_P = 64;
 constexpr int BT_KI = 16;
 template <typename R>
-__global__ __launch_bounds__(256) void k_basis_transform(const cpx<R>* __restrict__ A,
+__global__ __launch_bounds__(256, 3) void k_basis_transform(const cpx<R>* __restrict__ A,
                                                          const cpx<double>* __restrict__ Mt, int S,
                                                          size_t K, cpx<R>* __restrict__ D) {
   using M = mfma16<double>;
-  __shared__ cpx<double> sm[BT_J][BT_KI + 1];   // [j][i]
-  __shared__ cpx<double> sx[BT_KI][BT_P + 1];   // [i][p]
-  const int j0 = blockIdx.y * BT_J;
-  const size_t p0 = size_t(blockIdx.x) * BT_P;
+  constexpr int E = BT_KI * BT_J / 256;
+  __shared__ cpx<double> sm[2][BT_J][BT_KI + 1];   // [j][i]
+  const int jblocks = (S + BT_J - 1) / BT_J, L = xcd_logical(blockIdx.x, gridDim.x);
+  const int pb = L / jblocks;
+  const int j0 = (L - pb * jblocks) * BT_J;
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
   const int c = lane & 15, kl = lane >> 4;
+  const size_t pp = size_t(pb) * BT_P + w * 16 + c;
+  const size_t pr = min(pp, K - 1);
   M::acc dr[4], di[4];
 #pragma unroll
   for (int h = 0; h < 4; ++h) {
@@ -2175,47 +2211,54 @@ __global__ __launch_bounds__(256) void k_basis_transform(const cpx<R>* __restric
     di[h] = M::zero();
   }
   const int iend = min(S, j0 + BT_J);
-  for (int i0 = 0; i0 < iend; i0 += BT_KI) {
+  cpx<double> vm[E];
+  cpx<R> va[BT_KI / 4];
+  const auto load = [&](int i0) {
 #pragma unroll
-    for (int e = tid; e < BT_KI * BT_J; e += 256) {
-      const int il = e / BT_J, jl = e % BT_J;
-      const int i = i0 + il, j = j0 + jl;
-      sm[jl][il] = (i < S && j < S) ? Mt[size_t(i) * S + j] : cpx<double>{0.0, 0.0};
+    for (int e = 0; e < E; ++e) {
+      const int i = i0 + (tid + 256 * e) / BT_J, j = j0 + (tid + 256 * e) % BT_J;
+      vm[e] = Mt[size_t(min(i, S - 1)) * S + min(j, S - 1)];  // (states j >= S are not stored)
+      if (i >= S) vm[e] = {0.0, 0.0};
     }
 #pragma unroll
-    for (int e = tid; e < BT_KI * BT_P; e += 256) {
-      const int il = e / BT_P, pl = e % BT_P;
-      const int i = i0 + il;
-      const size_t pp = p0 + pl;
-      cpx<double> v = {0.0, 0.0};
-      if (i < S && pp < K) {
-        const cpx<R> a = A[size_t(i) * K + pp];
-        v = {double(a.x), double(a.y)};
+    for (int q = 0; q < BT_KI / 4; ++q) {
+      const int i = i0 + 4 * q + kl;
+      va[q] = A[size_t(min(i, S - 1)) * K + pr];
+      if (i >= S) va[q] = {R(0), R(0)};
+    }
+  };
+  load(0);
+  int buf = 0;
+  for (int i0 = 0; i0 < iend; i0 += BT_KI, buf ^= 1) {
+    cpx<R> b[BT_KI / 4];
+#pragma unroll
+    for (int q = 0; q < BT_KI / 4; ++q) b[q] = va[q];
+#pragma unroll
+    for (int e = 0; e < E; ++e) sm[buf][(tid + 256 * e) % BT_J][(tid + 256 * e) / BT_J] = vm[e];
+    __syncthreads();  // also: every wave is past the products of the other buffer, written next
+    load(i0 + BT_KI);  // (past the last state: zeros)
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+      // (wave-uniform) Mt is zero there, or no such states
+      if (i0 >= j0 + 16 * (h + 1) || j0 + 16 * h >= S) continue;
+#pragma unroll
+      for (int q = 0; q < BT_KI / 4; ++q) {
+        const cpx<double> a = sm[buf][h * 16 + c][4 * q + kl];  // A operand: row j, column i
+        const double bx = double(b[q].x), by = double(b[q].y);  // B operand: row i, column p
+        dr[h] = M::op(a.x, bx, dr[h]);
+        di[h] = M::op(a.x, by, di[h]);
+        dr[h] = M::op(-a.y, by, dr[h]);
+        di[h] = M::op(a.y, bx, di[h]);
       }
-      sx[il][pl] = v;
     }
-    __syncthreads();
-#pragma unroll
-    for (int ks = 0; ks < BT_KI; ks += 4) {
-      const cpx<double> a = sm[w * 16 + c][ks + kl];  // A operand: row j, column i
-#pragma unroll
-      for (int h = 0; h < 4; ++h) {
-        const cpx<double> b = sx[ks + kl][h * 16 + c];  // B operand: row i, column p
-        dr[h] = M::op(a.x, b.x, dr[h]);
-        dr[h] = M::op(-a.y, b.y, dr[h]);
-        di[h] = M::op(a.x, b.y, di[h]);
-        di[h] = M::op(a.y, b.x, di[h]);
-      }
-    }
-    __syncthreads();
   }
+  if (pp >= K) return;
 #pragma unroll
   for (int h = 0; h < 4; ++h) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int j = j0 + w * 16 + M::row(r, kl);
-      const size_t pp = p0 + h * 16 + c;
-      if (j < S && pp < K) D[size_t(j) * K + pp] = {R(dr[h][r]), R(di[h][r])};
+      const int j = j0 + h * 16 + M::row(r, kl);
+      if (j < S) D[size_t(j) * K + pp] = {R(dr[h][r]), R(di[h][r])};
     }
   }
 }
@@ -2710,8 +2753,8 @@ hipError_t launch_proj_scatter(const ProjTables& pt, const void* Cpart, int S, d
 int gram_chunks(int S, size_t K) {
   const int T = (S + GRAM_T - 1) / GRAM_T;
   const size_t pairs = size_t(T) * (T + 1) / 2;
-  size_t nc = (2048 + pairs - 1) / pairs;                              // enough workgroups
-  nc = std::min<size_t>(nc, 256);
+  size_t nc = std::max<size_t>(1, 1024 / pairs);                       // the four per CU that run at once
+  nc = std::min<size_t>(nc, 512);
   nc = std::min<size_t>(nc, std::max<size_t>(1, (size_t(64) << 20) / (size_t(S) * S * 16)));  // partials <= 64 MiB
   nc = std::min<size_t>(nc, std::max<size_t>(1, K / (4 * GRAM_KB)));   // chunks of >= 64 values
   return int(std::max<size_t>(nc, 1));
@@ -2727,11 +2770,11 @@ hipError_t launch_gram(const void* A, int S, size_t K, double scale, void* part,
   size_t kchunk = (K + nchunks - 1) / nchunks;
   kchunk = (kchunk + GRAM_KB - 1) / GRAM_KB * GRAM_KB;
   const unsigned used = unsigned((K + kchunk - 1) / kchunk);
-  nct_launch((k_gram_partial<R>), dim3(pairs, used), dim3(256), 0, st, reinterpret_cast<const cpx<R>*>(A), S, K,
+  nct_launch((k_gram_partial<R>), dim3(pairs * used), dim3(256), 0, st, reinterpret_cast<const cpx<R>*>(A), S, K,
              kchunk, reinterpret_cast<cpx<double>*>(part));
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  nct_launch(k_gram_reduce, dim3(nblocks(size_t(S) * S, 256)), dim3(256), 0, st,
+  nct_launch(k_gram_reduce, dim3(nblocks(size_t(S) * S, GRAM_RED)), dim3(256), 0, st,
              reinterpret_cast<const cpx<double>*>(part), S, int(used), scale, reinterpret_cast<cpx<double>*>(out));
   return hipGetLastError();
 }
@@ -2739,7 +2782,7 @@ hipError_t launch_gram(const void* A, int S, size_t K, double scale, void* part,
 template <typename R>
 hipError_t launch_basis_transform(const void* A, const void* Mt, int S, size_t K, void* D, hipStream_t st) {
   if (S <= 0) return hipErrorInvalidValue;
-  const dim3 grid(unsigned((K + BT_P - 1) / BT_P), unsigned((S + BT_J - 1) / BT_J));
+  const dim3 grid(unsigned((K + BT_P - 1) / BT_P) * unsigned((S + BT_J - 1) / BT_J));
   nct_launch((k_basis_transform<R>), grid, dim3(256), 0, st, reinterpret_cast<const cpx<R>*>(A),
              reinterpret_cast<const cpx<double>*>(Mt), S, K, reinterpret_cast<cpx<R>*>(D));
   return hipGetLastError();

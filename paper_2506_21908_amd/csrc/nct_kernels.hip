@@ -1555,7 +1555,10 @@ struct mfma16<float> {
   }
 };
 
-constexpr int KU = 4;   // k-steps whose operands are loaded together
+// k-steps whose operands are loaded together, with those of the next round under way: a chunk of 64 rows is
+// two rounds in FP32 (its operands take half the registers), four in FP64
+template <typename R>
+constexpr int proj_ku() { return 32 / int(sizeof(R)); }
 
 // Cpart[a][kc][p][i] = sum_{k in chunk} conj(beta[a][k][p]) W[i][k], k = 2 (J - off_a) + s.
 // One wave: PP/16 output tiles of 16 projectors x 16 states; A/B operands as
@@ -1566,7 +1569,7 @@ template <typename R, int PP, bool KQ>
 __global__ __launch_bounds__(64, 3) void k_proj_contract(ProjTables pt, const cpx<R>* __restrict__ W,
                                                       int S, cpx<double>* __restrict__ Cpart, PhaseTab ph) {
   using M = mfma16<R>;
-  constexpr int NMT = PP / 16;
+  constexpr int NMT = PP / 16, KU = proj_ku<R>();
   const int a = blockIdx.x, nt = blockIdx.y, kc = blockIdx.z;
   const int off = pt.row_off[a];
   const int K = 2 * (pt.row_off[a + 1] - off);
@@ -1644,21 +1647,17 @@ __device__ __forceinline__ cpx<double> proj_sum(const ProjTables& pt, const cpx<
   const size_t stride = size_t(pt.PP) * S;
   const cpx<double>* src = Cpart + (size_t(a) * pt.max_kchunks * pt.PP + p) * S + i;
   double sr = 0, si = 0;
-  int kc = 0;
-  for (; kc + 8 <= nch_a; kc += 8) {
-    cpx<double> v[8];
+  constexpr int U = 16;  // reads in flight: the sum is short, and each wait for memory counts
+  for (int kc = 0; kc < nch_a; kc += U) {
+    cpx<double> v[U];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = src[size_t(kc + u) * stride];
+    for (int u = 0; u < U; ++u) v[u] = src[size_t(min(kc + u, nch_a - 1)) * stride];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      sr += v[u].x;
-      si += v[u].y;
-    }
-  }
-  for (; kc < nch_a; ++kc) {
-    const cpx<double> v = src[size_t(kc) * stride];
-    sr += v.x;
-    si += v.y;
+    for (int u = 0; u < U; ++u)
+      if (kc + u < nch_a) {
+        sr += v[u].x;
+        si += v[u].y;
+      }
   }
   return {sr * dV, si * dV};
 }
@@ -1678,13 +1677,15 @@ static __global__ __launch_bounds__(256) void k_proj_reduce(ProjTables pt, const
 // The projector values of the next row tile are loaded ahead (of the first one before the sums), and as in
 // the contraction the register bound keeps the products out of accumulation registers: contraction and
 // scatter together 17.2 against 17.8 us at 32^3 x 16 FP64, H application 32 x 16 x 24 x 39 with its density
-// and fields 87 against 92 us.
-constexpr int PS_NT = 256;
+// and fields 87 against 92 us.  One coefficient per thread and sixteen reads of partials in flight, not
+// two of each and eight with the last ones singly: 8.6 -> 7.7 us at 16^3 x 8 mixed with two atoms.
+template <int PP>
+constexpr int ps_nt() { return 16 * PP; }  // one coefficient per thread
 template <typename R, int PP, bool KQ>
-__global__ __launch_bounds__(PS_NT, 4) void k_proj_scatter(ProjTables pt, const cpx<double>* __restrict__ Cpart,
+__global__ __launch_bounds__(ps_nt<PP>(), 4) void k_proj_scatter(ProjTables pt, const cpx<double>* __restrict__ Cpart,
                                                         int S, double dV, cpx<R>* __restrict__ Y, PhaseTab ph) {
   using M = mfma16<R>;
-  constexpr int KS = PP / 4;
+  constexpr int KS = PP / 4, NT = ps_nt<PP>();
   __shared__ cpx<R> ecs[PP][16];
   const int a = blockIdx.x, nt = blockIdx.y;
   const int off = pt.row_off[a];
@@ -1702,11 +1703,10 @@ __global__ __launch_bounds__(PS_NT, 4) void k_proj_scatter(ProjTables pt, const 
       xn[u] = row < K2 ? bv : cpx<R>{R(0), R(0)};
     }
   };
-  const int rt0 = blockIdx.z * (PS_NT / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int rt0 = blockIdx.z * (NT / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   load(rt0);
-#pragma unroll
-  for (int e = threadIdx.x; e < PP * 16; e += PS_NT) {
-    const int p = e >> 4, i = nt * 16 + (e & 15);
+  {
+    const int e = threadIdx.x, p = e >> 4, i = nt * 16 + (e & 15);
     cpx<R> v = {R(0), R(0)};
     if (i < S) {
       const cpx<double> c = proj_sum(pt, Cpart, S, dV, a, p, i);
@@ -1722,11 +1722,11 @@ __global__ __launch_bounds__(PS_NT, 4) void k_proj_scatter(ProjTables pt, const 
   cpx<R> ec[KS];
 #pragma unroll
   for (int u = 0; u < KS; ++u) ec[u] = ecs[4 * u + kl][col];
-  for (int rt = rt0; rt * 16 < K2; rt += gridDim.z * (PS_NT / 64)) {
+  for (int rt = rt0; rt * 16 < K2; rt += gridDim.z * (NT / 64)) {
     cpx<R> xb[KS];
 #pragma unroll
     for (int u = 0; u < KS; ++u) xb[u] = xn[u];
-    load(rt + gridDim.z * (PS_NT / 64));  // (past the last tile: its last row, dropped)
+    load(rt + gridDim.z * (NT / 64));  // (past the last tile: its last row, dropped)
     typename M::acc yr = M::zero(), yi = M::zero();
 #pragma unroll
     for (int u = 0; u < KS; ++u) {
@@ -2731,10 +2731,10 @@ static hipError_t launch_scatter_pp(const ProjTables& pt, const void* Cpart, int
                                     const PhaseTab& ph, hipStream_t st) {
   // shares of an atom's row tiles: one tile per wave where there are few (atom, states) pairs, down to
   // all tiles in one workgroup from 512 pairs on, where the repeated sums would cost more than they win
-  const int waves = PS_NT / 64, ntile = (S + 15) / 16;
+  const int waves = ps_nt<PP>() / 64, ntile = (S + 15) / 16;
   const int shares = std::max(1, std::min((pt.max_rowtiles + waves - 1) / waves, 512 / (pt.natoms * ntile)));
   const dim3 grid(pt.natoms, unsigned(ntile), unsigned(shares));
-  nct_launch((k_proj_scatter<R, PP, KQ>), grid, dim3(PS_NT), 0, st, pt, reinterpret_cast<const cpx<double>*>(Cpart), S,
+  nct_launch((k_proj_scatter<R, PP, KQ>), grid, dim3(ps_nt<PP>()), 0, st, pt, reinterpret_cast<const cpx<double>*>(Cpart), S,
              dV, reinterpret_cast<cpx<R>*>(Y), ph);
   return hipGetLastError();
 }

@@ -1578,18 +1578,21 @@ void free_all(nct_system* s) {
 
 
 // Cache policy of the state-sized passes, from the bytes of one state set |psi|.  Measured on
-// MI355X (256 MB Infinity Cache): up to ~64 MiB the buffers stay cache-resident between passes
-// and plain accesses are fastest; from there streaming (non-temporal) stores win; from ~192 MiB
-// streaming loads win as well.
+// MI355X (256 MB Infinity Cache): up to some size the buffers stay cache-resident between passes and
+// plain accesses are fastest; from there streaming (non-temporal) stores win, then streaming loads as
+// well.  FP32-mixed (transformed form, 4-5 buffers per stage): stores from 64 MiB, loads from 192 MiB.
+// FP64 (real-space form, 3 buffers) goes from plain straight to both.  Per step, plain / stores / both:
+// 32^3 x 64 (67 MB) 0.998 / 1.080 / 1.129 ms, 48^3 x 32 (113 MB) 1.606 / 1.679 / 1.711, 48^3 x 64 (226
+// MB) 3.278 / 3.153 / 3.122, 64^3 x 128 (1.1 GB) 14.16 / 13.03 / 12.39.
 #ifndef NCT_STREAM_STORE_MIN_BYTES
 #define NCT_STREAM_STORE_MIN_BYTES (64ull << 20)
 #endif
 #ifndef NCT_STREAM_LOAD_MIN_BYTES
 #define NCT_STREAM_LOAD_MIN_BYTES (192ull << 20)
 #endif
-static int stream_cache_mode(size_t psi_bytes) {
+static int stream_cache_mode(size_t psi_bytes, bool fp64) {
   if (psi_bytes >= NCT_STREAM_LOAD_MIN_BYTES) return 2;
-  if (psi_bytes >= NCT_STREAM_STORE_MIN_BYTES) return 1;
+  if (!fp64 && psi_bytes >= NCT_STREAM_STORE_MIN_BYTES) return 1;
   return 0;
 }
 
@@ -1646,7 +1649,7 @@ nct_status create_impl(const nct_params* p, nct_system** out) {
   s->fp64 = p->precision == NCT_FP64;
   s->roots = taylor_roots(p->taylor_order);
   s->cbytes = s->fp64 ? 16 : 8;
-  s->cache_mode = stream_cache_mode(size_t(2) * s->S * s->N * s->cbytes);
+  s->cache_mode = stream_cache_mode(size_t(2) * s->S * s->N * s->cbytes, s->fp64);
   s->st = static_cast<hipStream_t>(p->stream);
   s->one_stream = size_t(2) * s->S * s->N * s->cbytes <= one_stream_max_bytes(s->fp64);
   s->occ_h.assign(p->nstates, 1.0);

@@ -2366,7 +2366,9 @@ hipError_t launch_plane_yz(const int n[3], int S, const StageArgs<R>& a, const K
 #define X(A, B)                          \
   if (n[1] == A && n[2] == B) {          \
     if (a.cache_mode >= 2) Y(A, B, 2);   \
-    if (a.cache_mode == 1) Y(A, B, 1);   \
+    if constexpr (!D) {                  \
+      if (a.cache_mode == 1) Y(A, B, 1); \
+    }                                    \
     Y(A, B, 0);                          \
   }
   NCT_PLANE_PAIRS(X)
@@ -2397,7 +2399,9 @@ template <typename R, int NX, int PAIRS>
 static hipError_t launch_xv_p(const int n[3], int S, const StageArgs<R>& a, void* dst, const void* twx,
                               const KinTables& kt, hipStream_t st) {
   if (a.cache_mode >= 2) return launch_xv_m<R, NX, PAIRS, 2>(n, S, a, dst, twx, kt, st);
-  if (a.cache_mode == 1) return launch_xv_m<R, NX, PAIRS, 1>(n, S, a, dst, twx, kt, st);
+  if constexpr (sizeof(R) == 4) {  // FP64 has no streaming stores with plain loads
+    if (a.cache_mode == 1) return launch_xv_m<R, NX, PAIRS, 1>(n, S, a, dst, twx, kt, st);
+  }
   return launch_xv_m<R, NX, PAIRS, 0>(n, S, a, dst, twx, kt, st);
 }
 template <typename R>

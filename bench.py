@@ -69,7 +69,7 @@ def say(msg):
 
 
 def kernel_hash() -> str:
-    """Hash of the plane-pass source (its streaming helpers, both plane-stage kernels and the FFT
+    """Hash of the plane-pass source (its streaming helpers, the stage kernels of both forms and the FFT
     header they use): PMC traffic taken for it stays valid while this text is unchanged."""
     src = open(KERNEL_SOURCE).read()
     a, b = src.find(PLANE_BEGIN), src.find(PLANE_END)
@@ -309,7 +309,7 @@ def main():
     def roofline(tim, key, prec):
         ms, cnt, by, _ = tim["plane_stage"]
         achieved = (by / cnt) / (ms / cnt * 1e-3) / 1e9 if cnt else 0.0
-        return {"kernel": "k_plane_stage (fused plane pass)", "bound": "hbm",
+        return {"kernel": "k_plane_yz / k_plane_stage (plane pass)", "bound": "hbm",
                 "timed_launches": cnt, "timing_stride": TIMING_STRIDE,
                 "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": achieved / HBM_PEAK_GBS,

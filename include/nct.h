@@ -324,9 +324,9 @@ nct_status nct_backward_step(nct_system *sys, int tape_index, const void *psi_n_
 
 /* Kernel classes for the timing facility below. */
 enum {
-  NCT_K_PLANE_STAGE = 0,  /* fused plane pass of one H application / Taylor stage */
-  NCT_K_XPASS = 1,        /* column pass along x (kinetic multiplier) */
-  NCT_K_PLANE_FWD = 2,    /* forward yz transform of the input states */
+  NCT_K_PLANE_STAGE = 0,  /* plane pass of one H application / Taylor stage */
+  NCT_K_XPASS = 1,        /* column pass along x (kinetic multiplier, local potential in real space) */
+  NCT_K_PLANE_FWD = 2,    /* forward yz transform (or sphere rows) of the input states */
   NCT_K_DENSITY = 3,      /* spin density matrix reduction */
   NCT_K_FIELDS = 4,       /* Poisson solve, exchange, field totals */
   NCT_K_PROJ = 5,         /* projector contraction + scatter (MFMA) */

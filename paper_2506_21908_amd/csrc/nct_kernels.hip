@@ -1555,8 +1555,9 @@ struct mfma16<float> {
   }
 };
 
-// k-steps whose operands are loaded together, with those of the next round under way: a chunk of 64 rows is
-// two rounds in FP32 (its operands take half the registers), four in FP64
+// k-steps whose operands are loaded together: a chunk of 64 rows is two rounds in FP32, the second loaded
+// while the first is multiplied, and four in FP64, whose operands take twice the registers: loaded ahead
+// there they leave three waves per SIMD instead of four (64^3 x 256 with 16 atoms 95 against 78 us)
 template <typename R>
 constexpr int proj_ku() { return 32 / int(sizeof(R)); }
 
@@ -1570,6 +1571,7 @@ __global__ __launch_bounds__(64, 3) void k_proj_contract(ProjTables pt, const cp
                                                       int S, cpx<double>* __restrict__ Cpart, PhaseTab ph) {
   using M = mfma16<R>;
   constexpr int NMT = PP / 16, KU = proj_ku<R>();
+  constexpr bool AHEAD = sizeof(R) == 4;
   const int a = blockIdx.x, nt = blockIdx.y, kc = blockIdx.z;
   const int off = pt.row_off[a];
   const int K = 2 * (pt.row_off[a + 1] - off);
@@ -1606,8 +1608,9 @@ __global__ __launch_bounds__(64, 3) void k_proj_contract(ProjTables pt, const cp
       }
     }
   };
-  load(kc * KC);
+  if (AHEAD) load(kc * KC);
   for (int k0 = kc * KC; k0 < kend; k0 += 4 * KU) {
+    if (!AHEAD) load(k0);
     cpx<R> cw[KU], cb[KU][NMT];
 #pragma unroll
     for (int u = 0; u < KU; ++u) {
@@ -1615,7 +1618,7 @@ __global__ __launch_bounds__(64, 3) void k_proj_contract(ProjTables pt, const cp
 #pragma unroll
       for (int mt = 0; mt < NMT; ++mt) cb[u][mt] = bb[u][mt];
     }
-    if (k0 + 4 * KU < kend) load(k0 + 4 * KU);  // the next operands, while these are multiplied
+    if (AHEAD && k0 + 4 * KU < kend) load(k0 + 4 * KU);  // the next operands, while these are multiplied
 #pragma unroll
     for (int u = 0; u < KU; ++u) {
 #pragma unroll
@@ -1639,34 +1642,42 @@ __global__ __launch_bounds__(64, 3) void k_proj_contract(ProjTables pt, const cp
   }
 }
 
-// dV sum_kc Cpart[a][kc][p][i] in chunk order
-__device__ __forceinline__ cpx<double> proj_sum(const ProjTables& pt, const cpx<double>* __restrict__ Cpart, int S,
-                                                double dV, int a, int p, int i) {
+// dV sum_kc Cpart[a][kc][p + 16 c][i] in chunk order, c < NC, sixteen reads in flight: the sums are short,
+// and each wait for memory counts
+template <int NC>
+__device__ __forceinline__ void proj_sums(const ProjTables& pt, const cpx<double>* __restrict__ Cpart, int S, double dV,
+                                          int a, int p, int i, cpx<double> (&out)[NC]) {
+  constexpr int U = 16 / NC;
   const int K = 2 * (pt.row_off[a + 1] - pt.row_off[a]);
   const int nch_a = (K + pt.kc - 1) / pt.kc;
   const size_t stride = size_t(pt.PP) * S;
   const cpx<double>* src = Cpart + (size_t(a) * pt.max_kchunks * pt.PP + p) * S + i;
-  double sr = 0, si = 0;
-  constexpr int U = 16;  // reads in flight: the sum is short, and each wait for memory counts
-  for (int kc = 0; kc < nch_a; kc += U) {
-    cpx<double> v[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) v[u] = src[size_t(min(kc + u, nch_a - 1)) * stride];
+  for (int c = 0; c < NC; ++c) out[c] = {0.0, 0.0};
+  for (int kc = 0; kc < nch_a; kc += U) {
+    cpx<double> v[U][NC];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) v[u][c] = src[size_t(min(kc + u, nch_a - 1)) * stride + size_t(16 * c) * S];
 #pragma unroll
     for (int u = 0; u < U; ++u)
       if (kc + u < nch_a) {
-        sr += v[u].x;
-        si += v[u].y;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) out[c] = out[c] + v[u][c];
       }
   }
-  return {sr * dV, si * dV};
+#pragma unroll
+  for (int c = 0; c < NC; ++c) out[c] = {out[c].x * dV, out[c].y * dV};
 }
 // C[a][p][i] of the observables
 static __global__ __launch_bounds__(256) void k_proj_reduce(ProjTables pt, const cpx<double>* __restrict__ Cpart,
                                                             int S, double dV, cpx<double>* __restrict__ C) {
   const size_t idx = size_t(blockIdx.x) * 256 + threadIdx.x;
   if (idx >= size_t(pt.natoms) * pt.PP * S) return;
-  C[idx] = proj_sum(pt, Cpart, S, dV, int(idx / (size_t(S) * pt.PP)), int((idx / S) % pt.PP), int(idx % S));
+  cpx<double> c[1];
+  proj_sums<1>(pt, Cpart, S, dV, int(idx / (size_t(S) * pt.PP)), int((idx / S) % pt.PP), int(idx % S), c);
+  C[idx] = c[0];
 }
 
 // Y[i][s][J] = sum_p beta[J][s][p] E[a][p] C[a][p][i]; rows k = 2 (J - off_a) + s (KQ: times exp(-i k.d)).
@@ -1677,15 +1688,18 @@ static __global__ __launch_bounds__(256) void k_proj_reduce(ProjTables pt, const
 // The projector values of the next row tile are loaded ahead (of the first one before the sums), and as in
 // the contraction the register bound keeps the products out of accumulation registers: contraction and
 // scatter together 17.2 against 17.8 us at 32^3 x 16 FP64, H application 32 x 16 x 24 x 39 with its density
-// and fields 87 against 92 us.  One coefficient per thread and sixteen reads of partials in flight, not
-// two of each and eight with the last ones singly: 8.6 -> 7.7 us at 16^3 x 8 mixed with two atoms.
-template <int PP>
-constexpr int ps_nt() { return 16 * PP; }  // one coefficient per thread
+// and fields 87 against 92 us.  Sixteen reads of partials in flight, not
+// eight with the last ones singly: 8.6 -> 7.7 us at 16^3 x 8 mixed with two atoms.
+// FP64 takes one coefficient per thread (48^3 x 64 with four atoms, two steps, 6.39 against 6.58 ms with
+// 256 threads); FP32 256 threads: a workgroup of 512 waits for room beside the transformed form's column
+// pass (64^3 x 64 mixed with eight atoms 76 against 33 us).
+template <typename R, int PP>
+constexpr int ps_nt() { return sizeof(R) == 8 ? 16 * PP : 256; }
 template <typename R, int PP, bool KQ>
-__global__ __launch_bounds__(ps_nt<PP>(), 4) void k_proj_scatter(ProjTables pt, const cpx<double>* __restrict__ Cpart,
+__global__ __launch_bounds__((ps_nt<R, PP>()), 4) void k_proj_scatter(ProjTables pt, const cpx<double>* __restrict__ Cpart,
                                                         int S, double dV, cpx<R>* __restrict__ Y, PhaseTab ph) {
   using M = mfma16<R>;
-  constexpr int KS = PP / 4, NT = ps_nt<PP>();
+  constexpr int KS = PP / 4, NT = ps_nt<R, PP>();
   __shared__ cpx<R> ecs[PP][16];
   const int a = blockIdx.x, nt = blockIdx.y;
   const int off = pt.row_off[a];
@@ -1706,14 +1720,15 @@ __global__ __launch_bounds__(ps_nt<PP>(), 4) void k_proj_scatter(ProjTables pt, 
   const int rt0 = blockIdx.z * (NT / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   load(rt0);
   {
-    const int e = threadIdx.x, p = e >> 4, i = nt * 16 + (e & 15);
-    cpx<R> v = {R(0), R(0)};
-    if (i < S) {
-      const cpx<double> c = proj_sum(pt, Cpart, S, dV, a, p, i);
-      const double en = pt.energy[size_t(a) * PP + p];
-      v = {R(en * c.x), R(en * c.y)};
+    constexpr int NC = 16 * PP / NT;  // coefficients per thread
+    const int p = threadIdx.x >> 4, c16 = threadIdx.x & 15, i = nt * 16 + c16;
+    cpx<double> c[NC];
+    proj_sums<NC>(pt, Cpart, S, dV, a, p, min(i, S - 1), c);
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+      const double en = pt.energy[size_t(a) * PP + p + 16 * k];
+      ecs[p + 16 * k][c16] = i < S ? cpx<R>{R(en * c[k].x), R(en * c[k].y)} : cpx<R>{R(0), R(0)};
     }
-    ecs[p][e & 15] = v;
   }
   __syncthreads();
   const int i = nt * 16 + col;
@@ -2185,21 +2200,22 @@ static __global__ __launch_bounds__(256) void k_gram_reduce(const cpx<double>* _
 // every wave the same, since each holds all four tiles; the waves read A's columns straight
 // into the operand layout (four rows of 256 bytes per load) and share Mt through LDS, and both are loaded
 // one block of i ahead (96 states of 48^3 FP64: 226 against
-// 426 us with 16 states per wave and every i of the workgroup's block; three waves per SIMD for the reason
-// given at the overlap).
+// 426 us with 16 states per wave and every i of the workgroup's block; blocks of 16 i, which leave three
+// waves per SIMD instead of four, and all states of a column block at once, whose four shares take
+// unequal time, 7.08 against 6.20 ms with the overlap for 256 states of 64^3, which started at 7.54).
 constexpr int BT_J = 64;
 constexpr int BT_P = 64;
-constexpr int BT_KI = 16;
+constexpr int BT_KI = 8;
 template <typename R>
-__global__ __launch_bounds__(256, 3) void k_basis_transform(const cpx<R>* __restrict__ A,
+__global__ __launch_bounds__(256, 4) void k_basis_transform(const cpx<R>* __restrict__ A,
                                                          const cpx<double>* __restrict__ Mt, int S,
                                                          size_t K, cpx<R>* __restrict__ D) {
   using M = mfma16<double>;
   constexpr int E = BT_KI * BT_J / 256;
   __shared__ cpx<double> sm[2][BT_J][BT_KI + 1];   // [j][i]
-  const int jblocks = (S + BT_J - 1) / BT_J, L = xcd_logical(blockIdx.x, gridDim.x);
-  const int pb = L / jblocks;
-  const int j0 = (L - pb * jblocks) * BT_J;
+  const int jblocks = (S + BT_J - 1) / BT_J, pblocks = int((K + BT_P - 1) / BT_P);
+  const int jb = blockIdx.x / pblocks, pb = blockIdx.x - jb * pblocks;
+  const int j0 = (jblocks - 1 - jb) * BT_J;  // the longest first
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
   const int c = lane & 15, kl = lane >> 4;
   const size_t pp = size_t(pb) * BT_P + w * 16 + c;
@@ -2734,11 +2750,13 @@ template <typename R, int PP, bool KQ>
 static hipError_t launch_scatter_pp(const ProjTables& pt, const void* Cpart, int S, double dV, void* Y,
                                     const PhaseTab& ph, hipStream_t st) {
   // shares of an atom's row tiles: one tile per wave where there are few (atom, states) pairs, down to
-  // all tiles in one workgroup from 512 pairs on, where the repeated sums would cost more than they win
-  const int waves = ps_nt<PP>() / 64, ntile = (S + 15) / 16;
-  const int shares = std::max(1, std::min((pt.max_rowtiles + waves - 1) / waves, 512 / (pt.natoms * ntile)));
+  // all tiles in one workgroup from 128 pairs on: each share repeats the sums, and their reads slow the
+  // column pass beside them (48^3 x 64 mixed with four atoms 1.98 ms per step; 2.01 with up to 512
+  // workgroups, 2.02 with 64)
+  const int waves = ps_nt<R, PP>() / 64, ntile = (S + 15) / 16;
+  const int shares = std::max(1, std::min((pt.max_rowtiles + waves - 1) / waves, 128 / (pt.natoms * ntile)));
   const dim3 grid(pt.natoms, unsigned(ntile), unsigned(shares));
-  nct_launch((k_proj_scatter<R, PP, KQ>), grid, dim3(ps_nt<PP>()), 0, st, pt, reinterpret_cast<const cpx<double>*>(Cpart), S,
+  nct_launch((k_proj_scatter<R, PP, KQ>), grid, dim3(unsigned(ps_nt<R, PP>())), 0, st, pt, reinterpret_cast<const cpx<double>*>(Cpart), S,
              dV, reinterpret_cast<cpx<R>*>(Y), ph);
   return hipGetLastError();
 }

@@ -556,14 +556,17 @@ std::vector<std::complex<double>> taylor_roots(int K) {
   for (const C& z : up) out.push_back(std::conj(std::complex<double>(z)));
   return out;
 }
-// The product form is used where |z| E_max (E_max: the largest kinetic energy of the grid) is at least
-// this and K is at most kProductMaxOrder.  Its rounding against long double is no larger than the
-// Horner form's there: relative errors of one exponential at K = 4, h = 0.42 bohr, |z| = 0.025 (|z|
-// E_max = 2.1) 1.0e-16 against 1.6e-16, at 1.5 0.96e-16 against 1.09e-16, at 0.95 0.93e-16 against
-// 0.78e-16 (every stage rounds w once, the Horner form adds small terms to an exact x), K = 12 1.4e-16
-// against 1.5e-16, K = 16 1.6e-16 against 1.5e-16.
-constexpr double kProductMinZE = 1.25;
+// The product form is used from this |z| E_max on (E_max: the largest kinetic energy of the grid), up to
+// order kProductMaxOrder.  Each of its K stages rounds w once where the Horner form adds ever smaller terms
+// to an exact x, so its error hardly depends on |z| E_max while Horner's grows with it, and the two cross
+// at a |z| E_max that grows with K.  Relative 2-norm errors of one FP64 step against long double at 16^3,
+// smooth states (on white noise the product form is the better one from 1.9 on), product against Horner
+// in units of 1e-16: K = 4 at 1.3 2.2 / 1.6, at 2.1 2.06 / 2.06, at 2.5 2.1 / 2.5; K = 6 at 2.4 2.41 / 2.38;
+// K = 8 at 2.4 2.7 / 2.4, at 2.7 2.66 / 2.71; K = 12 at 1.3 3.5 / 1.6, at 2.8 3.1 / 2.8, at 3.2 3.1 / 3.4.
+// FP32 steps cross earlier (48^3 in units of 1e-7: K = 4 at 1.3 1.16 / 0.86, at 2.1 1.16 / 1.20; K = 12 at
+// 2.1 1.8 / 1.2, at 4.2 1.6 / 3.3).
 constexpr int kProductMaxOrder = 12;
+constexpr double product_min_ze(int K) { return 2.05 + 0.16 * (K > 4 ? K - 4 : 0); }
 
 // ---------------------------------------------------------------- engine
 template <typename R>
@@ -893,7 +896,7 @@ struct Engine {
       const double g = kPi * s->n[d] / s->prm.cell[d];
       emax += 0.5 * g * g;
     }
-    return z * emax >= kProductMinZE;
+    return z * emax >= product_min_ze(s->prm.taylor_order);
   }
   std::complex<double> product_coeff(int k, double a) const {
     const std::complex<double> z = imag_tau > 0.0 ? std::complex<double>(-imag_tau, 0.0) : std::complex<double>(0.0, -a);

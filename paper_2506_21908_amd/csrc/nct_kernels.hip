@@ -823,7 +823,11 @@ __global__ __launch_bounds__(256) void k_gather_rows(const cpx<R>* __restrict__ 
 // after the swap, so the waves' phases interleave freely.  Each XCD takes one eighth of the columns for
 // every state (where the column blocks divide by eight): its eighth of the fields stays in its L2, and
 // consecutive workgroups still read consecutive columns of one state.
-// XS: the Taylor base x is another array than w (else alpha w is used).
+// XS: the Taylor base x is another array than w (else alpha w is used).  It is loaded beside the last stage and
+// added last: the sum of the small terms rounds at their own size and x is rounded once here, not twice
+// (one FP64 step of smooth states at 16^3, |z| E_max = 0.95, against long double 1.14e-16, 1.35e-16 with x added
+// first; Horner steps take as long, 64^3 x 128 FP64 13.49 against 13.47 ms, or less at 96 points, where x waits for
+// no field, 96^3 x 32 FP64 12.9 against 13.3, 96^3 x 64 FP32 14.7 against 16.1).
 // A wave's columns: one 128-byte line per x-plane (FP32 with 64-byte halves 667 against 425 us per pass
 // at 64^3 x 256)
 template <typename R>
@@ -910,12 +914,10 @@ __global__ __launch_bounds__(128 * PAIRS, xv_mw(NX)) void k_xv(StageArgs<R> a, c
   for (int u = 0; u < IT; ++u) {
     const int it = min(lane + 64 * u, ITEMS - 1);
     const int x0 = it / CW, col = q0 + it % CW;
-    const uint32_t l0 = uint32_t(x0 * NYZ + it % CW), oc = l0 * uint32_t(sizeof(C)), of = l0 * uint32_t(sizeof(R));
     // laser potential, less its x term
     const R lyz = a.lg[3] + a.lg[1] * R(col / NZ) + a.lg[2] * R(col % NZ);
 #pragma unroll
     for (int q = 0; q < RX; ++q) {
-      const size_t eu = size_t(q * MX) * NYZ;
       const int p = u * RX + q;
       R fq[4];
 #pragma unroll
@@ -927,10 +929,8 @@ __global__ __launch_bounds__(128 * PAIRS, xv_mw(NX)) void k_xv(StageArgs<R> a, c
       // up: (v+bz) up + (bx - i by) dn ; dn: (v-bz) dn + (bx + i by) up
       const R d = s ? vl - bz : vl + bz, e = s ? -by : by;
       const C h = {d * ws.x + bx * wo.x + e * wo.y, d * ws.y + bx * wo.y - e * wo.x};
-      C xv = ws;
-      if constexpr (XS) xv = ld_stream<M>(at_bytes(xb + (off + eu), oc));
-      r[u][q].x = a.alpha * xv.x + (a.cre * h.x - a.cim * h.y);
-      r[u][q].y = a.alpha * xv.y + (a.cre * h.y + a.cim * h.x);
+      r[u][q] = {a.cre * h.x - a.cim * h.y, a.cre * h.y + a.cim * h.x};
+      if constexpr (!XS) r[u][q] = {a.alpha * ws.x + r[u][q].x, a.alpha * ws.y + r[u][q].y};
       if (!PRE) {
         pin(r[u][q]);
         sched_fence();
@@ -968,11 +968,17 @@ __global__ __launch_bounds__(128 * PAIRS, xv_mw(NX)) void k_xv(StageArgs<R> a, c
 #pragma unroll
         for (int q = 0; q < RX; ++q) v[u][q] = tile[it + q * MX * CW];
       }
+      C xv[RX];
+      if constexpr (XS) {
+#pragma unroll
+        for (int q = 0; q < RX; ++q) xv[q] = ld_stream<M>(at_bytes(xb + (off + size_t(q * MX) * NYZ), o));
+      }
       stage_butterfly<R, FX, 0, false>(v[u], tw, it / CW);
 #pragma unroll
       for (int q = 0; q < RX; ++q) {
         const C h = v[u][q];
-        const C t = {r[u][q].x + (a.cre * h.x - a.cim * h.y), r[u][q].y + (a.cre * h.y + a.cim * h.x)};
+        C t = {r[u][q].x + (a.cre * h.x - a.cim * h.y), r[u][q].y + (a.cre * h.y + a.cim * h.x)};
+        if constexpr (XS) t = {a.alpha * xv[q].x + t.x, a.alpha * xv[q].y + t.y};
         st_stream<M>(at_bytes(out + size_t(q * MX) * NYZ, o), t);
       }
     }

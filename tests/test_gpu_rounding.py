@@ -104,3 +104,18 @@ def test_step_mixed_rounding_on_smooth_states(gpu, K):
     err = float(np.sqrt((np.abs(got[-C:] - ref) ** 2).sum() / (np.abs(ref) ** 2).sum()))
     print(f"[case]   {err:.2e}", flush=True)
     assert err < 2 * 2.0 ** -24
+
+
+def test_step_fp64_rounds_the_base_last(gpu):
+    """Small |z| E_max: the Taylor base is added once per pass, after the small terms.  Two exponentials of two
+    roundings each make sqrt(4) 0.42 u = 0.84 u, the transforms 0.28 u: 0.89 u in all (1.09 u with the base rounded
+    twice in the column pass).  Bar: one unit roundoff."""
+    torch, nct = gpu
+    n, dt = (16, 16, 16), 2 * 0.5 / EMAX
+    print("[case] rounding FP64, base last", flush=True)
+    psi, F = smooth_inputs(n, 2, 42)
+    ref = frozen_step(psi, F, n, 4, dt, np.longdouble, np.clongdouble)
+    got = gpu_step(torch, nct, psi, F, n, 4, dt, nct.NCT_FP64).astype(np.clongdouble)
+    err = float(np.sqrt((np.abs(got - ref) ** 2).sum() / (np.abs(ref) ** 2).sum()))
+    print(f"[case]   {err:.2e}", flush=True)
+    assert err < 2.0 ** -53

@@ -212,7 +212,8 @@ nct_status nct_ground_state(nct_system *sys, void *psi_dev, int niter, double ta
  *     vector potential A(t) = -int_0^t E dt' (evaluated like B_ext: t_n for H_n, t_n + dt for
  *     H~): kinetic factor 1/2 |G + k + A|^2 and projector phases exp(+/- i (k + A).d), no scalar
  *     potential and no E.D term in E_loc.
- * Errors: NCT_ERR_ARG for any other value. */
+ * The first call with NCT_GAUGE_VELOCITY allocates device memory.
+ * Errors: NCT_ERR_ARG for any other value, NCT_ERR_OOM. */
 enum { NCT_GAUGE_LENGTH = 0, NCT_GAUGE_VELOCITY = 1 };
 nct_status nct_set_laser_gauge(nct_system *sys, int gauge);
 
@@ -223,8 +224,9 @@ nct_status nct_set_laser_gauge(nct_system *sys, int gauge);
  * exp(-i k_i.d) on scatter (d the grid point's displacement from the atom).  The k-point weights
  * enter through params.occ (f_i w_k).  States of one k-point are expected consecutive (the
  * ground-state solver orthonormalises each such run).  NULL returns to Gamma only.
- * Synchronises the stream.
- * Errors: NCT_ERR_ARG for a non-finite component. */
+ * The first call allocates device memory; an error leaves the vectors as they were unless it is
+ * NCT_ERR_HIP.  Synchronises the stream.
+ * Errors: NCT_ERR_ARG for a non-finite component, NCT_ERR_OOM. */
 nct_status nct_set_kpoints(nct_system *sys, const double *kvec);
 
 /* Set the potentials of Eq. (HNC-SDFT) and the external field of the Zeeman term
@@ -272,7 +274,9 @@ nct_status nct_get_fields(nct_system *sys, double t, double *fields_dev);
 /* hpsi = H psi: the spinor Kohn-Sham Hamiltonian of Eqs. (TDSDFT) and (HNC-SDFT) with the
  * pseudopotential of Eqs. (Vps), (Vps-soc): -1/2 nabla^2 + [v + b.sigma] + V_NL, with the current
  * fields, B_ext(t) and v_E(t).  psi and hpsi are distinct device buffers of the psi layout above
- * (caller-owned; hpsi is overwritten).
+ * (caller-owned; hpsi is overwritten).  Allocates nothing and does not synchronise: it may be recorded
+ * into a HIP graph, a system's first application included, and replays with the time, pulses and
+ * gauge it was recorded with, on the fields and Bloch vectors of the moment.
  * Errors: NCT_ERR_ARG (NULL or identical buffers), NCT_ERR_STATE (no fields yet: call
  * nct_density_magnetization with update_fields, or freeze fields with nct_set_potentials). */
 nct_status nct_apply_hamiltonian(nct_system *sys, const void *psi_dev, void *hpsi_dev, double t);

@@ -145,14 +145,17 @@ struct nct_system {
   void* Cpart = nullptr;
   void* C = nullptr;
   double* energy_dev = nullptr;
-  // Bloch phases of the sphere rows (real-space form): distinct vectors, run of each state, table for the vector
-  // potential phase_ka (valid if phase_ok)
-  double* kruns = nullptr;    // [runs][3]
+  // Bloch phases of the sphere rows (real-space form): runs of states that share a vector, run of each state,
+  // and one table row per run.  phases holds those of the Bloch vectors alone: nct_set_kpoints writes it, calls only
+  // read it.  phasesA holds those of the vectors plus A(t): every call in the velocity gauge writes it before its
+  // own first use, so a call recorded into a graph replays with its own A(t) whatever ran in between.  Both are
+  // allocated in the set-up calls and stay where they are.
+  double* kruns = nullptr;    // [S][3], one per run
   int* run_of = nullptr;      // [S]
-  void* phases = nullptr;     // complex [runs][Jtot]
-  int phase_runs = 0, phase_cap = 0;
-  bool phase_ok = false;
-  double phase_ka[3] = {0, 0, 0};
+  int phase_runs = 0;
+  void* phases = nullptr;     // complex [S][Jtot]
+  void* phasesA = nullptr;    // complex [phaseA_rows][Jtot]
+  int phaseA_rows = 0;        // 1, or S once there were Bloch vectors too
 
   // adjoint tape: per step 3K state vectors (Taylor iterates of the three exponentials,
   // psi_n, phi, psi~) and the densities / fields of H_n and H~
@@ -701,27 +704,22 @@ struct Engine {
 
   // The phase table (real-space form) of the current Bloch vectors and vector potential (null without either).
   // Called with ka set, on the main stream, after every earlier use of the table has joined it.
+  bool phaseA_ok = false;  // this call has written s->phasesA, for phaseA_ka
+  double phaseA_ka[3] = {0, 0, 0};
   nct_status phase_table(PhaseTab& ph) {
     ph = PhaseTab{};
     if (!RS || s->natoms == 0 || !kvR()) return NCT_OK;
-    nct_status r;
-    const int runs = s->has_k ? s->phase_runs : 1;
-    if (s->phase_cap < runs) {
-      s->phase_cap = 0;
-      if ((r = dalloc(s, size_t(runs) * s->pt.Jtot * s->cbytes, &s->phases)) != NCT_OK) return r;
-      s->phase_cap = runs;
-      s->phase_ok = false;
-    }
-    if (!s->phase_ok || ka[0] != s->phase_ka[0] || ka[1] != s->phase_ka[1] || ka[2] != s->phase_ka[2]) {
-      if ((r = check(launch_phases<R>(s->has_k ? s->kruns : s->kv_zero64, runs, ka, s->pt, s->phases, s->st), "phases")) !=
-          NCT_OK)
-        return r;
-      for (int d = 0; d < 3; ++d) s->phase_ka[d] = ka[d];
-      s->phase_ok = true;
-    }
-    ph.tab = s->phases;
     ph.run = s->has_k ? s->run_of : nullptr;
-    return NCT_OK;
+    if (!velocity_gauge(s)) {
+      ph.tab = s->phases;
+      return NCT_OK;
+    }
+    ph.tab = s->phasesA;
+    if (phaseA_ok && ka[0] == phaseA_ka[0] && ka[1] == phaseA_ka[1] && ka[2] == phaseA_ka[2]) return NCT_OK;
+    for (int d = 0; d < 3; ++d) phaseA_ka[d] = ka[d];
+    phaseA_ok = true;
+    return check(launch_phases<R>(s->has_k ? s->kruns : s->kv_zero64, s->has_k ? s->phase_runs : 1, ka, s->pt,
+                                  s->phasesA, s->st), "phases");
   }
 
   // NL projections of the sphere rows W -> Y (scatter rows).  Enqueued on the second
@@ -1813,6 +1811,18 @@ static nct_status density_magnetization_static(nct_system* s, const void* psi, d
 }
 
 // ================================================================ C ABI
+// Room for the velocity gauge's phase table (grows at most once, from 1 to S rows; the smaller one stays for graphs
+// recorded with it)
+static nct_status ensure_phasesA(nct_system* s, int rows) {
+  if (s->natoms == 0 || s->phaseA_rows >= rows) return NCT_OK;
+  void* p;
+  const nct_status r = dalloc(s, size_t(rows) * s->pt.Jtot * s->cbytes, &p);
+  if (r != NCT_OK) return r;
+  s->phasesA = p;
+  s->phaseA_rows = rows;
+  return NCT_OK;
+}
+
 extern "C" {
 
 nct_status nct_create_system(const nct_params* params, nct_system** out) {
@@ -1909,6 +1919,10 @@ nct_status nct_set_laser_gauge(nct_system* s, int gauge) {
     HIPCHK(s, hipMemsetAsync(s->kv_zero32, 0, n * sizeof(float), s->st));
     HIPCHK(s, hipStreamSynchronize(s->st));
   }
+  if (gauge == NCT_GAUGE_VELOCITY) {
+    const nct_status r = ensure_phasesA(s, s->has_k ? s->S : 1);
+    if (r != NCT_OK) return r;
+  }
   s->laser_gauge = gauge;
   return NCT_OK;
 }
@@ -1917,59 +1931,69 @@ nct_status nct_set_kpoints(nct_system* s, const double* kvec) {
   if (!s) return NCT_ERR_ARG;
   if (!kvec) {
     s->has_k = false;
-    s->phase_ok = false;  // a velocity gauge now takes the zero vectors
     return NCT_OK;
   }
   const size_t n = size_t(s->S) * 3;
   for (size_t k = 0; k < n; ++k)
     if (!std::isfinite(kvec[k])) return fail(s, NCT_ERR_ARG, "non-finite Bloch vector component %zu", k);
+  // everything is allocated before anything changes
   nct_status r;
+  void* p;
   if (!s->kv64) {
-    void* p;
     if ((r = dalloc(s, n * sizeof(double), &p)) != NCT_OK) return r;
     s->kv64 = static_cast<double*>(p);
+  }
+  if (!s->kv32) {
     if ((r = dalloc(s, n * sizeof(float), &p)) != NCT_OK) return r;
     s->kv32 = static_cast<float*>(p);
   }
-  s->krun.assign(1, 0);
-  for (int i = 1; i < s->S; ++i)
-    if (kvec[3 * i] != kvec[3 * i - 3] || kvec[3 * i + 1] != kvec[3 * i - 2] || kvec[3 * i + 2] != kvec[3 * i - 1])
-      s->krun.push_back(i);
-  s->krun.push_back(s->S);
-  s->krun_split = false;
-  for (size_t a = 0; a + 1 < s->krun.size(); ++a)
-    for (size_t b = a + 1; b + 1 < s->krun.size(); ++b) {
-      const double* ka = kvec + 3 * s->krun[a];
-      const double* kb = kvec + 3 * s->krun[b];
-      if (ka[0] == kb[0] && ka[1] == kb[1] && ka[2] == kb[2]) s->krun_split = true;
-    }
-  std::vector<float> k32(kvec, kvec + n);
-  HIPCHK(s, hipMemcpyAsync(s->kv64, kvec, n * sizeof(double), hipMemcpyHostToDevice, s->st));
-  HIPCHK(s, hipMemcpyAsync(s->kv32, k32.data(), n * sizeof(float), hipMemcpyHostToDevice, s->st));
-  if (s->natoms) {  // distinct vectors of the phase table
-    const int runs = int(s->krun.size()) - 1;
-    std::vector<double> kr(size_t(runs) * 3);
-    std::vector<int> ro(s->S);
-    for (int b = 0; b < runs; ++b) {
-      for (int d = 0; d < 3; ++d) kr[3 * b + d] = kvec[3 * size_t(s->krun[b]) + d];
-      for (int i = s->krun[b]; i < s->krun[b + 1]; ++i) ro[i] = b;
+  if (s->natoms) {
+    if (!s->kruns) {
+      if ((r = dalloc(s, n * sizeof(double), &p)) != NCT_OK) return r;
+      s->kruns = static_cast<double*>(p);
     }
     if (!s->run_of) {
-      void* p;
-      if ((r = dalloc(s, size_t(s->S) * 3 * sizeof(double), &p)) != NCT_OK) return r;
-      s->kruns = static_cast<double*>(p);
       if ((r = dalloc(s, size_t(s->S) * sizeof(int), &p)) != NCT_OK) return r;
       s->run_of = static_cast<int*>(p);
     }
+    if (!s->phases && (r = dalloc(s, size_t(s->S) * s->pt.Jtot * s->cbytes, &s->phases)) != NCT_OK) return r;
+    if (s->laser_gauge == NCT_GAUGE_VELOCITY && (r = ensure_phasesA(s, s->S)) != NCT_OK) return r;
+  }
+  std::vector<int> krun(1, 0);
+  for (int i = 1; i < s->S; ++i)
+    if (kvec[3 * i] != kvec[3 * i - 3] || kvec[3 * i + 1] != kvec[3 * i - 2] || kvec[3 * i + 2] != kvec[3 * i - 1])
+      krun.push_back(i);
+  krun.push_back(s->S);
+  bool split = false;
+  for (size_t a = 0; a + 1 < krun.size(); ++a)
+    for (size_t b = a + 1; b + 1 < krun.size(); ++b) {
+      const double* ka = kvec + 3 * krun[a];
+      const double* kb = kvec + 3 * krun[b];
+      if (ka[0] == kb[0] && ka[1] == kb[1] && ka[2] == kb[2]) split = true;
+    }
+  std::vector<float> k32(kvec, kvec + n);
+  const int runs = int(krun.size()) - 1;
+  std::vector<double> kr(size_t(runs) * 3);
+  std::vector<int> ro(s->S);
+  for (int b = 0; b < runs; ++b) {
+    for (int d = 0; d < 3; ++d) kr[3 * b + d] = kvec[3 * size_t(krun[b]) + d];
+    for (int i = krun[b]; i < krun[b + 1]; ++i) ro[i] = b;
+  }
+  s->has_k = false;  // until the new vectors are in place
+  HIPCHK(s, hipMemcpyAsync(s->kv64, kvec, n * sizeof(double), hipMemcpyHostToDevice, s->st));
+  HIPCHK(s, hipMemcpyAsync(s->kv32, k32.data(), n * sizeof(float), hipMemcpyHostToDevice, s->st));
+  if (s->natoms) {
     HIPCHK(s, hipMemcpyAsync(s->kruns, kr.data(), kr.size() * sizeof(double), hipMemcpyHostToDevice, s->st));
     HIPCHK(s, hipMemcpyAsync(s->run_of, ro.data(), ro.size() * sizeof(int), hipMemcpyHostToDevice, s->st));
-    s->phase_runs = runs;
-    s->phase_ok = false;
-    HIPCHK(s, hipStreamSynchronize(s->st));
+    const double zero[3] = {0, 0, 0};
+    if (s->fp64) HIPCHK(s, launch_phases<double>(s->kruns, runs, zero, s->pt, s->phases, s->st));
+    else HIPCHK(s, launch_phases<float>(s->kruns, runs, zero, s->pt, s->phases, s->st));
   }
   HIPCHK(s, hipStreamSynchronize(s->st));
+  s->phase_runs = runs;
+  s->krun.swap(krun);
+  s->krun_split = split;
   s->has_k = true;
-  s->phase_ok = false;
   return NCT_OK;
 }
 

@@ -288,6 +288,9 @@ nct_status nct_apply_hamiltonian(nct_system *sys, const void *psi_dev, void *hps
  * max_i |<psi_i|psi_i> - 1|, with
  *   E = sum_i f_i <psi_i|T|psi_i> + int (v_ext + v_E(t)) n + sum_i f_i sum_p E_p |C_p,i|^2
  *       + 1/2 int v_H n + int e_xc + mu_B B.M  (e_xc: exchange, plus PW92 correlation if xc = 2).
+ * The states after the call are the same bits with and without obs_host and tape.  In mixed precision, systems of
+ * more than 512 MiB of states apply H in another order of sums than smaller ones (both within FP32
+ * rounding of the FP64 step); nct_backward_step reverses a step in the order it was made in.
  * tape nonzero: record what nct_backward_step needs for each of these steps (requires
  * nsteps <= params.tape_steps); the record of step k of this call has tape_index k.
  * Returns NCT_ERR_NONFINITE if N_e became non-finite. */

@@ -131,8 +131,8 @@ struct nct_system {
   void* phi = nullptr;
   void* wbuf = nullptr;
   void* tmp = nullptr;
-  void* tmpk_phi = nullptr;   // FP32: kinetic column pass of phi (shared by the 2nd and 3rd exponentials);
-                              // FP64: adjoint of psi~
+  void* tmpk_phi = nullptr;   // transformed form: kinetic column pass of phi (shared by the 2nd and 3rd exponentials);
+                              // real-space form: adjoint of psi~
 
   // projectors
   ProjTables pt;
@@ -577,17 +577,19 @@ struct Engine {
   nct_system* s;
   static constexpr bool D = sizeof(R) == 8;
   // Real-space form of H (column pass T_x + V, plane pass T_yz and the projectors), else through
-  // (y,z)-transformed copies of the states.  FP64 always takes it; FP32 takes it for H applications
-  // (48^3 x 64 with its density and fields: 205 against 249 us) and for large steps that return the
-  // states alone (real_step).  Steps with observables or a tape, adjoint steps and ground states keep the
-  // transformed form in FP32: they return FP64 observables, energies and field gradients, into which
-  // the rounding of the FP32 states enters at 1e-8, and these stay reproducible digit for digit with
-  // earlier versions.
+  // (y,z)-transformed copies of the states.  FP64 always takes it, FP32 for H applications (48^3 x 64
+  // with its density and fields: 205 against 249 us) and for the steps and adjoint steps of large systems
+  // (real_step), never for ground states.  The choice depends on the system alone: a step gives the same states
+  // whether or not it records observables or a tape, and is reversed in the form it was made in.
   bool RS = D;
-  // FP32 steps: from two last-level caches (256 MiB each) of states on, where each pass over them counts
-  // in full.  64^3 x 256 with 16 atoms 13.1 against 17.9 ms, 96^3 x 128 26.7 against 29.7; below, where
-  // steps whose states go on into an adjoint are usual and the digits above matter, 48^3 x 64 1.70
-  // against 1.96 ms and 96 x 24 x 24 x 40 about even, it is not taken.
+  // FP32 steps: above 512 MiB of states.  This is not where the times cross.  Per step, transformed against
+  // real space: 48^3 27 MiB 0.685 / 0.693 ms, 54 1.127 / 0.998, 108 2.03 / 1.76, 216 3.84 / 3.31, 506 8.67 / 7.43;
+  // 64^3 256 MiB 4.38 / 3.44, 480 7.98 / 6.22; 96^3 216 MiB 4.13 / 3.76; 96 x 24 x 24 34 MiB 0.828 / 0.878, 101
+  // 2.31 / 2.49.  The two forms round the FP32 states differently (each within 3e-7 of FP64), and mixed calls
+  // return FP64 numbers that are sums of small differences of those states: a field gradient of 64^3 x 64
+  // moves by 2.4e-7 of its size with the form.  Systems up to two last-level caches (256 MiB each) keep the
+  // digits that such results have had; larger ones, where a step takes 14 % to 29 % less in real space (64^3 x
+  // 256 with 16 atoms 13.1 against 17.9 ms), do not.
   bool real_step() const { return size_t(2) * s->S * s->N * sizeof(cpx<R>) > (size_t(512) << 20); }
   const void* twx() const { return sizeof(R) == 8 ? s->tw64[0] : s->tw32[0]; }
   const void* twy() const { return sizeof(R) == 8 ? s->tw64[1] : s->tw32[1]; }
@@ -1005,6 +1007,12 @@ struct Engine {
     nct_status r;
     int ntiles = 0;
     at_time(t);
+    if constexpr (!D) {  // the kinetic energy is summed over (y,z)-transformed states
+      if (RS && (r = check(timed(s, NCT_K_PLANE_FWD, 2 * psiB(), 0, [&] {
+                   return launch_plane_fwd<R>(s->n, 2 * s->S, psi, s->psihat, nullptr, &s->pt, twy(), twz(), s->st,
+                                              ktab()); }), "plane_fwd")) != NCT_OK)
+        return r;
+    }
     if ((r = check(timed(s, NCT_K_OBS, (D ? 2 : 1) * psiB(), 0, [&] {
            if constexpr (D)
              return launch_energy_real(s->n, 2 * s->S, psi, twx(), twy(), twz(), kint(), s->epart, s->eplane, &ntiles,
@@ -1071,7 +1079,7 @@ struct Engine {
     const double dt = s->prm.dt;
     const int K = s->prm.taylor_order;
     void* cur = psi;
-    RS = D || (!obs_host && !T && real_step());
+    RS = D || real_step();
     if (T) {
       HIPCHK(s, hipMemcpyAsync(tvec(*T, 0, 0), psi, size_t(psiB()), hipMemcpyDeviceToDevice, s->st));
       cur = tvec(*T, 0, 0);
@@ -1294,6 +1302,7 @@ struct Engine {
     const int K = s->prm.taylor_order;
     const double dt = s->prm.dt;
     const size_t gb = 4 * s->N * 8;
+    RS = D || real_step();  // the form of the recorded step
     std::vector<void*> xs1(K), xs2(K), xs3(K);
     xs1[0] = tvec(T, idx, 0);
     xs2[0] = tvec(T, idx, K);

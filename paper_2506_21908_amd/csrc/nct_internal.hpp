@@ -213,7 +213,7 @@ hipError_t launch_axpby(void* y, const void* x, size_t count, R a_re, R a_im, R 
                         hipStream_t st);
 
 // Adjoint kernels
-// g += Re c mu^dagger (1, sigma) w, c = cre + i cim (FP32: cre is 0)
+// g += Re c mu^dagger (1, sigma) w, c = cre + i cim
 template <typename R>
 hipError_t launch_pair(const void* mu, const void* w, int S, size_t N, double cre, double cim, double* g,
                        hipStream_t st);

@@ -1783,15 +1783,16 @@ __global__ __launch_bounds__(256) void k_phases(const double* __restrict__ kruns
 // Pair reduction of one adjoint Taylor stage w_k = x + c H w_{k-1} with adjoint mu_k:
 //   g[0][p] += Re c sum_i mu_i^dagger w_i,  g[1+q][p] += Re c sum_i mu_i^dagger sigma_q w_i
 // i.e. dL = sum_r (g_v dv + g_b . db) for a perturbation dH = dv + db.sigma of the stage.  FP64 takes any
-// c = cre + i cim; the FP32 stages have c = -i gamma (cim = -gamma) and reduce the imaginary parts alone.
-template <typename R>
+// c = cre + i cim.  RE: with the real parts (FP64 always takes them, FP32 for c off the imaginary axis: Horner
+// stages have c = -i gamma, cim = -gamma).
+template <typename R, bool RE>
 __global__ __launch_bounds__(256) void k_pair(const cpx<R>* __restrict__ mu, const cpx<R>* __restrict__ w,
                                               int S, size_t N, double cre, double cim, double* __restrict__ g) {
   const size_t p = size_t(blockIdx.x) * 256 + threadIdx.x;
   if (p >= N) return;
   const double gamma = -cim;
   double s0 = 0, s1 = 0, s2 = 0, s3 = 0;
-  double t0 = 0, t1 = 0, t2 = 0, t3 = 0;  // real parts (FP64)
+  double t0 = 0, t1 = 0, t2 = 0, t3 = 0;  // real parts
 #pragma unroll 2
   for (int i = 0; i < S; ++i) {
     const cpx<R> mu_u = mu[size_t(2 * i) * N + p], mu_d = mu[size_t(2 * i + 1) * N + p];
@@ -1806,7 +1807,7 @@ __global__ __launch_bounds__(256) void k_pair(const cpx<R>* __restrict__ mu, con
     s1 += im_ad + im_bu;                 // sigma_x: conj(a) d + conj(b) u
     s2 += -re_ad + re_bu;                // sigma_y: -i conj(a) d + i conj(b) u  -> Im = -Re(a*d) + Re(b*u)
     s3 += im_au - im_bd;                 // sigma_z
-    if constexpr (sizeof(R) == 8) {
+    if constexpr (RE) {
       const double re_au = ar * ur + ai * ui, re_bd = br * dr + bi * di;
       t0 += re_au + re_bd;
       t1 += re_ad + re_bu;
@@ -1814,7 +1815,7 @@ __global__ __launch_bounds__(256) void k_pair(const cpx<R>* __restrict__ mu, con
       t3 += re_au - re_bd;
     }
   }
-  if constexpr (sizeof(R) == 8) {
+  if constexpr (RE) {
     g[p] += gamma * s0 + cre * t0;
     g[N + p] += gamma * s1 + cre * t1;
     g[2 * N + p] += gamma * s2 + cre * t2;
@@ -2380,10 +2381,11 @@ static hipError_t launch_plane_yz_m(int S, int NX, const StageArgs<R>& a, const 
 template <typename R>
 hipError_t launch_plane_yz(const int n[3], int S, const StageArgs<R>& a, const KinTables& kt,
                            const ProjTables& pt, const void* twy, const void* twz, hipStream_t st) {
-  constexpr bool D = sizeof(R) == 8;  // only the FP64 adjoint accumulates
-  if (a.acc && !D) return hipErrorInvalidValue;
+  // accumulation is for the adjoint, which takes this form in FP32 only for large states (cache mode 2)
+  constexpr bool D = sizeof(R) == 8;
+  if (a.acc && !D && a.cache_mode < 2) return hipErrorInvalidValue;
 #define Y(A, B, M)                                                                             \
-  return a.acc ? launch_plane_yz_m<R, A, B, M, D>(S, n[0], a, kt, pt, twy, twz, st)            \
+  return a.acc ? launch_plane_yz_m<R, A, B, M, D || M == 2>(S, n[0], a, kt, pt, twy, twz, st)  \
                : launch_plane_yz_m<R, A, B, M, false>(S, n[0], a, kt, pt, twy, twz, st)
 #define X(A, B)                          \
   if (n[1] == A && n[2] == B) {          \
@@ -2843,9 +2845,9 @@ hipError_t launch_axpby(void* y, const void* x, size_t count, R a_re, R a_im, R 
 template <typename R>
 hipError_t launch_pair(const void* mu, const void* w, int S, size_t N, double cre, double cim, double* g,
                        hipStream_t st) {
-  nct_launch((k_pair<R>), dim3(nblocks(N, 256)), dim3(256), 0, st,
-                     reinterpret_cast<const cpx<R>*>(mu), reinterpret_cast<const cpx<R>*>(w), S, N,
-                     cre, cim, g);
+  const auto kern = sizeof(R) == 8 || cre != 0.0 ? k_pair<R, true> : k_pair<R, false>;
+  nct_launch(kern, dim3(nblocks(N, 256)), dim3(256), 0, st, reinterpret_cast<const cpx<R>*>(mu),
+             reinterpret_cast<const cpx<R>*>(w), S, N, cre, cim, g);
   return hipGetLastError();
 }
 #if NCT_FP64_TU

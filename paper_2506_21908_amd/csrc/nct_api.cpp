@@ -563,13 +563,12 @@ std::vector<std::complex<double>> taylor_roots(int K) {
 // order kProductMaxOrder.  Each of its K stages rounds w once where the Horner form adds ever smaller terms
 // to an exact x, so its error hardly depends on |z| E_max while Horner's grows with it, and the two cross
 // at a |z| E_max that grows with K.  Relative 2-norm errors of one FP64 step against long double at 16^3,
-// smooth states (on white noise the product form is the better one from 1.9 on), product against Horner
-// in units of 1e-16: K = 4 at 1.3 2.2 / 1.6, at 2.1 2.06 / 2.06, at 2.5 2.1 / 2.5; K = 6 at 2.4 2.41 / 2.38;
-// K = 8 at 2.4 2.7 / 2.4, at 2.7 2.66 / 2.71; K = 12 at 1.3 3.5 / 1.6, at 2.8 3.1 / 2.8, at 3.2 3.1 / 3.4.
-// FP32 steps cross earlier (48^3 in units of 1e-7: K = 4 at 1.3 1.16 / 0.86, at 2.1 1.16 / 1.20; K = 12 at
-// 2.1 1.8 / 1.2, at 4.2 1.6 / 3.3).
+// smooth states, in units of 1e-16: K = 4 product 1.8, Horner 1.15 at 0.95, 1.55 at 1.7, 1.76 at 2.0; K = 6 2.0,
+// Horner 1.86 at 2.1; K = 8 2.2, Horner 2.15 at 2.4; K = 12 2.5, Horner 2.6 at 2.8, 3.2 at 3.2.  (On white noise
+// the Horner stages keep ahead: K = 4 at 2.1 3.5 against 2.9.  The transformed form, which neither is to fall
+// behind, has 2.0 and 4.1 there.)
 constexpr int kProductMaxOrder = 12;
-constexpr double product_min_ze(int K) { return 2.05 + 0.16 * (K > 4 ? K - 4 : 0); }
+constexpr double product_min_ze(int K) { return 2.05 + 0.1 * (K > 4 ? K - 4 : 0); }
 
 // ---------------------------------------------------------------- engine
 template <typename R>
@@ -782,13 +781,26 @@ struct Engine {
     for (int k = 0; k < 3; ++k) out[k] = R(kMuB * B[k]);
   }
 
+  // real-space stage whose base is w: the plane pass adds it, where it can
+  bool base_in_plane(const StageArgs<R>& sa) const {
+    return sa.x_base && sa.x_base == sa.w_in && real_base_in_plane(s->n[1], s->n[2]);
+  }
+  StageArgs<R> column_args(StageArgs<R> sa) const {
+    if (base_in_plane(sa)) sa.alpha = R(0);
+    return sa;
+  }
+  StageArgs<R> plane_args(StageArgs<R> sa) const {
+    if (base_in_plane(sa)) sa.walpha = sa.alpha;
+    return sa;
+  }
+
   // column pass of S states from state i0 on stream st (pointers at that state): RS: dst = alpha x + c
   // (T_x + V) w of the stage sa; FP32: dst = T src, both (y,z)-transformed
   nct_status xpass(const void* src, void* dst, const StageArgs<R>& sa, int i0, int S, hipStream_t st) {
     const double pb = psiB() * S / s->S;
     const double b = RS ? 2 * pb + (sa.x_base && sa.x_base != sa.w_in ? pb : 0.0) + 4.0 * s->N * sizeof(R) : 2 * pb;
     return check(timed_on(s, st, NCT_K_XPASS, b, 0, [&] {
-                   if (RS) return launch_xv<R>(s->n, S, sa, dst, twx(), kint(i0), st);
+                   if (RS) return launch_xv<R>(s->n, S, column_args(sa), dst, twx(), kint(i0), st);
                    return launch_xpass<R>(s->n, 2 * S, src, dst, g2x(), g2yz(), R(0.5 / double(s->N)), 0, twx(), st,
                                             s->cache_mode, ktab(i0)); }), "xpass");
   }
@@ -810,7 +822,7 @@ struct Engine {
     if (sa.W) b += rb;
     if (sa.acc) b += 2 * pb;
     return check(timed_on(s, st, NCT_K_PLANE_STAGE, b, 0, [&] {
-                   if (RS) return launch_plane_yz<R>(s->n, S, sa, kint(i0), s->pt, twy(), twz(), st);
+                   if (RS) return launch_plane_yz<R>(s->n, S, plane_args(sa), kint(i0), s->pt, twy(), twz(), st);
                    return transformed_stage(sa, S, st); }), "plane_stage");
   }
 

@@ -47,6 +47,7 @@ struct StageArgs {
   R lg[4] = {0, 0, 0, 0};         // laser potential lg[0] ix + lg[1] iy + lg[2] iz + lg[3]
   R cre = 1, cim = 0;             // coefficient c of H w
   R alpha = 0;                    // coefficient of x_base
+  R walpha = 0;                   // real-space plane pass: coefficient of w_in added to tmp_in (real_base_in_plane)
   const void* Y = nullptr;        // nonlocal scatter rows [S][2][Jtot], or null
   void* W = nullptr;              // output sphere rows [S][2][Jtot] of w_out, or null
   // adjoint extras: acc += w_out (if acc != null)
@@ -85,9 +86,13 @@ struct KinTables {
   }
 };
 
+// Real-space form, stages whose base is w itself: the plane pass adds alpha w, where it holds the points of w and of
+// the sum at the same time, else the column pass does.  One rounding less of the base either way it can be had.
+bool real_base_in_plane(int ny, int nz);
+
 // Launchers (return hipError_t of the launch).  n = {NX, NY, NZ}.
 // Real-space form (kv, state_off and ka of the stage arguments are unused: they are in kt):
-// column pass dst = alpha x_base + c (T_x + V) w_in, plane pass w_out = tmp_in + c (T_yz w_in + Y rows)
+// column pass dst = alpha x_base + c (T_x + V) w_in, plane pass w_out = tmp_in + walpha w_in + c (T_yz w_in + Y rows)
 // (w_out may be w_in), sphere rows of states, and kinetic energy partials: part [B][ntiles][2] (x part
 // of sum 1/2 |G + k|^2 |X|^2 / N and the norm sum |psi|^2 per column tile), eplane [B][NX] (y,z part
 // per plane).

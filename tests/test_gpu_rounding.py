@@ -119,3 +119,20 @@ def test_step_fp64_rounds_the_base_last(gpu):
     err = float(np.sqrt((np.abs(got - ref) ** 2).sum() / (np.abs(ref) ** 2).sum()))
     print(f"[case]   {err:.2e}", flush=True)
     assert err < 2.0 ** -53
+
+
+@pytest.mark.parametrize("K,ze", [(4, 2.2), (8, 2.6), (12, 3.0)])
+def test_product_stages_round_the_base_twice(gpu, K, ze):
+    """Product stages (|z| E_max beyond 2.05 + 0.1 (K - 4)) round w once with c (T_x + V) w and once with c T_yz w:
+    sqrt(4 K) 0.39 u for two exponentials of K stages (0.39 u: the rms of a rounding in 2-norm over the spread
+    of mantissas), the transforms' noise on smooth states well below.  Bar: a tenth more; a third rounding of
+    w per stage makes sqrt(6 K) 0.39 u, 1.22 times."""
+    torch, nct = gpu
+    n, dt = (16, 16, 16), 2 * ze / EMAX
+    print(f"[case] rounding FP64 product K={K}", flush=True)
+    psi, F = smooth_inputs(n, 2, 43)
+    ref = frozen_step(psi, F, n, K, dt, np.longdouble, np.clongdouble)
+    got = gpu_step(torch, nct, psi, F, n, K, dt, nct.NCT_FP64).astype(np.clongdouble)
+    err = float(np.sqrt((np.abs(got - ref) ** 2).sum() / (np.abs(ref) ** 2).sum()))
+    print(f"[case]   {err:.2e}", flush=True)
+    assert err < 1.1 * 0.39 * np.sqrt(4 * K) * 2.0 ** -53

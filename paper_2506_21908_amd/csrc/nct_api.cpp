@@ -62,6 +62,7 @@ struct nct_system {
   hipStream_t stB = nullptr, stB2 = nullptr;
   hipEvent_t evB_rows = nullptr, evB_proj = nullptr, ev_fork = nullptr, ev_join = nullptr;
   void* CpartB = nullptr;
+  void* ECB = nullptr;
   std::string err;
   std::vector<std::complex<double>> roots;  // of T_K (product form of the exponential)
   std::vector<DevBuf> owned;
@@ -143,6 +144,7 @@ struct nct_system {
   void* Y = nullptr;
   void* Yphi = nullptr;       // scatter rows of phi's first stage, shared by the 2nd and 3rd exponentials
   void* Cpart = nullptr;
+  void* EC = nullptr;         // coefficients of the scatter, where the chain has a stream of its own
   void* C = nullptr;
   double* energy_dev = nullptr;
   // Bloch phases of the sphere rows (real-space form): runs of states that share a vector, run of each state,
@@ -409,6 +411,7 @@ nct_status build_projectors(nct_system* s) {
   const size_t cp = size_t(s->natoms) * pt.PP * s->S;
   if ((r = dalloc(s, cp * pt.max_kchunks * 16, &s->Cpart)) != NCT_OK) return r;
   if ((r = dalloc(s, cp * 16, &s->C)) != NCT_OK) return r;
+  if (!s->one_stream && (r = dalloc(s, cp * s->cbytes, &s->EC)) != NCT_OK) return r;
   return NCT_OK;
 }
 
@@ -696,11 +699,16 @@ struct Engine {
                           frac * proj_flops(), [&] { return launch_proj_contract<R>(s->pt, W, S, Cpart, ph, st); }),
                  "proj_contract");
   }
-  nct_status scatter(const void* Cpart, int S, void* Y, const PhaseTab& ph, hipStream_t st) {
+  // (EC null: the scatter sums the partials itself)
+  nct_status scatter(const void* Cpart, void* EC, int S, void* Y, const PhaseTab& ph, hipStream_t st) {
     const double frac = double(S) / s->S;
-    return check(timed_on(s, st, NCT_K_PROJ, frac * rowsB() + beta_bytes() + coeff_bytes(frac) * s->pt.max_kchunks,
-                          frac * proj_flops(),
-                          [&] { return launch_proj_scatter<R>(s->pt, Cpart, S, s->dV, Y, ph, st); }), "proj_scatter");
+    const double ecB = double(s->natoms) * s->pt.PP * S * sizeof(R) * 2, partB = coeff_bytes(frac) * s->pt.max_kchunks;
+    nct_status r;
+    if (EC && (r = check(timed_on(s, st, NCT_K_PROJ, partB + ecB, 0, [&] {
+                           return launch_proj_coeffs<R>(s->pt, Cpart, S, s->dV, EC, st); }), "proj_coeffs")) != NCT_OK)
+      return r;
+    return check(timed_on(s, st, NCT_K_PROJ, frac * rowsB() + beta_bytes() + (EC ? ecB : partB), frac * proj_flops(), [&] {
+                   return launch_proj_scatter<R>(s->pt, Cpart, EC, S, s->dV, Y, ph, st); }), "proj_scatter");
   }
 
   // The phase table (real-space form) of the current Bloch vectors and vector potential (null without either).
@@ -730,11 +738,11 @@ struct Engine {
     nct_status r;
     PhaseTab ph;
     if ((r = phase_table(ph)) != NCT_OK) return r;
-    return projections_on(W, s->S, s->Cpart, s->Y, ph, s->st, s->st2, s->ev_rows, s->ev_proj);
+    return projections_on(W, s->S, s->Cpart, s->EC, s->Y, ph, s->st, s->st2, s->ev_rows, s->ev_proj);
   }
   // contraction and scatter of S states: on st2 once st has written the rows (the plane pass waits
   // for ev_proj), or on st itself
-  nct_status projections_on(const void* W, int S, void* Cpart, void* Y, const PhaseTab& ph, hipStream_t st,
+  nct_status projections_on(const void* W, int S, void* Cpart, void* EC, void* Y, const PhaseTab& ph, hipStream_t st,
                             hipStream_t st2, hipEvent_t ev_rows, hipEvent_t ev_proj) {
     nct_status r;
     if (!s->one_stream) {
@@ -743,7 +751,7 @@ struct Engine {
     }
     hipStream_t q = s->one_stream ? st : st2;
     if ((r = contract(W, S, Cpart, ph, q)) != NCT_OK) return r;
-    if ((r = scatter(Cpart, S, Y, ph, q)) != NCT_OK) return r;
+    if ((r = scatter(Cpart, EC, S, Y, ph, q)) != NCT_OK) return r;
     if (!s->one_stream) HIPCHK(s, hipEventRecord(ev_proj, st2));
     return NCT_OK;
   }
@@ -831,12 +839,12 @@ struct Engine {
     int i0, S;
     hipStream_t st, st2;
     hipEvent_t ev_rows, ev_proj;
-    void* Cpart;
+    void *Cpart, *EC;
   };
   int groups(Group* g) const {
-    g[0] = {0, s->ngroups > 1 ? s->S0 : s->S, s->st, s->st2, s->ev_rows, s->ev_proj, s->Cpart};
+    g[0] = {0, s->ngroups > 1 ? s->S0 : s->S, s->st, s->st2, s->ev_rows, s->ev_proj, s->Cpart, s->EC};
     if (s->ngroups == 1) return 1;
-    g[1] = {s->S0, s->S - s->S0, s->stB, s->stB2, s->evB_rows, s->evB_proj, s->CpartB};
+    g[1] = {s->S0, s->S - s->S0, s->stB, s->stB2, s->evB_rows, s->evB_proj, s->CpartB, s->ECB};
     return 2;
   }
   template <typename P>
@@ -876,7 +884,7 @@ struct Engine {
     void* ybuf = y_dst ? y_dst : s->Y;
     if (s->natoms && !y_src) {
       ph.state_off = g.i0;
-      if ((r = projections_on(offr(cW, g.i0), g.S, g.Cpart, offr(ybuf, g.i0), ph, g.st, g.st2, g.ev_rows,
+      if ((r = projections_on(offr(cW, g.i0), g.S, g.Cpart, g.EC, offr(ybuf, g.i0), ph, g.st, g.st2, g.ev_rows,
                               g.ev_proj)) != NCT_OK)
         return r;
     }
@@ -1760,6 +1768,7 @@ nct_status create_impl(const nct_params* p, nct_system** out) {
     if (s->natoms) {
       const size_t cp = size_t(s->natoms) * s->pt.PP * s->S;
       if ((r = dalloc(s, cp * s->pt.max_kchunks * 16, &s->CpartB)) != NCT_OK) return bail(r);
+      if (!s->one_stream && (r = dalloc(s, cp * s->cbytes, &s->ECB)) != NCT_OK) return bail(r);
     }
   }
   {  // this device's static scratch (allocation-free entry point): looked up once per device

@@ -183,15 +183,17 @@ hipError_t launch_phases(const double* kruns, int nruns, const double ka[3], con
                          hipStream_t st);
 
 // Projectors: chunk partials of beta^H W (per atom); C = dV times their sum (observables);
-// Y = beta E C from the partials.  With phases (ph.tab) the rows of W are taken times them, those of Y
+// Y = beta E C from the partials, or from EC = E C (complex R) where launch_proj_coeffs has made it.  With phases (ph.tab) the rows of W are taken times them, those of Y
 // times their conjugates.
 template <typename R>
 hipError_t launch_proj_contract(const ProjTables& pt, const void* W, int S, void* Cpart, const PhaseTab& ph,
                                 hipStream_t st);
 hipError_t launch_proj_reduce(const ProjTables& pt, const void* Cpart, int S, double dV, void* C, hipStream_t st);
 template <typename R>
-hipError_t launch_proj_scatter(const ProjTables& pt, const void* Cpart, int S, double dV, void* Y, const PhaseTab& ph,
-                               hipStream_t st);
+hipError_t launch_proj_coeffs(const ProjTables& pt, const void* Cpart, int S, double dV, void* EC, hipStream_t st);
+template <typename R>
+hipError_t launch_proj_scatter(const ProjTables& pt, const void* Cpart, const void* EC, int S, double dV, void* Y,
+                               const PhaseTab& ph, hipStream_t st);
 
 // Observables of the current state: assembles one 13-double row.
 struct ObsInputs {

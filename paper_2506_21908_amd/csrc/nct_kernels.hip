@@ -1707,27 +1707,41 @@ static __global__ __launch_bounds__(256) void k_proj_reduce(ProjTables pt, const
   C[idx] = c[0];
 }
 
+// EC[a][p][i] = E[a][p] C[a][p][i] of the scatter
+template <typename R>
+__global__ __launch_bounds__(256) void k_proj_coeffs(ProjTables pt, const cpx<double>* __restrict__ Cpart, int S,
+                                                     double dV, cpx<R>* __restrict__ EC) {
+  const size_t idx = size_t(blockIdx.x) * 256 + threadIdx.x;
+  if (idx >= size_t(pt.natoms) * pt.PP * S) return;
+  const int a = int(idx / (size_t(S) * pt.PP)), p = int((idx / S) % pt.PP);
+  cpx<double> c[1];
+  proj_sums<1>(pt, Cpart, S, dV, a, p, int(idx % S), c);
+  const double en = pt.energy[size_t(a) * pt.PP + p];
+  EC[idx] = {R(en * c[0].x), R(en * c[0].y)};
+}
+
 // Y[i][s][J] = sum_p beta[J][s][p] E[a][p] C[a][p][i]; rows k = 2 (J - off_a) + s (KQ: times exp(-i k.d)).
-// One workgroup per (atom, 16 states, share of the atom's row tiles).  It first sums the chunk partials
-// of its own 16 x PP coefficients, which all shares of an atom repeat: they are few and in L2, and a
-// launch of their own stood between the contraction and this one (5-39 us each time, on the path that
-// the plane pass waits for where the column pass is short).
+// One workgroup per (atom, 16 states, share of the atom's row tiles).  SUMS: it first sums the chunk partials of its
+// own 16 x PP coefficients, which all shares of an atom repeat.  That is for small systems, whose chain
+// runs on the main stream: a launch of its own stands on the path that the plane pass waits for (5-39 us each
+// time).  On a stream of its own the chain is hidden but for its share of memory and CUs, and there k_proj_coeffs
+// sums once: repeated sums made 48^3 x 128 mixed with 16 atoms 4.56 ms per step (4.38 now), 48^3 x 64
+// mixed with four 2.03 (2.00), and limiting the shares for them left four waves for all 111 row tiles of an atom.
 // The projector values of the next row tile are loaded ahead (of the first one before the sums), and as in
 // the contraction the register bound keeps the products out of accumulation registers: contraction and
 // scatter together 17.2 against 17.8 us at 32^3 x 16 FP64, H application 32 x 16 x 24 x 39 with its density
 // and fields 87 against 92 us.  Sixteen reads of partials in flight, not
 // eight with the last ones singly: 8.6 -> 7.7 us at 16^3 x 8 mixed with two atoms.
-// FP64 takes one coefficient per thread (48^3 x 64 with four atoms, two steps, 6.39 against 6.58 ms with
-// 256 threads); FP32 256 threads: a workgroup of 512 waits for room beside the transformed form's column
-// pass (64^3 x 64 mixed with eight atoms 76 against 33 us).
-template <typename R, int PP>
-constexpr int ps_nt() { return sizeof(R) == 8 ? 16 * PP : 256; }
-template <typename R, int PP, bool KQ>
-__global__ __launch_bounds__((ps_nt<R, PP>()), 4) void k_proj_scatter(ProjTables pt, const cpx<double>* __restrict__ Cpart,
-                                                        int S, double dV, cpx<R>* __restrict__ Y, PhaseTab ph) {
+// With the sums FP64 takes one coefficient per thread, FP32 256 threads (one or two); without, one wave.
+template <typename R, int PP, bool SUMS>
+constexpr int ps_nt() { return !SUMS ? 64 : (sizeof(R) == 8 ? 16 * PP : 256); }
+template <typename R, int PP, bool KQ, bool SUMS>
+__global__ __launch_bounds__((ps_nt<R, PP, SUMS>()), 4) void k_proj_scatter(ProjTables pt, const cpx<double>* __restrict__ Cpart,
+                                                        const cpx<R>* __restrict__ EC, int S, double dV,
+                                                        cpx<R>* __restrict__ Y, PhaseTab ph) {
   using M = mfma16<R>;
-  constexpr int KS = PP / 4, NT = ps_nt<R, PP>();
-  __shared__ cpx<R> ecs[PP][16];
+  constexpr int KS = PP / 4, NT = ps_nt<R, PP, SUMS>();
+  __shared__ cpx<R> ecs[SUMS ? PP : 1][16];
   const int a = blockIdx.x, nt = blockIdx.y;
   const int off = pt.row_off[a];
   const int K2 = 2 * (pt.row_off[a + 1] - off);
@@ -1745,25 +1759,33 @@ __global__ __launch_bounds__((ps_nt<R, PP>()), 4) void k_proj_scatter(ProjTables
     }
   };
   const int rt0 = blockIdx.z * (NT / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i = nt * 16 + col;
+  cpx<R> ec[KS];
+  if constexpr (!SUMS) {
+    if (rt0 * 16 >= K2) return;  // (one wave per workgroup, no barrier below)
+#pragma unroll
+    for (int u = 0; u < KS; ++u) {
+      const cpx<R> ev = EC[(size_t(a) * PP + 4 * u + kl) * S + min(i, S - 1)];
+      ec[u] = i < S ? ev : cpx<R>{R(0), R(0)};
+    }
+  }
   load(rt0);
-  {
+  if constexpr (SUMS) {
     constexpr int NC = 16 * PP / NT;  // coefficients per thread
-    const int p = threadIdx.x >> 4, c16 = threadIdx.x & 15, i = nt * 16 + c16;
+    const int p = threadIdx.x >> 4, c16 = threadIdx.x & 15, ic = nt * 16 + c16;
     cpx<double> c[NC];
-    proj_sums<NC>(pt, Cpart, S, dV, a, p, min(i, S - 1), c);
+    proj_sums<NC>(pt, Cpart, S, dV, a, p, min(ic, S - 1), c);
 #pragma unroll
     for (int k = 0; k < NC; ++k) {
       const double en = pt.energy[size_t(a) * PP + p + 16 * k];
-      ecs[p + 16 * k][c16] = i < S ? cpx<R>{R(en * c[k].x), R(en * c[k].y)} : cpx<R>{R(0), R(0)};
+      ecs[p + 16 * k][c16] = ic < S ? cpx<R>{R(en * c[k].x), R(en * c[k].y)} : cpx<R>{R(0), R(0)};
     }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < KS; ++u) ec[u] = ecs[4 * u + kl][col];
   }
-  __syncthreads();
-  const int i = nt * 16 + col;
   const cpx<R>* __restrict__ phase = nullptr;
   if constexpr (KQ) phase = ph.row<R>(min(i, S - 1), pt.Jtot);
-  cpx<R> ec[KS];
-#pragma unroll
-  for (int u = 0; u < KS; ++u) ec[u] = ecs[4 * u + kl][col];
   for (int rt = rt0; rt * 16 < K2; rt += gridDim.z * (NT / 64)) {
     cpx<R> xb[KS];
 #pragma unroll
@@ -2776,29 +2798,46 @@ hipError_t launch_phases(const double* kruns, int nruns, const double ka[3], con
   return hipGetLastError();
 }
 
-template <typename R, int PP, bool KQ>
-static hipError_t launch_scatter_pp(const ProjTables& pt, const void* Cpart, int S, double dV, void* Y,
-                                    const PhaseTab& ph, hipStream_t st) {
-  // shares of an atom's row tiles: one tile per wave where there are few (atom, states) pairs, down to
-  // all tiles in one workgroup from 128 pairs on: each share repeats the sums, and their reads slow the
-  // column pass beside them (48^3 x 64 mixed with four atoms 1.98 ms per step; 2.01 with up to 512
-  // workgroups, 2.02 with 64)
-  const int waves = ps_nt<R, PP>() / 64, ntile = (S + 15) / 16;
-  const int shares = std::max(1, std::min((pt.max_rowtiles + waves - 1) / waves, 128 / (pt.natoms * ntile)));
-  const dim3 grid(pt.natoms, unsigned(ntile), unsigned(shares));
-  nct_launch((k_proj_scatter<R, PP, KQ>), grid, dim3(unsigned(ps_nt<R, PP>())), 0, st, pt, reinterpret_cast<const cpx<double>*>(Cpart), S,
-             dV, reinterpret_cast<cpx<R>*>(Y), ph);
+template <typename R>
+hipError_t launch_proj_coeffs(const ProjTables& pt, const void* Cpart, int S, double dV, void* EC, hipStream_t st) {
+  if (pt.natoms == 0) return hipSuccess;
+  nct_launch(k_proj_coeffs<R>, dim3(nblocks(size_t(pt.natoms) * pt.PP * S, 256)), dim3(256), 0, st, pt,
+             reinterpret_cast<const cpx<double>*>(Cpart), S, dV, reinterpret_cast<cpx<R>*>(EC));
   return hipGetLastError();
 }
-template <typename R>
-hipError_t launch_proj_scatter(const ProjTables& pt, const void* Cpart, int S, double dV, void* Y, const PhaseTab& ph,
-                               hipStream_t st) {
-  if (pt.natoms == 0) return hipSuccess;
+
+template <typename R, int PP, bool KQ, bool SUMS>
+static hipError_t launch_scatter_pp(const ProjTables& pt, const void* Cpart, const void* EC, int S, double dV, void* Y,
+                                    const PhaseTab& ph, hipStream_t st) {
+  constexpr int NT = ps_nt<R, PP, SUMS>(), waves = NT / 64;
+  const int ntile = (S + 15) / 16;
+  // Shares of an atom's row tiles.  With the coefficients made: two tiles per wave (48^3 x 64 mixed with four atoms
+  // 2.00 ms per step, 32^3 x 64 FP64 1.05; with eight 2.06 and 1.16; one per wave 64^3 x 256 mixed with 16 atoms 13.64
+  // against 13.59).  With the sums in here, which every share repeats: one tile per wave where there
+  // are few (atom, states) pairs, up to 512 workgroups (96 x 24 x 24 x 40 mixed 0.80 ms per step, 0.83 with 128).
+  const int shares = SUMS ? std::max(1, std::min((pt.max_rowtiles + waves - 1) / waves, 512 / (pt.natoms * ntile)))
+                          : std::max(1, (pt.max_rowtiles + 1) / 2);
+  const dim3 grid(pt.natoms, unsigned(ntile), unsigned(shares));
+  nct_launch((k_proj_scatter<R, PP, KQ, SUMS>), grid, dim3(unsigned(NT)), 0, st, pt,
+             reinterpret_cast<const cpx<double>*>(Cpart), reinterpret_cast<const cpx<R>*>(EC), S, dV,
+             reinterpret_cast<cpx<R>*>(Y), ph);
+  return hipGetLastError();
+}
+template <typename R, bool SUMS>
+static hipError_t launch_scatter_k(const ProjTables& pt, const void* Cpart, const void* EC, int S, double dV, void* Y,
+                                   const PhaseTab& ph, hipStream_t st) {
   if (ph.tab)
-    return pt.PP == 16 ? launch_scatter_pp<R, 16, true>(pt, Cpart, S, dV, Y, ph, st)
-                       : launch_scatter_pp<R, 32, true>(pt, Cpart, S, dV, Y, ph, st);
-  return pt.PP == 16 ? launch_scatter_pp<R, 16, false>(pt, Cpart, S, dV, Y, ph, st)
-                     : launch_scatter_pp<R, 32, false>(pt, Cpart, S, dV, Y, ph, st);
+    return pt.PP == 16 ? launch_scatter_pp<R, 16, true, SUMS>(pt, Cpart, EC, S, dV, Y, ph, st)
+                       : launch_scatter_pp<R, 32, true, SUMS>(pt, Cpart, EC, S, dV, Y, ph, st);
+  return pt.PP == 16 ? launch_scatter_pp<R, 16, false, SUMS>(pt, Cpart, EC, S, dV, Y, ph, st)
+                     : launch_scatter_pp<R, 32, false, SUMS>(pt, Cpart, EC, S, dV, Y, ph, st);
+}
+template <typename R>
+hipError_t launch_proj_scatter(const ProjTables& pt, const void* Cpart, const void* EC, int S, double dV, void* Y,
+                               const PhaseTab& ph, hipStream_t st) {
+  if (pt.natoms == 0) return hipSuccess;
+  return EC ? launch_scatter_k<R, false>(pt, Cpart, EC, S, dV, Y, ph, st)
+            : launch_scatter_k<R, true>(pt, Cpart, EC, S, dV, Y, ph, st);
 }
 
 #if NCT_FP64_TU
@@ -2905,7 +2944,8 @@ hipError_t launch_density_backprop(const void* psi, const double* occ, const dou
                                         hipStream_t);                                              \
   template hipError_t launch_proj_contract<R>(const ProjTables&, const void*, int, void*, const PhaseTab&, \
                                               hipStream_t);                                        \
-  template hipError_t launch_proj_scatter<R>(const ProjTables&, const void*, int, double, void*,   \
+  template hipError_t launch_proj_coeffs<R>(const ProjTables&, const void*, int, double, void*, hipStream_t); \
+  template hipError_t launch_proj_scatter<R>(const ProjTables&, const void*, const void*, int, double, void*, \
                                              const PhaseTab&, hipStream_t);                        \
   template hipError_t launch_seed<R>(const void*, const double*, int, size_t, double, double,      \
                                      double, double, void*, hipStream_t);                          \

@@ -142,3 +142,36 @@ def test_mixed_step_of_large_states(gpu, n, S, K, dt, laser):
         s.close()
         out.append(x)
     assert float((out[1] - out[0]).abs().max() / out[0].abs().max()) < 1e-5
+
+
+@pytest.mark.parametrize("S,natoms,nch,prec,nk", [(2051, 1, 1, 0, 0), (2051, 3, 5, 0, 3), (2061, 8, 2, 0, 2),
+                                                  (8195, 1, 5, 1, 0), (8195, 5, 1, 1, 3), (8209, 2, 3, 1, 2),
+                                                  (37, 3, 5, 0, 3), (37, 3, 2, 1, 3)])
+def test_projector_chain_with_coefficients_made_first(gpu, S, natoms, nch, prec, nk):
+    """The chain on its own stream (states above 32 MiB FP64, 64 MiB mixed; the last two below): coefficients
+    summed once, row tiles in pairs, 16 and 32 padded projectors, ragged states, Bloch phases in runs of unequal
+    length.  The nonlocal term alone, as above."""
+    torch, nct = gpu
+    print(f"[case] chain, own stream S={S} natoms={natoms} channels={nch} prec={prec} nk={nk}", flush=True)
+    n, L = (8, 8, 8), (6.0,) * 3
+    assert S < 100 or 2 * S * 512 * (8 if prec else 16) > (64 if prec else 32) * 2 ** 20
+    w = I.make_system(n=n, L=L, nstates=32, case=111, natoms=natoms, min_sep=1.0)
+    w.channels = w.channels[:nch]
+    w.nstates, w.occ = S, np.ones(S)
+    w.psi0 = np.resize(w.psi0, (S,) + w.psi0.shape[1:]) * np.linspace(0.5, 1.5, S)[:, None, None, None, None]
+    if nk:
+        w.kvec = np.random.default_rng(6).uniform(-0.4, 0.4, (nk, 3))[np.minimum(np.arange(S) * nk // (S - 9), nk - 1)]
+    sysd = O.system_from_workload(w)
+    ref = O.apply_nonlocal(w.psi0, sysd.projs, sysd.grid, w.kvec if nk else None)
+    psi = nct.states_to_device(w.psi0, prec)
+    out = []
+    for scale in (1.0, 0.0):
+        for c in w.channels:
+            c.energy = c.energy if scale else 0.0
+        s = nct.system_from_workload(w, precision=prec)
+        s.set_potentials(fields=torch.zeros((4,) + n, dtype=torch.float64, device="cuda"))
+        hpsi = torch.empty_like(psi)
+        s.apply_hamiltonian(psi, hpsi, 0.0)
+        out.append(hpsi.cpu().numpy().astype(np.complex128))
+        s.close()
+    assert max_rel(out[0] - out[1], ref) < (2e-5 if prec else 1e-11)

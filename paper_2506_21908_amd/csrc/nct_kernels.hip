@@ -22,6 +22,7 @@
 
 #include "nct_fft.hpp"
 #include "nct_internal.hpp"
+#include "nct_tables.hpp"
 
 // This file is compiled once per precision (in parallel): NCT_FP64_TU 1 holds the FP64 instantiations
 // and everything that has no precision of its own, 0 the FP32 ones.
@@ -830,9 +831,9 @@ __global__ __launch_bounds__(64 * real_nw<R>(NY, NZ), real_mw(NY, NZ)) void k_pl
 template <typename R>
 __global__ __launch_bounds__(256) void k_gather_rows(const cpx<R>* __restrict__ psi, cpx<R>* __restrict__ W,
                                                      ProjTables pt, size_t N) {
-  const int J = blockIdx.y * 256 + threadIdx.x;
   const int b = blockIdx.x;
-  if (J < pt.Jtot) W[size_t(b) * pt.Jtot + J] = psi[size_t(b) * N + pt.rflat[J]];
+  for (int J = blockIdx.y * 256 + threadIdx.x; J < pt.Jtot; J += gridDim.y * 256)
+    W[size_t(b) * pt.Jtot + J] = psi[size_t(b) * N + pt.rflat[J]];
 }
 
 // Column pass: r = alpha x + c (T_x + V) w, T_x = IDFT_x 1/2 (G_x + k_x)^2 / NX DFT_x, in real space along
@@ -1816,9 +1817,8 @@ __global__ __launch_bounds__((ps_nt<R, PP, SUMS>()), 4) void k_proj_scatter(Proj
 template <typename R>
 __global__ __launch_bounds__(256) void k_phases(const double* __restrict__ kruns, double a0, double a1, double a2,
                                                 const R* __restrict__ disp, int Jtot, cpx<R>* __restrict__ out) {
-  const int J = blockIdx.y * 256 + threadIdx.x;
   const double* k = kruns + 3 * size_t(blockIdx.x);
-  if (J < Jtot)
+  for (int J = blockIdx.y * 256 + threadIdx.x; J < Jtot; J += gridDim.y * 256)
     out[size_t(blockIdx.x) * Jtot + J] = bloch_phase(R(k[0] + a0), R(k[1] + a1), R(k[2] + a2), disp + 3 * J);
 }
 
@@ -2448,7 +2448,7 @@ hipError_t launch_plane_yz(const int n[3], int S, const StageArgs<R>& a, const K
 template <typename R>
 hipError_t launch_gather_rows(const ProjTables& pt, const void* psi, void* W, int B, size_t N, hipStream_t st) {
   if (pt.natoms == 0 || pt.Jtot == 0) return hipSuccess;
-  nct_launch(k_gather_rows<R>, dim3(unsigned(B), nblocks(size_t(pt.Jtot), 256)), dim3(256), 0, st,
+  nct_launch(k_gather_rows<R>, dim3(unsigned(B), tables::row_blocks(pt.Jtot, 256)), dim3(256), 0, st,
              reinterpret_cast<const cpx<R>*>(psi), reinterpret_cast<cpx<R>*>(W), pt, N);
   return hipGetLastError();
 }
@@ -2793,7 +2793,7 @@ template <typename R>
 hipError_t launch_phases(const double* kruns, int nruns, const double ka[3], const ProjTables& pt, void* tab,
                          hipStream_t st) {
   if (pt.natoms == 0 || pt.Jtot == 0) return hipSuccess;
-  nct_launch(k_phases<R>, dim3(unsigned(nruns), nblocks(size_t(pt.Jtot), 256)), dim3(256), 0, st, kruns, ka[0], ka[1],
+  nct_launch(k_phases<R>, dim3(unsigned(nruns), tables::row_blocks(pt.Jtot, 256)), dim3(256), 0, st, kruns, ka[0], ka[1],
              ka[2], reinterpret_cast<const R*>(pt.disp), pt.Jtot, reinterpret_cast<cpx<R>*>(tab));
   return hipGetLastError();
 }

@@ -243,5 +243,13 @@ inline std::string build_projector_tables(const int n[3], const double cell[3], 
   return "";
 }
 
+// Grid y extent of a kernel that strides over the sphere rows in blocks of nt (the limit of that extent
+// would otherwise be reached at 16.8 million rows)
+constexpr unsigned kMaxGridY = 65535;
+inline unsigned row_blocks(int Jtot, unsigned nt) {
+  const unsigned nb = (unsigned(Jtot) + nt - 1) / nt;
+  return nb < kMaxGridY ? nb : kMaxGridY;
+}
+
 }  // namespace tables
 }  // namespace nct

@@ -59,22 +59,23 @@ def test_states_do_not_depend_on_the_outputs(gpu, n, S, K, dt, laser, nk):
     assert torch.equal(got[0][0], got[2][0])
     d = nct.system_from_workload(w)
     d.set_watchdog(0.0)
-    ref = d.step(psi0.to(torch.complex128), 0.3, 1, obs=True)
+    x = psi0.to(torch.complex128)
+    ref = d.step(x, 0.3, 1, obs=True)
     d.close()
+    # FP32 rounding of two exponentials, relative to the largest entry
+    assert float((got[0][0] - x).abs().max() / x.abs().max()) < 1e-5
     # sums over all states of quantities that carry 1e-6 at most
     err = np.abs(got[1][1][0, 1:12] - ref[0, 1:12]) / np.maximum(np.abs(ref[0, 1:12]), 1e-3 * np.abs(ref[0, 1:12]).max())
     print(f"[case]   observables {err.max():.1e}", flush=True)
     assert err.max() < 1e-5
 
 
-@pytest.mark.parametrize("n,S,K,dt,laser,nk", CASES)
-@pytest.mark.parametrize("frozen", [False, True])
+@pytest.mark.parametrize("n,S,K,dt,laser,nk,frozen",
+                         [c + (False,) for c in CASES] + [c + (True,) for c in CASES if not c[4] and not c[5]])
 def test_adjoint_in_the_form_of_the_step(gpu, n, S, K, dt, laser, nk, frozen):
     """Taped and recomputed adjoint steps give the same bits, and agree with FP64 (lambda to the FP32 rounding of
     the six exponentials, 2-norm bar 1e-5; dL/dB, sums of FP32 products, to 1e-4)."""
     torch, nct = gpu
-    if frozen and (laser or nk):
-        pytest.skip("frozen fields take no laser")
     print(f"[case] adjoint n={n} S={S} K={K} dt={dt} laser={laser!r} nk={nk} frozen={frozen}", flush=True)
     w, psi0 = _setup(torch, n, S, K, dt, laser, nk)
     F = None

@@ -127,8 +127,8 @@ struct nct_system {
   int obs_cap = 0;
 
   // device: psi-sized work (precision of the system)
-  void* psihat = nullptr;     // FP32, transformed form: (y,z)-transformed psi and phi
-  void* phihat = nullptr;
+  void* psihat = nullptr;     // FP32: (y,z)-transformed psi (transformed form, kinetic energy) and phi (transformed
+  void* phihat = nullptr;     // steps; null for systems whose steps take the real-space form)
   void* phi = nullptr;
   void* wbuf = nullptr;
   void* tmp = nullptr;
@@ -579,6 +579,9 @@ constexpr double product_min_ze(int K, bool imaginary) {
   return (imaginary ? 1.5 : 2.05) + 0.1 * (K > 4 ? K - 4 : 0);
 }
 
+// FP32 systems whose steps take the real-space form (reasons at Engine::real_step)
+bool mixed_real_step(const nct_system* s) { return size_t(2) * s->S * s->N * s->cbytes > (size_t(512) << 20); }
+
 // ---------------------------------------------------------------- engine
 template <typename R>
 struct Engine {
@@ -598,7 +601,7 @@ struct Engine {
   // moves by 2.4e-7 of its size with the form.  Systems up to two last-level caches (256 MiB each) keep the
   // digits that such results have had; larger ones, where a step takes 14 % to 29 % less in real space (64^3 x
   // 256 with 16 atoms 13.1 against 17.9 ms), do not.
-  bool real_step() const { return size_t(2) * s->S * s->N * sizeof(cpx<R>) > (size_t(512) << 20); }
+  bool real_step() const { return mixed_real_step(s); }
   const void* twx() const { return sizeof(R) == 8 ? s->tw64[0] : s->tw32[0]; }
   const void* twy() const { return sizeof(R) == 8 ? s->tw64[1] : s->tw32[1]; }
   const void* twz() const { return sizeof(R) == 8 ? s->tw64[2] : s->tw32[2]; }
@@ -1730,7 +1733,7 @@ nct_status create_impl(const nct_params* p, nct_system** out) {
   const size_t psib = size_t(s->S) * 2 * N * s->cbytes;
   if (!s->fp64) {
     if ((r = dalloc(s, psib, &s->psihat)) != NCT_OK) return bail(r);
-    if ((r = dalloc(s, psib, &s->phihat)) != NCT_OK) return bail(r);
+    if (!mixed_real_step(s) && (r = dalloc(s, psib, &s->phihat)) != NCT_OK) return bail(r);
   }
   if ((r = dalloc(s, psib, &s->phi)) != NCT_OK) return bail(r);
   if ((r = dalloc(s, psib, &s->wbuf)) != NCT_OK) return bail(r);

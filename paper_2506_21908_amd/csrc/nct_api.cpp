@@ -92,7 +92,7 @@ struct nct_system {
   float* g2x32 = nullptr;
   float* g2yz32 = nullptr;
   double* gs64[3] = {nullptr, nullptr, nullptr};  // signed G per axis (real-space form)
-  // FP32: signed G per axis (x digit-reversed, y and z per position of the transformed yz plane)
+  // transformed form: signed G per axis (x digit-reversed, y and z per position of the transformed yz plane)
   float *gsx32 = nullptr, *gsy32 = nullptr, *gsz32 = nullptr;
   // Bloch vectors [S][3] of the states (k-point sampling); null: Gamma only
   double* kv64 = nullptr;
@@ -112,7 +112,7 @@ struct nct_system {
   double* fpart = nullptr;     // [nblk][kFieldTot]
   double* ftot = nullptr;      // [kFieldTot]
   double* epart = nullptr;     // [2S][ntiles][2]
-  double* eplane = nullptr;    // [2S][NX] (FP64)
+  double* eplane = nullptr;    // [2S][NX] (y,z part of the kinetic energy, FP64 systems)
   double* obs_dev = nullptr;   // [cap][13]
   // per-step watchdog: N_e = sum_i f_i <psi_i|psi_i> after every self-consistent step of a call
   double* ne_hist = nullptr;   // [ne_cap]: slot 0 the initial states, slot k+1 after step k
@@ -812,7 +812,7 @@ struct Engine {
   }
 
   // column pass of S states from state i0 on stream st (pointers at that state): RS: dst = alpha x + c
-  // (T_x + V) w of the stage sa; FP32: dst = T src, both (y,z)-transformed
+  // (T_x + V) w of the stage sa; else dst = T src, both (y,z)-transformed
   nct_status xpass(const void* src, void* dst, const StageArgs<R>& sa, int i0, int S, hipStream_t st) {
     const double pb = psiB() * S / s->S;
     const double b = RS ? 2 * pb + (sa.x_base && sa.x_base != sa.w_in ? pb : 0.0) + 4.0 * s->N * sizeof(R) : 2 * pb;
@@ -881,12 +881,11 @@ struct Engine {
     return NCT_OK;
   }
 
-  // One H application of a state group: projector chain of rows cW (second stream, joined
-  // before the plane pass), column pass into tmp (FP32: of chat, the transformed copy of w), plane pass
-  // described by sa
-  // (full-size pointers; offset here to the group).  FP32 only:
-  // kin_dst: column-pass output buffer (default s->tmp); chat == nullptr: skip the column pass,
-  // sa_full.tmp_in already holds it.
+  // One H application of a state group: projector chain of rows cW (second stream, joined before the
+  // plane pass), column pass of chat into tmp (chat: the states w in real space, their transformed copy
+  // else), plane pass described by sa (full-size pointers; offset here to the group).  Transformed form
+  // only: kin_dst: column-pass output buffer (default s->tmp); chat == nullptr: skip the column
+  // pass, sa_full.tmp_in already holds it.
   nct_status stage_group(const Group& g, const void* cW, const void* chat, const StageArgs<R>& sa_full, PhaseTab ph,
                          void* kin_dst = nullptr, void* y_dst = nullptr, const void* y_src = nullptr) {
     nct_status r;
@@ -947,7 +946,7 @@ struct Engine {
   // stage_out[k-1] (k = 1..K-1), if given, receives w_k (the adjoint tape); else the work buffer.
   // kin_save: keep the first stage's column pass in this buffer; kin_reuse: take the first
   // stage's column pass from this buffer instead of recomputing it (same x, fields-independent).
-  // (FP32 only: in FP64 the column pass takes the fields as well.)
+  // (Transformed form only: in real space the column pass takes the fields as well.)
   // y_save / y_reuse: the same for the first stage's projector scatter rows (they depend on x
   // and the Bloch phases only).
   nct_status taylor(const void* x, const void* xhat, const void* xW, void* out, void* outhat,
@@ -1002,7 +1001,7 @@ struct Engine {
     return join_groups();
   }
 
-  // FP32: the next step's first column pass (kinetic part for psi^ at time t) into s->tmp on stK, so
+  // Transformed form: the next step's first column pass (kinetic part for psi^ at time t) into s->tmp on stK, so
   // that it overlaps the density and field update that follow on st; that step's first Taylor
   // stage takes it as kin_reuse after waiting for evK_out.
   nct_status early_kinetic(double t) {
@@ -1018,7 +1017,7 @@ struct Engine {
   }
 
   // What the first stage needs of states that no plane pass has just written: their sphere rows, and
-  // in FP32 their (y,z) transform into hat.  Returns in chat what the column pass takes.
+  // in the transformed form their (y,z) transform into hat.  Returns in chat what the column pass takes.
   nct_status prepare(const void* psi, void* hat, void* W, const void** chat = nullptr) {
     if (chat) *chat = RS ? psi : hat;
     if (RS) {

@@ -230,9 +230,8 @@ constexpr int kFenceBytes = 48;
 // ---------------------------------------------------------------- one LDS stage
 // NCT_TW_PRODUCTS (tuning macro): FP64 radix-8 butterflies read w1, w2 and w4 (1), w1 and w2 (2)
 // or w1 (3) from the table and form the other twiddles as products (at most three roundings).
-// Fewer values in flight: with three reads the FP64 64^2 plane pass spilled 56 instead of 72 B
-// per lane and ran 5575 instead of 5455 GB/s (64^3 x 256), and the FP64 48^2 one no longer
-// spills; two reads are what leave the forward FP64 64^2 kernel without spill.
+// Fewer values in flight than seven reads: with two the FP64 64^2 plane pass takes 123 of the 128
+// registers that four waves per SIMD leave it, without spill.
 #ifndef NCT_TW_PRODUCTS
 #define NCT_TW_PRODUCTS 2
 #endif

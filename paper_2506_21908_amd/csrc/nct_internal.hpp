@@ -37,8 +37,8 @@ struct ProjTables {
 
 template <typename R>
 struct StageArgs {
-  const void* tmp_in = nullptr;   // column-pass output: FP64 alpha x + c (T_x + V) w_in; FP32 T w_in, (y,z)-transformed
-  void* tmp_out = nullptr;        // FP32: 2D (y,z) transform of w_out, or null
+  const void* tmp_in = nullptr;   // column-pass output: real space alpha x + c (T_x + V) w_in, transformed form T w_in
+  void* tmp_out = nullptr;        // transformed form: 2D (y,z) transform of w_out, or null
   const void* w_in = nullptr;     // real-space input of this H application
   const void* x_base = nullptr;   // Taylor base x (null: alpha ignored)
   void* w_out = nullptr;          // alpha x + c H w_in
@@ -107,7 +107,7 @@ hipError_t launch_gather_rows(const ProjTables& pt, const void* psi, void* W, in
 hipError_t launch_energy_real(const int n[3], int B, const void* src, const void* twx, const void* twy,
                               const void* twz, const KinTables& kt, double* part, double* eplane, int* ntiles_out,
                               hipStream_t st);
-// FP32, transformed form (launch_xpass below also serves the FP64 Poisson solve)
+// Transformed form, FP32 (launch_xpass below also serves the FP64 Poisson solve)
 hipError_t launch_plane_stage(const int n[3], int S, const StageArgs<float>& a, const ProjTables& pt,
                               const void* twy, const void* twz, hipStream_t st);
 // Forward 2D transform of B planes-sets (batch entries, each [NX][NY][NZ]); optionally gathers

@@ -1,13 +1,15 @@
 // HIP kernels of the non-collinear TDDFT step for gfx950 (MI355X), wave64.
 //
 // H application (Eq. HNC-SDFT / TDSDFT) as two passes over HBM, in one of two forms:
-//   FP64, real space (the kinetic operator is a sum T_x + T_yz): k_xv, per column block and both
-//     spinor components, forms T_x w and the 2x2 local potential V w = [v + b.sigma] w on the Taylor
-//     base; k_plane_yz, per (spinor component, x-plane), adds T_yz w and the projector scatter rows, and
-//     gathers the sphere rows of the result for the next projection;
-//   FP32-mixed, with (y,z)-transformed copies: k_xpass (DFT_x -> multiply 1/2|G|^2/N -> IDFT_x on the
-//     transformed states) and k_plane_stage2 / k_plane_stage_r (IDFT_yz -> T w; V w; + scatter rows;
-//     Taylor update; sphere rows; DFT_yz of the result for the next column pass).
+//   real space (the kinetic operator is a sum T_x + T_yz): k_xv, per column block and both spinor
+//     components, forms T_x w and the 2x2 local potential V w = [v + b.sigma] w on the Taylor base;
+//     k_plane_yz, per (spinor component, x-plane), adds T_yz w and the projector scatter rows, and
+//     gathers the sphere rows of the result for the next projection.  Everything in FP64; in FP32
+//     single applications and the steps and adjoint steps of large systems;
+//   with (y,z)-transformed copies, FP32 only (the other steps, ground states): k_xpass (DFT_x ->
+//     multiply 1/2|G|^2/N -> IDFT_x on the transformed states) and k_plane_stage2 / k_plane_stage_r
+//     (IDFT_yz -> T w; V w; + scatter rows; Taylor update; sphere rows; DFT_yz of the result for the
+//     next column pass).
 // Densities, exchange, Hartree and reductions are FP64.  The projector
 // contraction <beta|psi> and its scatter-back run on the matrix cores
 // (v_mfma_f64_16x16x4f64 / v_mfma_f32_16x16x4f32).
@@ -612,9 +614,10 @@ constexpr size_t real_lds_bytes() {
   return (size_t(NY) * (NZ + 1) + NY + NZ) * sizeof(cpx<R>) + (NY + NZ) * sizeof(R);
 }
 
-// Plane pass: out = r + c (T_yz w + projector rows), one workgroup per (spinor component, x-plane), one
-// LDS plane.  All loads (the thread's points of w and of r) are issued up front (but see real_late); r
-// waits in registers while w goes through the plane.  out may be w.
+// Plane pass: out = r + c (T_yz w + projector rows), with walpha w in r where the stage's base is w
+// (plane_takes_base), one workgroup per (spinor component, x-plane), one LDS plane.  All loads (the
+// thread's points of w and of r) are issued up front (but see real_late); r waits in registers while w
+// goes through the plane.  out may be w.
 //
 // Each wave owns NZ / NW columns of the y transforms and NY / NW rows of the z transforms, so the
 // stages of one axis run without a workgroup barrier (LDS operations of a wave stay in order); only
@@ -655,7 +658,7 @@ __global__ __launch_bounds__(64 * real_nw<R>(NY, NZ), real_mw(NY, NZ)) void k_pl
   const C* win = reinterpret_cast<const C*>(a.w_in);
   const C* __restrict__ rin = reinterpret_cast<const C*>(a.tmp_in);
 
-  // sphere rows on this plane (RowMap): their scatter values go into r with the other operands
+  // sphere rows on this plane (pt.pmap): their scatter values go into r before the last stage
   const C* __restrict__ Y = reinterpret_cast<const C*>(a.Y);
   C* __restrict__ Wr = reinterpret_cast<C*>(a.W);
   const bool on_plane = (Y || Wr) && pt.pr_off[x + 1] > pt.pr_off[x];
@@ -1196,9 +1199,8 @@ constexpr int XP_NT = 256;  // threads of the energy column pass
 // stage has at least 512 butterflies take NCT_XPASS_NT_F32_WIDE: at 64 points 512 threads
 // measured 4848 against 4571 GB/s (64^3 x 256), while the 48-point tile (384 butterflies) and
 // the 32-column tile at 96 points lost with 512 (4324 against 4402, 4256 against 4543 GB/s), and
-// the 64-column tile at 96 points with 256 (4159 against 4717 GB/s).  FP64 at 64 points keeps 32
-// columns: a 64-column tile (64 KB, two workgroups per CU) measured 4940 GB/s with 512 threads and
-// 4630 with 256, against 4960.
+// the 64-column tile at 96 points with 256 (4159 against 4717 GB/s).  FP64 passes here are those of the
+// Poisson solve, one box of a few us.
 #ifndef NCT_XPASS_NT_F64
 #define NCT_XPASS_NT_F64 256
 #endif

@@ -1585,11 +1585,11 @@ struct mfma16<float> {
   }
 };
 
-// k-steps whose operands are loaded together: a chunk of 64 rows is two rounds in FP32, the second loaded
-// while the first is multiplied, and four in FP64, whose operands take twice the registers: loaded ahead
-// there they leave three waves per SIMD instead of four (64^3 x 256 with 16 atoms 95 against 78 us)
-template <typename R>
-constexpr int proj_ku() { return 32 / int(sizeof(R)); }
+// k-steps whose operands are loaded together.  Neither loaded ahead of the products before them nor eight at a time in
+// FP32: that wins 1 % where a system is small (48^3 x 32 mixed with four atoms 1.120 against 1.119 ms, 96 x 24 x
+// 24 x 40 0.801 against 0.805) and takes the registers of a wave per SIMD where it is not (32^3 x 200 mixed with two atoms
+// 1.97 against 1.87 ms, contraction 34 against 21 us).
+constexpr int KU = 4;
 
 // Cpart[a][kc][p][i] = sum_{k in chunk} conj(beta[a][k][p]) W[i][k], k = 2 (J - off_a) + s.
 // One wave: PP/16 output tiles of 16 projectors x 16 states; A/B operands as
@@ -1600,8 +1600,7 @@ template <typename R, int PP, bool KQ>
 __global__ __launch_bounds__(64, 3) void k_proj_contract(ProjTables pt, const cpx<R>* __restrict__ W,
                                                       int S, cpx<double>* __restrict__ Cpart, PhaseTab ph) {
   using M = mfma16<R>;
-  constexpr int NMT = PP / 16, KU = proj_ku<R>();
-  constexpr bool AHEAD = sizeof(R) == 4;
+  constexpr int NMT = PP / 16;
   const int a = blockIdx.x, nt = blockIdx.y, kc = blockIdx.z;
   const int off = pt.row_off[a];
   const int K = 2 * (pt.row_off[a + 1] - off);
@@ -1620,8 +1619,8 @@ __global__ __launch_bounds__(64, 3) void k_proj_contract(ProjTables pt, const cp
     ai[mt] = M::zero();
   }
   const int kend = min(K, kc * KC + KC);
-  cpx<R> bw[KU], bb[KU][NMT];
-  const auto load = [&](int k0) {
+  for (int k0 = kc * KC; k0 < kend; k0 += 4 * KU) {
+    cpx<R> bw[KU], bb[KU][NMT];
 #pragma unroll
     for (int u = 0; u < KU; ++u) {
       const int k = k0 + 4 * u + kl;
@@ -1637,26 +1636,14 @@ __global__ __launch_bounds__(64, 3) void k_proj_contract(ProjTables pt, const cp
         bb[u][mt] = ok ? v : cpx<R>{R(0), R(0)};
       }
     }
-  };
-  if (AHEAD) load(kc * KC);
-  for (int k0 = kc * KC; k0 < kend; k0 += 4 * KU) {
-    if (!AHEAD) load(k0);
-    cpx<R> cw[KU], cb[KU][NMT];
-#pragma unroll
-    for (int u = 0; u < KU; ++u) {
-      cw[u] = bw[u];
-#pragma unroll
-      for (int mt = 0; mt < NMT; ++mt) cb[u][mt] = bb[u][mt];
-    }
-    if (AHEAD && k0 + 4 * KU < kend) load(k0 + 4 * KU);  // the next operands, while these are multiplied
 #pragma unroll
     for (int u = 0; u < KU; ++u) {
 #pragma unroll
       for (int mt = 0; mt < NMT; ++mt) {
-        ar[mt] = M::op(cb[u][mt].x, cw[u].x, ar[mt]);
-        ar[mt] = M::op(cb[u][mt].y, cw[u].y, ar[mt]);
-        ai[mt] = M::op(cb[u][mt].x, cw[u].y, ai[mt]);
-        ai[mt] = M::op(-cb[u][mt].y, cw[u].x, ai[mt]);
+        ar[mt] = M::op(bb[u][mt].x, bw[u].x, ar[mt]);
+        ar[mt] = M::op(bb[u][mt].y, bw[u].y, ar[mt]);
+        ai[mt] = M::op(bb[u][mt].x, bw[u].y, ai[mt]);
+        ai[mt] = M::op(-bb[u][mt].y, bw[u].x, ai[mt]);
       }
     }
   }

@@ -840,8 +840,7 @@ __global__ __launch_bounds__(256) void k_gather_rows(const cpx<R>* __restrict__ 
 }
 
 // Column pass: r = alpha x + c (T_x + V) w, T_x = IDFT_x 1/2 (G_x + k_x)^2 / NX DFT_x, in real space along
-// y and z.  Each wave takes xk_cols consecutive yz columns of one spinor component (one 128-byte line
-// per x-plane); the neighbouring wave takes the other component of the same columns, and the two swap
+// y and z.  Each wave takes CW (xv_cols) consecutive yz columns of one spinor component; the neighbouring wave takes the other component of the same columns, and the two swap
 // their values of w through their LDS tiles for the 2x2 potential.  r waits in registers while w goes
 // through the tile: the first forward stage works on the values as they are loaded, the last forward
 // stage, the factor and the first inverse stage stay in registers.  No workgroup barrier is needed
@@ -853,22 +852,31 @@ __global__ __launch_bounds__(256) void k_gather_rows(const cpx<R>* __restrict__ 
 // (one FP64 step of smooth states at 16^3, |z| E_max = 0.95, against long double 1.14e-16, 1.35e-16 with x added
 // first; Horner steps take as long, 64^3 x 128 FP64 13.49 against 13.47 ms, or less at 96 points, where x waits for
 // no field, 96^3 x 32 FP64 12.9 against 13.3, 96^3 x 64 FP32 14.7 against 16.1).
-// A wave's columns: one 128-byte line per x-plane (FP32 with 64-byte halves 667 against 425 us per pass
-// at 64^3 x 256)
+// A wave's columns.  At least one 128-byte line per x-plane (FP32 with 64-byte halves 667 against 425 us per pass
+// at 64^3 x 256), and on short lines as many as give the first stage a butterfly per lane: lines of 8 to 32
+// points have 1 to 4 butterflies, so that 128 bytes of columns left 32 to 56 of a wave's lanes repeating the last one
+// (FP64 8 x 96 x 96 x 60 3.50 -> 1.84 ms per step, 24^3 x 300 2.62 -> 2.36, 32^3 x 200 3.00 -> 2.64, 16^3 x 60 0.258 ->
+// 0.245).  Where the plane's columns do not divide by that (12 x 12, 144 columns, lines of 8 points), 16.
 template <typename R>
-constexpr int xk_cols() { return 128 / int(sizeof(cpx<R>)); }
+constexpr int xv_cols(int nx) {
+  const int line = 128 / int(sizeof(cpx<R>)), m = nx / plan_radix(real_plan(nx), 0);
+  const int lanes = m == 1 ? 64 : 16;
+  return line * m >= 48 || lanes < line ? line : lanes;
+}
 // Column blocks per workgroup (two waves each): four blocks of lines of 48 and 64 points (FP64 64^3 x 256:
 // 512 bytes of a row per workgroup, 824 against 862 us per pass with two, 1021 with one, all with the
-// slower addressing above; 752 us = 5.7 TB/s now; FP32 373 us against 432 with two), two below, where the
-// grids are small and need the workgroups (21 against 26 us at 32^3 x 32) and at 96 points (LDS).
+// slower addressing above; 752 us = 5.7 TB/s now; FP32 373 us against 432 with two), two at 96 points (LDS) and on
+// shorter lines where 4096 workgroups remain (FP64 steps with two against one: 24^3 x 300, 5400 workgroups,
+// 2.36 / 2.48 ms; 32^3 x 200, 6400, 2.64 / 2.78; 24 x 48 x 48 x 60, 4320, 1.306 / 1.319), one below (16^3 x 300, 2400,
+// 1.035 / 1.025; 32^3 x 64, 2048, 1.053 / 1.047; 24^3 x 60, 1080, 0.491 / 0.485; 16^3 x 8 0.148 / 0.142).
 constexpr int xv_pairs(int nx) { return nx == 48 || nx == 64 ? 4 : 2; }
+constexpr size_t kXvTwoBlocksMin = 4096;
 // waves per SIMD that the registers must allow
 constexpr int xv_mw(int nx) { return nx == 96 ? 3 : 4; }
-template <typename R, int NX, int PAIRS, int M, bool XS>
+template <typename R, int NX, int CW, int PAIRS, int M, bool XS>
 __global__ __launch_bounds__(128 * PAIRS, xv_mw(NX)) void k_xv(StageArgs<R> a, cpx<R>* __restrict__ dst, int NY, int NZ,
                                                        int S, const cpx<R>* __restrict__ twx_g, KinTables kt) {
   using C = cpx<R>;
-  constexpr int CW = xk_cols<R>();
   constexpr int FX = real_plan(NX);
   constexpr int RX = plan_radix(FX, 0), MX = NX / RX;
   constexpr int ITEMS = CW * MX, IT = (ITEMS + 63) / 64;
@@ -2442,37 +2450,40 @@ hipError_t launch_gather_rows(const ProjTables& pt, const void* psi, void* W, in
   return hipGetLastError();
 }
 
-template <typename R, int NX, int PAIRS, int M>
+template <typename R, int NX, int CW, int PAIRS, int M>
 static hipError_t launch_xv_m(const int n[3], int S, const StageArgs<R>& a, void* dst, const void* twx,
                               const KinTables& kt, hipStream_t st) {
-  const dim3 grid(unsigned(n[1] * n[2] / (xk_cols<R>() * PAIRS)) * unsigned(S)), block(128 * PAIRS);
+  const dim3 grid(unsigned(n[1] * n[2] / (CW * PAIRS)) * unsigned(S)), block(128 * PAIRS);
   const auto d_ = reinterpret_cast<cpx<R>*>(dst);
   const auto t_ = reinterpret_cast<const cpx<R>*>(twx);
-  if (a.x_base && a.x_base != a.w_in) nct_launch((k_xv<R, NX, PAIRS, M, true>), grid, block, 0, st, a, d_, n[1], n[2], S, t_, kt);
-  else nct_launch((k_xv<R, NX, PAIRS, M, false>), grid, block, 0, st, a, d_, n[1], n[2], S, t_, kt);
+  if (a.x_base && a.x_base != a.w_in) nct_launch((k_xv<R, NX, CW, PAIRS, M, true>), grid, block, 0, st, a, d_, n[1], n[2], S, t_, kt);
+  else nct_launch((k_xv<R, NX, CW, PAIRS, M, false>), grid, block, 0, st, a, d_, n[1], n[2], S, t_, kt);
   return hipGetLastError();
 }
-template <typename R, int NX, int PAIRS>
+template <typename R, int NX, int CW, int PAIRS>
 static hipError_t launch_xv_p(const int n[3], int S, const StageArgs<R>& a, void* dst, const void* twx,
                               const KinTables& kt, hipStream_t st) {
-  if (a.cache_mode >= 2) return launch_xv_m<R, NX, PAIRS, 2>(n, S, a, dst, twx, kt, st);
+  if (a.cache_mode >= 2) return launch_xv_m<R, NX, CW, PAIRS, 2>(n, S, a, dst, twx, kt, st);
   if constexpr (sizeof(R) == 4) {  // FP64 has no streaming stores with plain loads
-    if (a.cache_mode == 1) return launch_xv_m<R, NX, PAIRS, 1>(n, S, a, dst, twx, kt, st);
+    if (a.cache_mode == 1) return launch_xv_m<R, NX, CW, PAIRS, 1>(n, S, a, dst, twx, kt, st);
   }
-  return launch_xv_m<R, NX, PAIRS, 0>(n, S, a, dst, twx, kt, st);
+  return launch_xv_m<R, NX, CW, PAIRS, 0>(n, S, a, dst, twx, kt, st);
 }
 template <typename R>
 hipError_t launch_xv(const int n[3], int S, const StageArgs<R>& a, void* dst, const void* twx,
                      const KinTables& kt, hipStream_t st) {
-  // every built plane holds a multiple of 16 columns, all but 12 x 12 a multiple of 32
-#define X(A)                                                                        \
-  if (n[0] == A) {                                                                  \
-    const int blocks = n[1] * n[2] / xk_cols<R>();                                  \
-    if constexpr (xv_pairs(A) == 4) {                                            \
-      if (blocks % 4 == 0) return launch_xv_p<R, A, 4>(n, S, a, dst, twx, kt, st);  \
-    }                                                                               \
-    if (blocks % 2 == 0) return launch_xv_p<R, A, 2>(n, S, a, dst, twx, kt, st);    \
-    return launch_xv_p<R, A, 1>(n, S, a, dst, twx, kt, st);                         \
+  // every built plane holds a multiple of 16 columns
+#define X(A)                                                                             \
+  if (n[0] == A) {                                                                       \
+    constexpr int CW = xv_cols<R>(A), P = xv_pairs(A);                                      \
+    const int cols = n[1] * n[2];                                                           \
+    const bool two = A >= 48 || size_t(cols / (2 * CW)) * S >= kXvTwoBlocksMin;             \
+    if (two && cols % (P * CW) == 0) return launch_xv_p<R, A, CW, P>(n, S, a, dst, twx, kt, st); \
+    if constexpr (P > 2)                                                                    \
+      if (cols % (2 * CW) == 0) return launch_xv_p<R, A, CW, 2>(n, S, a, dst, twx, kt, st); \
+    if constexpr (CW > 16)                                                                  \
+      if (cols % CW != 0) return launch_xv_p<R, A, 16, 1>(n, S, a, dst, twx, kt, st);       \
+    if constexpr (P > 1) return launch_xv_p<R, A, CW, 1>(n, S, a, dst, twx, kt, st);        \
   }
   NCT_LINES(X)
 #undef X

@@ -594,13 +594,13 @@ struct Engine {
   // whether or not it records observables or a tape, and is reversed in the form it was made in.
   bool RS = D;
   // FP32 steps: above 512 MiB of states.  This is not where the times cross.  Per step, transformed against
-  // real space: 48^3 27 MiB 0.685 / 0.693 ms, 54 1.127 / 0.998, 108 2.03 / 1.76, 216 3.84 / 3.31, 506 8.67 / 7.43;
-  // 64^3 256 MiB 4.38 / 3.44, 480 7.98 / 6.22; 96^3 216 MiB 4.13 / 3.76; 96 x 24 x 24 34 MiB 0.828 / 0.878, 101
-  // 2.31 / 2.49.  The two forms round the FP32 states differently (each within 3e-7 of FP64), and mixed calls
+  // real space: 48^3 27 MiB 0.684 / 0.703 ms, 54 1.12 / 1.00, 108 2.01 / 1.79, 216 3.85 / 3.35, 506 8.7 / 7.6;
+  // 64^3 256 MiB 4.35 / 3.48, 480 7.9 / 6.3; 96^3 216 MiB 4.1 / 3.85; 96 x 24 x 24 34 MiB 0.804 / 0.781, 101
+  // 2.11 / 1.88.  The two forms round the FP32 states differently (each within 3e-7 of FP64), and mixed calls
   // return FP64 numbers that are sums of small differences of those states: a field gradient of 64^3 x 64
   // moves by 2.4e-7 of its size with the form.  Systems up to two last-level caches (256 MiB each) keep the
-  // digits that such results have had; larger ones, where a step takes 14 % to 29 % less in real space (64^3 x
-  // 256 with 16 atoms 13.1 against 17.9 ms), do not.
+  // digits that such results have had; larger ones, where a step takes up to 28 % less in real space (64^3 x
+  // 256 with 16 atoms 13.9 against 17.6 ms, 96^3 x 128 26.8 against 28.8), do not.
   bool real_step() const { return mixed_real_step(s); }
   const void* twx() const { return sizeof(R) == 8 ? s->tw64[0] : s->tw32[0]; }
   const void* twy() const { return sizeof(R) == 8 ? s->tw64[1] : s->tw32[1]; }

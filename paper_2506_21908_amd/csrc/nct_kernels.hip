@@ -639,10 +639,10 @@ __global__ __launch_bounds__(64 * real_nw<R>(NY, NZ), real_mw(NY, NZ)) void k_pl
   constexpr int NP = NY * NZ, PZ = NZ + 1;
   constexpr int NW = real_nw<R>(NY, NZ), NT = 64 * NW;
   constexpr int CW = NZ / NW, RW = NY / NW;
-  constexpr int FY = real_plan(NY), FZ = real_plan(NZ);
+  constexpr int FY = plane_plan(NY), FZ = plane_plan(NZ);
   constexpr int RY = plan_radix(FY, 0), MY = NY / RY;
   constexpr int ITEMS = CW * MY, IT = (ITEMS + 63) / 64;
-  static_assert(NZ % NW == 0 && NY % NW == 0 && plan_nstages(NY) <= 2 && plan_nstages(NZ) <= 2, "plane split");
+  static_assert(NZ % NW == 0 && NY % NW == 0 && plan_nstages(FY) <= 2 && plan_nstages(FZ) <= 2, "plane split");
   extern __shared__ double4 smem_d4[];
   C* pl = reinterpret_cast<C*>(smem_d4);
   C* twy = pl + NY * PZ;
@@ -721,17 +721,17 @@ __global__ __launch_bounds__(64 * real_nw<R>(NY, NZ), real_mw(NY, NZ)) void k_pl
       for (int q = 0; q < RY; ++q) p[q * MY * PZ] = v[u][q];
     }
   }
-  if constexpr (plan_nstages(NY) > 1) {
+  if constexpr (plan_nstages(FY) > 1) {
     wave_sync();
     wave_stage<R, FY, 1, CW, 1, PZ, true>(cols, twy, lane);
   }
   group_sync<NW>();
-  if constexpr (plan_nstages(NZ) > 1) {
+  if constexpr (plan_nstages(FZ) > 1) {
     wave_stage<R, FZ, 0, RW, PZ, 1, true>(rows, twz, lane);
     wave_sync();
   }
   wave_middle<R, FZ, RW, PZ, 1>(rows, lane, [&](int line, int k) { return ty[w * RW + line] + tz[k]; });
-  if constexpr (plan_nstages(NZ) > 1) {
+  if constexpr (plan_nstages(FZ) > 1) {
     wave_sync();
     wave_stage<R, FZ, 0, RW, PZ, 1, false>(rows, twz, lane);
   }
@@ -765,7 +765,7 @@ __global__ __launch_bounds__(64 * real_nw<R>(NY, NZ), real_mw(NY, NZ)) void k_pl
         for (int q = 0; q < RY; ++q) y[u][q] = Y[rb + (J[u][q] >= 0 ? (J[u][q] & kRowMask) : 0)];
     }
   }
-  if constexpr (plan_nstages(NY) > 1) {
+  if constexpr (plan_nstages(FY) > 1) {
     wave_stage<R, FY, 1, CW, 1, PZ, false>(cols, twy, lane);
     wave_sync();
   }
@@ -853,21 +853,22 @@ __global__ __launch_bounds__(256) void k_gather_rows(const cpx<R>* __restrict__ 
 // first; Horner steps take as long, 64^3 x 128 FP64 13.49 against 13.47 ms, or less at 96 points, where x waits for
 // no field, 96^3 x 32 FP64 12.9 against 13.3, 96^3 x 64 FP32 14.7 against 16.1).
 // A wave's columns.  At least one 128-byte line per x-plane (FP32 with 64-byte halves 667 against 425 us per pass
-// at 64^3 x 256), and on short lines as many as give the first stage a butterfly per lane: lines of 8 to 32
+// at 64^3 x 256), and on short lines as many as give the first stage a butterfly per lane: lines of 8, 12, 16 and 32
 // points have 1 to 4 butterflies, so that 128 bytes of columns left 32 to 56 of a wave's lanes repeating the last one
-// (FP64 8 x 96 x 96 x 60 3.50 -> 1.84 ms per step, 24^3 x 300 2.62 -> 2.36, 32^3 x 200 3.00 -> 2.64, 16^3 x 60 0.258 ->
-// 0.245).  Where the plane's columns do not divide by that (12 x 12, 144 columns, lines of 8 points), 16.
+// (FP64 8 x 96 x 96 x 60 3.50 -> 1.84 ms per step, 32^3 x 200 3.00 -> 2.64, 16^3 x 60 0.258 -> 0.245).  Lines of 24 take
+// sixteen in FP64 too, two rounds of small butterflies (24^3 x 300 2.21 against 2.45 ms with eight, 2.18 with the 8 x
+// 3 plan; 24^3 x 1500 9.17, 9.76, 9.28).  Where the plane's columns do not divide by 64 (12 x 12, lines of 8 points), 16.
 template <typename R>
 constexpr int xv_cols(int nx) {
   const int line = 128 / int(sizeof(cpx<R>)), m = nx / plan_radix(real_plan(nx), 0);
   const int lanes = m == 1 ? 64 : 16;
-  return line * m >= 48 || lanes < line ? line : lanes;
+  return (line * m >= 48 && nx != 24) || lanes < line ? line : lanes;
 }
 // Column blocks per workgroup (two waves each): four blocks of lines of 48 and 64 points (FP64 64^3 x 256:
 // 512 bytes of a row per workgroup, 824 against 862 us per pass with two, 1021 with one, all with the
 // slower addressing above; 752 us = 5.7 TB/s now; FP32 373 us against 432 with two), two at 96 points (LDS) and on
 // shorter lines where 4096 workgroups remain (FP64 steps with two against one: 24^3 x 300, 5400 workgroups,
-// 2.36 / 2.48 ms; 32^3 x 200, 6400, 2.64 / 2.78; 24 x 48 x 48 x 60, 4320, 1.306 / 1.319), one below (16^3 x 300, 2400,
+// 2.36 / 2.48 ms with the 8 x 3 plan; 32^3 x 200, 6400, 2.64 / 2.78; 24 x 48 x 48 x 60, 4320, 1.306 / 1.319), one below (16^3 x 300, 2400,
 // 1.035 / 1.025; 32^3 x 64, 2048, 1.053 / 1.047; 24^3 x 60, 1080, 0.491 / 0.485; 16^3 x 8 0.148 / 0.142).
 constexpr int xv_pairs(int nx) { return nx == 48 || nx == 64 ? 4 : 2; }
 constexpr size_t kXvTwoBlocksMin = 4096;

@@ -570,6 +570,10 @@ std::vector<std::complex<double>> taylor_roots(int K) {
 // Horner 1.86 at 2.1; K = 8 2.2, Horner 2.15 at 2.4; K = 12 2.5, Horner 2.6 at 2.8, 3.2 at 3.2.  (On white noise
 // the Horner stages keep ahead: K = 4 at 2.1 3.5 against 2.9.  The transformed form, which neither is to fall
 // behind, has 2.0 and 4.1 there.)
+// Order of the factors: upper half plane first.  At high energies their moduli grow first and shrink last, so the
+// rounding of the first stages is damped (sum of squares over the stages and the grid's spectrum, K = 4, 2.1: 2.7);
+// the adjoint runs them backwards (7.3) and is left at 7.2e-16 for the taped gradient of 32^3 x 32 where
+// Horner stages of the transformed form had 6.8e-16.  No order does better for both (3.9 and 4.4 at best).
 constexpr int kProductMaxOrder = 12;
 // In imaginary time the product form is behind the transformed form up to about 1.3 only and ahead from 1.5 on
 // (one ground-state iteration at 16^3, K = 4, smooth states, mean of five: transformed, Horner, product with three
@@ -800,7 +804,7 @@ struct Engine {
 
   // real-space stage whose base is w: the plane pass adds it, where it can
   bool base_in_plane(const StageArgs<R>& sa) const {
-    return sa.x_base && sa.x_base == sa.w_in && real_base_in_plane(s->n[1], s->n[2]);
+    return sa.x_base && sa.x_base == sa.w_in && real_base_in_plane(s->n[1], s->n[2], D);
   }
   StageArgs<R> column_args(StageArgs<R> sa) const {
     if (base_in_plane(sa)) sa.alpha = R(0);

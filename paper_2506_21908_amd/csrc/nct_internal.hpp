@@ -88,7 +88,7 @@ struct KinTables {
 
 // Real-space form, stages whose base is w itself: the plane pass adds alpha w, where it holds the points of w and of
 // the sum at the same time, else the column pass does.  One rounding less of the base either way it can be had.
-bool real_base_in_plane(int ny, int nz);
+bool real_base_in_plane(int ny, int nz, bool fp64);
 
 // Launchers (return hipError_t of the launch).  n = {NX, NY, NZ}.
 // Real-space form (kv, state_off and ka of the stage arguments are unused: they are in kt):

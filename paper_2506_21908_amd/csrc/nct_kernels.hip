@@ -603,11 +603,12 @@ __host__ __device__ constexpr bool real_late(int ny, int nz) { return ny == 96 &
 // rounded twice per stage, not three times with two of them in the column pass (one FP64 step at 16^3, K = 4,
 // |z| E_max = 2.1, smooth states, against long double 1.78e-16 and 2.06e-16; the transformed form 2.01e-16).  The
 // transforms then wait for r as well: 64^3 x 256 FP64 25.27 against 25.48 ms per step, 32^3 x 32 0.713 / 0.712,
-// 24^3 x 64 0.769 / 0.764.  Not at 96^2 (r is late) and not at 48^2, whose six waves have less to run meanwhile
-// (48^3 x 64 3.28 against 3.20 ms) and whose error is below the transformed form's either way (6.4e-16 against
-// 6.5e-16 after two steps).
+// 24^3 x 64 0.769 / 0.764, 48^3 x 310 FP32 7.64 / 7.63.  Not at 96^2 (r is late) and not at 48^2 in FP64, whose six
+// waves have less to run meanwhile (48^3 x 64 3.28 against 3.20 ms) and whose error is below the transformed form's
+// either way (6.4e-16 against 6.5e-16 after two steps).
+template <typename R>
 __host__ __device__ constexpr bool plane_takes_base(int ny, int nz) {
-  return !real_late(ny, nz) && !(ny == 48 && nz == 48);
+  return !real_late(ny, nz) && !(sizeof(R) == 8 && ny == 48 && nz == 48);
 }
 template <typename R, int NY, int NZ>
 constexpr size_t real_lds_bytes() {
@@ -697,7 +698,7 @@ __global__ __launch_bounds__(64 * real_nw<R>(NY, NZ), real_mw(NY, NZ)) void k_pl
       tz[k] = R(0.5 / NP * (g * g));
     }
   }
-  if constexpr (plane_takes_base(NY, NZ)) {
+  if constexpr (plane_takes_base<R>(NY, NZ)) {
     if (a.walpha != R(0)) {  // the base of this stage is w: added here, it is rounded once and once with c T_yz w
 #pragma unroll
       for (int u = 0; u < IT; ++u)
@@ -2385,7 +2386,9 @@ static void nct_launch(F kern, dim3 grid, dim3 block, size_t lds, hipStream_t st
 #endif
 
 #if NCT_FP64_TU
-bool real_base_in_plane(int ny, int nz) { return plane_takes_base(ny, nz); }
+bool real_base_in_plane(int ny, int nz, bool fp64) {
+  return fp64 ? plane_takes_base<double>(ny, nz) : plane_takes_base<float>(ny, nz);
+}
 bool plane_pair_supported(int ny, int nz) {
 #define X(a, b) if (ny == a && nz == b) return true;
   NCT_PLANE_PAIRS(X)

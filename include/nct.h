@@ -276,7 +276,7 @@ nct_status nct_get_fields(nct_system *sys, double t, double *fields_dev);
  * fields, B_ext(t) and v_E(t).  psi and hpsi are distinct device buffers of the psi layout above
  * (caller-owned; hpsi is overwritten).  Allocates nothing and does not synchronise: it may be recorded
  * into a HIP graph, a system's first application included, and replays with the time, pulses and
- * gauge it was recorded with, on the fields and Bloch vectors of the moment.
+ * gauge it was recorded with, on the fields and (recorded with some) Bloch vectors of the moment.
  * Errors: NCT_ERR_ARG (NULL or identical buffers), NCT_ERR_STATE (no fields yet: call
  * nct_density_magnetization with update_fields, or freeze fields with nct_set_potentials). */
 nct_status nct_apply_hamiltonian(nct_system *sys, const void *psi_dev, void *hpsi_dev, double t);

@@ -740,8 +740,8 @@ struct Engine {
     if (phaseA_ok && ka[0] == phaseA_ka[0] && ka[1] == phaseA_ka[1] && ka[2] == phaseA_ka[2]) return NCT_OK;
     for (int d = 0; d < 3; ++d) phaseA_ka[d] = ka[d];
     phaseA_ok = true;
-    return check(launch_phases<R>(s->has_k ? s->kruns : s->kv_zero64, s->has_k ? s->phase_runs : 1, ka, s->pt,
-                                  s->phasesA, s->st), "phases");
+    return check(s->has_k ? launch_phases<R>(s->kruns, s->run_of + s->S - 1, s->phase_runs, ka, s->pt, s->phasesA, s->st)
+                          : launch_phases<R>(s->kv_zero64, nullptr, 1, ka, s->pt, s->phasesA, s->st), "phases");
   }
 
   // NL projections of the sphere rows W -> Y (scatter rows).  Enqueued on the second
@@ -2028,8 +2028,8 @@ nct_status nct_set_kpoints(nct_system* s, const double* kvec) {
     HIPCHK(s, hipMemcpyAsync(s->kruns, kr.data(), kr.size() * sizeof(double), hipMemcpyHostToDevice, s->st));
     HIPCHK(s, hipMemcpyAsync(s->run_of, ro.data(), ro.size() * sizeof(int), hipMemcpyHostToDevice, s->st));
     const double zero[3] = {0, 0, 0};
-    if (s->fp64) HIPCHK(s, launch_phases<double>(s->kruns, runs, zero, s->pt, s->phases, s->st));
-    else HIPCHK(s, launch_phases<float>(s->kruns, runs, zero, s->pt, s->phases, s->st));
+    if (s->fp64) HIPCHK(s, launch_phases<double>(s->kruns, s->run_of + s->S - 1, runs, zero, s->pt, s->phases, s->st));
+    else HIPCHK(s, launch_phases<float>(s->kruns, s->run_of + s->S - 1, runs, zero, s->pt, s->phases, s->st));
   }
   HIPCHK(s, hipStreamSynchronize(s->st));
   s->phase_runs = runs;

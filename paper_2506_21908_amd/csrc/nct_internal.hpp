@@ -178,13 +178,14 @@ struct PhaseTab {
     return static_cast<const cpx<R>*>(tab) + size_t(run ? run[state_off + i] : 0) * Jtot;
   }
 };
+// Fills the table of all runs; last_run: the run of the last state (null: one run); nruns: their number now.
 template <typename R>
-hipError_t launch_phases(const double* kruns, int nruns, const double ka[3], const ProjTables& pt, void* tab,
-                         hipStream_t st);
+hipError_t launch_phases(const double* kruns, const int* last_run, int nruns, const double ka[3], const ProjTables& pt,
+                         void* tab, hipStream_t st);
 
 // Projectors: chunk partials of beta^H W (per atom); C = dV times their sum (observables);
-// Y = beta E C from the partials, or from EC = E C (complex R) where launch_proj_coeffs has made it.  With phases (ph.tab) the rows of W are taken times them, those of Y
-// times their conjugates.
+// Y = beta E C from the partials, or from EC = E C (complex R) where launch_proj_coeffs has made it.  With
+// phases (ph.tab) the rows of W are taken times them, those of Y times their conjugates.
 template <typename R>
 hipError_t launch_proj_contract(const ProjTables& pt, const void* W, int S, void* Cpart, const PhaseTab& ph,
                                 hipStream_t st);

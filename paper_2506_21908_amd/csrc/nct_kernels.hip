@@ -1812,13 +1812,19 @@ __global__ __launch_bounds__((ps_nt<R, PP, SUMS>()), 4) void k_proj_scatter(Proj
   }
 }
 
-// Phases exp(i (k + A).d) of every sphere row for each distinct Bloch vector.
+// Phases exp(i (k + A).d) of every sphere row for each run of states.  The runs are counted from the last state's
+// in device memory (last_run null: one run), not from the grid: a launch recorded into a graph fills the table for
+// the Bloch vectors of the moment, which may be more runs than when it was recorded.
 template <typename R>
-__global__ __launch_bounds__(256) void k_phases(const double* __restrict__ kruns, double a0, double a1, double a2,
-                                                const R* __restrict__ disp, int Jtot, cpx<R>* __restrict__ out) {
-  const double* k = kruns + 3 * size_t(blockIdx.x);
-  for (int J = blockIdx.y * 256 + threadIdx.x; J < Jtot; J += gridDim.y * 256)
-    out[size_t(blockIdx.x) * Jtot + J] = bloch_phase(R(k[0] + a0), R(k[1] + a1), R(k[2] + a2), disp + 3 * J);
+__global__ __launch_bounds__(256) void k_phases(const double* __restrict__ kruns, const int* __restrict__ last_run,
+                                                double a0, double a1, double a2, const R* __restrict__ disp, int Jtot,
+                                                cpx<R>* __restrict__ out) {
+  const int nruns = last_run ? *last_run + 1 : 1;
+  for (int run = blockIdx.x; run < nruns; run += gridDim.x) {
+    const double* k = kruns + 3 * size_t(run);
+    for (int J = blockIdx.y * 256 + threadIdx.x; J < Jtot; J += gridDim.y * 256)
+      out[size_t(run) * Jtot + J] = bloch_phase(R(k[0] + a0), R(k[1] + a1), R(k[2] + a2), disp + 3 * J);
+  }
 }
 
 // ---------------------------------------------------------------- adjoint kernels
@@ -2794,11 +2800,11 @@ hipError_t launch_proj_reduce(const ProjTables& pt, const void* Cpart, int S, do
 }
 #endif
 template <typename R>
-hipError_t launch_phases(const double* kruns, int nruns, const double ka[3], const ProjTables& pt, void* tab,
-                         hipStream_t st) {
+hipError_t launch_phases(const double* kruns, const int* last_run, int nruns, const double ka[3], const ProjTables& pt,
+                         void* tab, hipStream_t st) {
   if (pt.natoms == 0 || pt.Jtot == 0) return hipSuccess;
-  nct_launch(k_phases<R>, dim3(unsigned(nruns), tables::row_blocks(pt.Jtot, 256)), dim3(256), 0, st, kruns, ka[0], ka[1],
-             ka[2], reinterpret_cast<const R*>(pt.disp), pt.Jtot, reinterpret_cast<cpx<R>*>(tab));
+  nct_launch(k_phases<R>, dim3(unsigned(nruns), tables::row_blocks(pt.Jtot, 256)), dim3(256), 0, st, kruns, last_run, ka[0],
+             ka[1], ka[2], reinterpret_cast<const R*>(pt.disp), pt.Jtot, reinterpret_cast<cpx<R>*>(tab));
   return hipGetLastError();
 }
 
@@ -2941,7 +2947,8 @@ hipError_t launch_density_backprop(const void* psi, const double* occ, const dou
   template hipError_t launch_xv<R>(const int*, int, const StageArgs<R>&, void*, const void*,       \
                                    const KinTables&, hipStream_t);                                 \
   template hipError_t launch_gather_rows<R>(const ProjTables&, const void*, void*, int, size_t, hipStream_t); \
-  template hipError_t launch_phases<R>(const double*, int, const double*, const ProjTables&, void*, hipStream_t); \
+  template hipError_t launch_phases<R>(const double*, const int*, int, const double*, const ProjTables&, void*, \
+                                       hipStream_t);                                                \
   template hipError_t launch_xpass<R>(const int*, int, const void*, void*, const R*, const R*, R,  \
                                       int, const void*, hipStream_t, int, KTables<R>);             \
   template hipError_t launch_density<R>(const void*, const double*, int, size_t, double*,          \

@@ -96,3 +96,39 @@ def test_changed_vectors_reach_later_applications(gpu):
             assert torch.equal(a, b)
             fresh.close()
     s.close()
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("gauge", ["length", "velocity"])
+def test_recorded_application_follows_vectors(gpu, prec, gauge):
+    """A recorded application replayed after the Bloch vectors were set again, in more runs and in fewer."""
+    torch, nct = gpu
+    print(f"[case] recorded, then vectors set again prec={prec} gauge={gauge}", flush=True)
+    n, S = (12, 12, 12), 6
+    w = _workload(n, S, False, "velocity")
+    rng = np.random.default_rng(5)
+    ks = [np.repeat(rng.uniform(-0.3, 0.3, (r, 3)), S // r, axis=0) for r in (2, 6, 1, 3)]
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        s, eager = (nct.system_from_workload(w, precision=prec, stream=st) for _ in range(2))
+        psi = nct.states_to_device(w.psi0, prec)
+        out, want = torch.zeros_like(psi), torch.empty_like(psi)
+        for x in (s, eager):
+            x.density_magnetization(psi, 0.0, update_fields=True)
+            x.set_laser_gauge(gauge)
+            x.set_kpoints(ks[0])
+        st.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=st):
+            s.apply_hamiltonian(psi, out, 0.5)
+        for kv in ks + ks[:2]:
+            s.set_kpoints(kv)
+            eager.set_kpoints(kv)
+            eager.apply_hamiltonian(psi, want, 0.5)
+            out.zero_()
+            g.replay()
+            st.synchronize()
+            assert torch.equal(out, want), len(np.unique(kv, axis=0))
+        del g
+    eager.close()
+    s.close()
